@@ -37,80 +37,226 @@ __global__ __launch_bounds__(EDGE_THREADS) void embed_fwd_kernel(const int* __re
     }
 }
 
-// ---- embedding backward, position table: dwpe[p] += sum over the sequences of dx[b*S + p], b ascending
-template <typename T>
-__global__ __launch_bounds__(EDGE_THREADS) void embed_bwd_wpe_kernel(const T* __restrict__ dx, float* __restrict__ dwpe, int B,
-                                                                     int S, int H) {
+// ---- embedding backward: one launch, two kinds of workgroups.
+//
+// Position table, dwpe[p] += sum over the sequences of dx[b*S + p], b ascending: one 16-byte piece
+// of a row per thread, eight sequences' pieces requested at a time.
+//
+// Token table, dwte[v] += sum of dx[t] over the positions t with token v.  Workgroup w owns the
+// tokens v with v mod EMB_OWNERS = w: every table row has one owner, so the sums need no atomics, and their
+// order is fixed by the positions alone.  Per window of EMB_WINDOW positions the workgroup
+//   1. lists its positions in ascending order (one ballot per 64 positions),
+//   2. finds the first entry of every distinct token in the list (a "head"),
+//   3. gives each head to one wavefront, which walks the list 64 entries at a time (ballot of
+//      "same token") and adds the rows in ascending order, several in flight;
+//   4. shares tokens with more than EMB_HOT entries among its eight wavefronts instead (wavefront k
+//      takes entries 8k..8k+7 of every 64; the partial rows are added in wavefront order): a frequent
+//      word would otherwise be one wavefront's serial chain of row loads.
+// What bounds it is latency (list, row, table row: a few dependent round trips), so there are
+// enough workgroups that a wavefront seldom has more than one or two tokens.  (One workgroup per
+// position, each scanning all tokens through LDS, took 301 us at 4096 positions x 1024 columns.)
+constexpr int EMB_THREADS = 512, EMB_WAVES = EMB_THREADS / WAVE;
+constexpr int EMB_WINDOW = 4096;
+constexpr int EMB_HOT = 16;
+constexpr int EMB_OWNERS = 1024;          // workgroups that share the token table (a power of two)
+typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));     // gradient tables need not be 16-byte aligned
+struct EmbedLds {
+    int tok[EMB_WINDOW];                  // owned tokens of the window, in position order
+    unsigned short pos[EMB_WINDOW];       // their positions within the window
+    unsigned short head[EMB_WINDOW];      // list index of the first entry of every distinct token
+    int counts[EMB_WAVES + 1];
+    int heads;
+};
+
+template <typename T, int MAXC> struct EmbedRow {
+    static constexpr int V = Elem<T>::VEC, FLY = MAXC <= 2 ? 8 : 4;      // rows in flight
+    float a[MAXC][V];
+    __device__ __forceinline__ void zero() {
+#pragma unroll
+        for (int i = 0; i < MAXC; ++i)
+#pragma unroll
+            for (int e = 0; e < V; ++e) a[i][e] = 0.f;
+    }
+    // adds the rows pos[j] of the entries j in `mask`, ascending
+    __device__ __forceinline__ void add_rows(const T* __restrict__ dx, const unsigned short* pos, unsigned long long mask, int nchunk,
+                                             int H, int lane) {
+        while (mask) {
+            uint4 q[FLY][MAXC];
+            bool ok[FLY];
+#pragma unroll
+            for (int u = 0; u < FLY; ++u) {
+                ok[u] = mask != 0;
+                const int j = ok[u] ? __ffsll((long long)mask) - 1 : 0;
+                mask &= mask - 1;
+                const T* row = dx + (size_t)pos[j] * H;
+                if (ok[u])
+#pragma unroll
+                    for (int i = 0; i < MAXC; ++i)
+                        if (lane + i * WAVE < nchunk) q[u][i] = *reinterpret_cast<const uint4*>(row + (lane + i * WAVE) * V);
+            }
+#pragma unroll
+            for (int u = 0; u < FLY; ++u)
+                if (ok[u])
+#pragma unroll
+                    for (int i = 0; i < MAXC; ++i)
+                        if (lane + i * WAVE < nchunk) {
+                            float v[V];
+                            load_vec<T>(reinterpret_cast<const T*>(&q[u][i]), v);
+#pragma unroll
+                            for (int e = 0; e < V; ++e) a[i][e] += v[e];
+                        }
+        }
+    }
+    __device__ __forceinline__ void add_to(float* __restrict__ out, int nchunk, int lane) const {
+#pragma unroll
+        for (int i = 0; i < MAXC; ++i)
+            if (lane + i * WAVE < nchunk) {
+                float* o = out + (size_t)(lane + i * WAVE) * V;
+#pragma unroll
+                for (int e = 0; e < V; e += 4) {
+                    f32x4_u t = *reinterpret_cast<const f32x4_u*>(o + e);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) t[k] += a[i][e + k];
+                    *reinterpret_cast<f32x4_u*>(o + e) = t;
+                }
+            }
+    }
+};
+
+template <typename T, int MAXC>
+__global__ __launch_bounds__(EMB_THREADS) void embed_bwd_kernel(const int* __restrict__ tokens, const T* __restrict__ dx,
+                                                                float* __restrict__ dwte, float* __restrict__ dwpe, int M, int S,
+                                                                int H, int vocab) {
     constexpr int V = Elem<T>::VEC;
-    const int p = blockIdx.x;
-    for (int c = threadIdx.x; c < H / V; c += EDGE_THREADS) {
+    extern __shared__ __attribute__((aligned(16))) char emb_smem[];
+    EmbedLds& sm = *reinterpret_cast<EmbedLds*>(emb_smem);
+    float* hot_row = reinterpret_cast<float*>(emb_smem + sizeof(EmbedLds));       // [H]
+    const int tid = threadIdx.x, lane = tid % WAVE, wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
+    const int nchunk = H / V;
+    if ((int)blockIdx.x >= EMB_OWNERS) {                            // position table
+        const size_t i = (size_t)(blockIdx.x - EMB_OWNERS) * EMB_THREADS + tid;
+        if (i >= (size_t)S * nchunk) return;
+        const T* src = dx + i * V;                              // position p = i / nchunk of sequence 0
+        const size_t stride = (size_t)S * H;
+        const int B = M / S;
         float acc[V];
 #pragma unroll
         for (int e = 0; e < V; ++e) acc[e] = 0.f;
-        for (int b = 0; b < B; ++b) {
-            float v[V];
-            load_vec<T>(dx + ((size_t)b * S + p) * H + c * V, v);
+        for (int b0 = 0; b0 < B; b0 += 8) {
+            uint4 q[8];
 #pragma unroll
-            for (int e = 0; e < V; ++e) acc[e] += v[e];
-        }
-        float* out = dwpe + (size_t)p * H + c * V;
+            for (int u = 0; u < 8; ++u) q[u] = *reinterpret_cast<const uint4*>(src + (size_t)min(b0 + u, B - 1) * stride);
 #pragma unroll
-        for (int e = 0; e < V; ++e) out[e] += acc[e];
-    }
-}
-
-// ---- embedding backward, token table.  One workgroup per position t.  It works only if t is the
-// first position that carries its token; it then adds up, in ascending position order, the rows of
-// every position with that token and adds the sum to the token's row.  One owner per table row
-// and a fixed order of additions: reproducible without atomics or a sort.
-template <typename T>
-__global__ __launch_bounds__(EDGE_THREADS) void embed_bwd_wte_kernel(const int* __restrict__ tokens, const T* __restrict__ dx,
-                                                                     float* __restrict__ dwte, int M, int H, int vocab) {
-    constexpr int V = Elem<T>::VEC;
-    __shared__ int hit[EDGE_THREADS];
-    __shared__ int earlier;
-    const int t = blockIdx.x, tid = threadIdx.x;
-    const int tok = min(max(tokens[t], 0), vocab - 1);
-    if (tid == 0) earlier = 0;
-    __syncthreads();
-    int seen = 0;
-    for (int u = tid; u < t; u += EDGE_THREADS) seen |= min(max(tokens[u], 0), vocab - 1) == tok;
-    if (seen) earlier = 1;                                      // benign race: every writer stores 1
-    __syncthreads();
-    if (earlier) return;                                        // uniform: read after the barrier
-    constexpr int MAXC = 2;                                     // chunks of V columns per thread: H <= 2 * 256 * V
-    float acc[MAXC][V];
-#pragma unroll
-    for (int i = 0; i < MAXC; ++i)
-#pragma unroll
-        for (int e = 0; e < V; ++e) acc[i][e] = 0.f;
-    for (int u0 = t - t % EDGE_THREADS; u0 < M; u0 += EDGE_THREADS) {
-        const int u = u0 + tid;
-        hit[tid] = u >= t && u < M && min(max(tokens[u], 0), vocab - 1) == tok;
-        __syncthreads();
-        for (int j = 0; j < EDGE_THREADS; ++j) {
-            if (!hit[j]) continue;                              // uniform
-#pragma unroll
-            for (int i = 0; i < MAXC; ++i) {
-                const int c = tid + i * EDGE_THREADS;
-                if (c < H / V) {
+            for (int u = 0; u < 8; ++u)
+                if (b0 + u < B) {
                     float v[V];
-                    load_vec<T>(dx + (size_t)(u0 + j) * H + c * V, v);
+                    load_vec<T>(reinterpret_cast<const T*>(&q[u]), v);
 #pragma unroll
-                    for (int e = 0; e < V; ++e) acc[i][e] += v[e];
+                    for (int e = 0; e < V; ++e) acc[e] += v[e];
                 }
+        }
+        float* out = dwpe + i * V;
+#pragma unroll
+        for (int e = 0; e < V; e += 4) {
+            f32x4_u t = *reinterpret_cast<const f32x4_u*>(out + e);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) t[k] += acc[e + k];
+            *reinterpret_cast<f32x4_u*>(out + e) = t;
+        }
+        return;
+    }
+    const int mine = (int)blockIdx.x;
+    for (int w0 = 0; w0 < M; w0 += EMB_WINDOW) {
+        // 1. the window's owned positions, ascending: wavefront k looks at positions [k, k+1) * 512
+        constexpr int GROUPS = EMB_WINDOW / EMB_WAVES / WAVE;
+        int tok[GROUPS];
+        unsigned long long own[GROUPS];
+        int n_wave = 0;
+        const int p0 = wave * (EMB_WINDOW / EMB_WAVES);
+#pragma unroll
+        for (int i = 0; i < GROUPS; ++i) {
+            const int t = w0 + p0 + i * WAVE + lane;
+            tok[i] = t < M ? min(max(tokens[t], 0), vocab - 1) : -1;        // ids outside the table are clamped, never followed
+        }
+#pragma unroll
+        for (int i = 0; i < GROUPS; ++i) {
+            own[i] = __ballot(tok[i] >= 0 && (tok[i] & (EMB_OWNERS - 1)) == mine);
+            n_wave += __popcll(own[i]);
+        }
+        if (lane == 0) sm.counts[wave] = n_wave;
+        if (tid == 0) sm.heads = 0;
+        __syncthreads();                                        // also: the previous window's list is no longer read
+        int at = 0, n = 0;
+#pragma unroll
+        for (int k = 0; k < EMB_WAVES; ++k) { const int c = sm.counts[k]; at += k < wave ? c : 0; n += c; }
+        n = __builtin_amdgcn_readfirstlane(n);
+#pragma unroll
+        for (int i = 0; i < GROUPS; ++i) {
+            if ((own[i] >> lane) & 1) {
+                const int j = at + __popcll(own[i] & ((1ull << lane) - 1));
+                sm.tok[j] = tok[i];
+                sm.pos[j] = (unsigned short)(p0 + i * WAVE + lane);
             }
+            at += __popcll(own[i]);
         }
         __syncthreads();
-    }
+        if (n == 0) continue;
+        // 2. heads: entries whose token does not occur earlier in the list (their order does not matter)
+        for (int j0 = 0; j0 < n; j0 += EMB_THREADS) {
+            const int j = j0 + tid;
+            const int v = j < n ? sm.tok[j] : -1;
+            bool seen = j >= n;
+            for (int k = 0; k < n; k += 16) {                   // entries beyond n are compared by nobody (k < j < n)
 #pragma unroll
-    for (int i = 0; i < MAXC; ++i) {
-        const int c = tid + i * EDGE_THREADS;
-        if (c < H / V) {
-            float* out = dwte + (size_t)tok * H + c * V;
-#pragma unroll
-            for (int e = 0; e < V; ++e) out[e] += acc[i][e];
+                for (int u = 0; u < 16; u += 4) {
+                    const int4 e = *reinterpret_cast<const int4*>(&sm.tok[k + u]);
+                    seen |= (k + u < j && e.x == v) || (k + u + 1 < j && e.y == v) || (k + u + 2 < j && e.z == v) || (k + u + 3 < j && e.w == v);
+                }
+                if (__ballot(!seen && k + 16 < j) == 0) break;
+            }
+            if (!seen) sm.head[atomicAdd(&sm.heads, 1)] = (unsigned short)j;
         }
+        __syncthreads();
+        const int heads = __builtin_amdgcn_readfirstlane(sm.heads);
+        const T* wdx = dx + (size_t)w0 * H;
+        EmbedRow<T, MAXC> row;
+        // 3. one wavefront per token
+        for (int hd = wave; hd < heads; hd += EMB_WAVES) {
+            const int first = __builtin_amdgcn_readfirstlane((int)sm.head[hd]), v = __builtin_amdgcn_readfirstlane(sm.tok[first]);
+            int count = 0;
+            for (int g = first & ~(WAVE - 1); g < n; g += WAVE) count += __popcll(__ballot(g + lane < n && sm.tok[min(g + lane, n - 1)] == v));
+            if (count > EMB_HOT) continue;
+            row.zero();
+            for (int g = first & ~(WAVE - 1); g < n; g += WAVE)
+                row.add_rows(wdx, sm.pos + g, __ballot(g + lane < n && sm.tok[min(g + lane, n - 1)] == v), nchunk, H, lane);
+            row.add_to(dwte + (size_t)v * H, nchunk, lane);
+        }
+        // 4. frequent tokens: all wavefronts (n > EMB_HOT is uniform, and so is every count)
+        if (n > EMB_HOT)
+            for (int hd = 0; hd < heads; ++hd) {
+                const int first = __builtin_amdgcn_readfirstlane((int)sm.head[hd]), v = __builtin_amdgcn_readfirstlane(sm.tok[first]);
+                int count = 0;
+                for (int g = first & ~(WAVE - 1); g < n; g += WAVE) count += __popcll(__ballot(g + lane < n && sm.tok[min(g + lane, n - 1)] == v));
+                if (count <= EMB_HOT) continue;
+                row.zero();
+                for (int g = first & ~(WAVE - 1); g < n; g += WAVE)
+                    row.add_rows(wdx, sm.pos + g, __ballot(g + lane < n && sm.tok[min(g + lane, n - 1)] == v) & (0xffull << (8 * wave)), nchunk, H, lane);
+                for (int k = 0; k < EMB_WAVES; ++k) {
+                    if (wave == k)
+#pragma unroll
+                        for (int i = 0; i < MAXC; ++i)
+                            if (lane + i * WAVE < nchunk) {
+                                float* o = hot_row + (lane + i * WAVE) * V;
+#pragma unroll
+                                for (int e = 0; e < V; ++e) {
+                                    row.a[i][e] += k ? o[e] : 0.f;
+                                    o[e] = row.a[i][e];
+                                }
+                            }
+                    __syncthreads();
+                }
+                if (wave == EMB_WAVES - 1) row.add_to(dwte + (size_t)v * H, nchunk, lane);
+            }
     }
 }
 
@@ -244,13 +390,22 @@ int chimera_op_embedding_bwd(int dtype, int tokens, int seq, int hidden, int voc
     const int vec = dtype == CHIMERA_F32 ? 4 : 8;
     if (hidden / vec > 2 * EDGE_THREADS) return fail(CHIMERA_EINVAL, "hidden=%d too wide for the embedding backward (max %d)", hidden, 2 * EDGE_THREADS * vec);
     hipStream_t s = (hipStream_t)hip_stream;
-    if (dtype == CHIMERA_F32) {
-        hipLaunchKernelGGL(embed_bwd_wte_kernel<float>, dim3(tokens), dim3(EDGE_THREADS), 0, s, d_tokens, (const float*)d_dx, d_dwte, tokens, hidden, vocab);
-        hipLaunchKernelGGL(embed_bwd_wpe_kernel<float>, dim3(seq), dim3(EDGE_THREADS), 0, s, (const float*)d_dx, d_dwpe, tokens / seq, seq, hidden);
-    } else {
-        hipLaunchKernelGGL(embed_bwd_wte_kernel<bf16_t>, dim3(tokens), dim3(EDGE_THREADS), 0, s, d_tokens, (const bf16_t*)d_dx, d_dwte, tokens, hidden, vocab);
-        hipLaunchKernelGGL(embed_bwd_wpe_kernel<bf16_t>, dim3(seq), dim3(EDGE_THREADS), 0, s, (const bf16_t*)d_dx, d_dwpe, tokens / seq, seq, hidden);
-    }
+    const int per_lane = (hidden / vec + WAVE - 1) / WAVE;
+    const size_t pieces = (size_t)seq * (hidden / vec), lds = sizeof(EmbedLds) + (size_t)hidden * sizeof(float);
+    const dim3 grid(EMB_OWNERS + (unsigned)((pieces + EMB_THREADS - 1) / EMB_THREADS)), block(EMB_THREADS);
+#define EMBED_BWD(T, C)                                                                                                \
+    hipLaunchKernelGGL((embed_bwd_kernel<T, C>), grid, block, lds, s, d_tokens, (const T*)d_dx, d_dwte, d_dwpe, tokens, seq, \
+                       hidden, vocab)
+#define EMBED_BWD_T(T)                                                                                                 \
+    do {                                                                                                               \
+        if (per_lane <= 1) EMBED_BWD(T, 1);                                                                            \
+        else if (per_lane <= 2) EMBED_BWD(T, 2);                                                                       \
+        else if (per_lane <= 4) EMBED_BWD(T, 4);                                                                       \
+        else EMBED_BWD(T, 8);                                                                                          \
+    } while (0)
+    if (dtype == CHIMERA_F32) EMBED_BWD_T(float); else EMBED_BWD_T(bf16_t);
+#undef EMBED_BWD_T
+#undef EMBED_BWD
     CHIMERA_LAUNCH_CHECK("embedding backward");
     return CHIMERA_OK;
 }
