@@ -283,7 +283,11 @@ int chimera_worker_bind(chimera_stage* down_stage, chimera_stage* up_stage);
 /* Replays chimera_schedule(CHIMERA_DIRECT, D, N, rank) on the bound stages in
  * list order, using each op's stash slot, and waits for the stream(s) once at
  * the end.  ENOMEM if a stage was bound with fewer slots than the schedule
- * needs.  Both stages must have no micro-batch in flight. */
+ * needs.  Both stages must have no micro-batch in flight.  Each stage's ops run
+ * in list order; the ops of different stages (different pipelines: no op of one
+ * needs a result of another) run beside each other on the stages' own streams,
+ * unless a stage has CHIMERA_OPT_OVERLAP = 0, their buffers overlap, or times are
+ * being taken (chimera_worker_set_timing, chimera_profile_enable). */
 int chimera_run_worker(int rank, int D, int N);
 /* Same for any algorithm; for the one-pipeline baselines only the down stage
  * is used and holds stage `rank`. */
@@ -305,7 +309,8 @@ int chimera_worker_bind_doubling(chimera_stage* down2, chimera_stage* up2);
  * halves of a backward.  With doubling every stage needs one stash slot more than the
  * largest slot index in its ops.  One wait per stream at the end. */
 int chimera_run_worker_pipes(int algo, int rank, int D, int N, int f);
-/* on != 0: bracket every op of the next replays with HIP events (off by default). */
+/* on != 0: bracket every op of the next replays with HIP events (off by default).  The stages
+ * then take turns, so that an op's time is its own. */
 int chimera_worker_set_timing(int on);
 /* Milliseconds the last chimera_run_worker* spent in forward ops and in
  * backward ops (HIP events around every op), and the op counts. */
