@@ -11,7 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libchimera.so")
 OBJ = os.path.join(HERE, "_build")
-SOURCES = ["schedule.cpp", "stage.hip", "rowwise.hip", "reference_kernels.hip", "gemm_mfma.hip", "attention_mfma.hip", "probe.hip", "edges.hip"]
+SOURCES = ["schedule.cpp", "stage.hip", "rowwise.hip", "reference_kernels.hip", "gemm_mfma.hip", "f32_mfma.hip", "attention_mfma.hip", "attention_f32.hip", "probe.hip", "edges.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
@@ -20,7 +20,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-u
 # in every loop step (softmax, rescaling); with the accumulators in the AGPR half of the register
 # file every such touch costs a v_accvgpr move each way, a quarter of the kernels' vector
 # instructions.  The VGPR form of the MFMA instructions avoids them.
-EXTRA_FLAGS = {"attention_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+EXTRA_FLAGS = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] for f in ("attention_mfma.hip", "attention_f32.hip")}
 
 
 def _compile(src):

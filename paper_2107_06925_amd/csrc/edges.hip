@@ -454,6 +454,7 @@ int chimera_head_loss(int dtype, int tokens, int hidden, int vocab, const void* 
     float* scratch = (float*)(ws + l.scratch);
     auto gemm = [&](const GemmArgs& g) {
         if (dtype == CHIMERA_BF16 && gemm_mfma_supports(g)) return gemm_mfma_bf16(g, hip_stream);
+        if (dtype == CHIMERA_F32 && gemm_f32_supports(g)) return gemm_f32(g, hip_stream);
         return gemm_reference(dtype, g, hip_stream);
     };
     // h = LayerNorm(y)

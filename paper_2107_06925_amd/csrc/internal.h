@@ -66,6 +66,12 @@ struct GemmArgs {
 };
 
 int gemm_reference(int dtype, const GemmArgs& g, void* stream);
+// float products on the matrix cores; the group: float-accumulating products of index-contiguous
+// operands in one launch, with column sums and overwriting as for the bf16 group below
+bool gemm_f32_supports(const GemmArgs& g);
+int gemm_f32(const GemmArgs& g, void* stream);
+bool gemm_f32_group_supports(int count, const GemmArgs* g);
+int gemm_f32_group(int count, const GemmArgs* g, float* const* bsum, int overwrite, void* stream);
 int gemm_mfma_bf16(const GemmArgs& g, void* stream);
 bool gemm_mfma_supports(const GemmArgs& g);
 // `count` float-accumulating products (index-contiguous operands, one contraction length) in one launch;
@@ -121,6 +127,9 @@ struct AttnArgs {
 };
 int attention_fwd_reference(int dtype, const AttnArgs& a, void* stream);
 int attention_bwd_reference(int dtype, const AttnArgs& a, void* stream);
+bool attention_f32_supports(const AttnArgs& a);
+int attention_fwd_f32(const AttnArgs& a, void* stream);
+int attention_bwd_f32(const AttnArgs& a, void* stream);     // does not need a.delta
 bool attention_mfma_supports(const AttnArgs& a);
 int attention_fwd_mfma(const AttnArgs& a, void* stream);
 int attention_bwd_mfma(const AttnArgs& a, void* stream);

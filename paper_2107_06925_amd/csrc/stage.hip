@@ -177,7 +177,10 @@ void layout(chimera_stage* st) {
 
 int gemm(chimera_stage* st, const GemmArgs& g, int cls, hipStream_t stream) {
     ProfScope prof(cls, 2.0 * g.m * g.n * g.k, stream);
-    if (st->dtype == CHIMERA_BF16 && st->kernels == 0 && gemm_mfma_supports(g)) return gemm_mfma_bf16(g, stream);
+    if (st->kernels == 0) {
+        if (st->dtype == CHIMERA_BF16 && gemm_mfma_supports(g)) return gemm_mfma_bf16(g, stream);
+        if (st->dtype == CHIMERA_F32 && gemm_f32_supports(g)) return gemm_f32(g, stream);
+    }
     return gemm_reference(st->dtype, g, stream);
 }
 
@@ -213,13 +216,19 @@ GemmArgs wgrad_args(int m, int n, int k, const void* x, const void* dy, float* d
 int linear_wgrad(chimera_stage* st, int m, int n, int k, const void* x, const void* dy, float* dw, hipStream_t stream) {
     return gemm(st, wgrad_args(m, n, k, x, dy, dw), PC_GEMM_WGRAD, stream);
 }
-// the four weight gradients of one block as one launch (bf16 matrix-core path only)
+// the four weight gradients of one block as one launch (matrix-core paths only)
 bool wgrad_group_ok(const chimera_stage* st, const GemmArgs (&g)[4]) {
-    return st->dtype == CHIMERA_BF16 && st->kernels == 0 && gemm_mfma_group_supports(4, g);
+    return st->kernels == 0 && (st->dtype == CHIMERA_BF16 ? gemm_mfma_group_supports(4, g) : gemm_f32_group_supports(4, g));
 }
 // One or two launches (the second takes the last row bands of one product on smaller tiles),
 // each timed as a class of its own so that a class is one kernel.
 int wgrad_group(chimera_stage* st, const GemmArgs (&g)[4], float* const (&db)[4], int overwrite, hipStream_t stream) {
+    if (st->dtype == CHIMERA_F32) {
+        double flop = 0;
+        for (int i = 0; i < 4; ++i) flop += 2.0 * g[i].m * g[i].n * g[i].k;
+        ProfScope prof(PC_GEMM_WGRAD, flop, stream);
+        return gemm_f32_group(4, g, db, overwrite, stream);
+    }
     GemmGroupPlan plan;
     TRY(gemm_mfma_group_plan(4, g, &plan));
     double flop = 0;
@@ -254,11 +263,13 @@ double attn_flop(const chimera_stage* st) {
 int st_attn_fwd(chimera_stage* st, const AttnArgs& a) {
     ProfScope prof(PC_ATTN_FWD, attn_flop(st), st->stream);
     if (st->dtype == CHIMERA_BF16 && st->kernels == 0 && attention_mfma_supports(a)) return attention_fwd_mfma(a, st->stream);
+    if (st->dtype == CHIMERA_F32 && st->kernels == 0 && attention_f32_supports(a)) return attention_fwd_f32(a, st->stream);
     return attention_fwd_reference(st->dtype, a, st->stream);
 }
 int st_attn_bwd(chimera_stage* st, const AttnArgs& a) {
     ProfScope prof(PC_ATTN_BWD, 2.0 * attn_flop(st), st->stream);
     if (st->dtype == CHIMERA_BF16 && st->kernels == 0 && attention_mfma_supports(a)) return attention_bwd_mfma(a, st->stream);
+    if (st->dtype == CHIMERA_F32 && st->kernels == 0 && attention_f32_supports(a)) return attention_bwd_f32(a, st->stream);
     return attention_bwd_reference(st->dtype, a, st->stream);
 }
 // algorithmic bytes of the row-wise kernels: every operand once, at the width it is stored in
@@ -970,6 +981,7 @@ int chimera_op_gemm(int dtype, int impl, int epilogue, int gelu_kind, int m, int
     g.bias = d_bias; g.r = d_r; g.c = d_c; g.c2 = d_c2; g.epilogue = epilogue; g.gelu_erf = gelu_kind ? 1 : 0;
     g.ws = d_workspace; g.ws_bytes = d_workspace ? workspace_bytes : 0;
     if (impl == 0 && dtype == CHIMERA_BF16 && gemm_mfma_supports(g)) return gemm_mfma_bf16(g, hip_stream);
+    if (impl == 0 && dtype == CHIMERA_F32 && gemm_f32_supports(g)) return gemm_f32(g, hip_stream);
     return gemm_reference(dtype, g, hip_stream);
 }
 
@@ -1040,6 +1052,7 @@ int chimera_op_attention_fwd(int dtype, int impl, int batch, int seq, int heads,
     a.batch = batch; a.seq = seq; a.heads = heads; a.head_dim = head_dim; a.causal = causal ? 1 : 0;
     a.qkv = d_qkv; a.ctx = d_ctx; a.lse = d_lse;
     if (impl == 0 && dtype == CHIMERA_BF16 && attention_mfma_supports(a)) return attention_fwd_mfma(a, hip_stream);
+    if (impl == 0 && dtype == CHIMERA_F32 && attention_f32_supports(a)) return attention_fwd_f32(a, hip_stream);
     return attention_fwd_reference(dtype, a, hip_stream);
 }
 
@@ -1051,6 +1064,7 @@ int chimera_op_attention_bwd(int dtype, int impl, int batch, int seq, int heads,
     a.batch = batch; a.seq = seq; a.heads = heads; a.head_dim = head_dim; a.causal = causal ? 1 : 0;
     a.qkv = d_qkv; a.ctx = (void*)d_ctx; a.lse = (float*)d_lse; a.dctx = d_dctx; a.dqkv = d_dqkv; a.delta = d_delta;
     if (impl == 0 && dtype == CHIMERA_BF16 && attention_mfma_supports(a)) return attention_bwd_mfma(a, hip_stream);
+    if (impl == 0 && dtype == CHIMERA_F32 && attention_f32_supports(a)) return attention_bwd_f32(a, hip_stream);
     return attention_bwd_reference(dtype, a, hip_stream);
 }
 

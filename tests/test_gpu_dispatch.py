@@ -66,3 +66,73 @@ def test_embedding_backward(tokens, seq, hidden, vocab, dtype):
     want_te, want_pe = eo.embedding_bwd(dx, ids, seq, vocab)
     assert_close(to_np(dwte), want_te, b.F32, "dwte")
     assert_close(to_np(dwpe), want_pe, b.F32, "dwpe")
+
+
+def _rand(shape, seed, dtype, scale=1.0):
+    a = np.random.default_rng(seed).standard_normal(shape).astype(np.float32) * scale
+    return synth.round_to_bf16(a) if dtype == b.BF16 else a
+
+
+# float products: 128 and 136 tiles of 64x64 (where the 32x32 form ends), one tile, ragged tiles, k with a remainder
+# in both forms and for four and eight wavefronts
+@pytest.mark.parametrize("m,n,k", [(512, 1024, 40), (520, 1024, 168), (8, 8, 8), (40, 104, 264), (200, 72, 1000), (1032, 520, 72)])
+@pytest.mark.parametrize("layout", ["fwd", "dgrad", "wgrad"])
+def test_float_gemm(m, n, k, layout):
+    import torch
+    print("float gemm", m, n, k, layout, flush=True)
+    a_kc, b_kc = {"fwd": (1, 0), "dgrad": (1, 1), "wgrad": (0, 0)}[layout]
+    A, B = _rand((m, k), 1, b.F32), _rand((k, n), 2, b.F32)
+    want = A.astype(np.float64) @ B.astype(np.float64)
+    c = torch.full((m, n), 0.5, device="cuda")
+    b.chimera_op_gemm(to_dev(A if a_kc else A.T, b.F32), to_dev(B.T if b_kc else B, b.F32), c, m, n, k, a_kc, b_kc,
+                      b.EPI_NONE if a_kc else b.EPI_ACCUM_F32)
+    assert_close(to_np(c) - (0.0 if a_kc else 0.5), want, b.F32)
+
+
+# float attention: head dimensions inside and at the end of each compiled size, rows around the 32-row tiles
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("batch,seq,heads,d", [(1, 33, 2, 4), (2, 31, 3, 36), (1, 129, 2, 64), (2, 160, 1, 100), (1, 97, 2, 128)])
+def test_float_attention(batch, seq, heads, d, causal):
+    _attention(b.F32, batch, seq, heads, d, causal)
+
+
+def _attention(dtype, batch, seq, heads, d, causal):
+    import torch
+    from oracle import block_oracle as bo
+    print("attention", dtype, batch, seq, heads, d, causal, flush=True)
+    H, M = heads * d, batch * seq
+    qkv, dctx = _rand((M, 3 * H), 1, dtype, 1.5), _rand((M, H), 2, dtype)
+    ctx64, probs = bo.attention_fwd(qkv.astype(np.float64), batch, seq, heads, causal)
+    want = bo.attention_bwd(dctx.astype(np.float64), qkv.astype(np.float64), probs, batch, seq, heads)
+    q = to_dev(qkv, dtype)
+    ctx, dqkv = torch.full((M, H), float("nan"), dtype=q.dtype, device="cuda"), torch.full_like(q, float("nan"))
+    lse, delta = torch.empty((batch, heads, seq), device="cuda"), torch.empty((batch, heads, seq), device="cuda")
+    b.chimera_op_attention_fwd(q, ctx, lse, batch, seq, heads, d, causal)
+    assert_close(to_np(ctx), ctx64, dtype, "ctx")
+    b.chimera_op_attention_bwd(q, ctx, lse, to_dev(dctx, dtype), dqkv, delta, batch, seq, heads, d, causal)
+    for name, lo in (("dq", 0), ("dk", H), ("dv", 2 * H)):
+        assert_close(to_np(dqkv)[:, lo:lo + H], want[:, lo:lo + H], dtype, name)
+
+
+# token counts that are no multiple of the contraction steps, and gradients that start from anything
+@pytest.mark.parametrize("dtype,hidden,heads,seq,microbatch", [(b.F32, 64, 2, 75, 1), (b.F32, 136, 2, 37, 3), (b.F32, 256, 4, 130, 2)])
+def test_stage_ragged_tokens(dtype, hidden, heads, seq, microbatch):
+    _stage(dtype, hidden, heads, seq, microbatch)
+
+
+def _stage(dtype, hidden, heads, seq, microbatch, causal=True):
+    from oracle import block_oracle as bo
+    from gpu_util import compare_grads, dtype_name
+    print("stage", dtype, hidden, heads, seq, microbatch, flush=True)
+    gain = synth.qk_gain_for(hidden) if dtype == b.BF16 else 1.0
+    st, params = make_stage(2, hidden, heads, seq, microbatch, dtype, 0, causal=causal, qk_gain=gain)
+    x, dy = synth.make_microbatch(seq * microbatch, hidden, 0, 0, dtype_name(dtype))
+    y, dx = st.set_io(0, to_dev(x, dtype), to_dev(dy, dtype))
+    st.grads.fill_(float("nan"))
+    st.zero_grads()
+    st.fwd(0)
+    st.bwd(0)
+    wy, wdx, gr = bo.stage_pass(x, dy, params, microbatch, seq, heads, causal)
+    compare_grads(st.read_grads(), gr, 2, hidden, dtype)
+    assert_close(to_np(y), wy, dtype, "y")
+    assert_close(to_np(dx), wdx, dtype, "dx")
