@@ -1,5 +1,8 @@
 // Fused attention on the CDNA4 matrix cores (bf16 in, float softmax and
-// accumulation), forward and backward, for head_dim 64 and 128.
+// accumulation), forward and backward, for head dimensions that are multiples of 8 up to
+// 128 (compiled for D = 64 and 128; below them the fixed operand's columns beyond the head
+// dimension are zeros, the others' repeat columns of the same head, and results beyond it
+// are not stored: half the matrix work at worst, while the softmax sets the time).
 //
 //   forward   per (sequence, head, 128 queries): loop over 64-key tiles with an
 //             online softmax; writes ctx and the log-sum-exp of every row.
@@ -60,14 +63,14 @@ template <int D> __device__ __forceinline__ int usw(int r) {
     return ((r & 3) << 2) | ((r >> 2) & 3);                                                     // 256-byte rows
 }
 template <int D>
-__device__ __forceinline__ void dma_utile(const bf16_t* __restrict__ g, int ld, int row0, int row_last, unsigned lds_base,
+__device__ __forceinline__ void dma_utile(const bf16_t* __restrict__ g, int ld, int row0, int row_last, int d, unsigned lds_base,
                                           int wave, int lane) {
     constexpr int KB = 64 * D * 2 / 1024, CPR = D / 8;
 #pragma unroll
     for (int n0 = 0; n0 < KB; n0 += NT / WAVE) {
         const int n = n0 + wave;
         const int row = n * (64 / CPR) + lane / CPR;
-        const int col = ((lane % CPR) ^ usw<D>(row)) << 3;
+        const int col = min((lane % CPR) ^ usw<D>(row), d / 8 - 1) << 3;
         lds_dma16(g + (size_t)min(row0 + row, row_last) * ld + col, lds_base + n * 1024);
     }
 }
@@ -137,15 +140,15 @@ inline unsigned attn_grid(const AttnArgs& a) {
 template <int D, bool CAUSAL>
 __global__ __launch_bounds__(NT) void attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx,
                                                       float* __restrict__ lse, int S, int heads, int batch,
-                                                      float scale_log2e) {
+                                                      int d, float scale_log2e) {
     constexpr int KS = D / 16, OT = D / 32;
     __shared__ __attribute__((aligned(16))) bf16_t Ks[2][64 * D];
     __shared__ __attribute__((aligned(16))) bf16_t Vs[2][64 * D];
-    const int H = heads * D, ld = 3 * H, bid = (int)blockIdx.x;
+    const int H = heads * d, ld = 3 * H, bid = (int)blockIdx.x;
     int rank, h, b;
     if (!attn_tile_of<CAUSAL>(bid, S, heads, batch, rank, h, b)) return;
     const int q0 = ((S + 127) / 128 - 1 - rank) * 128;       // longest (causal) tiles first
-    const bf16_t* base = qkv + (size_t)b * S * ld + h * D;
+    const bf16_t* base = qkv + (size_t)b * S * ld + h * d;
     const bf16_t* Kg = base + H;
     const bf16_t* Vg = base + 2 * H;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
@@ -156,12 +159,12 @@ __global__ __launch_bounds__(NT) void attn_fwd_kernel(const bf16_t* __restrict__
 
     const int kv_end = CAUSAL ? min(S, q0 + 128) : S;
     const int ntiles = (kv_end + 63) / 64;
-    dma_utile<D>(Kg, ld, 0, S - 1, ks0, wave, lane);
-    dma_utile<D>(Vg, ld, 0, S - 1, vs0, wave, lane);
+    dma_utile<D>(Kg, ld, 0, S - 1, d, ks0, wave, lane);
+    dma_utile<D>(Vg, ld, 0, S - 1, d, vs0, wave, lane);
 
     bf16x8 qf[KS];
 #pragma unroll
-    for (int kk = 0; kk < KS; ++kk) qf[kk] = load_frag(base + (size_t)qrow * ld + kk * 16 + g * 8, qrow < S);
+    for (int kk = 0; kk < KS; ++kk) qf[kk] = load_frag(base + (size_t)qrow * ld + kk * 16 + g * 8, qrow < S && kk * 16 + g * 8 < d);
 
     f32x16 o[OT];
 #pragma unroll
@@ -178,8 +181,8 @@ __global__ __launch_bounds__(NT) void attn_fwd_kernel(const bf16_t* __restrict__
         wait_vmcnt<0>();                   // this wavefront's share of tile t has landed
         __syncthreads();                   // everyone's has; and tile t-1 is consumed, so its buffer is free
         if (t + 1 < ntiles) {
-            dma_utile<D>(Kg, ld, k0 + 64, S - 1, ks0 + (buf ^ 1) * TILE_BYTES, wave, lane);
-            dma_utile<D>(Vg, ld, k0 + 64, S - 1, vs0 + (buf ^ 1) * TILE_BYTES, wave, lane);
+            dma_utile<D>(Kg, ld, k0 + 64, S - 1, d, ks0 + (buf ^ 1) * TILE_BYTES, wave, lane);
+            dma_utile<D>(Vg, ld, k0 + 64, S - 1, d, vs0 + (buf ^ 1) * TILE_BYTES, wave, lane);
         }
         const bool live = !CAUSAL || k0 <= wq0 + 31;          // wavefront-uniform: some key is visible
         if (live) {
@@ -250,7 +253,7 @@ __global__ __launch_bounds__(NT) void attn_fwd_kernel(const bf16_t* __restrict__
 
     if (qrow < S) {
         const float inv = 1.0f / lsum;
-        bf16_t* out = ctx + ((size_t)b * S + qrow) * H + h * D;
+        bf16_t* out = ctx + ((size_t)b * S + qrow) * H + h * d;
 #pragma unroll
         for (int t2 = 0; t2 < OT; ++t2)
 #pragma unroll
@@ -258,7 +261,7 @@ __global__ __launch_bounds__(NT) void attn_fwd_kernel(const bf16_t* __restrict__
                 bf16x4 v;
 #pragma unroll
                 for (int c = 0; c < 4; ++c) v[c] = (bf16_t)(o[t2][r4 * 4 + c] * inv);
-                *reinterpret_cast<bf16x4*>(out + t2 * 32 + 8 * r4 + 4 * g) = v;
+                if (t2 * 32 + 8 * r4 < d) *reinterpret_cast<bf16x4*>(out + t2 * 32 + 8 * r4 + 4 * g) = v;
             }
         if (g == 0) lse[((size_t)b * heads + h) * S + qrow] = (m + log2f(lsum)) * LN2;
     }
@@ -283,19 +286,19 @@ template <int D, bool CAUSAL>
 __device__ __forceinline__ void attn_bwd_dkv_role(AttnBwdLds<D>& sm, int bid, const bf16_t* __restrict__ qkv,
                                                   const bf16_t* __restrict__ dctx, const float* __restrict__ lse,
                                                   const float* __restrict__ delta, bf16_t* __restrict__ dqkv, int S,
-                                                  int heads, int batch, float scale) {
+                                                  int heads, int batch, int d, float scale) {
     constexpr int KS = D / 16, OT = D / 32;
     constexpr unsigned TILE_BYTES = 64 * D * 2;
     bf16_t (&Qs)[2][64 * D] = sm.t0;
     bf16_t (&Os)[2][64 * D] = sm.t1;
     float (&lse2)[2][64] = sm.lse2;
     float (&dl)[2][64] = sm.dl;
-    const int H = heads * D, ld = 3 * H;
+    const int H = heads * d, ld = 3 * H;
     int rank, h, b;
     if (!attn_tile_of<CAUSAL>(bid, S, heads, batch, rank, h, b)) return;
     const int j0 = rank * 128;             // the first keys meet the most queries
-    const bf16_t* base = qkv + (size_t)b * S * ld + h * D;
-    const bf16_t* dOg = dctx + (size_t)b * S * H + h * D;
+    const bf16_t* base = qkv + (size_t)b * S * ld + h * d;
+    const bf16_t* dOg = dctx + (size_t)b * S * H + h * d;
     const size_t stat0 = ((size_t)b * heads + h) * S;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -308,8 +311,8 @@ __device__ __forceinline__ void attn_bwd_dkv_role(AttnBwdLds<D>& sm, int bid, co
     float stat = 0.f;                      // lse (threads 0..63) or delta (threads 64..127) of the next tile
     auto fetch = [&](int t, int buf) {
         const int i0 = t * 64;
-        dma_utile<D>(base, ld, i0, S - 1, qs0 + buf * TILE_BYTES, wave, lane);
-        dma_utile<D>(dOg, H, i0, S - 1, os0 + buf * TILE_BYTES, wave, lane);
+        dma_utile<D>(base, ld, i0, S - 1, d, qs0 + buf * TILE_BYTES, wave, lane);
+        dma_utile<D>(dOg, H, i0, S - 1, d, os0 + buf * TILE_BYTES, wave, lane);
         if (tid < 128) {
             const int i = i0 + (tid & 63);
             stat = i < S ? (tid < 64 ? lse[stat0 + i] * LOG2E : delta[stat0 + i]) : 0.f;
@@ -320,8 +323,8 @@ __device__ __forceinline__ void attn_bwd_dkv_role(AttnBwdLds<D>& sm, int bid, co
     bf16x8 kf[KS], vf[KS];
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) {
-        kf[kk] = load_frag(base + H + (size_t)jrow * ld + kk * 16 + g * 8, jrow < S);
-        vf[kk] = load_frag(base + 2 * H + (size_t)jrow * ld + kk * 16 + g * 8, jrow < S);
+        kf[kk] = load_frag(base + H + (size_t)jrow * ld + kk * 16 + g * 8, jrow < S && kk * 16 + g * 8 < d);
+        vf[kk] = load_frag(base + 2 * H + (size_t)jrow * ld + kk * 16 + g * 8, jrow < S && kk * 16 + g * 8 < d);
     }
     f32x16 dk[OT], dv[OT];
 #pragma unroll
@@ -393,7 +396,7 @@ __device__ __forceinline__ void attn_bwd_dkv_role(AttnBwdLds<D>& sm, int bid, co
         if (t + 1 < ntiles) step(t + 1, std::integral_constant<int, 1>{});
     }
     if (jrow < S) {
-        bf16_t* out = dqkv + ((size_t)b * S + jrow) * ld + h * D;
+        bf16_t* out = dqkv + ((size_t)b * S + jrow) * ld + h * d;
 #pragma unroll
         for (int t2 = 0; t2 < OT; ++t2)
 #pragma unroll
@@ -401,6 +404,7 @@ __device__ __forceinline__ void attn_bwd_dkv_role(AttnBwdLds<D>& sm, int bid, co
                 bf16x4 a, c;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) { a[e] = (bf16_t)(dk[t2][r4 * 4 + e] * scale); c[e] = (bf16_t)dv[t2][r4 * 4 + e]; }
+                if (t2 * 32 + 8 * r4 >= d) continue;
                 *reinterpret_cast<bf16x4*>(out + H + t2 * 32 + 8 * r4 + 4 * g) = a;
                 *reinterpret_cast<bf16x4*>(out + 2 * H + t2 * 32 + 8 * r4 + 4 * g) = c;
             }
@@ -417,17 +421,17 @@ template <int D, bool CAUSAL, bool FORM_DELTA>
 __device__ __forceinline__ void attn_bwd_dq_role(AttnBwdLds<D>& sm, int bid, const bf16_t* __restrict__ qkv,
                                                  const bf16_t* __restrict__ dctx, const bf16_t* __restrict__ ctx,
                                                  const float* __restrict__ lse, float* __restrict__ delta,
-                                                 bf16_t* __restrict__ dqkv, int S, int heads, int batch, float scale) {
+                                                 bf16_t* __restrict__ dqkv, int S, int heads, int batch, int d, float scale) {
     constexpr int KS = D / 16, OT = D / 32;
     constexpr unsigned TILE_BYTES = 64 * D * 2;
     bf16_t (&Ks)[2][64 * D] = sm.t0;
     bf16_t (&Vs)[2][64 * D] = sm.t1;
-    const int H = heads * D, ld = 3 * H;
+    const int H = heads * d, ld = 3 * H;
     int rank, h, b;
     if (!attn_tile_of<CAUSAL>(bid, S, heads, batch, rank, h, b)) return;
     const int q0 = ((S + 127) / 128 - 1 - rank) * 128;
-    const bf16_t* base = qkv + (size_t)b * S * ld + h * D;
-    const bf16_t* dOg = dctx + (size_t)b * S * H + h * D;
+    const bf16_t* base = qkv + (size_t)b * S * ld + h * d;
+    const bf16_t* dOg = dctx + (size_t)b * S * H + h * d;
     const size_t stat0 = ((size_t)b * heads + h) * S;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -438,25 +442,25 @@ __device__ __forceinline__ void attn_bwd_dq_role(AttnBwdLds<D>& sm, int bid, con
     const int kv_end = CAUSAL ? min(S, q0 + 128) : S;
     const int ntiles = (kv_end + 63) / 64;
     auto fetch = [&](int t, int buf) {
-        dma_utile<D>(base + H, ld, t * 64, S - 1, ks0 + buf * TILE_BYTES, wave, lane);
-        dma_utile<D>(base + 2 * H, ld, t * 64, S - 1, vs0 + buf * TILE_BYTES, wave, lane);
+        dma_utile<D>(base + H, ld, t * 64, S - 1, d, ks0 + buf * TILE_BYTES, wave, lane);
+        dma_utile<D>(base + 2 * H, ld, t * 64, S - 1, d, vs0 + buf * TILE_BYTES, wave, lane);
     };
     fetch(0, 0);
 
     bf16x8 qf[KS], of[KS];
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) {
-        qf[kk] = load_frag(base + (size_t)qrow * ld + kk * 16 + g * 8, qrow < S);
-        of[kk] = load_frag(dOg + (size_t)qrow * H + kk * 16 + g * 8, qrow < S);
+        qf[kk] = load_frag(base + (size_t)qrow * ld + kk * 16 + g * 8, qrow < S && kk * 16 + g * 8 < d);
+        of[kk] = load_frag(dOg + (size_t)qrow * H + kk * 16 + g * 8, qrow < S && kk * 16 + g * 8 < d);
     }
     const float my_lse2 = qrow < S ? lse[stat0 + qrow] * LOG2E : 0.f;
     float my_dl = 0.f;
     if constexpr (FORM_DELTA) {
         // the lane pair (l, l^32) holds the whole row of dO
-        const bf16_t* Og = ctx + (size_t)b * S * H + h * D;
+        const bf16_t* Og = ctx + (size_t)b * S * H + h * d;
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) {
-            const bf16x8 cf = load_frag(Og + (size_t)qrow * H + kk * 16 + g * 8, qrow < S);
+            const bf16x8 cf = load_frag(Og + (size_t)qrow * H + kk * 16 + g * 8, qrow < S && kk * 16 + g * 8 < d);
 #pragma unroll
             for (int e = 0; e < 8; ++e) my_dl += (float)of[kk][e] * (float)cf[e];
         }
@@ -518,7 +522,7 @@ __device__ __forceinline__ void attn_bwd_dq_role(AttnBwdLds<D>& sm, int bid, con
         if (t + 1 < ntiles) step(t + 1, std::integral_constant<int, 1>{});
     }
     if (qrow < S) {
-        bf16_t* out = dqkv + ((size_t)b * S + qrow) * ld + h * D;
+        bf16_t* out = dqkv + ((size_t)b * S + qrow) * ld + h * d;
 #pragma unroll
         for (int t2 = 0; t2 < OT; ++t2)
 #pragma unroll
@@ -526,33 +530,33 @@ __device__ __forceinline__ void attn_bwd_dq_role(AttnBwdLds<D>& sm, int bid, con
                 bf16x4 a;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) a[e] = (bf16_t)(dq[t2][r4 * 4 + e] * scale);
-                *reinterpret_cast<bf16x4*>(out + t2 * 32 + 8 * r4 + 4 * g) = a;
+                if (t2 * 32 + 8 * r4 < d) *reinterpret_cast<bf16x4*>(out + t2 * 32 + 8 * r4 + 4 * g) = a;
             }
     }
 }
 
 // delta[sequence, head, position] = sum over the head dimension of dO * O: one lane per 8 elements
-// (16 bytes of each tensor), the D / 8 lanes of a (token, head) pair side by side.
+// (16 bytes of each tensor), D / 8 lanes of a (token, head) pair side by side (those beyond d add 0).
 template <int D>
 __global__ __launch_bounds__(NT) void attn_delta_kernel(const bf16_t* __restrict__ dctx, const bf16_t* __restrict__ ctx,
-                                                        float* __restrict__ delta, int S, int heads, int batch) {
+                                                        float* __restrict__ delta, int S, int heads, int batch, int d) {
     constexpr int LPH = D / 8;                                   // lanes per (token, head)
-    const size_t H = (size_t)heads * D, chunks = (size_t)batch * S * heads * LPH;
-    const size_t c = (size_t)blockIdx.x * NT + threadIdx.x;
+    const size_t th = ((size_t)blockIdx.x * NT + threadIdx.x) / LPH;
+    const int j = threadIdx.x % LPH;
+    const bool live = th < (size_t)batch * S * heads;
     float v = 0.f;
-    if (c < chunks) {
-        const bf16x8 a = *reinterpret_cast<const bf16x8*>(dctx + c * 8);
-        const bf16x8 o = *reinterpret_cast<const bf16x8*>(ctx + c * 8);
+    if (live && j * 8 < d) {
+        const bf16x8 a = *reinterpret_cast<const bf16x8*>(dctx + th * d + j * 8);
+        const bf16x8 o = *reinterpret_cast<const bf16x8*>(ctx + th * d + j * 8);
 #pragma unroll
         for (int e = 0; e < 8; ++e) v += (float)a[e] * (float)o[e];
     }
 #pragma unroll
     for (int off = LPH / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, WAVE);
-    if (c < chunks && (c % LPH) == 0) {
-        const size_t th = c / LPH, token = th / heads, h = th % heads;      // token = sequence * S + position
+    if (live && j == 0) {
+        const size_t token = th / heads, h = th % heads;         // token = sequence * S + position
         delta[((token / S) * heads + h) * S + token % S] = v;
     }
-    (void)H;
 }
 
 // Both backward kernels in one launch: workgroups come in groups of 8 (one per XCD), the groups
@@ -564,12 +568,12 @@ __global__ __launch_bounds__(NT) void attn_delta_kernel(const bf16_t* __restrict
 template <int D, bool CAUSAL>
 __global__ __launch_bounds__(NT) void attn_bwd_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx,
                                                       const float* __restrict__ lse, const float* __restrict__ delta,
-                                                      bf16_t* __restrict__ dqkv, int S, int heads, int batch, float scale) {
+                                                      bf16_t* __restrict__ dqkv, int S, int heads, int batch, int d, float scale) {
     __shared__ __attribute__((aligned(16))) AttnBwdLds<D> sm;
     const int blk = (int)blockIdx.x;
     const int role = (blk >> 3) & 1, bid = ((blk >> 4) << 3) | (blk & 7);
-    if (role == 0) attn_bwd_dkv_role<D, CAUSAL>(sm, bid, qkv, dctx, lse, delta, dqkv, S, heads, batch, scale);
-    else attn_bwd_dq_role<D, CAUSAL, false>(sm, bid, qkv, dctx, nullptr, lse, const_cast<float*>(delta), dqkv, S, heads, batch, scale);
+    if (role == 0) attn_bwd_dkv_role<D, CAUSAL>(sm, bid, qkv, dctx, lse, delta, dqkv, S, heads, batch, d, scale);
+    else attn_bwd_dq_role<D, CAUSAL, false>(sm, bid, qkv, dctx, nullptr, lse, const_cast<float*>(delta), dqkv, S, heads, batch, d, scale);
 }
 
 // The roles as launches of their own, dQ first (it forms delta): for many pairs, where each role
@@ -579,17 +583,17 @@ template <int D, bool CAUSAL>
 __global__ __launch_bounds__(NT) void attn_bwd_dq_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx,
                                                          const bf16_t* __restrict__ ctx, const float* __restrict__ lse,
                                                          float* __restrict__ delta, bf16_t* __restrict__ dqkv, int S,
-                                                         int heads, int batch, float scale) {
+                                                         int heads, int batch, int d, float scale) {
     __shared__ __attribute__((aligned(16))) AttnBwdLds<D> sm;
-    attn_bwd_dq_role<D, CAUSAL, true>(sm, (int)blockIdx.x, qkv, dctx, ctx, lse, delta, dqkv, S, heads, batch, scale);
+    attn_bwd_dq_role<D, CAUSAL, true>(sm, (int)blockIdx.x, qkv, dctx, ctx, lse, delta, dqkv, S, heads, batch, d, scale);
 }
 template <int D, bool CAUSAL>
 __global__ __launch_bounds__(NT) void attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx,
                                                           const float* __restrict__ lse, const float* __restrict__ delta,
-                                                          bf16_t* __restrict__ dqkv, int S, int heads, int batch,
+                                                          bf16_t* __restrict__ dqkv, int S, int heads, int batch, int d,
                                                           float scale) {
     __shared__ __attribute__((aligned(16))) AttnBwdLds<D> sm;
-    attn_bwd_dkv_role<D, CAUSAL>(sm, (int)blockIdx.x, qkv, dctx, lse, delta, dqkv, S, heads, batch, scale);
+    attn_bwd_dkv_role<D, CAUSAL>(sm, (int)blockIdx.x, qkv, dctx, lse, delta, dqkv, S, heads, batch, d, scale);
 }
 
 int check(const AttnArgs& a) {
@@ -600,7 +604,7 @@ int check(const AttnArgs& a) {
 }  // namespace
 
 bool attention_mfma_supports(const AttnArgs& a) {
-    if (a.head_dim != 64 && a.head_dim != 128) return false;
+    if (a.head_dim < 8 || a.head_dim > 128 || a.head_dim % 8) return false;
     if (a.batch < 1 || a.seq < 1 || a.heads < 1 || a.batch > 65535 || a.heads > 65535) return false;
     if (((unsigned long long)a.heads * a.batch + 7) * ((a.seq + 127) / 128) >= (1ull << 30)) return false;   // 1-D grid
     if ((uintptr_t)a.qkv & 15) return false;
@@ -615,8 +619,8 @@ int attention_fwd_mfma(const AttnArgs& a, void* stream) {
     hipStream_t s = (hipStream_t)stream;
 #define ATTN_FWD(D, C)                                                                                            \
     hipLaunchKernelGGL((attn_fwd_kernel<D, C>), grid, block, 0, s, (const bf16_t*)a.qkv, (bf16_t*)a.ctx, a.lse, a.seq, \
-                       a.heads, a.batch, sl2)
-    if (a.head_dim == 64) { if (a.causal) ATTN_FWD(64, true); else ATTN_FWD(64, false); }
+                       a.heads, a.batch, a.head_dim, sl2)
+    if (a.head_dim <= 64) { if (a.causal) ATTN_FWD(64, true); else ATTN_FWD(64, false); }
     else { if (a.causal) ATTN_FWD(128, true); else ATTN_FWD(128, false); }
 #undef ATTN_FWD
     CHIMERA_LAUNCH_CHECK("attention forward");
@@ -629,7 +633,7 @@ int attention_bwd_mfma(const AttnArgs& a, void* stream) {
     hipStream_t s = (hipStream_t)stream;
     const dim3 block(NT);
     const dim3 grid(attn_grid(a)), grid2(2 * attn_grid(a));    // one role / both roles; attn_grid is a multiple of 8
-    const size_t chunks = (size_t)a.batch * a.seq * a.heads * (a.head_dim / 8);
+    const size_t chunks = (size_t)a.batch * a.seq * a.heads * (a.head_dim <= 64 ? 8 : 16);
     const dim3 dgrid((unsigned)((chunks + NT - 1) / NT));
     const float scale = 1.0f / sqrtf((float)a.head_dim);
     // Few (sequence, head) pairs: one launch with both roles (measured: 448 workgroups per role
@@ -639,17 +643,17 @@ int attention_bwd_mfma(const AttnArgs& a, void* stream) {
     do {                                                                                                            \
         if (merged) {                                                                                               \
             hipLaunchKernelGGL((attn_delta_kernel<D>), dgrid, block, 0, s, (const bf16_t*)a.dctx, (const bf16_t*)a.ctx, \
-                               a.delta, a.seq, a.heads, a.batch);                                                   \
+                               a.delta, a.seq, a.heads, a.batch, a.head_dim);                                                   \
             hipLaunchKernelGGL((attn_bwd_kernel<D, C>), grid2, block, 0, s, (const bf16_t*)a.qkv, (const bf16_t*)a.dctx, \
-                               a.lse, a.delta, (bf16_t*)a.dqkv, a.seq, a.heads, a.batch, scale);                     \
+                               a.lse, a.delta, (bf16_t*)a.dqkv, a.seq, a.heads, a.batch, a.head_dim, scale);                     \
         } else {                                                                                                    \
             hipLaunchKernelGGL((attn_bwd_dq_kernel<D, C>), grid, block, 0, s, (const bf16_t*)a.qkv, (const bf16_t*)a.dctx, \
-                               (const bf16_t*)a.ctx, a.lse, a.delta, (bf16_t*)a.dqkv, a.seq, a.heads, a.batch, scale); \
+                               (const bf16_t*)a.ctx, a.lse, a.delta, (bf16_t*)a.dqkv, a.seq, a.heads, a.batch, a.head_dim, scale); \
             hipLaunchKernelGGL((attn_bwd_dkv_kernel<D, C>), grid, block, 0, s, (const bf16_t*)a.qkv, (const bf16_t*)a.dctx, \
-                               a.lse, a.delta, (bf16_t*)a.dqkv, a.seq, a.heads, a.batch, scale);                    \
+                               a.lse, a.delta, (bf16_t*)a.dqkv, a.seq, a.heads, a.batch, a.head_dim, scale);                    \
         }                                                                                                           \
     } while (0)
-    if (a.head_dim == 64) { if (a.causal) ATTN_BWD(64, true); else ATTN_BWD(64, false); }
+    if (a.head_dim <= 64) { if (a.causal) ATTN_BWD(64, true); else ATTN_BWD(64, false); }
     else { if (a.causal) ATTN_BWD(128, true); else ATTN_BWD(128, false); }
 #undef ATTN_BWD
     CHIMERA_LAUNCH_CHECK("attention backward");
