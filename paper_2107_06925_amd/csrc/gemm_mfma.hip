@@ -56,9 +56,11 @@ __device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ (row & 7
 
 typedef bf16_t bf16x4 __attribute__((ext_vector_type(4)));
 
+// The XOR of k-row k's 32-byte column blocks in a [BK][ROWS] tile (rows of 128 bytes have only four).
+template <int ROWS> __device__ __forceinline__ int kswz(int k) { return ROWS == 64 ? k & 2 : (k & 3) << 1; }
 // LDS element offset of the 16-byte chunk `ic` (8 rows) of k-row `k` in a [BK][ROWS] tile
 template <int ROWS> __device__ __forceinline__ int mc_off(int k, int ic) {
-    return k * ROWS + (((ic >> 1) ^ ((k & 3) << 1)) << 4) + ((ic & 1) << 3);
+    return k * ROWS + (((ic >> 1) ^ kswz<ROWS>(k)) << 4) + ((ic & 1) << 3);
 }
 
 template <int ROWS, int NT, bool KC> struct Staged {
@@ -125,7 +127,7 @@ __device__ __forceinline__ bf16x8 read_frag(const bf16_t* lds, int r0, int kk, i
         const int i = lane & 15, blk = (r0 >> 4) + ((lane >> 4) & 1);      // 16-row column block of this lane group
         const int k = kk * 16 + (lane >> 5) * 8 + (i >> 2);                // row this lane addresses (first read)
         typedef bf16x4 __attribute__((address_space(3))) * lds_v4;
-        const bf16_t* p0 = lds + k * ROWS + ((blk ^ ((k & 3) << 1)) << 4) + ((i & 3) << 2);
+        const bf16_t* p0 = lds + k * ROWS + ((blk ^ kswz<ROWS>(k)) << 4) + ((i & 3) << 2);
         const bf16_t* p1 = p0 + 4 * ROWS;                                  // rows k+4..k+7: same swizzle
         const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_v4)p0);
         const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_v4)p1);
@@ -458,12 +460,14 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_kernel(
 // issued through inline assembly so that the waits can be counted by hand
 // (s_waitcnt vmcnt(n) with the younger stages still outstanding).
 // Nothing can be zero-filled on this path: rows beyond the matrix are redirected to a
-// valid row (they only feed outputs that are never stored), and k must be a multiple
-// of BK (the caller falls back to the register-staged kernel otherwise).
+// valid row (they only feed outputs that are never stored), and the k % BK values behind
+// the last whole step come first, through registers and zero-filled, while the DMA of the
+// first whole steps is under way.
 
 // One output tile; `block_id` numbers the tiles of this product.  ONLY_EPI >= 0 compiles
 // that epilogue alone.
-template <int BM, int BN, int WGM, int WGN, int WGK, int NS, bool A_KC, bool B_KC, int ONLY_EPI>
+// SPS: ring stages per barrier (NS stages of BK each).
+template <int BM, int BN, int WGM, int WGN, int WGK, int NS, int SPS, bool A_KC, bool B_KC, int ONLY_EPI>
 __device__ __forceinline__ void gemm_async_tile(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, const bf16_t* __restrict__ bias,
     const bf16_t* __restrict__ R, void* __restrict__ C, bf16_t* __restrict__ C2, int m, int n, int k, int lda,
@@ -498,7 +502,8 @@ __device__ __forceinline__ void gemm_async_tile(
     // slots this thread's lane position fills.
     const bf16_t* ga[CA];
     const bf16_t* gb[CB];
-    auto source = [&](const bf16_t* base, int ld, int row0, int nrows, int rows_in_tile, bool kc, int slot) {
+    auto source = [&](const bf16_t* base, int ld, int row0, int nrows, auto rows_c, bool kc, int slot) {
+        constexpr int rows_in_tile = decltype(rows_c)::value;
         if (kc) {
             const int row = slot >> 3, p = slot & 7;
             const int c = p ^ (row & 7) ^ ((row >> 3) & 7);
@@ -507,15 +512,15 @@ __device__ __forceinline__ void gemm_async_tile(
         }
         const int per_row = rows_in_tile / 8;
         const int kk = slot / per_row, pc = slot % per_row;
-        const int ic = ((((pc >> 1) ^ ((kk & 3) << 1)) << 1) | (pc & 1));
+        const int ic = (((pc >> 1) ^ kswz<rows_in_tile>(kk)) << 1) | (pc & 1);
         int gi = row0 + ic * 8;
         if (gi >= nrows) gi = 0;
         return base + (size_t)kk * ld + gi;
     };
 #pragma unroll
-    for (int it = 0; it < CA; ++it) ga[it] = source(A, lda, i0, m, BM, A_KC, it * NT + tid);
+    for (int it = 0; it < CA; ++it) ga[it] = source(A, lda, i0, m, std::integral_constant<int, BM>{}, A_KC, it * NT + tid);
 #pragma unroll
-    for (int it = 0; it < CB; ++it) gb[it] = source(B, ldb, j0, n, BN, B_KC, it * NT + tid);
+    for (int it = 0; it < CB; ++it) gb[it] = source(B, ldb, j0, n, std::integral_constant<int, BN>{}, B_KC, it * NT + tid);
     const size_t step_a = A_KC ? (size_t)BK : (size_t)BK * lda;
     const size_t step_b = B_KC ? (size_t)BK : (size_t)BK * ldb;
     // LDS byte address of stage 0 (32-bit pointer in the LDS address space)
@@ -552,16 +557,8 @@ __device__ __forceinline__ void gemm_async_tile(
         for (int r = 0; r < 16; ++r) cs[b][r] = 0.f;
 
     const int KT = k / BK;
-#pragma unroll
-    for (int st = 0; st < NS - 1; ++st)
-        if (st < KT) issue(st);
-    int cur = 0, nxt = NS - 1;                 // stage computed now / stage the next issue fills
-    for (int kt = 0; kt < KT; ++kt) {
-        // the oldest outstanding group (step kt) must have landed; up to NS-2 younger ones may fly on
-        if (kt + NS - 2 < KT) wait_vmcnt<(NS - 2) * (CA + CB)>(); else wait_vmcnt<0>();
-        __syncthreads();                       // every wavefront's part of step kt is in LDS; step kt-1 is consumed
-        if (kt + NS - 1 < KT) issue(nxt);
-        const bf16_t* As = lds + cur * STAGE;
+    auto compute = [&](int stage) {
+        const bf16_t* As = lds + stage * STAGE;
         const bf16_t* Bs = As + BM * BK;
 #pragma unroll
         for (int ks = 0; ks < KSUB; ++ks) {
@@ -581,8 +578,37 @@ __device__ __forceinline__ void gemm_async_tile(
 #pragma unroll
                     for (int b = 0; b < TN; ++b) cs[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, bfr[b], cs[b], 0, 0, 0);
         }
-        cur = cur + 1 == NS ? 0 : cur + 1;
-        nxt = nxt + 1 == NS ? 0 : nxt + 1;
+    };
+    if (k % BK) {
+        Staged<BM, NT, A_KC> ra;
+        Staged<BN, NT, B_KC> rb;
+        load_tile<BM, NT, A_KC>(ra, A, lda, i0, m, KT * BK, k, tid);
+        load_tile<BN, NT, B_KC>(rb, B, ldb, j0, n, KT * BK, k, tid);
+#pragma unroll
+        for (int st = 0; st < NS - SPS; ++st)
+            if (st < KT) issue(st);
+        bf16_t* last = lds + (NS - 1) * STAGE;             // the stage that the first issue of the loop fills
+        store_tile<BM, NT, A_KC>(ra, last, tid);
+        store_tile<BN, NT, B_KC>(rb, last + BM * BK, tid);
+        __syncthreads();
+        compute(NS - 1);
+    } else {
+#pragma unroll
+        for (int st = 0; st < NS - SPS; ++st)
+            if (st < KT) issue(st);
+    }
+    int cur = 0, nxt = NS - SPS;               // stage computed now / stage the next issue fills
+    auto advance = [](int& st) { st = st + 1 == NS ? 0 : st + 1; };
+    for (int kt = 0; kt < KT; kt += SPS) {
+        // the SPS oldest outstanding stages must have landed; up to NS - 2 SPS younger ones may fly on
+        if (kt + NS - SPS <= KT) wait_vmcnt<(NS - 2 * SPS) * (CA + CB)>(); else wait_vmcnt<0>();
+        __syncthreads();                       // every wavefront's part of this step is in LDS; the previous one is consumed
+#pragma unroll
+        for (int u = 0; u < SPS; ++u)
+            if (kt + NS - SPS + u < KT) { issue(nxt); advance(nxt); }
+#pragma unroll
+        for (int u = 0; u < SPS; ++u)
+            if (SPS == 1 || kt + u < KT) { compute(cur); advance(cur); }
     }
 
     const int cb0 = j0 + wn0;
@@ -627,6 +653,41 @@ __device__ __forceinline__ void gemm_async_tile(
                 put_col_sums(v);
             }
         finish(acc, i0 + wm0);
+    } else if constexpr (TM == 1) {
+        // As below, but there is only one band of rows: the second wavefront hands it over and is done.
+        static_assert(WGK == 2 && sizeof(lds) >= (size_t)WGM * WGN * TN * 4 * 64 * sizeof(float4) + BN * sizeof(float), "LDS too small");
+        float4* xch = reinterpret_cast<float4*>(lds) + (size_t)wmn * TN * 4 * 64 + lane;
+        float* xcs = reinterpret_cast<float*>(reinterpret_cast<float4*>(lds) + (size_t)WGM * WGN * TN * 4 * 64) + wn0;
+        if (wk == 1) {
+            if constexpr (ONLY_EPI == EPI_ACCUM_F32)
+                if (col_sums && lane < 32)
+#pragma unroll
+                    for (int b = 0; b < TN; ++b) xcs[b * 32 + lane] = cs[b][0];
+#pragma unroll
+            for (int b = 0; b < TN; ++b)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    xch[(b * 4 + q) * 64] = make_float4(acc[0][b][4 * q], acc[0][b][4 * q + 1], acc[0][b][4 * q + 2], acc[0][b][4 * q + 3]);
+        }
+        __syncthreads();
+        if (wk == 0) {
+#pragma unroll
+            for (int b = 0; b < TN; ++b)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float4 v = xch[(b * 4 + q) * 64];
+                    acc[0][b][4 * q] += v.x; acc[0][b][4 * q + 1] += v.y; acc[0][b][4 * q + 2] += v.z; acc[0][b][4 * q + 3] += v.w;
+                }
+            if constexpr (ONLY_EPI == EPI_ACCUM_F32)
+                if (col_sums) {
+                    float v[TN];
+#pragma unroll
+                    for (int b = 0; b < TN; ++b) v[b] = cs[b][0] + (lane < 32 ? xcs[b * 32 + lane] : 0.f);
+                    put_col_sums(v);
+                }
+        }
+        __syncthreads();                       // the exchange area becomes the slabs
+        if (wk == 0) finish(acc, i0 + wm0);
     } else {
         // Two wavefronts hold partial sums of the same WM x WN block (one per k slice).  Each
         // keeps the upper or lower half of the rows: it hands the other half to its partner
@@ -682,12 +743,12 @@ __device__ __forceinline__ void gemm_async_tile(
     }
 }
 
-template <int BM, int BN, int WGM, int WGN, int WGK, int NS, bool A_KC, bool B_KC>
+template <int BM, int BN, int WGM, int WGN, int WGK, int NS, int SPS, bool A_KC, bool B_KC>
 __global__ __launch_bounds__(WGM* WGN * WGK * 64) void gemm_bf16_async_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, const bf16_t* __restrict__ bias,
     const bf16_t* __restrict__ R, void* __restrict__ C, bf16_t* __restrict__ C2, int m, int n, int k, int lda,
     int ldb, int epi, int epi_flag, int res_types, int tiles_m, int tiles_n, int group_m) {
-    gemm_async_tile<BM, BN, WGM, WGN, WGK, NS, A_KC, B_KC, -1>(A, B, bias, R, C, C2, m, n, k, lda, ldb, epi, epi_flag,
+    gemm_async_tile<BM, BN, WGM, WGN, WGK, NS, SPS, A_KC, B_KC, -1>(A, B, bias, R, C, C2, m, n, k, lda, ldb, epi, epi_flag,
                                                                 res_types, tiles_m, tiles_n, group_m, (int)blockIdx.x);
 }
 
@@ -708,7 +769,7 @@ struct GemmGroup {
     int overwrite;               // results replace C and bsum instead of being added
 };
 
-template <int BM, int BN, int WGM, int WGN, int WGK, int NS, bool A_KC, bool B_KC>
+template <int BM, int BN, int WGM, int WGN, int WGK, int NS, int SPS, bool A_KC, bool B_KC>
 __global__ __launch_bounds__(WGM* WGN * WGK * 64) void gemm_bf16_async_group_kernel(GemmGroup grp) {
     // each XCD takes a contiguous range of the group's tiles (products laid end to end), so that
     // its L2 sees few operand panels: one product's tiles are not dealt over all eight XCDs
@@ -719,7 +780,7 @@ __global__ __launch_bounds__(WGM* WGN * WGK * 64) void gemm_bf16_async_group_ker
 #pragma unroll
     for (int i = 1; i < GROUP_MAX; ++i)
         if (i < grp.count && gid >= grp.first[i]) p = i;
-    gemm_async_tile<BM, BN, WGM, WGN, WGK, NS, A_KC, B_KC, EPI_ACCUM_F32>(
+    gemm_async_tile<BM, BN, WGM, WGN, WGK, NS, SPS, A_KC, B_KC, EPI_ACCUM_F32>(
         grp.a[p], grp.b[p], nullptr, nullptr, grp.c[p], nullptr, grp.m[p], grp.n[p], grp.k, grp.lda[p], grp.ldb[p],
         EPI_ACCUM_F32, grp.overwrite, 0, grp.tiles_m[p], grp.tiles_n[p], grp.group_m[p], gid - grp.first[p], grp.bsum[p],
         false);
@@ -794,6 +855,13 @@ TileChoice forced_tile() { return tuning().forced; }
 
 constexpr int MAX_SPLITS = 8;
 
+// 64x64 tiles while they all fit on the chip at once, two per CU: a smaller product is bound by
+// its chain of latencies and by how many CUs pull its operands, not by the bytes a small tile
+// costs.  Measured, 128x128 -> 64x64: 400 x 960 x 320 6.6 -> 4.3 us, 632 x 1600 x 6400 (65 tiles of
+// 128x128, 250 of 64x64) 49 -> 29, 1264 x 1600 x 1600 (130, 500) 16.2 -> 12.7; beyond it turns:
+// 1024 x 2560 x 640 (160, 640) 9.8 -> 11.3, 632 x 4800 x 1600 (190, 750) 17.6 -> 21.
+bool small_tiles(long tiles64) { return tiles64 <= 2 * NUM_CUS && tuning().async_mode == ASYNC_AUTO; }
+
 // 256x256 (8 wavefronts) once the output has enough such tiles for most of the 256 CUs,
 // else 128x128 (4 wavefronts, two workgroups per CU); thresholds measured on MI355X.
 // A CU fills LDS from L2 at roughly 64 bytes per clock, so a 128x128x64 step (32 KiB for
@@ -813,6 +881,7 @@ TileChoice choose_tile(const GemmArgs& g) {
     }
     // (measured at 2048 x 4800 x 1600: 152 tiles of 256x256 on 256 CUs take 42 us, 608 of 128x128 48 us)
     if (t256 >= 144) return {256, 256, 1};
+    if (small_tiles((long)((g.m + 63) / 64) * ((g.n + 63) / 64))) return {64, 64, 1};
     return {128, 128, 1};
 }
 
@@ -835,13 +904,13 @@ int launch_layout(const GemmArgs& g, int splits, hipStream_t s) {
     return CHIMERA_OK;
 }
 
-template <int BM, int BN, int WGM, int WGN, int WGK, int NS>
+template <int BM, int BN, int WGM, int WGN, int WGK, int NS, int SPS = 1>
 int launch_async(const GemmArgs& g, hipStream_t s) {
     const int tm = (g.m + BM - 1) / BM, tn = (g.n + BN - 1) / BN;
     const dim3 grid(tm * tn), block(WGM * WGN * WGK * 64);
     const int gm = raster_group(tm, tn, (tm * tn + 7) / 8, BM, BN);
 #define CHIMERA_GEMM_LAUNCH(AKC, BKC)                                                                                \
-    hipLaunchKernelGGL((gemm_bf16_async_kernel<BM, BN, WGM, WGN, WGK, NS, AKC, BKC>), grid, block, 0, s,                   \
+    hipLaunchKernelGGL((gemm_bf16_async_kernel<BM, BN, WGM, WGN, WGK, NS, SPS, AKC, BKC>), grid, block, 0, s,                   \
                        (const bf16_t*)g.a, (const bf16_t*)g.b, (const bf16_t*)g.bias, (const bf16_t*)g.r, g.c,        \
                        (bf16_t*)g.c2, g.m, g.n, g.k, g.lda, g.ldb, g.epilogue, epilogue_flag(g),                            \
                        (g.r_f32 ? 1 : 0) | (g.c_f32 ? 2 : 0), tm, tn, gm)
@@ -861,13 +930,13 @@ void note_group_kernel(bool first, const char* name) {
     std::snprintf(dst + used, sizeof g_last_group_kernel - used, "%s%s", used ? " + " : "", name);
 }
 
-template <int BM, int BN, int WGM, int WGN, int WGK, int NS>
+template <int BM, int BN, int WGM, int WGN, int WGK, int NS, int SPS = 1>
 int launch_group(const GemmGroup& grp, hipStream_t s, bool first = true) {
     char name[96];
-    std::snprintf(name, sizeof name, "gemm_bf16_async_group_kernel<%d,%d,%d,%d,%d,%d,false,false>", BM, BN, WGM, WGN, WGK, NS);
+    std::snprintf(name, sizeof name, "gemm_bf16_async_group_kernel<%d,%d,%d,%d,%d,%d,%d,false,false>", BM, BN, WGM, WGN, WGK, NS, SPS);
     note_group_kernel(first, name);
     const dim3 grid(grp.first[grp.count]), block(WGM * WGN * WGK * 64);
-    hipLaunchKernelGGL((gemm_bf16_async_group_kernel<BM, BN, WGM, WGN, WGK, NS, false, false>), grid, block, 0, s, grp);
+    hipLaunchKernelGGL((gemm_bf16_async_group_kernel<BM, BN, WGM, WGN, WGK, NS, SPS, false, false>), grid, block, 0, s, grp);
     CHIMERA_LAUNCH_CHECK("bf16 gemm group");
     return CHIMERA_OK;
 }
@@ -876,7 +945,8 @@ int launch_group(const GemmGroup& grp, hipStream_t s, bool first = true) {
 
 bool gemm_mfma_supports(const GemmArgs& g) {
     if (!g.a_kc && g.b_kc) return false;                       // layout no linear layer needs
-    if ((g.k % 8) || (g.n % 8) || (g.lda % 8) || (g.ldb % 8)) return false;
+    if ((g.n % 8) || (g.lda % 8) || (g.ldb % 8)) return false;
+    if ((g.a_kc || g.b_kc) && (g.k % 8)) return false;         // index-contiguous operands are masked row by row: any k
     if (!g.a_kc && (g.m % 8)) return false;
     if (((uintptr_t)g.a | (uintptr_t)g.b) & 15) return false;  // 16-byte vector loads
     // operand elements are addressed with 32-bit offsets
@@ -904,7 +974,6 @@ int gemm_mfma_bf16(const GemmArgs& g, void* stream) {
     const TileChoice t = choose_tile(g);
     if (t.splits > 1 && (size_t)((g.m + 255) / 256) * ((g.n + 255) / 256) * sizeof(unsigned) > SPLITK_COUNTER_BYTES)
         return fail(CHIMERA_EINVAL, "too many tiles for split-K");
-    // the async kernels cannot zero-fill: whole k steps only, and at least 8 rows on each side.
     // 128x128 tiles: with one workgroup per CU, a workgroup of 4 wavefronts leaves one wavefront
     // per SIMD, and nothing covers its LDS latency and the barrier of every k step; then 8
     // wavefronts share the tile, two per 64x64 block, each taking half of every k step (their
@@ -913,7 +982,7 @@ int gemm_mfma_bf16(const GemmArgs& g, void* stream) {
     // form with its 2-stage ring (64 KiB of LDS, two workgroups per CU) is faster: 416 tiles of a
     // 4096 x 1600 x 6400 product take 109 us against 124 us, 208 tiles (2048 rows) 89 against 62.
     const int mode = tuning().async_mode;
-    const bool can_async = g.k % BK == 0 && g.m >= 8 && g.n >= 8 && t.splits == 1 && mode != ASYNC_OFF;
+    const bool can_async = t.splits == 1 && mode != ASYNC_OFF;
     if (can_async) {
         if (t.bm == 256 && t.bn == 256) {
             const int tm = (g.m + 255) / 256, tn = (g.n + 255) / 256;
@@ -936,6 +1005,12 @@ int gemm_mfma_bf16(const GemmArgs& g, void* stream) {
             }
             return launch_async<256, 256, 2, 4, 1, 2>(g, s);
         }
+        if (t.bm == 64) {
+            // one tile per CU at most: all of LDS for one workgroup, an eight-stage ring walked two stages per
+            // barrier by two wavefronts per SIMD (256 x 256 x 1024: 6.7 -> 6.1 us; 632 x 1600 x 6400: 28.4 -> 25.4)
+            if ((long)((g.m + 63) / 64) * ((g.n + 63) / 64) <= NUM_CUS) return launch_async<64, 64, 2, 2, 2, 8, 2>(g, s);
+            return launch_async<64, 64, 1, 2, 2, 4>(g, s);
+        }
         if (t.bm == 128 && t.bn == 128) {
             const long t128 = (long)((g.m + 127) / 128) * ((g.n + 127) / 128);
             const bool ksplit = mode != ASYNC_AUTO ? mode == ASYNC_KSLICED : t128 <= NUM_CUS;
@@ -952,7 +1027,7 @@ bool gemm_mfma_group_supports(int count, const GemmArgs* g) {
     if (count < 1 || count > GROUP_MAX || !g) return false;
     for (int i = 0; i < count; ++i) {
         if (g[i].a_kc || g[i].b_kc || g[i].epilogue != EPI_ACCUM_F32 || !gemm_mfma_supports(g[i])) return false;
-        if (g[i].k != g[0].k || g[i].k % BK || g[i].m < 8 || g[i].n < 8) return false;
+        if (g[i].k != g[0].k) return false;
         if ((uintptr_t)g[i].c & 15) return false;
     }
     return true;
@@ -975,6 +1050,7 @@ int launch_group_tiled(int count, const GemmArgs* g, float* const* bsum, int ove
     for (int i = 0; i < count; ++i) grp.group_m[i] = raster_group(grp.tiles_m[i], grp.tiles_n[i], (tiles + 7) / 8, tile, tile);
     for (int i = count; i <= GROUP_MAX; ++i) grp.first[i] = tiles;
     if (tile == 256) return launch_group<256, 256, 2, 4, 1, 2>(grp, stream, first);
+    if (tile == 64) return tiles <= NUM_CUS ? launch_group<64, 64, 2, 2, 2, 8, 2>(grp, stream, first) : launch_group<64, 64, 1, 2, 2, 4>(grp, stream, first);
     // two workgroups per CU or the k-sliced 8-wavefront form
     const int mode = tuning().async_mode;
     const bool ksplit = mode != ASYNC_AUTO ? mode == ASYNC_KSLICED : tiles <= NUM_CUS;
@@ -989,7 +1065,7 @@ int gemm_mfma_group_plan(int count, const GemmArgs* g, GemmGroupPlan* plan) {
     if (!plan) return fail(CHIMERA_EINVAL, "plan is NULL");
     if (!gemm_mfma_group_supports(count, g))
         return fail(CHIMERA_EINVAL, "bf16 gemm group: 1..%d float-accumulating products with index-contiguous operands, "
-                    "one contraction length (a multiple of %d)", GROUP_MAX, BK);
+                    "one contraction length", GROUP_MAX);
     static_assert(GROUP_MAX == sizeof(plan->head) / sizeof(plan->head[0]), "plan size");
     plan->count = count; plan->has_tail = 0; plan->tail_of = -1;
     for (int i = 0; i < count; ++i) plan->head[i] = g[i];
@@ -1000,7 +1076,10 @@ int gemm_mfma_group_plan(int count, const GemmArgs* g, GemmGroupPlan* plan) {
     long t256 = 0;
     for (int i = 0; i < count; ++i) t256 += (long)((g[i].m + 255) / 256) * ((g[i].n + 255) / 256);
     const TileChoice forced = forced_tile();
-    plan->tile = forced.bm == 256 || forced.bm == 128 ? forced.bm : (t256 >= 160 ? 256 : 128);
+    long t64 = 0;
+    for (int i = 0; i < count; ++i) t64 += (long)((g[i].m + 63) / 64) * ((g[i].n + 63) / 64);
+    plan->tile = forced.bm == 256 || forced.bm == 128 ? forced.bm
+                 : t256 >= 160 ? 256 : small_tiles(t64) ? 64 : 128;
     if (plan->tile != 256 || forced.bm) return CHIMERA_OK;
     // a nearly empty last round: the last row bands of one product go to a 128x128 launch
     int best_p = -1, best_b = 0;

@@ -998,6 +998,7 @@ int chimera_op_gemm_group_accumulate(int count, const int* h_m, const int* h_n, 
                                      float* const* h_bsum, int overwrite, void* hip_stream) {
     if (count < 1 || count > 4) return fail(CHIMERA_EINVAL, "group of %d products (1..4)", count);
     if (!h_m || !h_n || !h_a || !h_lda || !h_b || !h_ldb || !h_c) return fail(CHIMERA_EINVAL, "NULL argument array");
+    if (k % 64) return fail(CHIMERA_EINVAL, "k=%d must be a multiple of 64", k);
     GemmArgs g[4] = {};
     for (int i = 0; i < count; ++i) {
         if (!h_a[i] || !h_b[i] || !h_c[i]) return fail(CHIMERA_EINVAL, "NULL operand in product %d", i);

@@ -114,8 +114,34 @@ def _attention(dtype, batch, seq, heads, d, causal):
         assert_close(to_np(dqkv)[:, lo:lo + H], want[:, lo:lo + H], dtype, name)
 
 
+# bf16 head dimensions other than the compiled 64 and 128, and rows around the 128- and 64-row tiles
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("batch,seq,heads,d", [(1, 65, 3, 8), (2, 129, 2, 40), (1, 200, 2, 80), (9, 130, 32, 96), (1, 127, 2, 120)])
+def test_bf16_attention_head_dims(batch, seq, heads, d, causal):
+    _attention(b.BF16, batch, seq, heads, d, causal)
+
+
+# bf16 products on 64x64 tiles: the two forms meet at 256 tiles, the form ends at 512; k below one step, with a
+# remainder, and around the lengths of the rings; a single row
+@pytest.mark.parametrize("m,n,k", [(1, 8, 8), (1000, 1024, 72), (1024, 1032, 136), (64, 64, 448), (40, 72, 520), (200, 136, 1032),
+                                   (2048, 1024, 200), (2056, 1024, 192)])
+@pytest.mark.parametrize("layout", ["fwd", "dgrad", "wgrad"])
+def test_bf16_small_gemm(m, n, k, layout):
+    import torch
+    print("bf16 gemm", m, n, k, layout, flush=True)
+    a_kc, b_kc = {"fwd": (1, 0), "dgrad": (1, 1), "wgrad": (0, 0)}[layout]
+    m = m if a_kc else max(m, 8)
+    A, B = _rand((m, k), 1, b.BF16), _rand((k, n), 2, b.BF16)
+    want = A.astype(np.float64) @ B.astype(np.float64)
+    c = torch.full((m, n), 0.5, device="cuda", dtype=torch.bfloat16 if a_kc else torch.float32)
+    b.chimera_op_gemm(to_dev(A if a_kc else A.T, b.BF16), to_dev(B.T if b_kc else B, b.BF16), c, m, n, k, a_kc, b_kc,
+                      b.EPI_NONE if a_kc else b.EPI_ACCUM_F32)
+    assert_close(to_np(c) - (0.0 if a_kc else 0.5), want, b.BF16)
+
+
 # token counts that are no multiple of the contraction steps, and gradients that start from anything
-@pytest.mark.parametrize("dtype,hidden,heads,seq,microbatch", [(b.F32, 64, 2, 75, 1), (b.F32, 136, 2, 37, 3), (b.F32, 256, 4, 130, 2)])
+@pytest.mark.parametrize("dtype,hidden,heads,seq,microbatch", [(b.F32, 64, 2, 75, 1), (b.F32, 136, 2, 37, 3), (b.F32, 256, 4, 130, 2),
+                                                                 (b.BF16, 128, 2, 75, 1), (b.BF16, 136, 1, 37, 3), (b.BF16, 560, 7, 99, 1)])
 def test_stage_ragged_tokens(dtype, hidden, heads, seq, microbatch):
     _stage(dtype, hidden, heads, seq, microbatch)
 
