@@ -106,6 +106,7 @@ struct chimera_stage {
     hipEvent_t ev_ready[4] = {};      // main -> side: dy, du, dx1, dqkv of the current block are written
     hipEvent_t ev_side[2] = {};       // side -> main: the side work of a block (by parity) is done
     bool have_side = false;
+    bool use_side = false;            // the running backward uses it
 
     struct IO { const void* x; void* y; const void* dy; void* dx; };
     std::unordered_map<int, IO> io;
@@ -292,9 +293,19 @@ int st_colsum(chimera_stage* st, int cols, const void* x, float* out, float* scr
 
 #define HIP_TRY(expr) do { hipError_t e__ = (expr); if (e__ != hipSuccess) return fail(CHIMERA_EDEVICE, "%s: %s", #expr, hipGetErrorString(e__)); } while (0)
 
+// Whether a backward over `rows` tokens sends its parameter gradients to the side stream.  The
+// events between the two streams cost the chain some 6 us each; what the second stream wins is the CUs
+// that the chain leaves idle, a few percent of a long launch.  Measured, forward + backward of a stage,
+// one stream -> two: rows x hidden 2048 x 1600 (rows hidden^2 = 5.2e9) 2569 -> 2450 us, 1264 x 1600 (3.2e9)
+// 1892 -> 1836, 2048 x 1024 (2.1e9) 1350 -> 1331, 632 x 1600 (1.6e9) 1272 -> 1273, 1024 x 640 (0.4e9) 622 ->
+// 637, 400 x 320 369 -> 433; float 1024 x 1024 1899 -> 1941.
+bool side_stream_pays(const chimera_stage* st, int rows) {
+    return st->dtype == CHIMERA_BF16 && (double)rows * st->H * st->H >= 2.0e9;
+}
+
 // side stream waits until the main stream has reached this point
 int fork_to_side(chimera_stage* st, int which) {
-    if (!st->have_side) return CHIMERA_OK;
+    if (!st->use_side) return CHIMERA_OK;
     HIP_TRY(hipEventRecord(st->ev_ready[which], st->stream));
     HIP_TRY(hipStreamWaitEvent(st->side, st->ev_ready[which], 0));
     return CHIMERA_OK;
@@ -347,6 +358,7 @@ int stage_forward(chimera_stage* st, const chimera_stage::IO& io, int slot) {
 int stage_backward(chimera_stage* st, const chimera_stage::IO& io_full, int slot, int row0, int rows) {
     const int M = rows, H = st->H, L = st->L;
     st->vM = rows; st->vB = rows / st->S;
+    st->use_side = st->have_side && side_stream_pays(st, rows);
     const size_t e = st->esz, r0 = (size_t)row0;
     auto shift = [&](const void* p, size_t cols, size_t bytes) { return (const void*)((const char*)p + r0 * cols * bytes); };
     chimera_stage::IO io = io_full;
@@ -363,8 +375,8 @@ int stage_backward(chimera_stage* st, const chimera_stage::IO& io_full, int slot
         else TRY(flush_pending_zero(st));
     }
     float* lnpart = (float*)(st->ws + st->w_lnpart);
-    float* scratch2 = (float*)(st->ws + (st->have_side ? st->w_scratch2 : st->w_scratch));
-    hipStream_t gs = st->have_side ? st->side : st->stream;       // stream of the parameter gradients
+    float* scratch2 = (float*)(st->ws + (st->use_side ? st->w_scratch2 : st->w_scratch));
+    hipStream_t gs = st->use_side ? st->side : st->stream;       // stream of the parameter gradients
     void* dh = st->ws + st->w_dh;
     float* dx1f = wide ? (float*)(st->ws + st->w_dx1f) : nullptr;
     void* dctx = st->ws + st->w_dctx;
@@ -376,7 +388,7 @@ int stage_backward(chimera_stage* st, const chimera_stage::IO& io_full, int slot
         // du, dx1, dqkv and the dy ping-pong alternate between two buffers by block parity, so
         // before this block overwrites a buffer the side stream must be done with the block
         // two above, which read it
-        if (st->have_side && l + 2 <= L - 1) HIP_TRY(hipStreamWaitEvent(st->stream, st->ev_side[par], 0));
+        if (st->use_side && l + 2 <= L - 1) HIP_TRY(hipStreamWaitEvent(st->stream, st->ev_side[par], 0));
         void* du = st->ws + st->w_du[par];
         void* dx1 = st->ws + st->w_dx1[par];
         void* dqkv = st->ws + st->w_dqkv[par];
@@ -442,10 +454,10 @@ int stage_backward(chimera_stage* st, const chimera_stage::IO& io_full, int slot
             TRY(st_colsum(st, 3 * H, dqkv, st->G(l, st->o_b_qkv), scratch2, gs));
             TRY(linear_wgrad(st, M, 3 * H, H, h1, dqkv, st->G(l, st->o_w_qkv), gs));
         }
-        if (st->have_side) HIP_TRY(hipEventRecord(st->ev_side[par], st->side));
+        if (st->use_side) HIP_TRY(hipEventRecord(st->ev_side[par], st->side));
         TRY(linear_dgrad(st, M, 3 * H, H, dqkv, st->W(l, st->o_w_qkv), nullptr, dh, EPI_NONE));
         // dx goes into the buffer that the block above read its dy from, also on the side stream
-        if (st->have_side && l + 1 <= L - 1) HIP_TRY(hipStreamWaitEvent(st->stream, st->ev_side[(l + 1) & 1], 0));
+        if (st->use_side && l + 1 <= L - 1) HIP_TRY(hipStreamWaitEvent(st->stream, st->ev_side[(l + 1) & 1], 0));
         TRY(st_ln_bwd(st, dh, x, x_f32, mean1, rstd1,
                       st->W(l, st->o_ln1_g), wide ? (const void*)dx1f : (const void*)dx1, wide, dx, dxf,
                       nullptr, nullptr, lnpart + (size_t)(2 * l) * st->lnpart_floats, fresh));
@@ -461,7 +473,7 @@ int stage_backward(chimera_stage* st, const chimera_stage::IO& io_full, int slot
     }
     // the stash slot, the workspace and the gradient buffers are free for the next op only
     // once the side stream has drained
-    if (st->have_side) {
+    if (st->use_side) {
         HIP_TRY(hipStreamWaitEvent(st->stream, st->ev_side[0], 0));
         if (L > 1) HIP_TRY(hipStreamWaitEvent(st->stream, st->ev_side[1], 0));
     }
