@@ -365,7 +365,7 @@ size_t chimera_op_gemm_workspace_bytes(int m, int n, int k);
 int chimera_op_gemm_tuning(int tile_m, int tile_n, int splits, int async_mode);
 /* For reports: the kernel instantiation(s) the calling thread's last grouped launch
  * (chimera_op_gemm_group_accumulate, or a block's weight gradients inside chimera_bwd) went
- * to, e.g. "gemm_bf16_async_group_kernel<256,256,2,4,1,2,false,false>"; two names joined by
+ * to, e.g. "gemm_bf16_ring_group_kernel<256,256,2,4>"; two names joined by
  * " + " when the last row bands went out as a second launch.  Thread-local static storage,
  * never freed by the caller; "" before the first such launch. */
 const char* chimera_op_gemm_group_last_kernel(void);

@@ -46,6 +46,7 @@ namespace {
 
 typedef bf16_t bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int BK = 64;
 constexpr int GROUP_M = 8;       // tile rows per raster group
@@ -145,6 +146,30 @@ __device__ __forceinline__ bf16x8 read_frag(const bf16_t* lds, int r0, int kk, i
 template <int TN> struct EpiSlab {
     static constexpr int WN = TN * 32, STRIDE = WN + 8, FLOATS = 32 * STRIDE;
 };
+// Writers of one 32-row band of accumulators into a slab: 32x32 tiles, and 16x16 tiles (column l%16, rows
+// 4(l/16) + r).
+template <int TM, int TN> struct Acc32 {
+    const f32x16 (&acc)[TM][TN];
+    template <int BAND> __device__ __forceinline__ void put(float* slab, int lane) const {
+        const int l32 = lane & 31, lhi = lane >> 5;
+#pragma unroll
+        for (int b = 0; b < TN; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) slab[(8 * (r >> 2) + 4 * lhi + (r & 3)) * EpiSlab<TN>::STRIDE + b * 32 + l32] = acc[BAND][b][r];
+    }
+};
+template <int TM, int TN> struct Acc16 {
+    const f32x4 (&acc)[2 * TM][2 * TN];
+    template <int BAND> __device__ __forceinline__ void put(float* slab, int lane) const {
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2 * TN; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    slab[(16 * a + 4 * (lane >> 4) + r) * EpiSlab<TN>::STRIDE + b * 16 + (lane & 15)] = acc[BAND * 2 + a][b][r];
+    }
+};
 
 __device__ __forceinline__ void load8(const bf16_t* p, float* o) { load_vec<bf16_t>(p, o); }
 __device__ __forceinline__ void load8(const float* p, float* o) { load_vec<float>(p, o); load_vec<float>(p + 4, o + 4); }
@@ -179,8 +204,8 @@ template <> struct Raw8<float> {
 // (16 in a row for a 128-row wavefront tile: as long as a short k loop).  So the pieces of the
 // next DEPTH bands are requested before the current band is worked on: all bands when the
 // elements have 2 bytes, two bands when they are floats (registers).
-template <int EPI, bool RF32, bool CF32, int TM, int TN>
-__device__ __forceinline__ void epilogue(const f32x16 (&acc)[TM][TN], float* slab, int row_base, int col_base, int m,
+template <int EPI, bool RF32, bool CF32, int TM, int TN, typename Acc>
+__device__ __forceinline__ void epilogue(const Acc& acc, float* slab, int row_base, int col_base, int m,
                                          int n, const bf16_t* __restrict__ bias, const bf16_t* __restrict__ R,
                                          void* __restrict__ c, bf16_t* __restrict__ C2, int epi_flag, int lane) {
     constexpr int WN = EpiSlab<TN>::WN, STRIDE = EpiSlab<TN>::STRIDE;
@@ -193,7 +218,6 @@ __device__ __forceinline__ void epilogue(const f32x16 (&acc)[TM][TN], float* sla
     constexpr int DEPTH = !READS ? 1 : (READS_F32 ? (TM < 2 ? TM : 2) : TM);
     bf16_t* C = (bf16_t*)c;
     float* Cf = (float*)c;
-    const int l32 = lane & 31, lhi = lane >> 5;
     const int pr = lane / CPR, pc = (lane % CPR) * 8;
     const int gcol = col_base + pc;
     const bool reads = READS && !(EPI == EPI_ACCUM_F32 && epi_flag);      // an overwriting accumulate reads nothing
@@ -225,10 +249,7 @@ __device__ __forceinline__ void epilogue(const f32x16 (&acc)[TM][TN], float* sla
     auto band = [&](auto a_c) {
         constexpr int a = decltype(a_c)::value;
         constexpr int SLOT = a % DEPTH;
-#pragma unroll
-        for (int b = 0; b < TN; ++b)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) slab[(8 * (r >> 2) + 4 * lhi + (r & 3)) * STRIDE + b * 32 + l32] = acc[a][b][r];
+        acc.template put<a>(slab, lane);
         __builtin_amdgcn_s_waitcnt(0xc07f);                   // lgkmcnt(0): the slab is written (wavefront-private)
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
@@ -433,7 +454,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_kernel(
     static_assert(sizeof(lds) >= (size_t)WGM * WGN * EpiSlab<TN>::FLOATS * sizeof(float), "LDS too small for the epilogue");
     __syncthreads();
     float* slab = reinterpret_cast<float*>(lds) + (size_t)(tid >> 6) * EpiSlab<TN>::FLOATS;
-#define CHIMERA_EPI(E, RF, CF) epilogue<E, RF, CF, TM, TN>(acc, slab, rb0, cb0, m, n, bias, R, C, C2, epi_flag, lane)
+#define CHIMERA_EPI(E, RF, CF) epilogue<E, RF, CF, TM, TN>(Acc32<TM, TN>{acc}, slab, rb0, cb0, m, n, bias, R, C, C2, epi_flag, lane)
     switch (epi) {
         case EPI_NONE: CHIMERA_EPI(EPI_NONE, false, false); break;
         case EPI_BIAS: CHIMERA_EPI(EPI_BIAS, false, false); break;
@@ -617,8 +638,8 @@ __device__ __forceinline__ void gemm_async_tile(
     static_assert(sizeof(lds) >= (size_t)(NT / 64) * EpiSlab<TN>::FLOATS * sizeof(float), "LDS too small for the epilogue");
     __syncthreads();
     float* slab = reinterpret_cast<float*>(lds) + (size_t)(tid >> 6) * EpiSlab<TN>::FLOATS;
-    auto finish = [&](const auto& out, int rb0) {
-#define CHIMERA_EPI(E, RF, CF) epilogue<E, RF, CF>(out, slab, rb0, cb0, m, n, bias, R, C, C2, epi_flag, lane)
+    auto finish = [&]<int TMO>(const f32x16 (&out)[TMO][TN], int rb0) {
+#define CHIMERA_EPI(E, RF, CF) epilogue<E, RF, CF, TMO, TN>(Acc32<TMO, TN>{out}, slab, rb0, cb0, m, n, bias, R, C, C2, epi_flag, lane)
         if constexpr (ONLY_EPI == EPI_ACCUM_F32) { CHIMERA_EPI(EPI_ACCUM_F32, false, false); return; }
         switch (epi) {
             case EPI_NONE: CHIMERA_EPI(EPI_NONE, false, false); break;
@@ -743,6 +764,317 @@ __device__ __forceinline__ void gemm_async_tile(
     }
 }
 
+// ------------------------------------------------------------------ two-buffer form for large products
+// One 256x256 output tile by 8 wavefronts of 128x64 on v_mfma_f32_16x16x32_bf16; k in steps of 64
+// through two LDS buffers of 64 KiB, software pipelined across the barrier.
+//
+// What bounds it is power: with random operands the chip lowers its clock under matrix load (the same
+// launch on zeros runs 1.3 to 1.4 times as fast), so a product's rate is set by the energy per flop.
+//   * Measured in a loop over register operands: 16x16x32 instructions 2046 TFLOP/s, 32x32x16 1816;
+//     with every operand re-read from LDS at this tile's ratio 1706 and 1549.
+//   * Requests of 128-byte rows (64 k) cost less than two of 64 bytes: 4096^3, A B^T, 102 -> 95.5 us.
+// The schedule only has to keep the matrix pipes from waiting.  A wavefront's step is four phases,
+// {its first 64 rows, its other 64} x {k 0..31, 32..63}; each reads the next phase's operands out of LDS.
+//   * One memory instruction goes behind an MFMA at a time: requests in a burst fill the memory queue,
+//     and the wavefront's own MFMAs would wait behind them.
+//   * The requests of a step go out in the last phase of the step that frees its buffer and in the first
+//     phase of the next: the wait ahead of the barrier finds them two phases old.
+//   * No branch between the MFMAs of the steady state, buffer numbers known at compile time: both
+//     wavefronts of a SIMD reach such a point together, and its matrix pipe idles.
+// Measured against the five-slot 32-k ring on 32x32x16 before it, 4096^3: A B 120 -> 101 us, A B^T 110 -> 96,
+// A^T B 126 -> 110; 2048 x 6400 x 1600 42 -> 38; the weight gradients of a block of 1600 at 2048 tokens
+// with their column sums 154 -> 142.
+constexpr int RK = 64;
+// [row][64 k] tile (128-byte rows): 16-byte chunk c of row r sits at c ^ rswz(r).  A 16-byte LDS read is served
+// in four passes of 16 lanes, {0-3, 12-15, 20-23, 24-27} and so on; with lanes over rows l%16 and chunks l/16
+// this order puts each pass on all 64 banks.
+__device__ __forceinline__ int rswz(int r) { return (r >> 1) & 7; }
+// [k][ROWS] tile: the 32-byte column block j of k-row k sits at j ^ rkswz(k): a transposing read touches one
+// block in rows 8g..8g+3 of four lane groups g.
+__device__ __forceinline__ int rkswz(int k) { return (k & 3) | ((k >> 1) & 4); }
+
+__device__ __forceinline__ void lds_dma16_s(const void* sbase, unsigned voff, unsigned lds_base) {
+    asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "{m0}"(lds_base) : "memory");
+}
+template <int N, typename F> __device__ __forceinline__ void static_for(F&& f) {
+    if constexpr (N > 0) {
+        static_for<N - 1>(f);
+        f(std::integral_constant<int, N - 1>{});
+    }
+}
+
+template <int BM, int BN, int WGM, int WGN, bool A_KC, bool B_KC, int ONLY_EPI>
+__device__ __forceinline__ void gemm_ring_tile(
+    const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, const bf16_t* __restrict__ bias,
+    const bf16_t* __restrict__ R, void* __restrict__ C, bf16_t* __restrict__ C2, int m, int n, int k, int lda,
+    int ldb, int epi, int epi_flag, int res_types, int tiles_m, int tiles_n, int group_m, int block_id,
+    float* __restrict__ bsum = nullptr, bool xcd_remap = true) {
+    constexpr int NT = WGM * WGN * 64;
+    constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16, HM = TM / 2;      // 16x16 tiles per wavefront
+    constexpr int CA = BM * (RK / 8) / NT, CB = BN * (RK / 8) / NT, CS = CA + CB;     // 16-byte pieces per thread and stage
+    constexpr unsigned STAGE = (BM + BN) * RK * 2, ABYTES = BM * RK * 2;
+    constexpr int LDS_EPI = NT / 64 * EpiSlab<TN / 2>::FLOATS * 4, LDS_RING = 2 * (int)STAGE;
+    __shared__ __attribute__((aligned(1024))) char lds[LDS_RING > LDS_EPI ? LDS_RING : LDS_EPI];
+
+    const int nblk = tiles_m * tiles_n;
+    const int xcd = block_id & 7, local = block_id >> 3;
+    const int pid = xcd_remap ? xcd * (nblk >> 3) + min(xcd, nblk & 7) + local : block_id;
+    const int width = group_m * tiles_n;
+    const int first_m = (pid / width) * group_m;
+    const int gsz = min(tiles_m - first_m, group_m);
+    const int tile_m = first_m + (pid % width) % gsz;
+    const int tile_n = (pid % width) / gsz;
+    const int i0 = tile_m * BM, j0 = tile_n * BN;
+
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm0 = (wave / WGN) * WM, wn0 = (wave % WGN) * WN;
+
+    // Piece `slot` of a stage: its k inside the stage, and its byte offset from the tile's corner
+    // (rows beyond the matrix repeat its last ones: their results are not stored).
+    auto piece = [&](int ld, int row0, int nrows, auto rows_c, bool kc, int slot, int& kk) {
+        constexpr int rows = decltype(rows_c)::value;
+        if (kc) {
+            const int row = slot >> 3;
+            kk = ((slot & 7) ^ rswz(row)) * 8;
+            return (unsigned)((min(row0 + row, nrows - 1) - row0) * ld + kk) * 2u;
+        }
+        kk = slot / (rows / 8);
+        const int pc = slot % (rows / 8), ic = (((pc >> 1) ^ rkswz(kk)) << 1) | (pc & 1);
+        return (unsigned)(kk * ld + min(row0 + ic * 8, nrows - 8) - row0) * 2u;
+    };
+    // Requests of an index-contiguous operand lie whole k rows apart: one lane offset and a pointer each.
+    // Those of a k-contiguous one lie rows apart (clamped at the matrix's end): a lane offset each.
+    constexpr int OA = A_KC ? CA : 1, OB = B_KC ? CB : 1, PA = A_KC ? 1 : CA, PB = B_KC ? 1 : CB;
+    unsigned va[OA], vb[OB];
+    int ka, kb;                                // k inside the step of a lane's pieces (request i adds i * KI of an index-contiguous operand)
+    const char *sa[PA], *sb[PB];
+    constexpr int KIA = NT / (BM / 8), KIB = NT / (BN / 8);
+#pragma unroll
+    for (int it = 0; it < OA; ++it) va[it] = piece(lda, i0, m, std::integral_constant<int, BM>{}, A_KC, it * NT + tid, ka);
+#pragma unroll
+    for (int it = 0; it < OB; ++it) vb[it] = piece(ldb, j0, n, std::integral_constant<int, BN>{}, B_KC, it * NT + tid, kb);
+#pragma unroll
+    for (int it = 0; it < PA; ++it) sa[it] = (const char*)(A + (A_KC ? (size_t)i0 * lda : (size_t)i0 + (size_t)it * KIA * lda));
+#pragma unroll
+    for (int it = 0; it < PB; ++it) sb[it] = (const char*)(B + (B_KC ? (size_t)j0 * ldb : (size_t)j0 + (size_t)it * KIB * ldb));
+    static_assert(KIA % 16 == 0 && KIB % 16 == 0, "requests of one lane share a swizzle");
+    const size_t step_a = (A_KC ? (size_t)RK : (size_t)RK * lda) * 2, step_b = (B_KC ? (size_t)RK : (size_t)RK * ldb) * 2;
+    const unsigned lds0 = lds_address(lds), dma0 = lds0 + wave * 1024;
+
+    // Operand reads: lane l holds k 8(l/16)..+7 of row (column) l%16 of a 16-row tile.
+    typedef bf16x8 __attribute__((address_space(3))) * lds_v8;
+    typedef bf16x4 __attribute__((address_space(3))) * lds_v4;
+    // half h (32 k) of buffer q: the offset field of an LDS instruction reaches over one buffer (64 KiB)
+    // Column block b of an index-contiguous operand sits at its first one's address with b exchanged in.
+    constexpr int NPA = A_KC ? 2 : 1, NPB = B_KC ? 2 : 1;
+    static_assert((TM & (TM - 1)) == 0 && TM <= 8 && (TN & (TN - 1)) == 0 && TN <= 8, "column blocks exchange within 256 bytes");
+    unsigned pa[NPA], pb[NPB];
+    auto read_base = [&](auto rows_c, bool kc, int row0, int h) {
+        constexpr int rows = decltype(rows_c)::value;
+        if (kc) return lds0 + (unsigned)((row0 + l16) * 128 + ((4 * h + g) ^ rswz(row0 + l16)) * 16);
+        const int kk = 8 * g + (l16 >> 2);
+        return lds0 + (unsigned)(kk * rows * 2 + ((row0 >> 4) ^ rkswz(kk)) * 32 + (l16 & 3) * 8);
+    };
+#pragma unroll
+    for (int a = 0; a < NPA; ++a) pa[a] = read_base(std::integral_constant<int, BM>{}, A_KC, wm0, a);
+#pragma unroll
+    for (int b = 0; b < NPB; ++b) pb[b] = read_base(std::integral_constant<int, BN>{}, B_KC, wn0, b) + ABYTES;
+    auto read_tr = [&](unsigned p, int rows) {                 // rows k and k + 4 share a swizzle
+        const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_v4)(size_t)p);
+        const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_v4)(size_t)(p + 8 * rows));
+        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    };
+    bf16x8 fa[TM], fb[2][TN];
+    // An address moves to the other buffer behind its last read from this one.
+    auto read_a = [&](auto a_c, auto h_c, auto q_c) {
+        constexpr int a = decltype(a_c)::value, h = decltype(h_c)::value, q = decltype(q_c)::value;
+        constexpr unsigned move = q ? 0u - STAGE : STAGE;
+        if constexpr (A_KC) {
+            fa[a] = *(lds_v8)(size_t)(pa[h] + a * 2048);
+            if constexpr (a == TM - 1) pa[h] += move;
+        } else {
+            fa[a] = read_tr((pa[0] ^ (a * 32)) + h * 64 * BM, BM);
+            if constexpr (h == 1 && a == TM - 1) pa[0] += move;
+        }
+    };
+    auto read_b = [&](auto b_c, auto h_c, auto q_c) {
+        constexpr int b = decltype(b_c)::value, h = decltype(h_c)::value, q = decltype(q_c)::value;
+        constexpr unsigned move = q ? 0u - STAGE : STAGE;
+        if constexpr (B_KC) {
+            fb[h][b] = *(lds_v8)(size_t)(pb[h] + b * 2048);
+            if constexpr (b == TN - 1) pb[h] += move;
+        } else {
+            fb[h][b] = read_tr((pb[0] ^ (b * 32)) + h * 64 * BN, BN);
+            if constexpr (h == 1 && b == TN - 1) pb[0] += move;
+        }
+    };
+
+    f32x4 acc[TM][TN];
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // Optional by-product: bsum[j] += sum over the contraction index of B(k, j), one more MFMA per 16
+    // columns with an all-ones A in the wavefronts at the top edge of the first tile row - in a loop of
+    // their own: a choice per MFMA costs the others a third of their rate.
+    const bool col_sums = ONLY_EPI == EPI_ACCUM_F32 && bsum != nullptr && tile_m == 0 && wm0 == 0;
+    f32x4 cs[TN];
+    bf16x8 ones;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) ones[q] = (bf16_t)1.0f;
+#pragma unroll
+    for (int b = 0; b < TN; ++b) cs[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // HM x TN MFMAs of one phase, between(i) behind the i-th
+    auto phase = [&](auto half_c, auto set_c, auto sums_c, auto&& between) {
+        constexpr int half = decltype(half_c)::value, set = decltype(set_c)::value;
+        constexpr bool sums = decltype(sums_c)::value;
+        static_for<HM * TN>([&](auto i_c) {
+            constexpr int i = decltype(i_c)::value, a = half * HM + i / TN, b = i % TN;
+            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[a], fb[set][b], acc[a][b], 0, 0, 0);
+            if constexpr (sums && a == 0) cs[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, fb[set][b], cs[b], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            between(i_c);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    auto meet = [&] {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // lgkmcnt(0), and all but the N youngest requests have landed
+    auto arrived = [](auto n_c) {
+        constexpr int N = decltype(n_c)::value;
+        __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | ((N >> 4) << 14));
+    };
+
+    // The k % 64 values behind the last whole step come first, zero-filled through registers, as
+    // step 0; the whole steps follow.
+    const int rest = k % RK, KT = k / RK + (rest ? 1 : 0);
+    if (rest) {
+        const size_t ea = (size_t)(k / RK) * step_a, eb = (size_t)(k / RK) * step_b;
+        auto fill = [&](const char* base, unsigned off, int kk, unsigned to) {
+            f32x4 v = {0.f, 0.f, 0.f, 0.f};
+            if (kk < rest) v = *reinterpret_cast<const f32x4*>(base + off);
+            typedef f32x4 __attribute__((address_space(3))) * lds_f4;
+            *(lds_f4)(size_t)(to + lane * 16) = v;
+        };
+#pragma unroll
+        for (int it = 0; it < CA; ++it) fill(sa[A_KC ? 0 : it] + ea, va[A_KC ? it : 0], A_KC ? ka : ka + it * KIA, dma0 + it * NT * 16);
+#pragma unroll
+        for (int it = 0; it < CB; ++it) fill(sb[B_KC ? 0 : it] + eb, vb[B_KC ? it : 0], B_KC ? kb : kb + it * KIB, dma0 + ABYTES + it * NT * 16);
+    }
+    // Request i of a step into buffer q
+    auto request = [&](auto i_c, auto q_c) {
+        constexpr int i = decltype(i_c)::value, q = decltype(q_c)::value;
+        if constexpr (i < CA) {
+            lds_dma16_s(sa[A_KC ? 0 : i], va[A_KC ? i : 0], dma0 + q * STAGE + i * NT * 16);
+            if constexpr (!A_KC || i == CA - 1) sa[A_KC ? 0 : i] += step_a;
+        } else {
+            constexpr int j = i - CA;
+            lds_dma16_s(sb[B_KC ? 0 : j], vb[B_KC ? j : 0], dma0 + q * STAGE + ABYTES + j * NT * 16);
+            if constexpr (!B_KC || j == CB - 1) sb[B_KC ? 0 : j] += step_b;
+        }
+    };
+#define CHIMERA_C(V) std::integral_constant<int, (V)>{}
+    constexpr int ROOM_B = HM * TN - TN - HM, ROOM_A = HM * TN - HM;
+    constexpr int D3 = CS / 2 < ROOM_B ? CS / 2 : ROOM_B, D0 = CS - D3;       // a step's requests in their first and second phase
+    if (!rest) static_for<CS>([&](auto i) { request(i, CHIMERA_C(0)); });
+    if (KT > 1) { static_for<CS>([&](auto i) { if constexpr (decltype(i)::value < D3) request(i, CHIMERA_C(1)); }); arrived(CHIMERA_C(D3)); }
+    else arrived(CHIMERA_C(0));
+    meet();
+    static_for<TN>([&](auto b) { read_b(b, CHIMERA_C(0), CHIMERA_C(0)); });
+    static_for<HM>([&](auto a) { read_a(a, CHIMERA_C(0), CHIMERA_C(0)); });
+
+    // Step t in buffer q = t mod 2.  ALWAYS: further requests are due (the steady state: no branch between the
+    // MFMAs - both wavefronts of a SIMD reach it at the same time, and the matrix pipe idles).
+    constexpr int G3 = ROOM_B / D3, G0 = ROOM_A / D0;
+    static_assert(G3 >= 1 && G0 >= 1, "room for a step's requests");
+    auto step = [&](auto q_c, auto always_c, auto sums_c, int t) {
+        constexpr int q = decltype(q_c)::value;
+        constexpr bool always = decltype(always_c)::value;
+        const bool more1 = always || t + 1 < KT, more2 = always || t + 2 < KT;
+        phase(CHIMERA_C(0), CHIMERA_C(0), sums_c, [&](auto i_c) {
+            constexpr int i = decltype(i_c)::value;
+            if constexpr (i < HM) read_a(CHIMERA_C(HM + i), CHIMERA_C(0), q_c);
+            else if constexpr ((i - HM) % G0 == 0 && (i - HM) / G0 < D0) { if (more1) request(CHIMERA_C(D3 + (i - HM) / G0), CHIMERA_C(q ^ 1)); }
+        });
+        phase(CHIMERA_C(1), CHIMERA_C(0), sums_c, [&](auto i_c) {
+            constexpr int i = decltype(i_c)::value;
+            if constexpr (i < TN) read_b(i_c, CHIMERA_C(1), q_c);
+            else if constexpr (i < TN + HM) read_a(CHIMERA_C(i - TN), CHIMERA_C(1), q_c);
+        });
+        phase(CHIMERA_C(0), CHIMERA_C(1), sums_c, [&](auto i_c) {
+            constexpr int i = decltype(i_c)::value;
+            if constexpr (i < HM) read_a(CHIMERA_C(HM + i), CHIMERA_C(1), q_c);
+        });
+        arrived(CHIMERA_C(0));
+        meet();
+        phase(CHIMERA_C(1), CHIMERA_C(1), sums_c, [&](auto i_c) {
+            constexpr int i = decltype(i_c)::value;
+            if constexpr (i < TN) read_b(i_c, CHIMERA_C(0), CHIMERA_C(q ^ 1));
+            else if constexpr (i < TN + HM) read_a(CHIMERA_C(i - TN), CHIMERA_C(0), CHIMERA_C(q ^ 1));
+            else if constexpr ((i - TN - HM) % G3 == 0 && (i - TN - HM) / G3 < D3) { if (more2) request(CHIMERA_C((i - TN - HM) / G3), q_c); }
+        });
+    };
+    auto steps = [&](auto sums_c) {
+        int t = 0;
+        for (; t + 3 < KT; t += 2) { step(CHIMERA_C(0), std::true_type{}, sums_c, 0); step(CHIMERA_C(1), std::true_type{}, sums_c, 0); }
+        for (; t < KT; t += 2) {
+            step(CHIMERA_C(0), std::false_type{}, sums_c, t);
+            if (t + 1 < KT) step(CHIMERA_C(1), std::false_type{}, sums_c, t + 1);
+        }
+    };
+    if constexpr (ONLY_EPI == EPI_ACCUM_F32) {
+        if (col_sums) steps(std::true_type{});
+        else steps(std::false_type{});
+    } else {
+        steps(std::false_type{});
+    }
+#undef CHIMERA_C
+
+    const int cb0 = j0 + wn0, rb0 = i0 + wm0;
+    __syncthreads();                           // the slots become the wavefronts' slabs
+    float* slab = reinterpret_cast<float*>(lds) + (size_t)wave * EpiSlab<TN / 2>::FLOATS;
+    if constexpr (ONLY_EPI == EPI_ACCUM_F32)
+        if (col_sums && lane < 16)             // every row of these accumulators is the column sum
+#pragma unroll
+            for (int b = 0; b < TN; ++b) {
+                const int col = cb0 + b * 16 + lane;
+                if (col < n) bsum[col] = epi_flag ? cs[b][0] : bsum[col] + cs[b][0];
+            }
+    const Acc16<TM / 2, TN / 2> out{acc};
+#define CHIMERA_EPI(E, RF, CF) epilogue<E, RF, CF, TM / 2, TN / 2>(out, slab, rb0, cb0, m, n, bias, R, C, C2, epi_flag, lane)
+    if constexpr (ONLY_EPI == EPI_ACCUM_F32) { CHIMERA_EPI(EPI_ACCUM_F32, false, false); return; }
+    switch (epi) {
+        case EPI_NONE: CHIMERA_EPI(EPI_NONE, false, false); break;
+        case EPI_BIAS: CHIMERA_EPI(EPI_BIAS, false, false); break;
+        case EPI_BIAS_GELU: CHIMERA_EPI(EPI_BIAS_GELU, false, false); break;
+        case EPI_BIAS_RESIDUAL:
+            if (res_types == 0) CHIMERA_EPI(EPI_BIAS_RESIDUAL, false, false);
+            else if (res_types == 1) CHIMERA_EPI(EPI_BIAS_RESIDUAL, true, false);
+            else if (res_types == 2) CHIMERA_EPI(EPI_BIAS_RESIDUAL, false, true);
+            else CHIMERA_EPI(EPI_BIAS_RESIDUAL, true, true);
+            break;
+        case EPI_DGELU: CHIMERA_EPI(EPI_DGELU, false, false); break;
+        default: CHIMERA_EPI(EPI_ACCUM_F32, false, false); break;
+    }
+#undef CHIMERA_EPI
+}
+
+template <int BM, int BN, int WGM, int WGN, bool A_KC, bool B_KC>
+__global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_ring_kernel(
+    const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, const bf16_t* __restrict__ bias,
+    const bf16_t* __restrict__ R, void* __restrict__ C, bf16_t* __restrict__ C2, int m, int n, int k, int lda,
+    int ldb, int epi, int epi_flag, int res_types, int tiles_m, int tiles_n, int group_m) {
+    gemm_ring_tile<BM, BN, WGM, WGN, A_KC, B_KC, -1>(A, B, bias, R, C, C2, m, n, k, lda, ldb, epi, epi_flag, res_types,
+                                                          tiles_m, tiles_n, group_m, (int)blockIdx.x);
+}
+
 template <int BM, int BN, int WGM, int WGN, int WGK, int NS, int SPS, bool A_KC, bool B_KC>
 __global__ __launch_bounds__(WGM* WGN * WGK * 64) void gemm_bf16_async_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, const bf16_t* __restrict__ bias,
@@ -769,17 +1101,34 @@ struct GemmGroup {
     int overwrite;               // results replace C and bsum instead of being added
 };
 
-template <int BM, int BN, int WGM, int WGN, int WGK, int NS, int SPS, bool A_KC, bool B_KC>
-__global__ __launch_bounds__(WGM* WGN * WGK * 64) void gemm_bf16_async_group_kernel(GemmGroup grp) {
-    // each XCD takes a contiguous range of the group's tiles (products laid end to end), so that
-    // its L2 sees few operand panels: one product's tiles are not dealt over all eight XCDs
+// The product of a group launch that this workgroup belongs to, and its tile's number inside the
+// group: each XCD takes a contiguous range of the group's tiles (products laid end to end), so that
+// its L2 sees few operand panels: one product's tiles are not dealt over all eight XCDs.
+__device__ __forceinline__ int group_product(const GemmGroup& grp, int& gid) {
     const int total = grp.first[grp.count];
     const int xcd = (int)blockIdx.x & 7, local = (int)blockIdx.x >> 3;
-    const int gid = xcd * (total >> 3) + min(xcd, total & 7) + local;
+    gid = xcd * (total >> 3) + min(xcd, total & 7) + local;
     int p = 0;
 #pragma unroll
     for (int i = 1; i < GROUP_MAX; ++i)
         if (i < grp.count && gid >= grp.first[i]) p = i;
+    return p;
+}
+
+template <int BM, int BN, int WGM, int WGN>
+__global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_ring_group_kernel(GemmGroup grp) {
+    int gid;
+    const int p = group_product(grp, gid);
+    gemm_ring_tile<BM, BN, WGM, WGN, false, false, EPI_ACCUM_F32>(
+        grp.a[p], grp.b[p], nullptr, nullptr, grp.c[p], nullptr, grp.m[p], grp.n[p], grp.k, grp.lda[p], grp.ldb[p],
+        EPI_ACCUM_F32, grp.overwrite, 0, grp.tiles_m[p], grp.tiles_n[p], grp.group_m[p], gid - grp.first[p], grp.bsum[p],
+        false);
+}
+
+template <int BM, int BN, int WGM, int WGN, int WGK, int NS, int SPS, bool A_KC, bool B_KC>
+__global__ __launch_bounds__(WGM* WGN * WGK * 64) void gemm_bf16_async_group_kernel(GemmGroup grp) {
+    int gid;
+    const int p = group_product(grp, gid);
     gemm_async_tile<BM, BN, WGM, WGN, WGK, NS, SPS, A_KC, B_KC, EPI_ACCUM_F32>(
         grp.a[p], grp.b[p], nullptr, nullptr, grp.c[p], nullptr, grp.m[p], grp.n[p], grp.k, grp.lda[p], grp.ldb[p],
         EPI_ACCUM_F32, grp.overwrite, 0, grp.tiles_m[p], grp.tiles_n[p], grp.group_m[p], gid - grp.first[p], grp.bsum[p],
@@ -922,12 +1271,40 @@ int launch_async(const GemmArgs& g, hipStream_t s) {
     return CHIMERA_OK;
 }
 
+template <int BM, int BN, int WGM, int WGN>
+int launch_ring(const GemmArgs& g, hipStream_t s) {
+    const int tm = (g.m + BM - 1) / BM, tn = (g.n + BN - 1) / BN;
+    const dim3 grid(tm * tn), block(WGM * WGN * 64);
+    const int gm = raster_group(tm, tn, (tm * tn + 7) / 8, BM, BN);
+#define CHIMERA_GEMM_LAUNCH(AKC, BKC)                                                                                \
+    hipLaunchKernelGGL((gemm_bf16_ring_kernel<BM, BN, WGM, WGN, AKC, BKC>), grid, block, 0, s,                     \
+                       (const bf16_t*)g.a, (const bf16_t*)g.b, (const bf16_t*)g.bias, (const bf16_t*)g.r, g.c,        \
+                       (bf16_t*)g.c2, g.m, g.n, g.k, g.lda, g.ldb, g.epilogue, epilogue_flag(g),                            \
+                       (g.r_f32 ? 1 : 0) | (g.c_f32 ? 2 : 0), tm, tn, gm)
+    if (g.a_kc && !g.b_kc) CHIMERA_GEMM_LAUNCH(true, false);
+    else if (g.a_kc && g.b_kc) CHIMERA_GEMM_LAUNCH(true, true);
+    else CHIMERA_GEMM_LAUNCH(false, false);
+#undef CHIMERA_GEMM_LAUNCH
+    CHIMERA_LAUNCH_CHECK("bf16 gemm (ring)");
+    return CHIMERA_OK;
+}
+
 // Name of the kernel instantiation(s) the last grouped launch on this thread went to (for reports).
 thread_local char g_last_group_kernel[192] = "";
 void note_group_kernel(bool first, const char* name) {
     char* dst = g_last_group_kernel;
     const size_t used = first ? 0 : std::strlen(dst);
     std::snprintf(dst + used, sizeof g_last_group_kernel - used, "%s%s", used ? " + " : "", name);
+}
+
+template <int BM, int BN, int WGM, int WGN>
+int launch_group_ring(const GemmGroup& grp, hipStream_t s) {
+    char name[96];
+    std::snprintf(name, sizeof name, "gemm_bf16_ring_group_kernel<%d,%d,%d,%d>", BM, BN, WGM, WGN);
+    note_group_kernel(true, name);
+    hipLaunchKernelGGL((gemm_bf16_ring_group_kernel<BM, BN, WGM, WGN>), dim3(grp.first[grp.count]), dim3(WGM * WGN * 64), 0, s, grp);
+    CHIMERA_LAUNCH_CHECK("bf16 gemm group");
+    return CHIMERA_OK;
 }
 
 template <int BM, int BN, int WGM, int WGN, int WGK, int NS, int SPS = 1>
@@ -998,12 +1375,12 @@ int gemm_mfma_bf16(const GemmArgs& g, void* stream) {
                 tail.c = (char*)g.c + m0 * g.n * csz;
                 if (g.c2) tail.c2 = (char*)g.c2 + m0 * g.n * 2;
                 if (g.r) tail.r = (const char*)g.r + m0 * g.n * (g.r_f32 ? 4 : 2);
-                if (int rc = launch_async<256, 256, 2, 4, 1, 2>(head, s)) return rc;
+                if (int rc = launch_ring<256, 256, 2, 4>(head, s)) return rc;
                 const long t128 = (long)((tail.m + 127) / 128) * ((tail.n + 127) / 128);
                 if (t128 <= NUM_CUS) return launch_async<128, 128, 2, 2, 2, 3>(tail, s);
                 return launch_async<128, 128, 2, 2, 1, 2>(tail, s);
             }
-            return launch_async<256, 256, 2, 4, 1, 2>(g, s);
+            return launch_ring<256, 256, 2, 4>(g, s);
         }
         if (t.bm == 64) {
             // one tile per CU at most: all of LDS for one workgroup, an eight-stage ring walked two stages per
@@ -1049,7 +1426,7 @@ int launch_group_tiled(int count, const GemmArgs* g, float* const* bsum, int ove
     }
     for (int i = 0; i < count; ++i) grp.group_m[i] = raster_group(grp.tiles_m[i], grp.tiles_n[i], (tiles + 7) / 8, tile, tile);
     for (int i = count; i <= GROUP_MAX; ++i) grp.first[i] = tiles;
-    if (tile == 256) return launch_group<256, 256, 2, 4, 1, 2>(grp, stream, first);
+    if (tile == 256) return launch_group_ring<256, 256, 2, 4>(grp, stream);
     if (tile == 64) return tiles <= NUM_CUS ? launch_group<64, 64, 2, 2, 2, 8, 2>(grp, stream, first) : launch_group<64, 64, 1, 2, 2, 4>(grp, stream, first);
     // two workgroups per CU or the k-sliced 8-wavefront form
     const int mode = tuning().async_mode;

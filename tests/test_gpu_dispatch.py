@@ -139,9 +139,36 @@ def test_bf16_small_gemm(m, n, k, layout):
     assert_close(to_np(c) - (0.0 if a_kc else 0.5), want, b.BF16)
 
 
+# bf16 products on 256x256 tiles: one to six steps of 64 with and without a remainder, ragged rows and columns
+@pytest.mark.parametrize("m,n,k", [(3080, 2824, 8), (3080, 2824, 64), (3080, 2824, 72), (3080, 2824, 128), (3080, 3064, 200),
+                                   (2817, 3072, 320), (3072, 3080, 384)])
+@pytest.mark.parametrize("layout", ["fwd", "dgrad", "wgrad"])
+def test_bf16_large_tiles(m, n, k, layout):
+    test_bf16_small_gemm(m if layout != "wgrad" else m // 8 * 8 + 8, n, k, layout)
+
+
+# grouped weight gradients with column sums on 256x256 tiles
+@pytest.mark.parametrize("k", [64, 128, 192, 320])
+def test_bf16_large_groups(k):
+    import torch
+    print("bf16 group", k, flush=True)
+    shapes = [(1032, 1544), (2056, 1032), (1032, 2312), (1032, 1288)]
+    probs, sums, want = [], [], []
+    for i, (m, n) in enumerate(shapes):
+        X, Y = _rand((k, m), i, b.BF16), _rand((k, n), 10 + i, b.BF16)
+        probs.append((to_dev(X, b.BF16), to_dev(Y, b.BF16), torch.full((m, n), 0.5, device="cuda")))
+        sums.append(torch.full((n,), 0.25, device="cuda"))
+        want.append((X.astype(np.float64).T @ Y.astype(np.float64), Y.astype(np.float64).sum(0)))
+    b.chimera_op_gemm_group_accumulate(probs, k, sums)
+    for (_, _, c), bs, (wc, wb) in zip(probs, sums, want):
+        assert_close(to_np(c) - 0.5, wc, b.BF16)
+        assert_close(to_np(bs) - 0.25, wb, b.BF16)
+
+
 # token counts that are no multiple of the contraction steps, and gradients that start from anything
 @pytest.mark.parametrize("dtype,hidden,heads,seq,microbatch", [(b.F32, 64, 2, 75, 1), (b.F32, 136, 2, 37, 3), (b.F32, 256, 4, 130, 2),
-                                                                 (b.BF16, 128, 2, 75, 1), (b.BF16, 136, 1, 37, 3), (b.BF16, 560, 7, 99, 1)])
+                                                                 (b.BF16, 128, 2, 75, 1), (b.BF16, 136, 1, 37, 3), (b.BF16, 560, 7, 99, 1),
+                                                                 (b.BF16, 1024, 16, 75, 2)])
 def test_stage_ragged_tokens(dtype, hidden, heads, seq, microbatch):
     _stage(dtype, hidden, heads, seq, microbatch)
 
