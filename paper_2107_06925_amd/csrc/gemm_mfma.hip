@@ -764,9 +764,11 @@ __device__ __forceinline__ void gemm_async_tile(
     }
 }
 
-// ------------------------------------------------------------------ two-buffer form for large products
-// One 256x256 output tile by 8 wavefronts of 128x64 on v_mfma_f32_16x16x32_bf16; k in steps of 64
-// through two LDS buffers of 64 KiB, software pipelined across the barrier.
+// ------------------------------------------------------------------ tiles of 128x128 and 256x256
+// One output tile on v_mfma_f32_16x16x32_bf16, k in steps of 64 through LDS buffers, software
+// pipelined across the barrier.  WGK = 1: wavefronts of 128x64 (256x256, 8 of them) or 64x64 (128x128,
+// 4 of them, two workgroups per CU) and two buffers.  WGK = 2, for 128x128 with one workgroup per CU: 8
+// wavefronts, two on each 64x64 block, each taking half of every step's k, over a ring of four buffers.
 //
 // What bounds it is power: with random operands the chip lowers its clock under matrix load (the same
 // launch on zeros runs 1.3 to 1.4 times as fast), so a product's rate is set by the energy per flop.
@@ -783,7 +785,12 @@ __device__ __forceinline__ void gemm_async_tile(
 //     wavefronts of a SIMD reach such a point together, and its matrix pipe idles.
 // Measured against the five-slot 32-k ring on 32x32x16 before it, 4096^3: A B 120 -> 101 us, A B^T 110 -> 96,
 // A^T B 126 -> 110; 2048 x 6400 x 1600 42 -> 38; the weight gradients of a block of 1600 at 2048 tokens
-// with their column sums 154 -> 142.
+// with their column sums 154 -> 142.  128x128, two workgroups per CU: 4096 x 1600 x 6400 97 -> 77.
+//
+// With WGK = 2 a step of a wavefront is 16 MFMAs only, and two buffers would be requested a quarter of a
+// microsecond ahead: less than memory answers in (4096 x 1024 x 50304 ran 16 % slower so).  Four buffers of
+// 32 KiB let requests go out three steps ahead.  2048 x 1600 x 4800 41 -> 33 us, 4096 x 1024 x 4096 39 -> 33,
+// 632 x 4800 x 1600 16.4 -> 14.1.
 constexpr int RK = 64;
 // [row][64 k] tile (128-byte rows): 16-byte chunk c of row r sits at c ^ rswz(r).  A 16-byte LDS read is served
 // in four passes of 16 lanes, {0-3, 12-15, 20-23, 24-27} and so on; with lanes over rows l%16 and chunks l/16
@@ -803,17 +810,17 @@ template <int N, typename F> __device__ __forceinline__ void static_for(F&& f) {
     }
 }
 
-template <int BM, int BN, int WGM, int WGN, bool A_KC, bool B_KC, int ONLY_EPI>
+template <int BM, int BN, int WGM, int WGN, int WGK, bool A_KC, bool B_KC, int ONLY_EPI>
 __device__ __forceinline__ void gemm_ring_tile(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, const bf16_t* __restrict__ bias,
     const bf16_t* __restrict__ R, void* __restrict__ C, bf16_t* __restrict__ C2, int m, int n, int k, int lda,
     int ldb, int epi, int epi_flag, int res_types, int tiles_m, int tiles_n, int group_m, int block_id,
     float* __restrict__ bsum = nullptr, bool xcd_remap = true) {
-    constexpr int NT = WGM * WGN * 64;
+    constexpr int NT = WGM * WGN * WGK * 64, NS = WGK == 1 ? 2 : 4;
     constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16, HM = TM / 2;      // 16x16 tiles per wavefront
     constexpr int CA = BM * (RK / 8) / NT, CB = BN * (RK / 8) / NT, CS = CA + CB;     // 16-byte pieces per thread and stage
     constexpr unsigned STAGE = (BM + BN) * RK * 2, ABYTES = BM * RK * 2;
-    constexpr int LDS_EPI = NT / 64 * EpiSlab<TN / 2>::FLOATS * 4, LDS_RING = 2 * (int)STAGE;
+    constexpr int LDS_EPI = NT / 64 * EpiSlab<TN / 2>::FLOATS * 4, LDS_RING = NS * (int)STAGE;
     __shared__ __attribute__((aligned(1024))) char lds[LDS_RING > LDS_EPI ? LDS_RING : LDS_EPI];
 
     const int nblk = tiles_m * tiles_n;
@@ -828,7 +835,8 @@ __device__ __forceinline__ void gemm_ring_tile(
 
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm0 = (wave / WGN) * WM, wn0 = (wave % WGN) * WN;
+    const int wk = wave / (WGM * WGN), wmn = wave % (WGM * WGN);
+    const int wm0 = (wmn / WGN) * WM, wn0 = (wmn % WGN) * WN;
 
     // Piece `slot` of a stage: its k inside the stage, and its byte offset from the tile's corner
     // (rows beyond the matrix repeat its last ones: their results are not stored).
@@ -873,13 +881,13 @@ __device__ __forceinline__ void gemm_ring_tile(
     auto read_base = [&](auto rows_c, bool kc, int row0, int h) {
         constexpr int rows = decltype(rows_c)::value;
         if (kc) return lds0 + (unsigned)((row0 + l16) * 128 + ((4 * h + g) ^ rswz(row0 + l16)) * 16);
-        const int kk = 8 * g + (l16 >> 2);
+        const int kk = 32 * h + 8 * g + (l16 >> 2);
         return lds0 + (unsigned)(kk * rows * 2 + ((row0 >> 4) ^ rkswz(kk)) * 32 + (l16 & 3) * 8);
     };
 #pragma unroll
-    for (int a = 0; a < NPA; ++a) pa[a] = read_base(std::integral_constant<int, BM>{}, A_KC, wm0, a);
+    for (int a = 0; a < NPA; ++a) pa[a] = read_base(std::integral_constant<int, BM>{}, A_KC, wm0, WGK == 2 ? wk : a);
 #pragma unroll
-    for (int b = 0; b < NPB; ++b) pb[b] = read_base(std::integral_constant<int, BN>{}, B_KC, wn0, b) + ABYTES;
+    for (int b = 0; b < NPB; ++b) pb[b] = read_base(std::integral_constant<int, BN>{}, B_KC, wn0, WGK == 2 ? wk : b) + ABYTES;
     auto read_tr = [&](unsigned p, int rows) {                 // rows k and k + 4 share a swizzle
         const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_v4)(size_t)p);
         const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_v4)(size_t)(p + 8 * rows));
@@ -889,8 +897,11 @@ __device__ __forceinline__ void gemm_ring_tile(
     // An address moves to the other buffer behind its last read from this one.
     auto read_a = [&](auto a_c, auto h_c, auto q_c) {
         constexpr int a = decltype(a_c)::value, h = decltype(h_c)::value, q = decltype(q_c)::value;
-        constexpr unsigned move = q ? 0u - STAGE : STAGE;
-        if constexpr (A_KC) {
+        constexpr unsigned move = q ? 0u - STAGE : STAGE, far = q / 2 * 2 * STAGE, near = q % 2 * STAGE;
+        if constexpr (WGK == 2) {
+            if constexpr (A_KC) fa[a] = *(lds_v8)(size_t)((pa[0] + far) + near + a * 2048);
+            else fa[a] = read_tr(((pa[0] ^ (a * 32)) + far) + near, BM);
+        } else if constexpr (A_KC) {
             fa[a] = *(lds_v8)(size_t)(pa[h] + a * 2048);
             if constexpr (a == TM - 1) pa[h] += move;
         } else {
@@ -900,8 +911,11 @@ __device__ __forceinline__ void gemm_ring_tile(
     };
     auto read_b = [&](auto b_c, auto h_c, auto q_c) {
         constexpr int b = decltype(b_c)::value, h = decltype(h_c)::value, q = decltype(q_c)::value;
-        constexpr unsigned move = q ? 0u - STAGE : STAGE;
-        if constexpr (B_KC) {
+        constexpr unsigned move = q ? 0u - STAGE : STAGE, far = q / 2 * 2 * STAGE, near = q % 2 * STAGE;
+        if constexpr (WGK == 2) {
+            if constexpr (B_KC) fb[h][b] = *(lds_v8)(size_t)((pb[0] + far) + near + b * 2048);
+            else fb[h][b] = read_tr(((pb[0] ^ (b * 32)) + far) + near, BN);
+        } else if constexpr (B_KC) {
             fb[h][b] = *(lds_v8)(size_t)(pb[h] + b * 2048);
             if constexpr (b == TN - 1) pb[h] += move;
         } else {
@@ -952,16 +966,15 @@ __device__ __forceinline__ void gemm_ring_tile(
         __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | ((N >> 4) << 14));
     };
 
-    // The k % 64 values behind the last whole step come first, zero-filled through registers, as
-    // step 0; the whole steps follow.
+    // The k values behind the last whole step come first, as step 0 (lanes beyond them store zeros in
+    // place of their request); the whole steps follow.
     const int rest = k % RK, KT = k / RK + (rest ? 1 : 0);
     if (rest) {
         const size_t ea = (size_t)(k / RK) * step_a, eb = (size_t)(k / RK) * step_b;
         auto fill = [&](const char* base, unsigned off, int kk, unsigned to) {
-            f32x4 v = {0.f, 0.f, 0.f, 0.f};
-            if (kk < rest) v = *reinterpret_cast<const f32x4*>(base + off);
             typedef f32x4 __attribute__((address_space(3))) * lds_f4;
-            *(lds_f4)(size_t)(to + lane * 16) = v;
+            if (kk < rest) lds_dma16_s(base, off, to);
+            else *(lds_f4)(size_t)(to + lane * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
         };
 #pragma unroll
         for (int it = 0; it < CA; ++it) fill(sa[A_KC ? 0 : it] + ea, va[A_KC ? it : 0], A_KC ? ka : ka + it * KIA, dma0 + it * NT * 16);
@@ -981,52 +994,95 @@ __device__ __forceinline__ void gemm_ring_tile(
         }
     };
 #define CHIMERA_C(V) std::integral_constant<int, (V)>{}
-    constexpr int ROOM_B = HM * TN - TN - HM, ROOM_A = HM * TN - HM;
-    constexpr int D3 = CS / 2 < ROOM_B ? CS / 2 : ROOM_B, D0 = CS - D3;       // a step's requests in their first and second phase
-    if (!rest) static_for<CS>([&](auto i) { request(i, CHIMERA_C(0)); });
-    if (KT > 1) { static_for<CS>([&](auto i) { if constexpr (decltype(i)::value < D3) request(i, CHIMERA_C(1)); }); arrived(CHIMERA_C(D3)); }
-    else arrived(CHIMERA_C(0));
-    meet();
-    static_for<TN>([&](auto b) { read_b(b, CHIMERA_C(0), CHIMERA_C(0)); });
-    static_for<HM>([&](auto a) { read_a(a, CHIMERA_C(0), CHIMERA_C(0)); });
-
-    // Step t in buffer q = t mod 2.  ALWAYS: further requests are due (the steady state: no branch between the
-    // MFMAs - both wavefronts of a SIMD reach it at the same time, and the matrix pipe idles).
-    constexpr int G3 = ROOM_B / D3, G0 = ROOM_A / D0;
-    static_assert(G3 >= 1 && G0 >= 1, "room for a step's requests");
-    auto step = [&](auto q_c, auto always_c, auto sums_c, int t) {
-        constexpr int q = decltype(q_c)::value;
-        constexpr bool always = decltype(always_c)::value;
-        const bool more1 = always || t + 1 < KT, more2 = always || t + 2 < KT;
-        phase(CHIMERA_C(0), CHIMERA_C(0), sums_c, [&](auto i_c) {
-            constexpr int i = decltype(i_c)::value;
-            if constexpr (i < HM) read_a(CHIMERA_C(HM + i), CHIMERA_C(0), q_c);
-            else if constexpr ((i - HM) % G0 == 0 && (i - HM) / G0 < D0) { if (more1) request(CHIMERA_C(D3 + (i - HM) / G0), CHIMERA_C(q ^ 1)); }
-        });
-        phase(CHIMERA_C(1), CHIMERA_C(0), sums_c, [&](auto i_c) {
-            constexpr int i = decltype(i_c)::value;
-            if constexpr (i < TN) read_b(i_c, CHIMERA_C(1), q_c);
-            else if constexpr (i < TN + HM) read_a(CHIMERA_C(i - TN), CHIMERA_C(1), q_c);
-        });
-        phase(CHIMERA_C(0), CHIMERA_C(1), sums_c, [&](auto i_c) {
-            constexpr int i = decltype(i_c)::value;
-            if constexpr (i < HM) read_a(CHIMERA_C(HM + i), CHIMERA_C(1), q_c);
-        });
-        arrived(CHIMERA_C(0));
-        meet();
-        phase(CHIMERA_C(1), CHIMERA_C(1), sums_c, [&](auto i_c) {
-            constexpr int i = decltype(i_c)::value;
-            if constexpr (i < TN) read_b(i_c, CHIMERA_C(0), CHIMERA_C(q ^ 1));
-            else if constexpr (i < TN + HM) read_a(CHIMERA_C(i - TN), CHIMERA_C(0), CHIMERA_C(q ^ 1));
-            else if constexpr ((i - TN - HM) % G3 == 0 && (i - TN - HM) / G3 < D3) { if (more2) request(CHIMERA_C((i - TN - HM) / G3), q_c); }
-        });
-    };
     auto steps = [&](auto sums_c) {
-        int t = 0;
-        for (; t + 3 < KT; t += 2) { step(CHIMERA_C(0), std::true_type{}, sums_c, 0); step(CHIMERA_C(1), std::true_type{}, sums_c, 0); }
-        for (; t < KT; t += 2) {
-            step(CHIMERA_C(0), std::false_type{}, sums_c, t);
-            if (t + 1 < KT) step(CHIMERA_C(1), std::false_type{}, sums_c, t + 1);
+        if constexpr (WGK == 1) {
+            constexpr int ROOM_B = HM * TN - TN - HM, ROOM_A = HM * TN - HM;
+            constexpr int D3 = CS / 2 < ROOM_B ? CS / 2 : ROOM_B, D0 = CS - D3;       // a step's requests in their first and second phase
+            if (!rest) static_for<CS>([&](auto i) { request(i, CHIMERA_C(0)); });
+            if (KT > 1) { static_for<CS>([&](auto i) { if constexpr (decltype(i)::value < D3) request(i, CHIMERA_C(1)); }); arrived(CHIMERA_C(D3)); }
+            else arrived(CHIMERA_C(0));
+            meet();
+            static_for<TN>([&](auto b) { read_b(b, CHIMERA_C(0), CHIMERA_C(0)); });
+            static_for<HM>([&](auto a) { read_a(a, CHIMERA_C(0), CHIMERA_C(0)); });
+
+            // Step t in buffer q = t mod 2.  ALWAYS: further requests are due (the steady state: no branch between the
+            // MFMAs - both wavefronts of a SIMD reach it at the same time, and the matrix pipe idles).
+            constexpr int G3 = ROOM_B / D3, G0 = ROOM_A / D0;
+            static_assert(G3 >= 1 && G0 >= 1, "room for a step's requests");
+            auto step = [&](auto q_c, auto always_c, int t) {
+                constexpr int q = decltype(q_c)::value;
+                constexpr bool always = decltype(always_c)::value;
+                const bool more1 = always || t + 1 < KT, more2 = always || t + 2 < KT;
+                phase(CHIMERA_C(0), CHIMERA_C(0), sums_c, [&](auto i_c) {
+                    constexpr int i = decltype(i_c)::value;
+                    if constexpr (i < HM) read_a(CHIMERA_C(HM + i), CHIMERA_C(0), q_c);
+                    else if constexpr ((i - HM) % G0 == 0 && (i - HM) / G0 < D0) { if (more1) request(CHIMERA_C(D3 + (i - HM) / G0), CHIMERA_C(q ^ 1)); }
+                });
+                phase(CHIMERA_C(1), CHIMERA_C(0), sums_c, [&](auto i_c) {
+                    constexpr int i = decltype(i_c)::value;
+                    if constexpr (i < TN) read_b(i_c, CHIMERA_C(1), q_c);
+                    else if constexpr (i < TN + HM) read_a(CHIMERA_C(i - TN), CHIMERA_C(1), q_c);
+                });
+                phase(CHIMERA_C(0), CHIMERA_C(1), sums_c, [&](auto i_c) {
+                    constexpr int i = decltype(i_c)::value;
+                    if constexpr (i < HM) read_a(CHIMERA_C(HM + i), CHIMERA_C(1), q_c);
+                });
+                arrived(CHIMERA_C(0));
+                meet();
+                phase(CHIMERA_C(1), CHIMERA_C(1), sums_c, [&](auto i_c) {
+                    constexpr int i = decltype(i_c)::value;
+                    if constexpr (i < TN) read_b(i_c, CHIMERA_C(0), CHIMERA_C(q ^ 1));
+                    else if constexpr (i < TN + HM) read_a(CHIMERA_C(i - TN), CHIMERA_C(0), CHIMERA_C(q ^ 1));
+                    else if constexpr ((i - TN - HM) % G3 == 0 && (i - TN - HM) / G3 < D3) { if (more2) request(CHIMERA_C((i - TN - HM) / G3), q_c); }
+                });
+            };
+            int t = 0;
+            for (; t + 3 < KT; t += 2) { step(CHIMERA_C(0), std::true_type{}, 0); step(CHIMERA_C(1), std::true_type{}, 0); }
+            for (; t < KT; t += 2) {
+                step(CHIMERA_C(0), std::false_type{}, t);
+                if (t + 1 < KT) step(CHIMERA_C(1), std::false_type{}, t + 1);
+            }
+        } else {
+            // Wavefronts of either k half share the stages of a ring of NS slots.  In step t they request stage
+            // t + NS - 1 into the slot that step t - 1 was the last to read.
+            if (!rest) static_for<CS>([&](auto i) { request(i, CHIMERA_C(0)); });
+            static_for<NS - 2>([&](auto j) {
+                constexpr int q = decltype(j)::value + 1;
+                if (q < KT) static_for<CS>([&](auto i) { request(i, CHIMERA_C(q)); });
+            });
+            // all but the `younger` stages behind it have landed
+            auto landed = [&](int younger) {
+                if (younger >= NS - 2) arrived(CHIMERA_C((NS - 2) * CS));
+                else if (younger == 1) arrived(CHIMERA_C(CS));
+                else arrived(CHIMERA_C(0));
+            };
+            static_assert(NS == 4, "landed() counts up to two younger stages");
+            landed(KT - 1);
+            meet();
+            static_for<TN>([&](auto b) { read_b(b, CHIMERA_C(0), CHIMERA_C(0)); });
+            static_for<HM>([&](auto a) { read_a(a, CHIMERA_C(0), CHIMERA_C(0)); });
+            auto step = [&](auto q_c, auto always_c, int t) {
+                constexpr int q = decltype(q_c)::value, next = (q + 1) % NS;
+                constexpr bool always = decltype(always_c)::value;
+                const bool more = always || t + NS - 1 < KT;
+                phase(CHIMERA_C(0), CHIMERA_C(q & 1), sums_c, [&](auto i_c) {
+                    constexpr int i = decltype(i_c)::value;
+                    if constexpr (i < HM) read_a(CHIMERA_C(HM + i), CHIMERA_C(0), q_c);
+                    else if constexpr (i < HM + CS) { if (more) request(CHIMERA_C(i - HM), CHIMERA_C((q + NS - 1) % NS)); }
+                });
+                static_assert(HM + CS <= HM * TN && TN + HM <= HM * TN, "room behind the MFMAs");
+                if constexpr (always) arrived(CHIMERA_C((NS - 2) * CS));
+                else landed(KT - 2 - t);
+                meet();
+                phase(CHIMERA_C(1), CHIMERA_C(q & 1), sums_c, [&](auto i_c) {
+                    constexpr int i = decltype(i_c)::value;
+                    if constexpr (i < TN) read_b(i_c, CHIMERA_C(next & 1), CHIMERA_C(next));
+                    else if constexpr (i < TN + HM) read_a(CHIMERA_C(i - TN), CHIMERA_C(0), CHIMERA_C(next));
+                });
+            };
+            int t = 0;
+            for (; t + 2 * NS - 2 < KT; t += NS) static_for<NS>([&](auto q) { step(q, std::true_type{}, 0); });
+            for (; t < KT; t += NS) static_for<NS>([&](auto q) { if (t + q < KT) step(q, std::false_type{}, t + q); });
         }
     };
     if constexpr (ONLY_EPI == EPI_ACCUM_F32) {
@@ -1037,41 +1093,89 @@ __device__ __forceinline__ void gemm_ring_tile(
     }
 #undef CHIMERA_C
 
-    const int cb0 = j0 + wn0, rb0 = i0 + wm0;
-    __syncthreads();                           // the slots become the wavefronts' slabs
+    const int cb0 = j0 + wn0;
+    auto put_col_sums = [&](const float* v) {
+#pragma unroll
+        for (int b = 0; b < TN; ++b) {
+            const int col = cb0 + b * 16 + lane;
+            if (lane < 16 && col < n) bsum[col] = epi_flag ? v[b] : bsum[col] + v[b];
+        }
+    };
     float* slab = reinterpret_cast<float*>(lds) + (size_t)wave * EpiSlab<TN / 2>::FLOATS;
-    if constexpr (ONLY_EPI == EPI_ACCUM_F32)
-        if (col_sums && lane < 16)             // every row of these accumulators is the column sum
+    auto finish = [&](const auto& out, auto rows_c, int rb0) {
+        constexpr int TO = decltype(rows_c)::value;              // 32-row bands of this wavefront
+#define CHIMERA_EPI(E, RF, CF) epilogue<E, RF, CF, TO, TN / 2>(out, slab, rb0, cb0, m, n, bias, R, C, C2, epi_flag, lane)
+        if constexpr (ONLY_EPI == EPI_ACCUM_F32) { CHIMERA_EPI(EPI_ACCUM_F32, false, false); return; }
+        switch (epi) {
+            case EPI_NONE: CHIMERA_EPI(EPI_NONE, false, false); break;
+            case EPI_BIAS: CHIMERA_EPI(EPI_BIAS, false, false); break;
+            case EPI_BIAS_GELU: CHIMERA_EPI(EPI_BIAS_GELU, false, false); break;
+            case EPI_BIAS_RESIDUAL:
+                if (res_types == 0) CHIMERA_EPI(EPI_BIAS_RESIDUAL, false, false);
+                else if (res_types == 1) CHIMERA_EPI(EPI_BIAS_RESIDUAL, true, false);
+                else if (res_types == 2) CHIMERA_EPI(EPI_BIAS_RESIDUAL, false, true);
+                else CHIMERA_EPI(EPI_BIAS_RESIDUAL, true, true);
+                break;
+            case EPI_DGELU: CHIMERA_EPI(EPI_DGELU, false, false); break;
+            default: CHIMERA_EPI(EPI_ACCUM_F32, false, false); break;
+        }
+#undef CHIMERA_EPI
+    };
+    __syncthreads();                           // the buffers become the wavefronts' slabs
+    if constexpr (WGK == 1) {
+        if constexpr (ONLY_EPI == EPI_ACCUM_F32)
+            if (col_sums) {                    // every row of these accumulators is the column sum
+                float v[TN];
+#pragma unroll
+                for (int b = 0; b < TN; ++b) v[b] = cs[b][0];
+                put_col_sums(v);
+            }
+        finish(Acc16<TM / 2, TN / 2>{acc}, std::integral_constant<int, TM / 2>{}, i0 + wm0);
+    } else {
+        // Two wavefronts hold partial sums of the same block.  Each keeps the upper or lower half of its rows:
+        // it hands the other half to its partner through LDS and adds what the partner hands over.
+        static_assert(WGK == 2 && TM % 4 == 0, "bands of 32 rows");
+        constexpr int PER_WAVE = HM * TN * 64;                   // 16 bytes each
+        static_assert(sizeof(lds) >= NT / 64 * PER_WAVE * 16 + BN * sizeof(float), "LDS too small for the exchange");
+        f32x4* xch = reinterpret_cast<f32x4*>(lds);
+        float* xcs = reinterpret_cast<float*>(xch + NT / 64 * PER_WAVE) + wn0;
+        if constexpr (ONLY_EPI == EPI_ACCUM_F32)
+            if (col_sums && wk == 1 && lane < 16)
+#pragma unroll
+                for (int b = 0; b < TN; ++b) xcs[b * 16 + lane] = cs[b][0];
+        f32x4* send = xch + (size_t)wave * PER_WAVE + lane;
+        const f32x4* recv = xch + (size_t)(wave ^ (WGM * WGN)) * PER_WAVE + lane;
+        f32x4 own[HM][TN];
+#pragma unroll
+        for (int a = 0; a < HM; ++a)
 #pragma unroll
             for (int b = 0; b < TN; ++b) {
-                const int col = cb0 + b * 16 + lane;
-                if (col < n) bsum[col] = epi_flag ? cs[b][0] : bsum[col] + cs[b][0];
+                send[(a * TN + b) * 64] = wk ? acc[a][b] : acc[HM + a][b];
+                own[a][b] = wk ? acc[HM + a][b] : acc[a][b];
             }
-    const Acc16<TM / 2, TN / 2> out{acc};
-#define CHIMERA_EPI(E, RF, CF) epilogue<E, RF, CF, TM / 2, TN / 2>(out, slab, rb0, cb0, m, n, bias, R, C, C2, epi_flag, lane)
-    if constexpr (ONLY_EPI == EPI_ACCUM_F32) { CHIMERA_EPI(EPI_ACCUM_F32, false, false); return; }
-    switch (epi) {
-        case EPI_NONE: CHIMERA_EPI(EPI_NONE, false, false); break;
-        case EPI_BIAS: CHIMERA_EPI(EPI_BIAS, false, false); break;
-        case EPI_BIAS_GELU: CHIMERA_EPI(EPI_BIAS_GELU, false, false); break;
-        case EPI_BIAS_RESIDUAL:
-            if (res_types == 0) CHIMERA_EPI(EPI_BIAS_RESIDUAL, false, false);
-            else if (res_types == 1) CHIMERA_EPI(EPI_BIAS_RESIDUAL, true, false);
-            else if (res_types == 2) CHIMERA_EPI(EPI_BIAS_RESIDUAL, false, true);
-            else CHIMERA_EPI(EPI_BIAS_RESIDUAL, true, true);
-            break;
-        case EPI_DGELU: CHIMERA_EPI(EPI_DGELU, false, false); break;
-        default: CHIMERA_EPI(EPI_ACCUM_F32, false, false); break;
+        __syncthreads();
+#pragma unroll
+        for (int a = 0; a < HM; ++a)
+#pragma unroll
+            for (int b = 0; b < TN; ++b) own[a][b] += recv[(a * TN + b) * 64];
+        if constexpr (ONLY_EPI == EPI_ACCUM_F32)
+            if (col_sums && wk == 0) {
+                float v[TN];
+#pragma unroll
+                for (int b = 0; b < TN; ++b) v[b] = cs[b][0] + (lane < 16 ? xcs[b * 16 + lane] : 0.f);
+                put_col_sums(v);
+            }
+        __syncthreads();                       // the exchange area becomes the slabs
+        finish(Acc16<TM / 4, TN / 2>{own}, std::integral_constant<int, TM / 4>{}, i0 + wm0 + wk * HM * 16);
     }
-#undef CHIMERA_EPI
 }
 
-template <int BM, int BN, int WGM, int WGN, bool A_KC, bool B_KC>
-__global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_ring_kernel(
+template <int BM, int BN, int WGM, int WGN, int WGK, bool A_KC, bool B_KC>
+__global__ __launch_bounds__(WGM* WGN * WGK * 64, 2) void gemm_bf16_ring_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, const bf16_t* __restrict__ bias,
     const bf16_t* __restrict__ R, void* __restrict__ C, bf16_t* __restrict__ C2, int m, int n, int k, int lda,
     int ldb, int epi, int epi_flag, int res_types, int tiles_m, int tiles_n, int group_m) {
-    gemm_ring_tile<BM, BN, WGM, WGN, A_KC, B_KC, -1>(A, B, bias, R, C, C2, m, n, k, lda, ldb, epi, epi_flag, res_types,
+    gemm_ring_tile<BM, BN, WGM, WGN, WGK, A_KC, B_KC, -1>(A, B, bias, R, C, C2, m, n, k, lda, ldb, epi, epi_flag, res_types,
                                                           tiles_m, tiles_n, group_m, (int)blockIdx.x);
 }
 
@@ -1115,11 +1219,11 @@ __device__ __forceinline__ int group_product(const GemmGroup& grp, int& gid) {
     return p;
 }
 
-template <int BM, int BN, int WGM, int WGN>
-__global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_ring_group_kernel(GemmGroup grp) {
+template <int BM, int BN, int WGM, int WGN, int WGK>
+__global__ __launch_bounds__(WGM* WGN * WGK * 64, 2) void gemm_bf16_ring_group_kernel(GemmGroup grp) {
     int gid;
     const int p = group_product(grp, gid);
-    gemm_ring_tile<BM, BN, WGM, WGN, false, false, EPI_ACCUM_F32>(
+    gemm_ring_tile<BM, BN, WGM, WGN, WGK, false, false, EPI_ACCUM_F32>(
         grp.a[p], grp.b[p], nullptr, nullptr, grp.c[p], nullptr, grp.m[p], grp.n[p], grp.k, grp.lda[p], grp.ldb[p],
         EPI_ACCUM_F32, grp.overwrite, 0, grp.tiles_m[p], grp.tiles_n[p], grp.group_m[p], gid - grp.first[p], grp.bsum[p],
         false);
@@ -1271,13 +1375,13 @@ int launch_async(const GemmArgs& g, hipStream_t s) {
     return CHIMERA_OK;
 }
 
-template <int BM, int BN, int WGM, int WGN>
+template <int BM, int BN, int WGM, int WGN, int WGK>
 int launch_ring(const GemmArgs& g, hipStream_t s) {
     const int tm = (g.m + BM - 1) / BM, tn = (g.n + BN - 1) / BN;
-    const dim3 grid(tm * tn), block(WGM * WGN * 64);
+    const dim3 grid(tm * tn), block(WGM * WGN * WGK * 64);
     const int gm = raster_group(tm, tn, (tm * tn + 7) / 8, BM, BN);
 #define CHIMERA_GEMM_LAUNCH(AKC, BKC)                                                                                \
-    hipLaunchKernelGGL((gemm_bf16_ring_kernel<BM, BN, WGM, WGN, AKC, BKC>), grid, block, 0, s,                     \
+    hipLaunchKernelGGL((gemm_bf16_ring_kernel<BM, BN, WGM, WGN, WGK, AKC, BKC>), grid, block, 0, s,                     \
                        (const bf16_t*)g.a, (const bf16_t*)g.b, (const bf16_t*)g.bias, (const bf16_t*)g.r, g.c,        \
                        (bf16_t*)g.c2, g.m, g.n, g.k, g.lda, g.ldb, g.epilogue, epilogue_flag(g),                            \
                        (g.r_f32 ? 1 : 0) | (g.c_f32 ? 2 : 0), tm, tn, gm)
@@ -1297,12 +1401,12 @@ void note_group_kernel(bool first, const char* name) {
     std::snprintf(dst + used, sizeof g_last_group_kernel - used, "%s%s", used ? " + " : "", name);
 }
 
-template <int BM, int BN, int WGM, int WGN>
-int launch_group_ring(const GemmGroup& grp, hipStream_t s) {
+template <int BM, int BN, int WGM, int WGN, int WGK>
+int launch_group_ring(const GemmGroup& grp, hipStream_t s, bool first = true) {
     char name[96];
-    std::snprintf(name, sizeof name, "gemm_bf16_ring_group_kernel<%d,%d,%d,%d>", BM, BN, WGM, WGN);
-    note_group_kernel(true, name);
-    hipLaunchKernelGGL((gemm_bf16_ring_group_kernel<BM, BN, WGM, WGN>), dim3(grp.first[grp.count]), dim3(WGM * WGN * 64), 0, s, grp);
+    std::snprintf(name, sizeof name, "gemm_bf16_ring_group_kernel<%d,%d,%d,%d,%d>", BM, BN, WGM, WGN, WGK);
+    note_group_kernel(first, name);
+    hipLaunchKernelGGL((gemm_bf16_ring_group_kernel<BM, BN, WGM, WGN, WGK>), dim3(grp.first[grp.count]), dim3(WGM * WGN * WGK * 64), 0, s, grp);
     CHIMERA_LAUNCH_CHECK("bf16 gemm group");
     return CHIMERA_OK;
 }
@@ -1353,11 +1457,10 @@ int gemm_mfma_bf16(const GemmArgs& g, void* stream) {
         return fail(CHIMERA_EINVAL, "too many tiles for split-K");
     // 128x128 tiles: with one workgroup per CU, a workgroup of 4 wavefronts leaves one wavefront
     // per SIMD, and nothing covers its LDS latency and the barrier of every k step; then 8
-    // wavefronts share the tile, two per 64x64 block, each taking half of every k step (their
-    // partial sums meet in LDS at the end), over a 3-stage ring of 96 KiB - one such workgroup
-    // per CU, so more than NUM_CUS tiles would take it two rounds.  Beyond that the 4-wavefront
-    // form with its 2-stage ring (64 KiB of LDS, two workgroups per CU) is faster: 416 tiles of a
-    // 4096 x 1600 x 6400 product take 109 us against 124 us, 208 tiles (2048 rows) 89 against 62.
+    // wavefronts share the tile, two per 64x64 block (their partial sums meet in LDS at the end),
+    // over a ring of 128 KiB - one such workgroup per CU, so more than NUM_CUS tiles would take it
+    // two rounds.  Beyond that the 4-wavefront form with its two buffers (64 KiB of LDS, two
+    // workgroups per CU) is faster.
     const int mode = tuning().async_mode;
     const bool can_async = t.splits == 1 && mode != ASYNC_OFF;
     if (can_async) {
@@ -1375,12 +1478,12 @@ int gemm_mfma_bf16(const GemmArgs& g, void* stream) {
                 tail.c = (char*)g.c + m0 * g.n * csz;
                 if (g.c2) tail.c2 = (char*)g.c2 + m0 * g.n * 2;
                 if (g.r) tail.r = (const char*)g.r + m0 * g.n * (g.r_f32 ? 4 : 2);
-                if (int rc = launch_ring<256, 256, 2, 4>(head, s)) return rc;
+                if (int rc = launch_ring<256, 256, 2, 4, 1>(head, s)) return rc;
                 const long t128 = (long)((tail.m + 127) / 128) * ((tail.n + 127) / 128);
-                if (t128 <= NUM_CUS) return launch_async<128, 128, 2, 2, 2, 3>(tail, s);
-                return launch_async<128, 128, 2, 2, 1, 2>(tail, s);
+                if (t128 <= NUM_CUS) return launch_ring<128, 128, 2, 2, 2>(tail, s);
+                return launch_ring<128, 128, 2, 2, 1>(tail, s);
             }
-            return launch_ring<256, 256, 2, 4>(g, s);
+            return launch_ring<256, 256, 2, 4, 1>(g, s);
         }
         if (t.bm == 64) {
             // one tile per CU at most: all of LDS for one workgroup, an eight-stage ring walked two stages per
@@ -1391,8 +1494,8 @@ int gemm_mfma_bf16(const GemmArgs& g, void* stream) {
         if (t.bm == 128 && t.bn == 128) {
             const long t128 = (long)((g.m + 127) / 128) * ((g.n + 127) / 128);
             const bool ksplit = mode != ASYNC_AUTO ? mode == ASYNC_KSLICED : t128 <= NUM_CUS;
-            if (ksplit) return launch_async<128, 128, 2, 2, 2, 3>(g, s);
-            return launch_async<128, 128, 2, 2, 1, 2>(g, s);
+            if (ksplit) return launch_ring<128, 128, 2, 2, 2>(g, s);
+            return launch_ring<128, 128, 2, 2, 1>(g, s);
         }
     }
     if (t.bm == 256 && t.bn == 256) return launch_layout<256, 256, 2, 4, 1>(g, t.splits, s);
@@ -1426,13 +1529,13 @@ int launch_group_tiled(int count, const GemmArgs* g, float* const* bsum, int ove
     }
     for (int i = 0; i < count; ++i) grp.group_m[i] = raster_group(grp.tiles_m[i], grp.tiles_n[i], (tiles + 7) / 8, tile, tile);
     for (int i = count; i <= GROUP_MAX; ++i) grp.first[i] = tiles;
-    if (tile == 256) return launch_group_ring<256, 256, 2, 4>(grp, stream);
+    if (tile == 256) return launch_group_ring<256, 256, 2, 4, 1>(grp, stream);
     if (tile == 64) return tiles <= NUM_CUS ? launch_group<64, 64, 2, 2, 2, 8, 2>(grp, stream, first) : launch_group<64, 64, 1, 2, 2, 4>(grp, stream, first);
     // two workgroups per CU or the k-sliced 8-wavefront form
     const int mode = tuning().async_mode;
     const bool ksplit = mode != ASYNC_AUTO ? mode == ASYNC_KSLICED : tiles <= NUM_CUS;
-    if (ksplit) return launch_group<128, 128, 2, 2, 2, 3>(grp, stream, first);
-    return launch_group<128, 128, 2, 2, 1, 2>(grp, stream, first);
+    if (ksplit) return launch_group_ring<128, 128, 2, 2, 2>(grp, stream, first);
+    return launch_group_ring<128, 128, 2, 2, 1>(grp, stream, first);
 }
 }  // namespace
 

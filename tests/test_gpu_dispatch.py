@@ -147,12 +147,21 @@ def test_bf16_large_tiles(m, n, k, layout):
     test_bf16_small_gemm(m if layout != "wgrad" else m // 8 * 8 + 8, n, k, layout)
 
 
-# grouped weight gradients with column sums on 256x256 tiles
-@pytest.mark.parametrize("k", [64, 128, 192, 320])
-def test_bf16_large_groups(k):
+# bf16 products on 128x128 tiles: up to one per CU (a ring of four steps) and beyond (two buffers)
+@pytest.mark.parametrize("k", [8, 72, 128, 192, 264, 320, 456, 520, 584])
+@pytest.mark.parametrize("m,n", [(2056, 1032), (3080, 2056)])
+@pytest.mark.parametrize("layout", ["fwd", "dgrad", "wgrad"])
+def test_bf16_middle_tiles(m, n, k, layout):
+    test_bf16_small_gemm(m, n, k, layout)
+
+
+# grouped weight gradients with column sums on 256x256 tiles and on both forms of 128x128 tiles
+@pytest.mark.parametrize("k", [64, 128, 192, 320, 576])
+@pytest.mark.parametrize("shapes", [[(1032, 1544), (2056, 1032), (1032, 2312), (1032, 1288)], [(1032, 1544), (1032, 520)],
+                                    [(1032, 1544), (2056, 1032), (1032, 1032)]])
+def test_bf16_groups(k, shapes):
     import torch
-    print("bf16 group", k, flush=True)
-    shapes = [(1032, 1544), (2056, 1032), (1032, 2312), (1032, 1288)]
+    print("bf16 group", k, shapes, flush=True)
     probs, sums, want = [], [], []
     for i, (m, n) in enumerate(shapes):
         X, Y = _rand((k, m), i, b.BF16), _rand((k, n), 10 + i, b.BF16)
