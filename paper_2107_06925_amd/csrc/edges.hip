@@ -313,6 +313,78 @@ __global__ __launch_bounds__(EDGE_THREADS) void xent_kernel(T* __restrict__ z, c
     }
 }
 
+// The same for bf16 rows that fit a workgroup's registers (up to NT * NV pieces of 16 bytes, kept as they
+// arrive): the row is read once and written once.  What bounds it is that traffic as long as the exponentials
+// hide behind it, which the general kernel's do not (expf and a running maximum are some 50 vector instructions
+// an element, and it reads the row twice): 4096 x 50304 231 -> 155 us.  So the maximum comes first, an exponential is the
+// hardware's exp2 of (z - max) log2(e) - the difference of two bf16 values first, which leaves no common
+// error in the sum - and 64 registers a lane keep two workgroups of 1024 on a CU, one loading while the other works.
+template <int NT, int NV>
+__global__ __launch_bounds__(NT, 8) void xent_row_kernel(bf16_t* __restrict__ z, const int* __restrict__ targets,
+                                                         float* __restrict__ loss_rows, int vocab, float scale) {
+    constexpr int NW = NT / WAVE;
+    constexpr float LOG2E = 1.4426950408889634f;
+    __shared__ float red_m[NW], red_s[NW];
+    const int t = blockIdx.x, tid = threadIdx.x, lane = tid % WAVE, wave = tid / WAVE, nchunk = vocab / 8;
+    bf16_t* row = z + (size_t)t * vocab;
+    uint4 q[NV];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int c = tid + i * NT;
+        if (c < nchunk) q[i] = *reinterpret_cast<const uint4*>(row + c * 8);
+        else q[i] = make_uint4(0xff80ff80u, 0xff80ff80u, 0xff80ff80u, 0xff80ff80u);      // -inf: adds nothing
+    }
+    const int tgt = min(max(targets[t], 0), vocab - 1);
+    const float z_tgt = (float)row[tgt];
+    auto unpack = [&](int i, float* v) {
+        // widened anew in every pass: kept from pass to pass, the floats would take 64 registers more and spill
+        asm volatile("" : "+v"(q[i].x), "+v"(q[i].y), "+v"(q[i].z), "+v"(q[i].w));
+        load_vec<bf16_t>(reinterpret_cast<const bf16_t*>(&q[i]), v);
+    };
+    float m = -3.0e38f;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        float v[8];
+        unpack(i, v);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) m = fmaxf(m, v[e]);
+    }
+    m = wave_max(m);
+    if (lane == 0) red_m[wave] = m;
+    __syncthreads();                                  // also: the target logit has been read
+    m = wave_max(red_m[lane % NW]);
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        float v[8];
+        unpack(i, v);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = __builtin_amdgcn_exp2f((v[e] - m) * LOG2E);
+        s += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+    }
+    s = wave_sum(s);
+    if (lane == 0) red_s[wave] = s;
+    __syncthreads();
+    const float gs = wave_sum(lane < NW ? red_s[lane] : 0.f);
+    const float inv = 1.0f / gs;
+    if (tid == 0) loss_rows[t] = scale * (m + logf(gs) - z_tgt);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int c = tid + i * NT;
+        if (c >= nchunk) continue;
+        float v[8];
+        unpack(i, v);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = __builtin_amdgcn_exp2f((v[e] - m) * LOG2E) * inv;
+        if (c == tgt / 8)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] -= e == tgt % 8 ? 1.0f : 0.0f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] *= scale;
+        store_vec<bf16_t>(row + c * 8, v);
+    }
+}
+
 // loss[0] += sum of loss_rows in a fixed order (one workgroup)
 __global__ __launch_bounds__(EDGE_THREADS) void loss_sum_kernel(const float* __restrict__ loss_rows, int n, float* __restrict__ loss) {
     __shared__ float red[EDGE_THREADS];
@@ -419,8 +491,20 @@ int chimera_op_softmax_xent(int dtype, int rows, int vocab, void* d_logits, cons
     hipStream_t s = (hipStream_t)hip_stream;
     if (dtype == CHIMERA_F32)
         hipLaunchKernelGGL(xent_kernel<float>, dim3(rows), dim3(EDGE_THREADS), 0, s, (float*)d_logits, d_targets, d_loss_rows, vocab, scale);
-    else
-        hipLaunchKernelGGL(xent_kernel<bf16_t>, dim3(rows), dim3(EDGE_THREADS), 0, s, (bf16_t*)d_logits, d_targets, d_loss_rows, vocab, scale);
+    else {
+        // registers for the row: a small workgroup as long as four pieces a thread do, else 1024 threads; beyond
+        // eight pieces a thread (65536 columns) the row stays in memory
+        bf16_t* z = (bf16_t*)d_logits;
+#define XENT_ROW(NT, NV) hipLaunchKernelGGL((xent_row_kernel<NT, NV>), dim3(rows), dim3(NT), 0, s, z, d_targets, d_loss_rows, vocab, scale)
+        if (vocab <= 256 * 8) XENT_ROW(256, 1);
+        else if (vocab <= 512 * 8) XENT_ROW(256, 2);
+        else if (vocab <= 1024 * 8) XENT_ROW(256, 4);
+        else if (vocab <= 2048 * 8) XENT_ROW(1024, 2);
+        else if (vocab <= 4096 * 8) XENT_ROW(1024, 4);
+        else if (vocab <= 8192 * 8) XENT_ROW(1024, 8);
+        else hipLaunchKernelGGL(xent_kernel<bf16_t>, dim3(rows), dim3(EDGE_THREADS), 0, s, z, d_targets, d_loss_rows, vocab, scale);
+#undef XENT_ROW
+    }
     CHIMERA_LAUNCH_CHECK("softmax cross-entropy");
     hipLaunchKernelGGL(loss_sum_kernel, dim3(1), dim3(EDGE_THREADS), 0, s, d_loss_rows, rows, d_loss);
     CHIMERA_LAUNCH_CHECK("loss sum");

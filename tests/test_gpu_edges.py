@@ -64,6 +64,36 @@ def test_softmax_xent(dtype, rows, vocab):
     assert_close(to_np(loss_rows)[:len(per_row)], np.array(per_row), b.F32, "loss per row")
 
 
+@pytest.mark.parametrize("vocab", [2048, 2056, 4096, 4104, 8192, 8200, 16384, 16392, 32768, 32776, 65536, 65544])
+def test_softmax_xent_row_sizes(vocab):
+    # ends of the ranges of the row kernels' sizes, extreme logits, targets at both ends of the row
+    import torch
+    print("xent row", vocab, flush=True)
+    rows = 5
+    z = _rand((rows, vocab), 21, b.BF16, 3.0)
+    z[1] = synth.round_to_bf16(z[1] * 30)                     # one entry holds nearly all of the probability
+    z[2] = -3.0e38
+    z[2, vocab - 3] = 3.0e38                                  # the widest finite range
+    z[2] = synth.round_to_bf16(z[2])
+    z[3, ::2] = -np.inf                                       # masked entries
+    targets = np.array([0, vocab - 1, vocab - 3, 1, vocab // 2], dtype=np.int32)
+    dz = to_dev(z, b.BF16)
+    loss_rows, loss = torch.empty(rows, device="cuda"), torch.zeros(1, device="cuda")
+    b.chimera_op_softmax_xent(dz, torch.from_numpy(targets).cuda(), 0.25, loss_rows, loss)
+    torch.cuda.synchronize()
+    x = z.astype(np.float64)
+    m = x.max(axis=1, keepdims=True)
+    s = np.exp(x - m).sum(axis=1, keepdims=True)
+    p = np.exp(x - m) / s
+    rng = np.arange(rows)
+    want_loss = 0.25 * ((m + np.log(s))[:, 0] - x[rng, targets])
+    p[rng, targets] -= 1
+    # float sums and exponentials: 1e-5 of the larger of the loss and the row's logits it is a difference of
+    bound = 1e-5 * np.maximum(np.abs(want_loss), 0.25 * np.abs(m[:, 0]))
+    assert np.all(np.abs(to_np(loss_rows) - want_loss) <= bound)
+    assert_close(to_np(dz), 0.25 * p, b.BF16, "dz")
+
+
 @pytest.mark.parametrize("dtype,tokens,hidden,vocab", [(b.F32, 256, 128, 1024), (b.BF16, 512, 256, 2048), (b.BF16, 200, 136, 1000),
                                                        (b.BF16, 4096, 1024, 50304)])
 def test_head_loss(dtype, tokens, hidden, vocab):
@@ -92,6 +122,7 @@ def test_head_loss(dtype, tokens, hidden, vocab):
     assert_close(to_np(dw), 2 * want["dw_head"], dtype, "dw_head")
     assert_close(to_np(dg), 2 * want["dlnf_g"], dtype, "dlnf_g")
     assert_close(to_np(db), 2 * want["dlnf_b"], dtype, "dlnf_b")
+
 
 
 def test_edge_argument_errors():
