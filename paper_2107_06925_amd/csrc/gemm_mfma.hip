@@ -815,7 +815,7 @@ __device__ __forceinline__ void gemm_ring_tile(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, const bf16_t* __restrict__ bias,
     const bf16_t* __restrict__ R, void* __restrict__ C, bf16_t* __restrict__ C2, int m, int n, int k, int lda,
     int ldb, int epi, int epi_flag, int res_types, int tiles_m, int tiles_n, int group_m, int block_id,
-    float* __restrict__ bsum = nullptr, bool xcd_remap = true) {
+    float* __restrict__ bsum = nullptr, bool xcd_remap = true, int col0 = 0) {
     constexpr int NT = WGM * WGN * WGK * 64, NS = WGK == 1 ? 2 : 4;
     constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16, HM = TM / 2;      // 16x16 tiles per wavefront
     constexpr int CA = BM * (RK / 8) / NT, CB = BN * (RK / 8) / NT, CS = CA + CB;     // 16-byte pieces per thread and stage
@@ -831,7 +831,7 @@ __device__ __forceinline__ void gemm_ring_tile(
     const int gsz = min(tiles_m - first_m, group_m);
     const int tile_m = first_m + (pid % width) % gsz;
     const int tile_n = (pid % width) / gsz;
-    const int i0 = tile_m * BM, j0 = tile_n * BN;
+    const int i0 = tile_m * BM, j0 = col0 + tile_n * BN;
 
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1174,9 +1174,9 @@ template <int BM, int BN, int WGM, int WGN, int WGK, bool A_KC, bool B_KC>
 __global__ __launch_bounds__(WGM* WGN * WGK * 64, 2) void gemm_bf16_ring_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, const bf16_t* __restrict__ bias,
     const bf16_t* __restrict__ R, void* __restrict__ C, bf16_t* __restrict__ C2, int m, int n, int k, int lda,
-    int ldb, int epi, int epi_flag, int res_types, int tiles_m, int tiles_n, int group_m) {
+    int ldb, int epi, int epi_flag, int res_types, int tiles_m, int tiles_n, int group_m, int col0) {
     gemm_ring_tile<BM, BN, WGM, WGN, WGK, A_KC, B_KC, -1>(A, B, bias, R, C, C2, m, n, k, lda, ldb, epi, epi_flag, res_types,
-                                                          tiles_m, tiles_n, group_m, (int)blockIdx.x);
+                                                          tiles_m, tiles_n, group_m, (int)blockIdx.x, nullptr, true, col0);
 }
 
 template <int BM, int BN, int WGM, int WGN, int WGK, int NS, int SPS, bool A_KC, bool B_KC>
@@ -1245,8 +1245,8 @@ __global__ __launch_bounds__(WGM* WGN * WGK * 64) void gemm_bf16_async_group_ker
 // second launch with 128x128 tiles instead.  Cost estimate in units of one 256x256 round: a round
 // of 128x128 tiles (quarter of the flops, 1.6x the time per flop) counts 0.45.  Returns the b
 // that minimises it (0: leave the product whole); `other` = 256x256 tiles of the launch that do
-// not belong to this product.
-int bands_to_peel(long other, int tm, int tn, int n) {
+// not belong to this product.  Columns are counted by the same rule with rows and columns exchanged.
+int bands_to_peel(long other, int tm, int tn, int n, double* cost = nullptr) {
     const int tn128 = (n + 127) / 128;
     auto rounds = [](long tiles) { return (double)((tiles + NUM_CUS - 1) / NUM_CUS); };
     const double whole = rounds(other + (long)tm * tn);
@@ -1256,6 +1256,7 @@ int bands_to_peel(long other, int tm, int tn, int n) {
         const double est = rounds(other + (long)(tm - b) * tn) + 0.45 * rounds((long)b * 2 * tn128);
         if (est < best) { best = est; best_b = b; }
     }
+    if (cost) *cost = best;
     return best_b;
 }
 
@@ -1375,16 +1376,17 @@ int launch_async(const GemmArgs& g, hipStream_t s) {
     return CHIMERA_OK;
 }
 
+// Columns [col0, col0 + 256 * cols256) of the product, or from col0 on.
 template <int BM, int BN, int WGM, int WGN, int WGK>
-int launch_ring(const GemmArgs& g, hipStream_t s) {
-    const int tm = (g.m + BM - 1) / BM, tn = (g.n + BN - 1) / BN;
+int launch_ring(const GemmArgs& g, hipStream_t s, int col0 = 0, int cols256 = 0) {
+    const int tm = (g.m + BM - 1) / BM, tn = cols256 ? cols256 * (256 / BN) : (g.n - col0 + BN - 1) / BN;
     const dim3 grid(tm * tn), block(WGM * WGN * WGK * 64);
     const int gm = raster_group(tm, tn, (tm * tn + 7) / 8, BM, BN);
 #define CHIMERA_GEMM_LAUNCH(AKC, BKC)                                                                                \
     hipLaunchKernelGGL((gemm_bf16_ring_kernel<BM, BN, WGM, WGN, WGK, AKC, BKC>), grid, block, 0, s,                     \
                        (const bf16_t*)g.a, (const bf16_t*)g.b, (const bf16_t*)g.bias, (const bf16_t*)g.r, g.c,        \
                        (bf16_t*)g.c2, g.m, g.n, g.k, g.lda, g.ldb, g.epilogue, epilogue_flag(g),                            \
-                       (g.r_f32 ? 1 : 0) | (g.c_f32 ? 2 : 0), tm, tn, gm)
+                       (g.r_f32 ? 1 : 0) | (g.c_f32 ? 2 : 0), tm, tn, gm, col0)
     if (g.a_kc && !g.b_kc) CHIMERA_GEMM_LAUNCH(true, false);
     else if (g.a_kc && g.b_kc) CHIMERA_GEMM_LAUNCH(true, true);
     else CHIMERA_GEMM_LAUNCH(false, false);
@@ -1466,7 +1468,17 @@ int gemm_mfma_bf16(const GemmArgs& g, void* stream) {
     if (can_async) {
         if (t.bm == 256 && t.bn == 256) {
             const int tm = (g.m + 255) / 256, tn = (g.n + 255) / 256;
-            const int b = forced_tile().bm ? 0 : bands_to_peel(0, tm, tn, g.n);
+            double by_rows = 0, by_columns = 0;
+            const int b = forced_tile().bm ? 0 : bands_to_peel(0, tm, tn, g.n, &by_rows);
+            const int bc = forced_tile().bm ? 0 : bands_to_peel(0, tn, tm, g.m, &by_columns);
+            if (bc > 0 && by_columns < by_rows && g.n - (tn - bc) * 256 >= 8) {
+                // columns in the same way: wide outputs of few tile rows (1024 x 50304 x 4096, 788 tiles:
+                // three full rounds and 20 tiles: 482 -> 386 + 41 us)
+                const int col0 = (tn - bc) * 256;
+                if (int rc = launch_ring<256, 256, 2, 4, 1>(g, s, 0, tn - bc)) return rc;
+                if ((long)((g.m + 127) / 128) * ((g.n - col0 + 127) / 128) <= NUM_CUS) return launch_ring<128, 128, 2, 2, 2>(g, s, col0);
+                return launch_ring<128, 128, 2, 2, 1>(g, s, col0);
+            }
             if (b > 0 && g.m - (tm - b) * 256 >= 8) {
                 // rows [0, m0) with 256x256 tiles, rows [m0, m) with 128x128 tiles
                 const size_t m0 = (size_t)(tm - b) * 256;

@@ -147,6 +147,13 @@ def test_bf16_large_tiles(m, n, k, layout):
     test_bf16_small_gemm(m if layout != "wgrad" else m // 8 * 8 + 8, n, k, layout)
 
 
+# 260 tiles of 256x256 in four tile rows: the last columns go to 128x128 tiles
+@pytest.mark.parametrize("m,n,k", [(1000, 16424, 72), (1024, 16640, 200), (776, 16392, 128)])
+@pytest.mark.parametrize("layout", ["fwd", "dgrad", "wgrad"])
+def test_bf16_peeled_columns(m, n, k, layout):
+    test_bf16_small_gemm(m, n, k, layout)
+
+
 # bf16 products on 128x128 tiles: up to one per CU (a ring of four steps) and beyond (two buffers)
 @pytest.mark.parametrize("k", [8, 72, 128, 192, 264, 320, 456, 520, 584])
 @pytest.mark.parametrize("m,n", [(2056, 1032), (3080, 2056)])
