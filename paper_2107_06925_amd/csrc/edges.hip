@@ -411,7 +411,7 @@ int check_edge(int dtype, int tokens, int seq, int hidden, int vocab, bool vocab
 
 size_t aligned(size_t b) { return (b + 255) / 256 * 256; }
 
-struct HeadLayout { size_t h, mean, rstd, logits, loss_rows, dh, scratch, total; };
+struct HeadLayout { size_t h, mean, rstd, logits, loss_rows, dh, scratch, need, slabs, total; };
 HeadLayout head_layout(int dtype, int M, int H, int V) {
     const size_t e = dtype == CHIMERA_F32 ? 4 : 2;
     HeadLayout l{};
@@ -424,6 +424,9 @@ HeadLayout head_layout(int dtype, int M, int H, int V) {
     l.loss_rows = take((size_t)M * 4);
     l.dh = take((size_t)M * H * e);
     l.scratch = take(layernorm_bwd_scratch_floats(M, H) * 4);
+    // the slabs of the data gradient's partial sums; a workspace that holds only what comes before them does too
+    l.need = b;
+    l.slabs = take(dtype == CHIMERA_BF16 ? gemm_mfma_split_bytes(M, H, V) : 0);
     l.total = b;
     return l;
 }
@@ -524,7 +527,7 @@ int chimera_head_loss(int dtype, int tokens, int hidden, int vocab, const void* 
     if (!d_y || !d_targets || !d_lnf_g || !d_lnf_b || !d_w_head || !d_dy || !d_dlnf_g || !d_dlnf_b || !d_dw_head || !d_loss || !d_workspace)
         return fail(CHIMERA_EINVAL, "NULL operand");
     const HeadLayout l = head_layout(dtype, tokens, hidden, vocab);
-    if (workspace_bytes < l.total) return fail(CHIMERA_ENOMEM, "workspace holds %zu bytes, need %zu", workspace_bytes, l.total);
+    if (workspace_bytes < l.need) return fail(CHIMERA_ENOMEM, "workspace holds %zu bytes, need %zu", workspace_bytes, l.need);
     if (((uintptr_t)d_workspace & 255) || (((uintptr_t)d_y | (uintptr_t)d_dy | (uintptr_t)d_w_head | (uintptr_t)d_dw_head) & 15))
         return fail(CHIMERA_EINVAL, "workspace must be 256-byte aligned, tensors 16-byte aligned");
     const int M = tokens, H = hidden, V = vocab;
@@ -552,7 +555,10 @@ int chimera_head_loss(int dtype, int tokens, int hidden, int vocab, const void* 
     // dh = dz W^T
     GemmArgs d{};
     d.m = M; d.n = H; d.k = V; d.a = logits; d.lda = V; d.a_kc = 1; d.b = d_w_head; d.ldb = V; d.b_kc = 1; d.c = dh; d.epilogue = EPI_NONE;
-    EDGE_TRY(gemm(d));
+    if (dtype == CHIMERA_BF16 && l.total > l.need && workspace_bytes >= l.total && gemm_mfma_supports(d))
+        EDGE_TRY(gemm_mfma_split(d, (float*)(ws + l.slabs), hip_stream));
+    else
+        EDGE_TRY(gemm(d));
     // dW += h^T dz
     GemmArgs w{};
     w.m = H; w.n = V; w.k = M; w.a = h; w.lda = H; w.a_kc = 0; w.b = logits; w.ldb = V; w.b_kc = 0; w.c = d_dw_head; w.epilogue = EPI_ACCUM_F32;

@@ -1179,6 +1179,36 @@ __global__ __launch_bounds__(WGM* WGN * WGK * 64, 2) void gemm_bf16_ring_kernel(
                                                           tiles_m, tiles_n, group_m, (int)blockIdx.x, nullptr, true, col0);
 }
 
+// A long contraction with few output tiles, cut along k: workgroups [s * tiles, (s+1) * tiles) (numbered so
+// that an XCD works on few splits) write the partial sums over k in [s * k_per, (s+1) * k_per) to float slab s;
+// split_sum_kernel adds the slabs in their order.  No workgroup waits for another.
+template <int BM, int BN, int WGM, int WGN, int WGK>
+__global__ __launch_bounds__(WGM* WGN * WGK * 64, 2) void gemm_bf16_ring_split_kernel(
+    const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, float* __restrict__ slabs, int m, int n, int k, int lda, int ldb,
+    int tiles_m, int tiles_n, int group_m, int splits, int k_per) {
+    const int tiles = tiles_m * tiles_n, total = tiles * splits;
+    const int xcd = (int)blockIdx.x & 7, local = (int)blockIdx.x >> 3;
+    const int pid = xcd * (total >> 3) + min(xcd, total & 7) + local;
+    const int split = pid / tiles, k0 = split * k_per;
+    gemm_ring_tile<BM, BN, WGM, WGN, WGK, true, true, EPI_ACCUM_F32>(
+        A + k0, B + k0, nullptr, nullptr, slabs + (size_t)split * m * n, nullptr, m, n, min(k_per, k - k0), lda, ldb,
+        EPI_ACCUM_F32, 1, 0, tiles_m, tiles_n, group_m, pid % tiles, nullptr, false);
+}
+
+__global__ __launch_bounds__(256) void split_sum_kernel(const float* __restrict__ slabs, size_t elems, int splits, bf16_t* __restrict__ c) {
+    const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 8;
+    if (i >= elems) return;
+    float v[8];
+    load8(slabs + i, v);
+    for (int s = 1; s < splits; ++s) {
+        float u[8];
+        load8(slabs + (size_t)s * elems + i, u);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += u[e];
+    }
+    store8(c + i, v);
+}
+
 template <int BM, int BN, int WGM, int WGN, int WGK, int NS, int SPS, bool A_KC, bool B_KC>
 __global__ __launch_bounds__(WGM* WGN * WGK * 64) void gemm_bf16_async_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, const bf16_t* __restrict__ bias,
@@ -1513,6 +1543,58 @@ int gemm_mfma_bf16(const GemmArgs& g, void* stream) {
     if (t.bm == 256 && t.bn == 256) return launch_layout<256, 256, 2, 4, 1>(g, t.splits, s);
     if (t.bm == 128 && t.bn == 128) return launch_layout<128, 128, 2, 2, 1>(g, 1, s);
     return fail(CHIMERA_EINVAL, "no %dx%d gemm tile", t.bm, t.bn);
+}
+
+// How a product of k-contiguous operands is cut along k (splits = 1: not at all): fewer tiles than CUs leave
+// CUs idle, and 256x256 tiles cost a third less energy and time per flop than the 128x128 tiles that an uncut
+// product of 64 to 143 of them takes.  Model of the time in us, constants measured: a step of 64 k of a round of
+// tiles, against the float slabs written and read (at 4.5 TB/s) and the launch that adds them.
+// 4096 x 1024 x 50304 462 -> 355 + 12 us; a head's whole pass over 1000 x 512 x 20000 164 -> 131, 128 x 128 x 65536
+// 252 -> 87, 1111 x 776 x 50304 507 -> 443, 632 x 1600 x 50304 589 -> 515 us.
+struct SplitPlan { int tile, splits, k_per; };
+static SplitPlan split_plan(int m, int n, int k) {
+    const long steps = (k + RK - 1) / RK, t256 = (long)((m + 255) / 256) * ((n + 255) / 256), t128 = (long)((m + 127) / 128) * ((n + 127) / 128);
+    const long t64 = (long)((m + 63) / 64) * ((n + 63) / 64);
+    SplitPlan best{0, 1, k};
+    if (forced_tile().bm || tuning().async_mode != ASYNC_AUTO || t256 >= 144) return best;
+    constexpr double STEP256 = 1.4, STEP128 = 0.5, STEP64 = 0.25, SLAB = 8 / 4.5e6, LAUNCH = 10;
+    auto rounds = [](long tiles) { return (double)((tiles + NUM_CUS - 1) / NUM_CUS); };
+    double cost = steps * (t64 <= 2 * NUM_CUS ? rounds(t64) * STEP64 : rounds(t128) * STEP128);
+    cost *= 0.9;                                         // a split must pay clearly
+    for (int s = 2; s <= 64 && steps / s >= 8; ++s) {
+        const long per = (steps + s - 1) / s;
+        if ((steps + per - 1) / per != s) continue;
+        const double slabs = SLAB * s * m * n + LAUNCH;
+        const double c256 = rounds(t256 * s) * per * STEP256 + slabs, c128 = rounds(t128 * s) * per * STEP128 + slabs;
+        if (c256 < cost) { cost = c256; best = {256, s, (int)per * RK}; }
+        if (c128 < cost) { cost = c128; best = {128, s, (int)per * RK}; }
+    }
+    return best;
+}
+size_t gemm_mfma_split_bytes(int m, int n, int k) {
+    const SplitPlan p = split_plan(m, n, k);
+    return p.splits > 1 ? (size_t)p.splits * m * n * sizeof(float) : 0;
+}
+int gemm_mfma_split(const GemmArgs& g, float* slabs, void* stream) {
+    if (!gemm_mfma_supports(g) || !g.a_kc || !g.b_kc || g.epilogue != EPI_NONE || ((uintptr_t)g.c | (uintptr_t)slabs) & 15)
+        return fail(CHIMERA_EINVAL, "split product: k-contiguous operands and a plain bf16 result");
+    const SplitPlan p = split_plan(g.m, g.n, g.k);
+    if (p.splits < 2) return gemm_mfma_bf16(g, stream);
+    hipStream_t s = (hipStream_t)stream;
+    const int tm = (g.m + p.tile - 1) / p.tile, tn = (g.n + p.tile - 1) / p.tile;
+    const int gm = raster_group(tm, tn, std::min(tm * tn, (tm * tn * p.splits + 7) / 8), p.tile, p.tile);
+    const dim3 grid(tm * tn * p.splits), block(512);
+#define CHIMERA_SPLIT_LAUNCH(...)                                                                                       \
+    hipLaunchKernelGGL((gemm_bf16_ring_split_kernel<__VA_ARGS__>), grid, block, 0, s, (const bf16_t*)g.a, (const bf16_t*)g.b, \
+                       slabs, g.m, g.n, g.k, g.lda, g.ldb, tm, tn, gm, p.splits, p.k_per)
+    if (p.tile == 256) CHIMERA_SPLIT_LAUNCH(256, 256, 2, 4, 1);
+    else CHIMERA_SPLIT_LAUNCH(128, 128, 2, 2, 2);
+#undef CHIMERA_SPLIT_LAUNCH
+    CHIMERA_LAUNCH_CHECK("bf16 gemm (split)");
+    const size_t elems = (size_t)g.m * g.n;
+    hipLaunchKernelGGL(split_sum_kernel, dim3((unsigned)((elems / 8 + 255) / 256)), dim3(256), 0, s, slabs, elems, p.splits, (bf16_t*)g.c);
+    CHIMERA_LAUNCH_CHECK("split sum");
+    return CHIMERA_OK;
 }
 
 bool gemm_mfma_group_supports(int count, const GemmArgs* g) {

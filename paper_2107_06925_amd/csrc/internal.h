@@ -74,6 +74,10 @@ bool gemm_f32_group_supports(int count, const GemmArgs* g);
 int gemm_f32_group(int count, const GemmArgs* g, float* const* bsum, int overwrite, void* stream);
 int gemm_mfma_bf16(const GemmArgs& g, void* stream);
 bool gemm_mfma_supports(const GemmArgs& g);
+// C = A B^T (both k-contiguous, no epilogue), cut along k where few output tiles meet a long contraction: `slabs`
+// holds gemm_mfma_split_bytes (0: not cut, `slabs` is not used)
+int gemm_mfma_split(const GemmArgs& g, float* slabs, void* stream);
+size_t gemm_mfma_split_bytes(int m, int n, int k);
 // `count` float-accumulating products (index-contiguous operands, one contraction length) in one launch;
 // bsum (may be null, entries may be null): bsum[p][j] += sum_k B_p(k, j), the bias gradient of a linear layer;
 // overwrite != 0: C_p and bsum_p receive the results instead of accumulating them

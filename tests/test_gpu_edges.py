@@ -124,6 +124,35 @@ def test_head_loss(dtype, tokens, hidden, vocab):
     assert_close(to_np(db), 2 * want["dlnf_b"], dtype, "dlnf_b")
 
 
+@pytest.mark.parametrize("tokens,hidden,vocab", [(130, 136, 20008), (1, 8, 16384), (264, 520, 30072), (40, 1032, 65528), (1100, 392, 12296)])
+def test_head_split_data_gradient(tokens, hidden, vocab):
+    # Few output tiles over a long vocabulary: the data gradient is cut along it where the workspace has
+    # room for the partial sums, and whole where it only holds the rest.
+    import torch
+    print("head split", tokens, hidden, vocab, flush=True)
+    y, w = _rand((tokens, hidden), 31, b.BF16, 1.5), _rand((hidden, vocab), 32, b.BF16, 0.05)
+    g, be = synth.round_to_bf16((1 + 0.1 * _rand((hidden,), 33, b.BF16)).astype(np.float32)), _rand((hidden,), 34, b.BF16, 0.1)
+    targets = np.random.default_rng(35).integers(0, vocab, size=tokens).astype(np.int32)
+    want = eo.head_fwd_bwd(y, targets, g, be, w, 1.0 / tokens)
+    full = b.lib().chimera_head_workspace_bytes(b.BF16, tokens, hidden, vocab)
+    b.check(b.lib().chimera_op_gemm_tuning(0, 0, 0, 1))         # register-staged products only: never cut
+    try:
+        least = b.lib().chimera_head_workspace_bytes(b.BF16, tokens, hidden, vocab)
+    finally:
+        b.check(b.lib().chimera_op_gemm_tuning(0, 0, 0, 0))
+    assert full > least and (full - least) % (tokens * hidden * 4) < 256        # whole slabs, rounded up to 256 bytes
+    for size in (full, full - 1, least):
+        dy = torch.empty((tokens, hidden), dtype=torch.bfloat16, device="cuda")
+        dg, db = torch.zeros(hidden, device="cuda"), torch.zeros(hidden, device="cuda")
+        dw, loss = torch.zeros((hidden, vocab), device="cuda"), torch.zeros(1, device="cuda")
+        ws = torch.full((size,), 0xff, dtype=torch.uint8, device="cuda")         # NaN wherever nothing is written
+        b.chimera_head_loss(to_dev(y, b.BF16), torch.from_numpy(targets).cuda(), to_dev(g, b.BF16), to_dev(be, b.BF16),
+                            to_dev(w, b.BF16), 1.0 / tokens, dy, dg, db, dw, loss, workspace=ws)
+        torch.cuda.synchronize()
+        assert_close(to_np(dy), want["dy"], b.BF16, "dy")
+        assert_close(to_np(dg), want["dlnf_g"], b.BF16, "dlnf_g")
+        assert_close(to_np(dw), want["dw_head"], b.BF16, "dw_head")
+
 
 def test_edge_argument_errors():
     import torch
