@@ -768,7 +768,8 @@ __device__ __forceinline__ void gemm_async_tile(
 // One output tile on v_mfma_f32_16x16x32_bf16, k in steps of 64 through LDS buffers, software
 // pipelined across the barrier.  WGK = 1: wavefronts of 128x64 (256x256, 8 of them) or 64x64 (128x128,
 // 4 of them, two workgroups per CU) and two buffers.  WGK = 2, for 128x128 with one workgroup per CU: 8
-// wavefronts, two on each 64x64 block, each taking half of every step's k, over a ring of four buffers.
+// wavefronts, two on each 64x64 block, each taking half of every step's k, over a ring of four buffers; for
+// 256x128 the same with blocks of 128x64 and three buffers.
 //
 // What bounds it is power: with random operands the chip lowers its clock under matrix load (the same
 // launch on zeros runs 1.3 to 1.4 times as fast), so a product's rate is set by the energy per flop.
@@ -816,7 +817,7 @@ __device__ __forceinline__ void gemm_ring_tile(
     const bf16_t* __restrict__ R, void* __restrict__ C, bf16_t* __restrict__ C2, int m, int n, int k, int lda,
     int ldb, int epi, int epi_flag, int res_types, int tiles_m, int tiles_n, int group_m, int block_id,
     float* __restrict__ bsum = nullptr, bool xcd_remap = true, int col0 = 0) {
-    constexpr int NT = WGM * WGN * WGK * 64, NS = WGK == 1 ? 2 : 4;
+    constexpr int NT = WGM * WGN * WGK * 64, NS = WGK == 1 ? 2 : BM * BN > 128 * 128 ? 3 : 4;
     constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16, HM = TM / 2;      // 16x16 tiles per wavefront
     constexpr int CA = BM * (RK / 8) / NT, CB = BN * (RK / 8) / NT, CS = CA + CB;     // 16-byte pieces per thread and stage
     constexpr unsigned STAGE = (BM + BN) * RK * 2, ABYTES = BM * RK * 2;
@@ -1053,36 +1054,38 @@ __device__ __forceinline__ void gemm_ring_tile(
             // all but the `younger` stages behind it have landed
             auto landed = [&](int younger) {
                 if (younger >= NS - 2) arrived(CHIMERA_C((NS - 2) * CS));
-                else if (younger == 1) arrived(CHIMERA_C(CS));
+                else if (NS == 4 && younger == 1) arrived(CHIMERA_C(CS));
                 else arrived(CHIMERA_C(0));
             };
-            static_assert(NS == 4, "landed() counts up to two younger stages");
+            static_assert(NS == 3 || NS == 4, "landed() counts up to two younger stages");
             landed(KT - 1);
             meet();
             static_for<TN>([&](auto b) { read_b(b, CHIMERA_C(0), CHIMERA_C(0)); });
             static_for<HM>([&](auto a) { read_a(a, CHIMERA_C(0), CHIMERA_C(0)); });
-            auto step = [&](auto q_c, auto always_c, int t) {
-                constexpr int q = decltype(q_c)::value, next = (q + 1) % NS;
+            // step u of an unrolled group: slot u mod NS, operand set u mod 2
+            auto step = [&](auto u_c, auto always_c, int t) {
+                constexpr int u = decltype(u_c)::value, q = u % NS, next = (q + 1) % NS, set = u & 1;
                 constexpr bool always = decltype(always_c)::value;
                 const bool more = always || t + NS - 1 < KT;
-                phase(CHIMERA_C(0), CHIMERA_C(q & 1), sums_c, [&](auto i_c) {
+                phase(CHIMERA_C(0), CHIMERA_C(set), sums_c, [&](auto i_c) {
                     constexpr int i = decltype(i_c)::value;
-                    if constexpr (i < HM) read_a(CHIMERA_C(HM + i), CHIMERA_C(0), q_c);
+                    if constexpr (i < HM) read_a(CHIMERA_C(HM + i), CHIMERA_C(0), CHIMERA_C(q));
                     else if constexpr (i < HM + CS) { if (more) request(CHIMERA_C(i - HM), CHIMERA_C((q + NS - 1) % NS)); }
                 });
                 static_assert(HM + CS <= HM * TN && TN + HM <= HM * TN, "room behind the MFMAs");
                 if constexpr (always) arrived(CHIMERA_C((NS - 2) * CS));
                 else landed(KT - 2 - t);
                 meet();
-                phase(CHIMERA_C(1), CHIMERA_C(q & 1), sums_c, [&](auto i_c) {
+                phase(CHIMERA_C(1), CHIMERA_C(set), sums_c, [&](auto i_c) {
                     constexpr int i = decltype(i_c)::value;
-                    if constexpr (i < TN) read_b(i_c, CHIMERA_C(next & 1), CHIMERA_C(next));
+                    if constexpr (i < TN) read_b(i_c, CHIMERA_C(set ^ 1), CHIMERA_C(next));
                     else if constexpr (i < TN + HM) read_a(CHIMERA_C(i - TN), CHIMERA_C(0), CHIMERA_C(next));
                 });
             };
             int t = 0;
-            for (; t + 2 * NS - 2 < KT; t += NS) static_for<NS>([&](auto q) { step(q, std::true_type{}, 0); });
-            for (; t < KT; t += NS) static_for<NS>([&](auto q) { if (t + q < KT) step(q, std::false_type{}, t + q); });
+            constexpr int U = NS % 2 ? 2 * NS : NS;
+            for (; t + U + NS - 2 < KT; t += U) static_for<U>([&](auto u) { step(u, std::true_type{}, 0); });
+            for (; t < KT; t += U) static_for<U>([&](auto u) { if (t + u < KT) step(u, std::false_type{}, t + u); });
         }
     };
     if constexpr (ONLY_EPI == EPI_ACCUM_F32) {
@@ -1346,6 +1349,23 @@ constexpr int MAX_SPLITS = 8;
 // 1024 x 2560 x 640 (160, 640) 9.8 -> 11.3, 632 x 4800 x 1600 (190, 750) 17.6 -> 21.
 bool small_tiles(long tiles64) { return tiles64 <= 2 * NUM_CUS && tuning().async_mode == ASYNC_AUTO; }
 
+// 256x128 tiles for a product that shares the chip with another stage's: it should then take little of the
+// chip's time, not little time.  Alone it is slower than 128x128, whose tiles are twice as many (4096 x 1024 x
+// 4096 40 -> 56 us, 2048 x 1600 x 6400 57 -> 82), but it spends a third fewer CU-microseconds, a quarter less
+// traffic into LDS and a third less out of it, and the other stage has work for the CUs it leaves.  Replays of
+// two stages, 128x128 -> 256x128: bert48 21.1 -> 20.6 ms, gpt2-1p3b-n32 103.4 -> 100.2, gpt2-deep 52.3 -> 50.5, three
+// blocks of 2048 at 3000 tokens 13.2 -> 12.7.  With fewer than 100 tiles the two stages together leave the chip
+// half empty (1024 wide at 3000 tokens, 96 tiles: 8.2 -> 8.4 ms; 768 at 4096, 96: 7.3 -> 7.5), with k below 1024 the larger
+// epilogue weighs more than the loop saves (512 wide at 4096 tokens, 192 tiles: 4.69 -> 4.77).  The two-per-CU form of
+// 64x64 tiles (257 to 512 of them) gives way earlier, from 60 tiles on, where k is long: four blocks of 2048 at 1024
+// tokens 8.06 -> 7.53 ms, six of 1024 at 2048 tokens 6.71 -> 6.59; not at 512 wide, k up to 2048 (4.69 -> 4.74).
+bool wide_tiles(const GemmArgs& g) {
+    if (!g.beside || tuning().async_mode != ASYNC_AUTO) return false;
+    const long t2 = (long)((g.m + 255) / 256) * ((g.n + 127) / 128), t64 = (long)((g.m + 63) / 64) * ((g.n + 63) / 64);
+    if (t2 > NUM_CUS) return false;
+    return (t2 >= 100 && g.k >= 1024) || (t2 >= 60 && t64 > NUM_CUS && small_tiles(t64) && g.k > 2048);
+}
+
 // 256x256 (8 wavefronts) once the output has enough such tiles for most of the 256 CUs,
 // else 128x128 (4 wavefronts, two workgroups per CU); thresholds measured on MI355X.
 // A CU fills LDS from L2 at roughly 64 bytes per clock, so a 128x128x64 step (32 KiB for
@@ -1365,6 +1385,7 @@ TileChoice choose_tile(const GemmArgs& g) {
     }
     // (measured at 2048 x 4800 x 1600: 152 tiles of 256x256 on 256 CUs take 42 us, 608 of 128x128 48 us)
     if (t256 >= 144) return {256, 256, 1};
+    if (wide_tiles(g)) return {256, 128, 1};
     if (small_tiles((long)((g.m + 63) / 64) * ((g.n + 63) / 64))) return {64, 64, 1};
     return {128, 128, 1};
 }
@@ -1527,6 +1548,7 @@ int gemm_mfma_bf16(const GemmArgs& g, void* stream) {
             }
             return launch_ring<256, 256, 2, 4, 1>(g, s);
         }
+        if (t.bm == 256) return launch_ring<256, 128, 2, 2, 2>(g, s);
         if (t.bm == 64) {
             // one tile per CU at most: all of LDS for one workgroup, an eight-stage ring walked two stages per
             // barrier by two wavefronts per SIMD (256 x 256 x 1024: 6.7 -> 6.1 us; 632 x 1600 x 6400: 28.4 -> 25.4)

@@ -61,6 +61,7 @@ struct GemmArgs {
     void* c2;                           // [m,n]
     int epilogue;
     int gelu_erf;
+    int beside;                         // work of other streams shares the chip with this launch
     void* ws;                           // optional split-K workspace (bf16 matrix-core path), may be null
     size_t ws_bytes;
 };

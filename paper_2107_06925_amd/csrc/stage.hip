@@ -107,6 +107,7 @@ struct chimera_stage {
     hipEvent_t ev_side[2] = {};       // side -> main: the side work of a block (by parity) is done
     bool have_side = false;
     bool use_side = false;            // the running backward uses it
+    bool beside = false;              // a replay runs this stage beside another one
 
     struct IO { const void* x; void* y; const void* dy; void* dx; };
     std::unordered_map<int, IO> io;
@@ -189,6 +190,7 @@ int gemm(chimera_stage* st, const GemmArgs& g, int cls, hipStream_t stream) {
 int linear_fwd(chimera_stage* st, int m, int n, int k, const void* x, const void* w, const void* bias, const void* r,
                void* c, void* c2, int epi, int r_f32 = 0, int c_f32 = 0) {
     GemmArgs g{};
+    g.beside = st->beside;
     g.m = m; g.n = n; g.k = k;
     g.a = x; g.lda = k; g.a_kc = 1;
     g.b = w; g.ldb = n; g.b_kc = 0;
@@ -199,6 +201,7 @@ int linear_fwd(chimera_stage* st, int m, int n, int k, const void* x, const void
 // dX[m,k] = dY[m,n] W^T, W stored [k, n]: contraction over n, contiguous in both.
 int linear_dgrad(chimera_stage* st, int m, int n, int k, const void* dy, const void* w, const void* r, void* dx, int epi) {
     GemmArgs g{};
+    g.beside = st->beside;
     g.m = m; g.n = k; g.k = n;
     g.a = dy; g.lda = n; g.a_kc = 1;
     g.b = w; g.ldb = n; g.b_kc = 1;
@@ -880,6 +883,7 @@ int chimera_run_worker_pipes(int algo, int rank, int D, int N, int f) {
         if (j != hipSuccess && !rc) rc = fail(CHIMERA_EDEVICE, "worker replay: %s", hipGetErrorString(j));
         l.st->stream = wk.lanes[l.lane];
         l.st->have_side = false;
+        l.st->beside = true;
     }
     for (size_t i = 0; i < ops.size() && !rc; ++i) {
         const Op& o = ops[i];
@@ -907,6 +911,7 @@ int chimera_run_worker_pipes(int algo, int rank, int D, int N, int f) {
         if (j != hipSuccess && !rc) rc = fail(CHIMERA_EDEVICE, "worker replay: %s", hipGetErrorString(j));
         l.st->stream = l.home;
         l.st->have_side = l.side;
+        l.st->beside = false;
     }
     // one wait per distinct stream
     hipError_t e = hipSuccess;

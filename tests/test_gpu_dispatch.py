@@ -11,9 +11,9 @@ from gpu_util import assert_close, make_stage, to_dev, to_np
 pytestmark = pytest.mark.gpu
 
 
-def _worker(overlap, shared_dx):
+def _worker(overlap, shared_dx, D=4, N=8, L=2, H=128, heads=2, S=72, B=1):
     import torch
-    D, N, rank, L, H, heads, S, B = 4, 8, 1, 2, 128, 2, 72, 1
+    rank = 1
     need = b.stash_slots_needed(b.DIRECT, D, N, rank)
     stages = []
     for pipe, sid in ((0, rank), (1, D - 1 - rank)):
@@ -46,6 +46,22 @@ def test_replay_beside_equals_replay_in_turn(shared):
     dx = torch.zeros((72, 128), device="cuda", dtype=torch.bfloat16) if shared else None
     for a, c in zip(_worker(True, dx), _worker(False, dx)):
         assert torch.equal(a, c)
+
+
+# Products of 256x128 tiles, which only a replay of two stages beside each other takes: up to 256 of 128x128 in
+# turn (the same order of summation), beyond them with ragged rows, columns and k, and in place of 64x64.  Two
+# orders of summing a few thousand products in float differ by less than a bf16 rounding; each of a block's
+# results is rounded a few times: well within the bf16 bar.
+@pytest.mark.parametrize("H,heads,S,B,same", [(1024, 16, 1000, 4, True), (1032, 43, 1300, 3, False), (2048, 16, 512, 2, False)])
+def test_replay_beside_wide_tiles(H, heads, S, B, same):
+    import torch
+    print("replay lanes, wide tiles", H, S, B, flush=True)
+    shape = dict(D=2, N=2, L=1, H=H, heads=heads, S=S, B=B)
+    for i, (a, c) in enumerate(zip(_worker(True, None, **shape), _worker(False, None, **shape))):
+        if same:
+            assert torch.equal(a, c)
+        else:
+            assert_close(to_np(a), to_np(c), b.BF16, "output %d" % i)
 
 
 # tokens: all the same, few distinct, more than one window of the list; widths of one to eight pieces per lane
