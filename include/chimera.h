@@ -365,7 +365,7 @@ size_t chimera_op_gemm_workspace_bytes(int m, int n, int k);
 int chimera_op_gemm_tuning(int tile_m, int tile_n, int splits, int async_mode);
 /* For reports: the kernel instantiation(s) the calling thread's last grouped launch
  * (chimera_op_gemm_group_accumulate, or a block's weight gradients inside chimera_bwd) went
- * to, e.g. "gemm_bf16_ring_group_kernel<256,256,2,4>"; two names joined by
+ * to, e.g. "gemm_bf16_ring_group_kernel<256,256,2,4,1>"; two names joined by
  * " + " when the last row bands went out as a second launch.  Thread-local static storage,
  * never freed by the caller; "" before the first such launch. */
 const char* chimera_op_gemm_group_last_kernel(void);
@@ -470,7 +470,9 @@ int chimera_op_softmax_xent(int dtype, int rows, int vocab, void* d_logits, cons
  *   [hidden, vocab] (float) += their gradients.
  * `scale` is the weight of these tokens in the mini-batch loss (1 / token count for a mean).
  * d_workspace: chimera_head_workspace_bytes(dtype, tokens, hidden, vocab) bytes, 256-byte
- * aligned (it holds h, the logits and their gradient).  ENOMEM if it is too small. */
+ * aligned (it holds h, the logits and their gradient, and in bf16 partial sums of the data
+ * gradient; a workspace without room for those alone still serves, more slowly).  ENOMEM if
+ * it is too small. */
 size_t chimera_head_workspace_bytes(int dtype, int tokens, int hidden, int vocab);
 int chimera_head_loss(int dtype, int tokens, int hidden, int vocab, const void* d_y,
                       const int32_t* d_targets, const void* d_lnf_g, const void* d_lnf_b,

@@ -1,15 +1,15 @@
-// bf16 GEMM on the CDNA4 matrix cores (v_mfma_f32_32x32x16_bf16), float
-// accumulation, for the three products of a linear layer:
+// bf16 GEMM on the CDNA4 matrix cores, float accumulation, for the three products of a linear layer:
 //   forward  Y  = X W      A k-contiguous, B stored [k, n]
 //   dgrad    dX = dY W^T   A k-contiguous, B k-contiguous
 //   wgrad    dW += X^T dY  A stored [k, m], B stored [k, n]  (k = tokens)
 //
-// One workgroup of 4 or 8 wavefronts computes a BM x BN tile; each wavefront
-// owns a 128x64 or 64x64 part of it as a grid of 32x32 MFMA tiles whose
-// accumulators never leave the registers.  The k loop moves BK = 64 at a time
-// through LDS with two buffers: while the matrix cores work on buffer b, the
-// loads of the next k step are already in flight to registers and are written
-// to buffer b^1 afterwards, one barrier per step.
+// One workgroup computes a tile of the output; its wavefronts own parts of it as a grid of MFMA
+// tiles whose accumulators never leave the registers.  Three kernels, by size (choose_tile):
+//   gemm_ring_tile    256x256, 256x128 and 128x128 tiles on v_mfma_f32_16x16x32_bf16
+//   gemm_async_tile   64x64 tiles on v_mfma_f32_32x32x16_bf16, a ring of k steps
+//   gemm_bf16_kernel  the register-staged form: split-K and shapes on request
+// The k loop moves BK = 64 at a time through LDS, the next steps in flight.  What follows on
+// LDS layouts is the latter two's; gemm_ring_tile's own differ in their exchanges and are described there.
 //
 // An operand that is k-contiguous in memory (X in the forward, both operands of
 // dgrad) sits in LDS as [row][k], 128 bytes per row, and lane l reads its MFMA
@@ -665,16 +665,8 @@ __device__ __forceinline__ void gemm_async_tile(
                 if (col < n) bsum[col] = epi_flag ? v[b] : bsum[col] + v[b];
             }
     };
-    if constexpr (WGK == 1) {
-        if constexpr (ONLY_EPI == EPI_ACCUM_F32)
-            if (col_sums) {
-                float v[TN];
-#pragma unroll
-                for (int b = 0; b < TN; ++b) v[b] = cs[b][0];
-                put_col_sums(v);
-            }
-        finish(acc, i0 + wm0);
-    } else if constexpr (TM == 1) {
+    static_assert(WGK == 2, "two wavefronts per block");
+    if constexpr (TM == 1) {
         // As below, but there is only one band of rows: the second wavefront hands it over and is done.
         static_assert(WGK == 2 && sizeof(lds) >= (size_t)WGM * WGN * TN * 4 * 64 * sizeof(float4) + BN * sizeof(float), "LDS too small");
         float4* xch = reinterpret_cast<float4*>(lds) + (size_t)wmn * TN * 4 * 64 + lane;
