@@ -1334,6 +1334,10 @@ TileChoice forced_tile() { return tuning().forced; }
 
 constexpr int MAX_SPLITS = 8;
 
+// The LDS-DMA kernels address a lane's rows of a k-contiguous operand by 32-bit byte offsets from the tile's
+// corner, up to 255 rows away; wider rows go to the register-staged kernel, whose element offsets reach 2^32.
+bool far_rows(const GemmArgs& g) { return (g.a_kc && g.lda >= 1 << 23) || (g.b_kc && g.ldb >= 1 << 23); }
+
 // 64x64 tiles while they all fit on the chip at once, two per CU: a smaller product is bound by
 // its chain of latencies and by how many CUs pull its operands, not by the bytes a small tile
 // costs.  Measured, 128x128 -> 64x64: 400 x 960 x 320 6.6 -> 4.3 us, 632 x 1600 x 6400 (65 tiles of
@@ -1497,7 +1501,9 @@ int gemm_mfma_bf16(const GemmArgs& g, void* stream) {
     if (!gemm_mfma_supports(g)) return fail(CHIMERA_EINVAL, "bf16 matrix-core gemm: unsupported shape or layout");
     if (g.epilogue < EPI_NONE || g.epilogue > EPI_ACCUM_F32) return fail(CHIMERA_EINVAL, "unknown epilogue %d", g.epilogue);
     hipStream_t s = (hipStream_t)stream;
-    const TileChoice t = choose_tile(g);
+    const bool far = far_rows(g);
+    TileChoice t = choose_tile(g);
+    if (far && (t.bm == 64 || t.bm != t.bn)) t = {128, 128, 1};
     if (t.splits > 1 && (size_t)((g.m + 255) / 256) * ((g.n + 255) / 256) * sizeof(unsigned) > SPLITK_COUNTER_BYTES)
         return fail(CHIMERA_EINVAL, "too many tiles for split-K");
     // 128x128 tiles: with one workgroup per CU, a workgroup of 4 wavefronts leaves one wavefront
@@ -1507,7 +1513,7 @@ int gemm_mfma_bf16(const GemmArgs& g, void* stream) {
     // two rounds.  Beyond that the 4-wavefront form with its two buffers (64 KiB of LDS, two
     // workgroups per CU) is faster.
     const int mode = tuning().async_mode;
-    const bool can_async = t.splits == 1 && mode != ASYNC_OFF;
+    const bool can_async = t.splits == 1 && mode != ASYNC_OFF && !far;
     if (can_async) {
         if (t.bm == 256 && t.bn == 256) {
             const int tm = (g.m + 255) / 256, tn = (g.n + 255) / 256;
@@ -1593,7 +1599,7 @@ int gemm_mfma_split(const GemmArgs& g, float* slabs, void* stream) {
     if (!gemm_mfma_supports(g) || !g.a_kc || !g.b_kc || g.epilogue != EPI_NONE || ((uintptr_t)g.c | (uintptr_t)slabs) & 15)
         return fail(CHIMERA_EINVAL, "split product: k-contiguous operands and a plain bf16 result");
     const SplitPlan p = split_plan(g.m, g.n, g.k);
-    if (p.splits < 2) return gemm_mfma_bf16(g, stream);
+    if (p.splits < 2 || far_rows(g)) return gemm_mfma_bf16(g, stream);
     hipStream_t s = (hipStream_t)stream;
     const int tm = (g.m + p.tile - 1) / p.tile, tn = (g.n + p.tile - 1) / p.tile;
     const int gm = raster_group(tm, tn, std::min(tm * tn, (tm * tn * p.splits + 7) / 8), p.tile, p.tile);

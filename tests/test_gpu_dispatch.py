@@ -163,6 +163,24 @@ def test_bf16_large_tiles(m, n, k, layout):
     test_bf16_small_gemm(m if layout != "wgrad" else m // 8 * 8 + 8, n, k, layout)
 
 
+# rows so far apart that 255 of them exceed 32-bit byte offsets: each operand in turn, sizes of every tile
+@pytest.mark.parametrize("m,n,k", [(264, 72, 72), (264, 4616, 64)])
+def test_bf16_far_rows(m, n, k):
+    import torch
+    print("bf16 gemm far rows", m, n, k, flush=True)
+    ld = (1 << 23) + 8
+    A, B = _rand((m, k), 1, b.BF16), _rand((n, k), 2, b.BF16)
+    far = torch.empty((m, ld), device="cuda", dtype=torch.bfloat16)
+    far[:, :k] = to_dev(A, b.BF16)
+    want = A.astype(np.float64) @ B.astype(np.float64).T
+    c = torch.empty((m, n), device="cuda", dtype=torch.bfloat16)
+    b.chimera_op_gemm(far, to_dev(B, b.BF16), c, m, n, k, 1, 1, lda=ld)
+    assert_close(to_np(c), want, b.BF16)
+    c = torch.empty((n, m), device="cuda", dtype=torch.bfloat16)
+    b.chimera_op_gemm(to_dev(B, b.BF16), far, c, n, m, k, 1, 1, ldb=ld)
+    assert_close(to_np(c), want.T, b.BF16)
+
+
 # 260 tiles of 256x256 in four tile rows: the last columns go to 128x128 tiles
 @pytest.mark.parametrize("m,n,k", [(1000, 16424, 72), (1024, 16640, 200), (776, 16392, 128)])
 @pytest.mark.parametrize("layout", ["fwd", "dgrad", "wgrad"])
