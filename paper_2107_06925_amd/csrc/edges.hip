@@ -184,8 +184,8 @@ __global__ __launch_bounds__(EMB_THREADS) void embed_bwd_kernel(const int* __res
             n_wave += __popcll(own[i]);
         }
         if (lane == 0) sm.counts[wave] = n_wave;
-        if (tid == 0) sm.heads = 0;
-        __syncthreads();                                        // also: the previous window's list is no longer read
+        __syncthreads();                                        // also: the previous window's list and number of heads are no longer read
+        if (tid == 0) sm.heads = 0;                             // counted up behind the next barrier
         int at = 0, n = 0;
 #pragma unroll
         for (int k = 0; k < EMB_WAVES; ++k) { const int c = sm.counts[k]; at += k < wave ? c : 0; n += c; }

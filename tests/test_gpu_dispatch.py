@@ -84,6 +84,24 @@ def test_embedding_backward(tokens, seq, hidden, vocab, dtype):
     assert_close(to_np(dwpe), want_pe, b.F32, "dwpe")
 
 
+# Several windows of the list with at most a few entries of a token in each: no workgroup meets a frequent token, so
+# between its windows only the windows' own barriers order the wavefronts.  Small whole numbers: float sums are exact.
+@pytest.mark.parametrize("tokens,hidden,vocab,dtype", [(8193, 64, 1024, b.BF16), (30000, 512, 5000, b.BF16), (40960, 264, 40000, b.F32)])
+def test_embedding_backward_windows(tokens, hidden, vocab, dtype):
+    import torch
+    print("embedding backward windows", tokens, hidden, vocab, dtype, flush=True)
+    rng = np.random.default_rng(3)
+    ids = rng.permutation(np.arange(tokens) % vocab).astype(np.int32)
+    dx = rng.integers(-8, 9, size=(tokens, hidden)).astype(np.float32)
+    want = np.zeros((vocab, hidden), dtype=np.float32)
+    np.add.at(want, ids, dx)
+    dwte, dwpe = torch.zeros((vocab, hidden), device="cuda"), torch.zeros((1, hidden), device="cuda")
+    for n in range(1, 4):
+        b.chimera_op_embedding_bwd(torch.from_numpy(ids).cuda(), 1, to_dev(dx, dtype), dwte, dwpe)
+        assert np.array_equal(to_np(dwte), n * want)
+        assert np.array_equal(to_np(dwpe)[0], n * dx.sum(0))
+
+
 def _rand(shape, seed, dtype, scale=1.0):
     a = np.random.default_rng(seed).standard_normal(shape).astype(np.float32) * scale
     return synth.round_to_bf16(a) if dtype == b.BF16 else a
