@@ -842,7 +842,7 @@ __device__ __forceinline__ void gemm_ring_tile(
         }
         kk = slot / (rows / 8);
         const int pc = slot % (rows / 8), ic = (((pc >> 1) ^ rkswz(kk)) << 1) | (pc & 1);
-        return (unsigned)(kk * ld + min(row0 + ic * 8, nrows - 8) - row0) * 2u;
+        return ((unsigned)kk * (unsigned)ld + (unsigned)(min(row0 + ic * 8, nrows - 8) - row0)) * 2u;     // kk < k: see far_operand
     };
     // Requests of an index-contiguous operand lie whole k rows apart: one lane offset and a pointer each.
     // Those of a k-contiguous one lie rows apart (clamped at the matrix's end): a lane offset each.
@@ -1334,9 +1334,15 @@ TileChoice forced_tile() { return tuning().forced; }
 
 constexpr int MAX_SPLITS = 8;
 
-// The LDS-DMA kernels address a lane's rows of a k-contiguous operand by 32-bit byte offsets from the tile's
-// corner, up to 255 rows away; wider rows go to the register-staged kernel, whose element offsets reach 2^32.
-bool far_rows(const GemmArgs& g) { return (g.a_kc && g.lda >= 1 << 23) || (g.b_kc && g.ldb >= 1 << 23); }
+// gemm_ring_tile addresses a lane's pieces by 32-bit byte offsets from the tile's corner: up to 255 rows away
+// in a k-contiguous operand, up to 31 rows of k (as many as there are) and 255 elements in an index-contiguous one.
+// Operands that reach further go to the register-staged kernel, whose element offsets reach 2^32.  (A group's never do
+// where k is 64 or more: k * ld < 2^32 bounds ld; a stage's rows are at most 16384 elements long.)
+bool far_operand(const GemmArgs& g) {
+    const long k_rows = std::min(g.k, 32) - 1;
+    auto far = [&](int k_contiguous, long ld) { return k_contiguous ? ld >= 1l << 23 : k_rows * ld + 256 >= 1l << 31; };
+    return far(g.a_kc, g.lda) || far(g.b_kc, g.ldb);
+}
 
 // 64x64 tiles while they all fit on the chip at once, two per CU: a smaller product is bound by
 // its chain of latencies and by how many CUs pull its operands, not by the bytes a small tile
@@ -1501,7 +1507,7 @@ int gemm_mfma_bf16(const GemmArgs& g, void* stream) {
     if (!gemm_mfma_supports(g)) return fail(CHIMERA_EINVAL, "bf16 matrix-core gemm: unsupported shape or layout");
     if (g.epilogue < EPI_NONE || g.epilogue > EPI_ACCUM_F32) return fail(CHIMERA_EINVAL, "unknown epilogue %d", g.epilogue);
     hipStream_t s = (hipStream_t)stream;
-    const bool far = far_rows(g);
+    const bool far = far_operand(g);
     TileChoice t = choose_tile(g);
     if (far && (t.bm == 64 || t.bm != t.bn)) t = {128, 128, 1};
     if (t.splits > 1 && (size_t)((g.m + 255) / 256) * ((g.n + 255) / 256) * sizeof(unsigned) > SPLITK_COUNTER_BYTES)
@@ -1599,7 +1605,7 @@ int gemm_mfma_split(const GemmArgs& g, float* slabs, void* stream) {
     if (!gemm_mfma_supports(g) || !g.a_kc || !g.b_kc || g.epilogue != EPI_NONE || ((uintptr_t)g.c | (uintptr_t)slabs) & 15)
         return fail(CHIMERA_EINVAL, "split product: k-contiguous operands and a plain bf16 result");
     const SplitPlan p = split_plan(g.m, g.n, g.k);
-    if (p.splits < 2 || far_rows(g)) return gemm_mfma_bf16(g, stream);
+    if (p.splits < 2 || far_operand(g)) return gemm_mfma_bf16(g, stream);
     hipStream_t s = (hipStream_t)stream;
     const int tm = (g.m + p.tile - 1) / p.tile, tn = (g.n + p.tile - 1) / p.tile;
     const int gm = raster_group(tm, tn, std::min(tm * tn, (tm * tn * p.splits + 7) / 8), p.tile, p.tile);

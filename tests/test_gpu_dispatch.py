@@ -199,6 +199,29 @@ def test_bf16_far_rows(m, n, k):
     assert_close(to_np(c), want.T, b.BF16)
 
 
+# few rows of k, so far apart that 31 (or 15) of them exceed 32-bit byte offsets, and the widest that do not: index-contiguous
+# operands on 128x128 and 256x256 tiles
+@pytest.mark.parametrize("m,n,k,ld", [(2048, 2048, 32, 70000000), (2048, 2048, 32, 69273648), (2048, 2056, 32, 69273648), (2048, 2048, 56, 70000000),
+                                      (3080, 2824, 16, 143165584), (3080, 2824, 16, 143165552), (264, 72, 32, 70000000)])
+def test_bf16_far_k_rows(m, n, k, ld):
+    import torch
+    print("bf16 gemm far k rows", m, n, k, ld, flush=True)
+    A, B = _rand((m, k), 1, b.BF16), _rand((k, n), 2, b.BF16)
+    want = A.astype(np.float64) @ B.astype(np.float64)
+    far = torch.empty((k, ld), device="cuda", dtype=torch.bfloat16)
+    far[:, :n] = to_dev(B, b.BF16)
+    c = torch.empty((m, n), device="cuda", dtype=torch.bfloat16)
+    b.chimera_op_gemm(to_dev(A, b.BF16), far, c, m, n, k, 1, 0, ldb=ld)
+    assert_close(to_np(c), want, b.BF16)
+    c = torch.zeros((m, n), device="cuda")
+    b.chimera_op_gemm(to_dev(A.T, b.BF16), far, c, m, n, k, 0, 0, b.EPI_ACCUM_F32, ldb=ld)
+    assert_close(to_np(c), want, b.BF16)
+    far[:, :m] = to_dev(A.T, b.BF16)
+    c = torch.zeros((m, n), device="cuda")
+    b.chimera_op_gemm(far, to_dev(B, b.BF16), c, m, n, k, 0, 0, b.EPI_ACCUM_F32, lda=ld)
+    assert_close(to_np(c), want, b.BF16)
+
+
 # 260 tiles of 256x256 in four tile rows: the last columns go to 128x128 tiles
 @pytest.mark.parametrize("m,n,k", [(1000, 16424, 72), (1024, 16640, 200), (776, 16392, 128)])
 @pytest.mark.parametrize("layout", ["fwd", "dgrad", "wgrad"])
