@@ -596,6 +596,11 @@ __global__ __launch_bounds__(NT) void attn_bwd_dkv_kernel(const bf16_t* __restri
     attn_bwd_dkv_role<D, CAUSAL>(sm, (int)blockIdx.x, qkv, dctx, lse, delta, dqkv, S, heads, batch, d, scale);
 }
 
+// ctx in the forward (which has no dctx), ctx, dctx and dqkv in the backward
+bool misaligned(const AttnArgs& a) {
+    return a.dctx ? ((uintptr_t)a.ctx | (uintptr_t)a.dctx | (uintptr_t)a.dqkv) & 15 : (uintptr_t)a.ctx & 7;
+}
+
 int check(const AttnArgs& a) {
     if (!attention_mfma_supports(a)) return fail(CHIMERA_EINVAL, "matrix-core attention: unsupported shape (head_dim %d)", a.head_dim);
     return CHIMERA_OK;
@@ -608,12 +613,14 @@ bool attention_mfma_supports(const AttnArgs& a) {
     if (a.batch < 1 || a.seq < 1 || a.heads < 1 || a.batch > 65535 || a.heads > 65535) return false;
     if (((unsigned long long)a.heads * a.batch + 7) * ((a.seq + 127) / 128) >= (1ull << 30)) return false;   // 1-D grid
     if ((uintptr_t)a.qkv & 15) return false;
-    return true;
+    // Other buffers that 8- and 16-byte accesses cannot take: at the compiled head dimensions the call is refused
+    // (it would run many times slower without a word), at the others the plain kernels serve it.
+    return a.head_dim == 64 || a.head_dim == 128 || !misaligned(a);
 }
 
 int attention_fwd_mfma(const AttnArgs& a, void* stream) {
     if (int rc = check(a)) return rc;
-    if ((uintptr_t)a.ctx & 7) return fail(CHIMERA_EINVAL, "ctx must be 8-byte aligned");
+    if (misaligned(a)) return fail(CHIMERA_EINVAL, "ctx must be 8-byte aligned");
     const dim3 grid(attn_grid(a)), block(NT);
     const float sl2 = LOG2E / sqrtf((float)a.head_dim);
     hipStream_t s = (hipStream_t)stream;
@@ -629,7 +636,7 @@ int attention_fwd_mfma(const AttnArgs& a, void* stream) {
 
 int attention_bwd_mfma(const AttnArgs& a, void* stream) {
     if (int rc = check(a)) return rc;
-    if (((uintptr_t)a.ctx | (uintptr_t)a.dctx | (uintptr_t)a.dqkv) & 15) return fail(CHIMERA_EINVAL, "attention buffers must be 16-byte aligned");
+    if (misaligned(a)) return fail(CHIMERA_EINVAL, "attention buffers must be 16-byte aligned");
     hipStream_t s = (hipStream_t)stream;
     const dim3 block(NT);
     const dim3 grid(attn_grid(a)), grid2(2 * attn_grid(a));    // one role / both roles; attn_grid is a multiple of 8

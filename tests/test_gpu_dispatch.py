@@ -155,6 +155,43 @@ def test_bf16_attention_head_dims(batch, seq, heads, d, causal):
     _attention(b.BF16, batch, seq, heads, d, causal)
 
 
+# results and gradients at addresses that wide accesses cannot take: served at head dimensions other than 64 and 128, refused there
+@pytest.mark.parametrize("d,served", [(40, True), (96, True), (64, False), (128, False)])
+@pytest.mark.parametrize("shifted", ["ctx", "dctx", "dqkv"])
+def test_bf16_attention_alignment(d, served, shifted):
+    import torch
+    from oracle import block_oracle as bo
+    print("attention alignment", d, shifted, flush=True)
+    batch, seq, heads = 1, 70, 2
+    H = heads * d
+    qkv, dctx = _rand((seq, 3 * H), 1, b.BF16, 1.5), _rand((seq, H), 2, b.BF16)
+    ctx64, probs = bo.attention_fwd(qkv.astype(np.float64), batch, seq, heads, True)
+    want = bo.attention_bwd(dctx.astype(np.float64), qkv.astype(np.float64), probs, batch, seq, heads)
+
+    def place(name, shape):
+        at = 2 if name == shifted else 0                     # 4 bytes past a boundary
+        n = shape[0] * shape[1]
+        return torch.zeros(n + at, device="cuda", dtype=torch.bfloat16)[at:].view(shape)
+
+    q, ctx, do, dqkv = to_dev(qkv, b.BF16), place("ctx", (seq, H)), place("dctx", (seq, H)), place("dqkv", (seq, 3 * H))
+    do.copy_(to_dev(dctx, b.BF16))
+    lse, delta = torch.empty((batch, heads, seq), device="cuda"), torch.empty((batch, heads, seq), device="cuda")
+    if not served and shifted == "ctx":
+        with pytest.raises(b.ChimeraError) as e:
+            b.chimera_op_attention_fwd(q, ctx, lse, batch, seq, heads, d, True)
+        assert e.value.code == b.EINVAL
+        return
+    b.chimera_op_attention_fwd(q, ctx, lse, batch, seq, heads, d, True)
+    assert_close(to_np(ctx), ctx64, b.BF16, "ctx")
+    if not served:
+        with pytest.raises(b.ChimeraError) as e:
+            b.chimera_op_attention_bwd(q, ctx, lse, do, dqkv, delta, batch, seq, heads, d, True)
+        assert e.value.code == b.EINVAL
+        return
+    b.chimera_op_attention_bwd(q, ctx, lse, do, dqkv, delta, batch, seq, heads, d, True)
+    assert_close(to_np(dqkv), want, b.BF16, "dqkv")
+
+
 # bf16 products on 64x64 tiles: the two forms meet at 256 tiles, the form ends at 512; k below one step, with a
 # remainder, and around the lengths of the rings; a single row
 @pytest.mark.parametrize("m,n,k", [(1, 8, 8), (1000, 1024, 72), (1024, 1032, 136), (64, 64, 448), (40, 72, 520), (200, 136, 1032),
