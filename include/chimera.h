@@ -285,9 +285,15 @@ int chimera_worker_bind(chimera_stage* down_stage, chimera_stage* up_stage);
  * the end.  ENOMEM if a stage was bound with fewer slots than the schedule
  * needs.  Both stages must have no micro-batch in flight.  Each stage's ops run
  * in list order; the ops of different stages (different pipelines: no op of one
- * needs a result of another) run beside each other on the stages' own streams,
- * unless a stage has CHIMERA_OPT_OVERLAP = 0, their buffers overlap, or times are
- * being taken (chimera_worker_set_timing, chimera_profile_enable). */
+ * needs a result of another) run beside each other on streams of the library's own
+ * (the stages' streams wait for them), unless a stage has CHIMERA_OPT_OVERLAP = 0,
+ * their buffers overlap, times are being taken (chimera_worker_set_timing,
+ * chimera_profile_enable) or the device has no second hardware queue to give: then
+ * the stages take turns.  chimera_worker_last_lanes tells which it was.
+ * The first replay that can run stages beside each other waits for the stages' streams,
+ * creates up to four streams and launches a few tiny kernels to see that they have
+ * queues of their own (one or two milliseconds); where too few are found, a later
+ * replay looks again. */
 int chimera_run_worker(int rank, int D, int N);
 /* Same for any algorithm; for the one-pipeline baselines only the down stage
  * is used and holds stage `rank`. */
@@ -310,7 +316,8 @@ int chimera_worker_bind_doubling(chimera_stage* down2, chimera_stage* up2);
  * largest slot index in its ops.  One wait per stream at the end. */
 int chimera_run_worker_pipes(int algo, int rank, int D, int N, int f);
 /* on != 0: bracket every op of the next replays with HIP events (off by default).  The stages
- * then take turns, so that an op's time is its own. */
+ * then take turns, so that an op's time is its own (and the tiles of its products those of
+ * a stage that has the chip to itself). */
 int chimera_worker_set_timing(int on);
 /* Milliseconds the last chimera_run_worker* spent in forward ops and in
  * backward ops (HIP events around every op), and the op counts. */
@@ -319,10 +326,13 @@ int chimera_worker_last_timing(double* h_fwd_ms, double* h_bwd_ms, int* h_nf, in
  * every launch, i.e. up to (not including) its wait for the streams: the replay is bound by
  * the host once this approaches the iteration time. */
 int chimera_worker_last_enqueue_ms(double* h_ms);
+/* The number of streams on which the last chimera_run_worker* ran its stages beside each
+ * other; 1: the stages took turns. */
+int chimera_worker_last_lanes(int* h_lanes);
 
 /* Per-kernel-class timing of everything the stages launch while enabled: a HIP
- * event pair brackets every launch (this slows the replay a little, so keep it
- * off when timing whole iterations).  Classes: 0 GEMM forward, 1 GEMM dgrad,
+ * event pair brackets every launch (this slows the replay a little, and the stages of a
+ * replay take turns, so keep it off when timing whole iterations).  Classes: 0 GEMM forward, 1 GEMM dgrad,
  * 2 GEMM wgrad, 3 attention forward, 4 attention backward, 5 LayerNorm forward,
  * 6 LayerNorm backward, 7 column sums, 8 the second launch of a block's weight
  * gradients (row bands that leave the 256x256 launch for smaller tiles; class 2 is

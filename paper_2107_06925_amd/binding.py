@@ -69,6 +69,7 @@ _SIGNATURES = {
     "chimera_profile_read": (_i, [_i, C.POINTER(C.c_double), C.POINTER(C.c_longlong), C.POINTER(C.c_double)]),
     "chimera_model_select": (_i, [_i, _i, C.c_int64, C.c_double, C.c_double, C.c_double, _i, _i, _p, _p, _p]),
     "chimera_worker_last_enqueue_ms": (_i, [_p]),
+    "chimera_worker_last_lanes": (_i, [_p]),
     "chimera_op_gemm_workspace_bytes": (_sz, [_i, _i, _i]),
     "chimera_op_gemm_tuning": (_i, [_i, _i, _i, _i]),
     "chimera_op_gemm_group_last_kernel": (C.c_char_p, []),
@@ -324,6 +325,12 @@ def chimera_worker_last_timing():
 def chimera_worker_last_enqueue_ms():
     v = C.c_double()
     check(lib().chimera_worker_last_enqueue_ms(C.byref(v)))
+    return v.value
+
+
+def chimera_worker_last_lanes():
+    v = C.c_int(0)
+    check(lib().chimera_worker_last_lanes(C.byref(v)))
     return v.value
 
 

@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
+#include <bit>
 #include <cstdio>
 #include <cstring>
 #include <unordered_map>
@@ -523,37 +525,47 @@ struct Worker {
     int nf = 0, nb = 0;
     double enqueue_ms = 0;                    // host time of the last replay up to its final wait
     std::vector<hipStream_t> lanes;           // streams on which a replay runs its stages beside each other
-    int lanes_device = -1, lanes_tried = 0;
+    int lanes_device = -1;
+    int lanes_wait = 0, lanes_backoff = 0;    // replays until more lanes are looked for again; doubles with every failure
+    int lanes_used = 1;                       // by the last replay
 } g_worker;
 
-// The worker's lanes: at most MAX_LANES streams for the whole process, made when a worker with
-// several pipelines is first bound and kept from then on.  HIP deals streams over four hardware
-// queues, and two streams that share one run strictly one after the other (of 12 streams made in a
-// row a third of the pairs did, neighbours among them), so a candidate becomes a lane only if its
-// work was seen to run beside every earlier lane's: a kernel on the one waits, 100 us at most, for a
-// word that a kernel on the other writes.  Fewer lanes than wanted only means less overlap.
+// The worker's lanes: at most MAX_LANES streams for the whole process, made by the first replay that can use
+// them and kept from then on.  HIP deals streams over four hardware queues, and two streams that share one
+// run strictly one after the other (of 12 streams made in a row a third of the pairs did, neighbours among
+// them), so a candidate becomes a lane only if its work was seen to run beside every earlier lane's: a kernel
+// on the one waits, a bounded time, for a word that a kernel on the other writes.  What was seen is certain; not
+// to see it may also mean that other work held the CUs or the host up between the two launches.  So the attempts
+// get longer (earlier work in either queue is over by the second), and a replay that found too few lanes runs with those
+// and a later one looks again: the 2nd, 6th, 14th, ... after it, so that a device with fewer queues does not pay each time.
 constexpr int MAX_LANES = 4, MAX_CANDIDATES = 10;
 __device__ int lane_word, lane_seen;
 __global__ void lane_post_kernel(int token) { __hip_atomic_store(&lane_word, token, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__global__ void lane_wait_kernel(int token) {
+__global__ void lane_wait_kernel(int token, int ticks) {
     const long long t0 = wall_clock64();                      // 100 MHz
     int seen = 0;
-    while (!seen && wall_clock64() - t0 < 10000) seen = __hip_atomic_load(&lane_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == token;
+    while (!seen && wall_clock64() - t0 < ticks) seen = __hip_atomic_load(&lane_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == token;
     lane_seen = seen ? token : 0;
 }
 bool run_beside(hipStream_t a, hipStream_t b) {
     static int token = 0;
-    for (int attempt = 0; attempt < 2; ++attempt) {          // the first also loads the kernels
+    for (int ticks : {10000, 10000, 100000}) {               // 100 us (the first also loads the kernels), 100 us, 1 ms
         ++token;
-        hipLaunchKernelGGL(lane_wait_kernel, dim3(1), dim3(1), 0, a, token);
+        hipLaunchKernelGGL(lane_wait_kernel, dim3(1), dim3(1), 0, a, token, ticks);
         hipLaunchKernelGGL(lane_post_kernel, dim3(1), dim3(1), 0, b, token);
         int seen = 0;
+        if (hipMemcpyFromSymbolAsync(&seen, HIP_SYMBOL(lane_seen), sizeof seen, 0, hipMemcpyDeviceToHost, a) != hipSuccess) return false;
         if (hipStreamSynchronize(a) != hipSuccess || hipStreamSynchronize(b) != hipSuccess) return false;
-        if (hipMemcpyFromSymbol(&seen, HIP_SYMBOL(lane_seen), sizeof seen) != hipSuccess) return false;
         if (seen == token) return true;
     }
     return false;
 }
+// A capture that another thread has under way does not forbid this thread's synchronisations and new streams.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
 void make_lanes(Worker& wk, int want) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return;
@@ -561,19 +573,26 @@ void make_lanes(Worker& wk, int want) {
         for (hipStream_t s : wk.lanes) { (void)hipStreamSynchronize(s); (void)hipStreamDestroy(s); }
         wk.lanes.clear();
         wk.lanes_device = dev;
-        wk.lanes_tried = 0;
+        wk.lanes_wait = wk.lanes_backoff = 0;
     }
     want = std::min(want, MAX_LANES);
+    if ((int)wk.lanes.size() >= want) return;
+    if (wk.lanes_wait > 0) { --wk.lanes_wait; return; }
+    RelaxedCapture relaxed;
+    for (const chimera_stage* st : wk.pipes)
+        if (st && hipStreamSynchronize(st->stream) != hipSuccess) { (void)hipGetLastError(); return; }
     std::vector<hipStream_t> unfit;          // kept until the end, so that the next candidate gets another queue
-    while ((int)wk.lanes.size() < want && wk.lanes_tried < MAX_CANDIDATES) {
+    for (int tried = 0; (int)wk.lanes.size() < want && tried < MAX_CANDIDATES; ++tried) {
         hipStream_t s = nullptr;
-        ++wk.lanes_tried;
-        if (hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess) { (void)hipGetLastError(); break; }
+        if (hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess) break;
         bool ok = true;
         for (hipStream_t l : wk.lanes) ok = ok && run_beside(l, s);
         (ok ? wk.lanes : unfit).push_back(s);
     }
+    (void)hipGetLastError();                 // a failure here is no failure of the launches that follow
     for (hipStream_t s : unfit) (void)hipStreamDestroy(s);
+    if ((int)wk.lanes.size() < want) wk.lanes_wait = wk.lanes_backoff = std::min(2 * wk.lanes_backoff + 1, 1023);
+    else wk.lanes_backoff = 0;
 }
 }  // namespace
 
@@ -766,7 +785,6 @@ int chimera_worker_bind_pipes(chimera_stage* const* h_stages, int count) {
     }
     g_worker.pipes.assign(h_stages, h_stages + count);
     g_worker.fwd2[0] = g_worker.fwd2[1] = nullptr;
-    if (count > 1) make_lanes(g_worker, count);
     return CHIMERA_OK;
 }
 
@@ -851,32 +869,35 @@ int chimera_run_worker_pipes(int algo, int rank, int D, int N, int f) {
     // the buffers of two lanes meet.
     struct OnLane { chimera_stage* st; hipStream_t home; bool side; int lane; };
     std::vector<OnLane> on_lane;
+    std::vector<char> runs(pipes, 0);                 // pipelines with ops in this list
+    for (const Op& o : ops) runs[o.pipe] = 1;
+    auto stages_of = [&](int p) { return std::array<chimera_stage*, 2>{wk.pipes[p], p < 2 && recompute ? wk.fwd2[p] : nullptr}; };
+    bool beside = !wk.timing && !g_prof.on && std::count(runs.begin(), runs.end(), 1) >= 2;
+    for (int p = 0; p < pipes; ++p)
+        if (runs[p])
+            for (const chimera_stage* st : stages_of(p)) beside = beside && (!st || st->overlap);
+    if (beside) make_lanes(wk, pipes);
     const int lanes = (int)wk.lanes.size();
-    if (!wk.timing && !g_prof.on && lanes >= 2) {
+    if (beside && lanes >= 2) {
         std::vector<LaneRange> ranges;
-        bool ok = true;
-        int used = 0;
-        for (int p = 0; p < pipes && ok; ++p) {
-            chimera_stage* both[2] = {wk.pipes[p], p < 2 && recompute ? wk.fwd2[p] : nullptr};
-            bool any = false;
-            for (const Op& o : ops) {
-                if (o.pipe != p) continue;
-                any = true;
-                const bool dbl = o.kind == CHIMERA_OP_F2;
-                add_io_ranges(both[dbl], both[dbl]->io.at(o.mb), p % lanes, dbl || o.kind == CHIMERA_OP_F || recompute,
-                              !dbl && o.kind != CHIMERA_OP_F, ranges);
-            }
-            if (!any) continue;
-            ++used;
-            for (chimera_stage* st : both) {
+        for (const Op& o : ops) {
+            const bool dbl = o.kind == CHIMERA_OP_F2;
+            const chimera_stage* st = stages_of(o.pipe)[dbl];
+            add_io_ranges(st, st->io.at(o.mb), o.pipe % lanes, dbl || o.kind == CHIMERA_OP_F || recompute, !dbl && o.kind != CHIMERA_OP_F, ranges);
+        }
+        for (int p = 0; p < pipes; ++p) {
+            if (!runs[p]) continue;
+            for (chimera_stage* st : stages_of(p)) {
                 if (!st) continue;
-                ok = ok && st->overlap;
                 add_stage_ranges(st, p % lanes, ranges);
                 on_lane.push_back({st, st->stream, st->have_side, p % lanes});
             }
         }
-        if (!ok || used < 2 || !lanes_independent(ranges, lanes)) on_lane.clear();
+        if (!lanes_independent(ranges, lanes)) on_lane.clear();
     }
+    unsigned lanes_taken = 0;
+    for (const OnLane& l : on_lane) lanes_taken |= 1u << l.lane;
+    wk.lanes_used = std::max(1, std::popcount(lanes_taken));
     for (OnLane& l : on_lane) {
         hipError_t j = hipEventRecord(l.st->ev_ready[0], l.home);
         if (j == hipSuccess) j = hipStreamWaitEvent(wk.lanes[l.lane], l.st->ev_ready[0], 0);
@@ -955,6 +976,12 @@ int chimera_worker_last_timing(double* h_fwd_ms, double* h_bwd_ms, int* h_nf, in
 int chimera_worker_last_enqueue_ms(double* h_ms) {
     if (!h_ms) return fail(CHIMERA_EINVAL, "h_ms is NULL");
     *h_ms = g_worker.enqueue_ms;
+    return CHIMERA_OK;
+}
+
+int chimera_worker_last_lanes(int* h_lanes) {
+    if (!h_lanes) return fail(CHIMERA_EINVAL, "h_lanes is NULL");
+    *h_lanes = g_worker.lanes_used;
     return CHIMERA_OK;
 }
 

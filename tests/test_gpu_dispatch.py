@@ -35,6 +35,7 @@ def _worker(overlap, shared_dx, D=4, N=8, L=2, H=128, heads=2, S=72, B=1):
     for st in stages:
         st.zero_grads()
     b.chimera_run_worker(rank, D, N)
+    assert b.chimera_worker_last_lanes() == (2 if overlap and shared_dx is None else 1)
     torch.cuda.synchronize()
     return [t.clone() for t in outs] + [st.grads.clone() for st in stages]
 
@@ -46,6 +47,81 @@ def test_replay_beside_equals_replay_in_turn(shared):
     dx = torch.zeros((72, 128), device="cuda", dtype=torch.bfloat16) if shared else None
     for a, c in zip(_worker(True, dx), _worker(False, dx)):
         assert torch.equal(a, c)
+
+
+# In a process of its own, so that the replay is the first to look for streams: binding stays legal under stream capture; the
+# search may meet a busy GPU or another thread's capture; with a single hardware queue the stages take turns.
+_FIRST_REPLAY = """
+import threading
+import torch
+from paper_2107_06925_amd import binding as b
+what = %r
+stages, io = [], []
+for pipe in (0, 1):
+    st = b.Stage(1, 128, 2, 64, 1, b.BF16, stash_slots=2)
+    st.weights.normal_(0, 0.02)
+    stages.append(st)
+for o in b.chimera_schedule(b.DIRECT, 2, 2, 0):
+    if o.kind == b.OP_F:
+        x = torch.randn(64, 128, device="cuda").bfloat16()
+        io += [x, stages[o.pipe].set_io(o.mb, x, x)]
+x, graph = torch.zeros(1024, device="cuda"), torch.cuda.CUDAGraph()
+begun, end = threading.Event(), threading.Event()
+torch.cuda.synchronize()
+
+def capture():
+    with torch.cuda.stream(torch.cuda.Stream()), torch.cuda.graph(graph):
+        x.add_(1)
+        if what == "bind":
+            b.chimera_worker_bind(*stages)
+        begun.set()
+        end.wait(30)
+        x.add_(1)
+
+if what == "bind":
+    end.set()
+    capture()
+else:
+    b.chimera_worker_bind(*stages)
+    if what == "thread":
+        other = threading.Thread(target=capture)
+        other.start()
+        begun.wait(30)
+    elif what == "busy":
+        a = torch.randn(4096, 4096, device="cuda").bfloat16()
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(100):
+                a @ a
+b.chimera_run_worker(0, 2, 2)
+lanes = [b.chimera_worker_last_lanes()]
+if what == "thread":
+    end.set()
+    other.join()
+if what in ("bind", "thread"):
+    graph.replay()
+    torch.cuda.synchronize()
+    assert float(x[0]) == 2.0
+for _ in range(3):
+    b.chimera_run_worker(0, 2, 2)
+    lanes.append(b.chimera_worker_last_lanes())
+b.chimera_worker_set_timing(True)
+b.chimera_run_worker(0, 2, 2)
+lanes.append(b.chimera_worker_last_lanes())
+print("lanes", *lanes)
+"""
+
+
+@pytest.mark.parametrize("what", ["idle", "bind", "busy", "thread", "one queue"])
+def test_first_replay_finds_its_streams(what):
+    import os
+    import subprocess
+    import sys
+    print("first replay", what, flush=True)
+    env = dict(os.environ, **({"GPU_MAX_HW_QUEUES": "1"} if what == "one queue" else {}))
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", _FIRST_REPLAY % what], cwd=root, env=env, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stderr[-2000:]
+    assert r.stdout.split() == ["lanes"] + ["1" if what == "one queue" else "2"] * 4 + ["1"]
 
 
 # Products of 256x128 tiles, which only a replay of two stages beside each other takes: up to 256 of 128x128 in
