@@ -31,7 +31,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int NT = 256, NW = 4, TILE = 32;
 constexpr float NEG_BIG = -1.0e30f;
 constexpr float LOG2E = 1.4426950408889634f;
-constexpr float LN2 = 0.6931471805599453f;
+constexpr float LN2 = 0.6931471805599453f, LN2_LOW = -1.9046543e-9f;     // the float and what it lacks
 
 struct Shape { int S, heads, batch, d; };
 
@@ -123,6 +123,14 @@ __device__ __forceinline__ void store_rows(float* __restrict__ row, const f32x4 
     }
 }
 
+// A probability of the backward, exp(score * scale - lse): the difference is rounded once, in natural units, and what the
+// product with log2(e) rounds off comes back behind the hardware's exp2.  (From a log-sum-exp in log2 units, rounded on the way
+// there, it would carry 1.2 to 1.5 times the error.)
+__device__ __forceinline__ float prob(float score, float scale, float lse) {
+    const float x = __builtin_fmaf(score, scale, -lse), t = x * LOG2E, e = __builtin_amdgcn_exp2f(t);
+    return e == 0.f ? 0.f : __builtin_fmaf(e, __builtin_fmaf(-t, LN2, x), e);        // x may be -inf
+}
+
 template <int D, bool CAUSAL>
 __global__ __launch_bounds__(NT) void attn_fwd_f32_kernel(const float* __restrict__ qkv, float* __restrict__ ctx,
                                                           float* __restrict__ lse, Shape sh, float scale_log2e) {
@@ -197,7 +205,7 @@ __global__ __launch_bounds__(NT) void attn_fwd_f32_kernel(const float* __restric
     combine<D>(lds, o, out, wave, lane);
     if (qrow < S) {
         store_rows<D>(ctx + ((size_t)b * S + qrow) * H + h * d, out, 1.0f / total, d, wave, g);
-        if (wave == 0 && g == 0) lse[((size_t)b * sh.heads + h) * S + qrow] = (M + log2f(total)) * LN2;
+        if (wave == 0 && g == 0) lse[((size_t)b * sh.heads + h) * S + qrow] = __builtin_fmaf(M, LN2, __builtin_fmaf(M, LN2_LOW, logf(total)));
     }
 }
 
@@ -218,7 +226,7 @@ __device__ __forceinline__ void dq_role(float* lds, int bid, const float* __rest
     q.load(base + (size_t)qr * ld, d, g, true);
     dO.load(dctx + ((size_t)b * S + qr) * H + h * d, d, g, true);
     o.load(ctx + ((size_t)b * S + qr) * H + h * d, d, g, true);
-    const float lse2 = lse[((size_t)b * sh.heads + h) * S + qr] * LOG2E, c2 = scale * LOG2E;
+    const float my_lse = lse[((size_t)b * sh.heads + h) * S + qr];
     float delta = 0.f;
 #pragma unroll
     for (int i = 0; i < D / 8; ++i)
@@ -239,7 +247,7 @@ __device__ __forceinline__ void dq_role(float* lds, int bid, const float* __rest
         kt.load(base + H, ld, k0, S - 1, d, l32, g);
         f32x16 p = dot_rows<D>(k, q), dp = dot_rows<D>(v, dO);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(p[r], c2, -lse2));
+        for (int r = 0; r < 16; ++r) p[r] = prob(p[r], scale, my_lse);
         if (k0 + TILE > S || (CAUSAL && k0 + TILE - 1 > q0)) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
@@ -272,7 +280,6 @@ __device__ __forceinline__ void dkv_role(float* lds, int bid, const float* __res
     const float* lseg = lse + ((size_t)b * sh.heads + h) * S;
     const int lane = threadIdx.x & 63, l32 = lane & 31, g = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int jrow = j0 + l32, jr = min(jrow, S - 1);
-    const float c2 = scale * LOG2E;
     RowFrag<D> k, v;
     k.load(base + H + (size_t)jr * ld, d, g, true);
     v.load(base + 2 * H + (size_t)jr * ld, d, g, true);
@@ -290,7 +297,7 @@ __device__ __forceinline__ void dkv_role(float* lds, int bid, const float* __res
         o.load(Og + (size_t)ir * H, d, g, true);
         dOt.load(dOg, H, i0, S - 1, d, l32, g);
         qt.load(base, ld, i0, S - 1, d, l32, g);
-        const float lse2 = lseg[ir] * LOG2E;
+        const float my_lse = lseg[ir];
         float delta = 0.f;                       // of row l32; the rows of the score registers fetch theirs from its lane
 #pragma unroll
         for (int i = 0; i < D / 8; ++i)
@@ -302,7 +309,7 @@ __device__ __forceinline__ void dkv_role(float* lds, int bid, const float* __res
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int ii = 8 * (r >> 2) + 4 * g + (r & 3);
-            p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(p[r], c2, -__shfl(lse2, ii, WAVE)));
+            p[r] = prob(p[r], scale, __shfl(my_lse, ii, WAVE));
             if (edge && (i0 + ii >= S || (CAUSAL && i0 + ii < jrow))) p[r] = 0.f;
             dp[r] = p[r] * (dp[r] - __shfl(delta, ii, WAVE));
         }
