@@ -293,7 +293,10 @@ int chimera_worker_bind(chimera_stage* down_stage, chimera_stage* up_stage);
  * The first replay that can run stages beside each other waits for the stages' streams,
  * creates up to four streams and launches a few tiny kernels to see that they have
  * queues of their own (one or two milliseconds); where too few are found, a later
- * replay looks again. */
+ * replay looks again.
+ * Beside another stage a bf16 product may take other tiles, which add the same terms
+ * in another order: a replay repeated under the same conditions gives the same bits,
+ * one that takes turns may differ from it by the rounding of float sums. */
 int chimera_run_worker(int rank, int D, int N);
 /* Same for any algorithm; for the one-pipeline baselines only the down stage
  * is used and holds stage `rank`. */
