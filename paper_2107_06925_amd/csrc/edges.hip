@@ -319,6 +319,9 @@ __global__ __launch_bounds__(EDGE_THREADS) void xent_kernel(T* __restrict__ z, c
 // an element, and it reads the row twice): 4096 x 50304 231 -> 155 us.  So the maximum comes first, an exponential is the
 // hardware's exp2 of (z - max) log2(e) - the difference of two bf16 values first, which leaves no common
 // error in the sum - and 64 registers a lane keep two workgroups of 1024 on a CU, one loading while the other works.
+// The rounded product costs a probability e^-x up to 6e-8 x relative, against a bf16 result's 2e-3.  Made good with two
+// more operations an element the kernel is 10 % slower and its loss rows and gradients are no nearer to float64 (3.2e-8 and
+// 1.17e-4 relative at 4096 x 50304).
 template <int NT, int NV>
 __global__ __launch_bounds__(NT, 8) void xent_row_kernel(bf16_t* __restrict__ z, const int* __restrict__ targets,
                                                          float* __restrict__ loss_rows, int vocab, float scale) {

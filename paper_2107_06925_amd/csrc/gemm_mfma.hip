@@ -763,8 +763,11 @@ __device__ __forceinline__ void gemm_async_tile(
 // wavefronts, two on each 64x64 block, each taking half of every step's k, over a ring of four buffers; for
 // 256x128 the same with blocks of 128x64 and three buffers.
 //
-// What bounds it is power: with random operands the chip lowers its clock under matrix load (the same
-// launch on zeros runs 1.3 to 1.4 times as fast), so a product's rate is set by the energy per flop.
+// What bounds it (256x256, counters of one round of 256 tiles, random operands): a step is 2048 clocks of MFMAs
+// on each SIMD and takes 2220 to 2390, so the loop keeps the matrix pipes 86 to 92 % busy; launch, first tiles and
+// the epilogue's HBM traffic cost another 18 000 clocks (51 000 with a float accumulate), as much as 8 (22) steps: over
+// the whole kernel the pipes are busy 45 % at k = 512, 60 % at 1024, 79 % at 4096.  Power comes after that: the
+// same launch on zeros is 14 % faster at 4096^3, 1 to 6 % at the sizes of the replays (2048 x 6400 x 1600 46.7 -> 45.7 us).
 //   * Measured in a loop over register operands: 16x16x32 instructions 2046 TFLOP/s, 32x32x16 1816;
 //     with every operand re-read from LDS at this tile's ratio 1706 and 1549.
 //   * Requests of 128-byte rows (64 k) cost less than two of 64 bytes: 4096^3, A B^T, 102 -> 95.5 us.
@@ -787,7 +790,8 @@ __device__ __forceinline__ void gemm_async_tile(
 constexpr int RK = 64;
 // [row][64 k] tile (128-byte rows): 16-byte chunk c of row r sits at c ^ rswz(r).  A 16-byte LDS read is served
 // in four passes of 16 lanes, {0-3, 12-15, 20-23, 24-27} and so on; with lanes over rows l%16 and chunks l/16
-// this order puts each pass on all 64 banks.
+// this order puts each pass on all 64 banks.  (The loop's reads meet no conflicts, in any layout: their counter does not
+// grow with k.  The 7 to 30 % of LDS cycles it shows for a whole kernel are the epilogue's slabs, 4096 clocks a 256x256 tile.)
 __device__ __forceinline__ int rswz(int r) { return (r >> 1) & 7; }
 // [k][ROWS] tile: the 32-byte column block j of k-row k sits at j ^ rkswz(k): a transposing read touches one
 // block in rows 8g..8g+3 of four lane groups g.
@@ -1268,7 +1272,9 @@ __global__ __launch_bounds__(WGM* WGN * WGK * 64) void gemm_bf16_async_group_ker
 // costs as much as a full one.  The products here can be cut along m without touching the data
 // (row bands of A and C are just pointer offsets), so the last `b` bands of 256 rows may go to a
 // second launch with 128x128 tiles instead.  Cost estimate in units of one 256x256 round: a round
-// of 128x128 tiles (quarter of the flops, 1.6x the time per flop) counts 0.45.  Returns the b
+// of 128x128 tiles (a quarter of the flops) counts 0.45.  Measured, launch included: 0.36 to 0.39 of a 256x256
+// round at one tile per CU (k = 1600: 18.4 against 49.5 us A B, 24.5 against 68 A^T B), 0.34 each of two rounds
+// at two per CU; the rest stands for what an estimate in whole rounds leaves out.  Returns the b
 // that minimises it (0: leave the product whole); `other` = 256x256 tiles of the launch that do
 // not belong to this product.  Columns are counted by the same rule with rows and columns exchanged.
 int bands_to_peel(long other, int tm, int tn, int n, double* cost = nullptr) {
@@ -1346,9 +1352,10 @@ bool far_operand(const GemmArgs& g) {
 
 // 64x64 tiles while they all fit on the chip at once, two per CU: a smaller product is bound by
 // its chain of latencies and by how many CUs pull its operands, not by the bytes a small tile
-// costs.  Measured, 128x128 -> 64x64: 400 x 960 x 320 6.6 -> 4.3 us, 632 x 1600 x 6400 (65 tiles of
-// 128x128, 250 of 64x64) 49 -> 29, 1264 x 1600 x 1600 (130, 500) 16.2 -> 12.7; beyond it turns:
-// 1024 x 2560 x 640 (160, 640) 9.8 -> 11.3, 632 x 4800 x 1600 (190, 750) 17.6 -> 21.
+// costs.  Measured, 128x128 -> 64x64: 632 x 1600 x 1600 (65 tiles of 128x128, 250 of 64x64) 13.7 -> 9.2 us,
+// 632 x 1600 x 6400 55 -> 31, 1024 x 1280 x 5120 (80, 320) 48.6 -> 42.4, 1264 x 1600 x 6400 (130, 500) 55.0 -> 52.3,
+// 1024 x 2048 x 2048 (128, 512) 16.2 -> 16.5; beyond it turns: 1024 x 2560 x 640 (160, 640) 9.8 -> 11.9,
+// 632 x 4800 x 1600 (190, 750) 17.7 -> 23.9, 1264 x 2400 x 6400 (190, 760) 60.6 -> 82.9.
 bool small_tiles(long tiles64) { return tiles64 <= 2 * NUM_CUS && tuning().async_mode == ASYNC_AUTO; }
 
 // 256x128 tiles for a product that shares the chip with another stage's: it should then take little of the
@@ -1574,7 +1581,8 @@ int gemm_mfma_bf16(const GemmArgs& g, void* stream) {
 // How a product of k-contiguous operands is cut along k (splits = 1: not at all): fewer tiles than CUs leave
 // CUs idle, and 256x256 tiles cost a third less energy and time per flop than the 128x128 tiles that an uncut
 // product of 64 to 143 of them takes.  Model of the time in us, constants measured: a step of 64 k of a round of
-// tiles, against the float slabs written and read (at 4.5 TB/s) and the launch that adds them.
+// tiles (A B^T, k 1024 to 8192: 256x256 1.55 to 1.63 from random operands that miss the caches, 128x128 0.50 to 0.56, 64x64
+// 0.18 to 0.30), against the float slabs written and read (at 4.5 TB/s) and the launch that adds them.
 // 4096 x 1024 x 50304 462 -> 355 + 12 us; a head's whole pass over 1000 x 512 x 20000 164 -> 131, 128 x 128 x 65536
 // 252 -> 87, 1111 x 776 x 50304 507 -> 443, 632 x 1600 x 50304 589 -> 515 us.
 struct SplitPlan { int tile, splits, k_per; };

@@ -538,6 +538,8 @@ struct Worker {
 // to see it may also mean that other work held the CUs or the host up between the two launches.  So the attempts
 // get longer (earlier work in either queue is over by the second), and a replay that found too few lanes runs with those
 // and a later one looks again: the 2nd, 6th, 14th, ... after it, so that a device with fewer queues does not pay each time.
+// Four lanes against two for workers of four pipelines: bert48 19.6 against 20.0 ms, gpt2-1p3b (N = 8) 43.6 against 43.6,
+// the tiny float worker 0.56 against 0.55.
 constexpr int MAX_LANES = 4, MAX_CANDIDATES = 10;
 __device__ int lane_word, lane_seen;
 __global__ void lane_post_kernel(int token) { __hip_atomic_store(&lane_word, token, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
