@@ -115,11 +115,11 @@ template <int ROWS, int BK, int NT, bool KC> struct OpTile {
     }
 };
 
-// Two wavefronts share a 32x32 block, each with half of every k step: with one 64x64 tile per CU there
+// Two wavefronts share a 32x32 block (TM = TN = 1), each with half of every k step: with one 64x64 tile per CU there
 // is otherwise one wavefront per SIMD, and nothing runs while it waits for a barrier or LDS.
 template <bool A_KC, bool B_KC, int EPI>
 __global__ __launch_bounds__(8 * WAVE) void gemm_f32_tile_kernel(F32Launch L) {
-    constexpr int BM = 64, BN = 64, BK = 32, NT = 8 * WAVE, GRPS = BK / 8 / 2;
+    constexpr int BM = 64, BN = 64, BK = 32, WGK = 2, NT = 4 * WGK * WAVE, WM = BM / 2, WN = BN / 2, TM = WM / 32, TN = WN / 32, GRPS = BK / 8 / WGK;
     using TA = OpTile<BM, BK, NT, A_KC>;
     using TB = OpTile<BN, BK, NT, B_KC>;
     __shared__ __attribute__((aligned(16))) float lds[3][TA::FLOATS + TB::FLOATS];
@@ -129,14 +129,20 @@ __global__ __launch_bounds__(8 * WAVE) void gemm_f32_tile_kernel(F32Launch L) {
     const float* __restrict__ A = p.a;
     const float* __restrict__ B = p.b;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, g = lane >> 5, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wk = wave >> 2, wm0 = ((wave >> 1) & 1) * 32, wn0 = (wave & 1) * 32;
+    const int wk = wave >> 2, wm0 = ((wave >> 1) & 1) * WM, wn0 = (wave & 1) * WN;
 
-    f32x16 acc;
+    f32x16 acc[TM][TN];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
     // column sums of B come from the fragments that the top wavefronts of the first tile row hold anyway
     const bool col_sums = EPI == EPI_ACCUM_F32 && p.bsum && tile_m == 0 && wm0 == 0;
-    float cs = 0.f;
+    float cs[TN];
+#pragma unroll
+    for (int b = 0; b < TN; ++b) cs[b] = 0.f;
 
     // Loads run in register sets three steps ahead of LDS (a step is 0.4 us of matrix work, a load that
     // misses L2 takes twice that) and LDS two steps ahead of the matrix cores, in rings of three walked
@@ -154,10 +160,13 @@ __global__ __launch_bounds__(8 * WAVE) void gemm_f32_tile_kernel(F32Launch L) {
         ra[u].store(lds[u], tid);
         rb[u].store(lds[u] + TA::FLOATS, tid);
     };
-    f32x4 fa[2], fb[2];
+    f32x4 fa[2][TM], fb[2][TN];
     auto read = [&](int s, int buf, int gi) {
-        fa[s] = TA::frag(lds[buf], wm0 + l32, wk * GRPS + gi, g);
-        fb[s] = TB::frag(lds[buf] + TA::FLOATS, wn0 + l32, wk * GRPS + gi, g);
+        const int grp = wk * GRPS + gi;
+#pragma unroll
+        for (int a = 0; a < TM; ++a) fa[s][a] = TA::frag(lds[buf], wm0 + a * 32 + l32, grp, g);
+#pragma unroll
+        for (int b = 0; b < TN; ++b) fb[s][b] = TB::frag(lds[buf] + TA::FLOATS, wn0 + b * 32 + l32, grp, g);
     };
 #pragma unroll
     for (int u = 0; u < NB; ++u)
@@ -182,43 +191,57 @@ __global__ __launch_bounds__(8 * WAVE) void gemm_f32_tile_kernel(F32Launch L) {
                 if (gi + 1 < GRPS) read(s ^ 1, u, gi + 1);
                 else if (kt + 1 < KT) read(s ^ 1, (u + 1) % NB, 0);
                 if constexpr (EPI == EPI_ACCUM_F32)
-                    if (col_sums) cs += (fb[s][0] + fb[s][1]) + (fb[s][2] + fb[s][3]);
+                    if (col_sums)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[s][j], fb[s][j], acc, 0, 0, 0);
+                        for (int b = 0; b < TN; ++b) cs[b] += (fb[s][b][0] + fb[s][b][1]) + (fb[s][b][2] + fb[s][b][3]);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int a = 0; a < TM; ++a)
+#pragma unroll
+                        for (int b = 0; b < TN; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[s][a][j], fb[s][b][j], acc[a][b], 0, 0, 0);
             }
             __syncthreads();                   // step kt + 2 is in LDS, and everyone is done with step kt
         }
     }
-    // The two wavefronts hold partial sums of one block: each hands over one half of its registers and
-    // finishes the other (registers 0..7 or 8..15, i.e. 16 of the block's rows).
-    constexpr int R = 8;
-    static_assert(sizeof(lds) >= 8 * R * WAVE * sizeof(float) + BN * sizeof(float), "LDS too small for the exchange");
-    float* xch = &lds[0][0];
-    float* xcs = xch + 8 * R * WAVE;
-    __syncthreads();
+    // Two wavefronts with partial sums of one block: each hands over one half of its registers and
+    // finishes the other (registers 0..7 or 8..15 of every 32x32 tile, i.e. 16 of its rows).
+    constexpr int R = 16 / WGK;
+    {
+        static_assert(TM == 1 && TN == 1, "one tile per wavefront");
+        static_assert(sizeof(lds) >= 8 * R * WAVE * sizeof(float) + BN * sizeof(float), "LDS too small for the exchange");
+        float* xch = &lds[0][0];
+        float* xcs = xch + 8 * R * WAVE;
+        __syncthreads();
 #pragma unroll
-    for (int r = 0; r < R; ++r) xch[(wave * R + r) * WAVE + lane] = wk ? acc[r] : acc[R + r];
-    if (col_sums) {
-        cs += __shfl_xor(cs, 32, WAVE);
-        if (wk && g == 0) xcs[wn0 + l32] = cs;
-    }
-    __syncthreads();
+        for (int r = 0; r < R; ++r) xch[(wave * R + r) * WAVE + lane] = wk ? acc[0][0][r] : acc[0][0][R + r];
+        if (col_sums) {
+            cs[0] += __shfl_xor(cs[0], 32, WAVE);
+            if (wk && g == 0) xcs[wn0 + l32] = cs[0];
+        }
+        __syncthreads();
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const float other = xch[((wave ^ 4) * R + r) * WAVE + lane];
-        acc[r] = wk ? other + acc[R + r] : acc[r] + other;
+        for (int r = 0; r < R; ++r) {
+            const float other = xch[((wave ^ 4) * R + r) * WAVE + lane];
+            acc[0][0][r] = wk ? other + acc[0][0][R + r] : acc[0][0][r] + other;
+        }
+        if (col_sums && !wk) cs[0] += xcs[wn0 + l32];
     }
-    if (col_sums && !wk) cs += xcs[wn0 + l32];
     // register r of lane l: row 8(r/4) + 4g + r%4, column l%32 - 128 contiguous bytes per half wavefront
-    const int col = j0 + wn0 + l32;
-    if (col >= n) return;
-    if constexpr (EPI == EPI_ACCUM_F32)
-        if (col_sums && g == 0 && wk == 0) p.bsum[col] = L.flag ? cs : p.bsum[col] + cs;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int row = i0 + wm0 + wk * 16 + 8 * (r >> 2) + 4 * g + (r & 3);
-        const float v = acc[r];
-        if (row < m) finish<EPI, 1>(p, L.flag, row, col, &v);
+    for (int b = 0; b < TN; ++b) {
+        const int col = j0 + wn0 + b * 32 + l32;
+        if (col >= n) continue;
+        if constexpr (EPI == EPI_ACCUM_F32)
+            if (col_sums && g == 0 && wk == 0) p.bsum[col] = L.flag ? cs[b] : p.bsum[col] + cs[b];
+#pragma unroll
+        for (int a = 0; a < TM; ++a)
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int row = i0 + wm0 + a * 32 + wk * 16 + 8 * (r >> 2) + 4 * g + (r & 3);
+                const float v = acc[a][b][r];
+                if (row < m) finish<EPI, 1>(p, L.flag, row, col, &v);
+            }
     }
 }
 
