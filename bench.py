@@ -216,9 +216,11 @@ def main():
     }
 
     if not args.no_profile:
-        # two more iterations, same launches: one with an event pair around every op (F_t, B_t), one
-        # with an event pair around every kernel launch (the per-kernel events cost some 20 % of an
-        # op's time, so the two are not taken together)
+        # two more iterations: one with an event pair around every op (F_t, B_t), one with an event pair
+        # around every kernel launch (the per-kernel events cost some 20 % of an op's time, so the two are
+        # not taken together).  In both the stages take turns, with the parameter gradients beside the chain:
+        # an op's time is then its own, and products of few tiles run on 128x128 tiles where the timed
+        # iterations, whose stages run beside each other, take 256x128.
         b.chimera_worker_set_timing(True)
         step()
         torch.cuda.synchronize()
@@ -243,6 +245,7 @@ def main():
             "traffic": _roofline_traffic(cfg.name) if (not args.no_overlap and algo == b.DIRECT and f == 1 and rank == 0) else None,
             "launches_per_step": wg["launches"], "avg_launch_us": wg["ms"] * 1e3 / max(wg["launches"], 1),
             "flop_per_launch": wg["work"] / max(wg["launches"], 1),
+            "note": "from one more iteration in which the two stages take turns; kernel_classes, all_stage_gemms and stage_times too",
         }
         gemm_classes = ("gemm_fwd", "gemm_dgrad", "gemm_wgrad", "gemm_wgrad_tail")
         gemm_ms = sum(prof[k]["ms"] for k in gemm_classes)
@@ -324,7 +327,8 @@ def main():
         out["edges"] = _time_edges(cfg, dtype, args.vocab)
     if not args.no_profile and not args.no_overlap and not args.no_single_stream:
         # The same workload with every kernel alone on the chip (one stream per stage): context for the
-        # fractions above, whose durations include sharing the chip with the stage's second stream.
+        # fractions above, whose durations include sharing the chip with the stage's second stream, and for
+        # the iteration time, in which the stages share it.
         out["single_stream"] = _single_stream(args)
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = _cpu_baseline(cfg)
