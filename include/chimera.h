@@ -443,7 +443,9 @@ int chimera_op_colsum(int dtype, int rows, int cols, const void* d_x, float* d_o
                       float* d_scratch, void* hip_stream);
 /* ctx[M,H] = softmax(q k^T / sqrt(d) [+ causal mask]) v per (sequence, head),
  * q, k, v read from qkv [M, 3H]; lse [batch, heads, seq] float = log-sum-exp
- * of the scaled scores (kept for the backward). */
+ * of the scaled scores (kept for the backward).  Values are expected to be finite: the
+ * matrix-core kernels multiply whole tiles, masked entries by exact zeros, so a NaN or an
+ * infinity may also reach rows that the mask keeps it from (up to 127 positions away). */
 int chimera_op_attention_fwd(int dtype, int impl, int batch, int seq, int heads, int head_dim,
                              int causal, const void* d_qkv, void* d_ctx, float* d_lse,
                              void* hip_stream);
