@@ -485,6 +485,28 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_kernel(
 // the last whole step come first, through registers and zero-filled, while the DMA of the
 // first whole steps is under way.
 
+// What the next product reads from HBM (the weights of the next linear layer) is touched by this one between its
+// k loop and its epilogue: 64 lines of 128 bytes per wavefront and instruction, the range dealt over the launch, four
+// bytes of each line into a strip of LDS that nobody reads.  The lines are then in the memory-side cache when
+// the next launch asks for them.  A CU has some 60 KiB of requests under way at most (61 to 68 GB/s per CU from HBM with every
+// tile here, 80 to 96 from the memory-side cache; requesting further ahead changes nothing), so a k loop that is short of
+// operands waits for the latency of the slower one, and weights come from HBM in every pass.
+// Measured, A in the memory-side cache, B untouched -> touched: A B^T 2048 x 1600 x 6400 57 -> 44 us on 128x128
+// tiles, 82 -> 68 on 256x128 (on two streams 44.6 -> 37.9 each), 4096 x 1024 x 4096 48.6 -> 41.4, A B 2048 x 4800 x 1600
+// 42.9 -> 40.6 (31.0 -> 28.0), 632 x 4800 x 1600 18.6 -> 16.7, 1264 x 1600 x 6400 50.5 -> 44.6; with A from HBM too
+// nothing is won.  Inside the loop the touches cost more on two streams (2048 x 1600 x 6400 37.9 -> 42.5), behind the
+// epilogue too (39.1; 2048 x 1600 x 1600 28.1 -> 30.3 on one).  Touching the backward's stashed operands as well was slower
+// than not (gpt2-1p3b-n32 97.8 -> 99.4 ms, gpt2-deep 50.2 -> 51.2).
+struct Ahead { const char* p; unsigned bytes; };
+constexpr unsigned AHEAD_PIECE = 64 * 128, AHEAD_STRIP = 256;
+__device__ __forceinline__ void touch_ahead(const Ahead& ahead, int wave, int waves, int lane, unsigned strip) {
+    // pieces beyond the range repeat its last word
+    for (size_t at = ((size_t)blockIdx.x * waves + wave) * AHEAD_PIECE; at < ahead.bytes; at += (size_t)gridDim.x * waves * AHEAD_PIECE) {
+        const unsigned off = min((unsigned)at + (unsigned)lane * 128u, ahead.bytes - 4u);
+        asm volatile("global_load_lds_dword %0, %1" ::"v"(off), "s"(ahead.p), "{m0}"(strip) : "memory");
+    }
+}
+
 // One output tile; `block_id` numbers the tiles of this product.  ONLY_EPI >= 0 compiles
 // that epilogue alone.
 // SPS: ring stages per barrier (NS stages of BK each).
@@ -493,7 +515,7 @@ __device__ __forceinline__ void gemm_async_tile(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, const bf16_t* __restrict__ bias,
     const bf16_t* __restrict__ R, void* __restrict__ C, bf16_t* __restrict__ C2, int m, int n, int k, int lda,
     int ldb, int epi, int epi_flag, int res_types, int tiles_m, int tiles_n, int group_m, int block_id,
-    float* __restrict__ bsum = nullptr, bool xcd_remap = true) {
+    float* __restrict__ bsum = nullptr, bool xcd_remap = true, const Ahead& ahead = {nullptr, 0}) {
     constexpr int NT = WGM * WGN * WGK * 64;
     constexpr int KSUB = BK / 16 / WGK;                                   // 16-wide k slices per wavefront and step
     static_assert(KSUB >= 1 && KSUB * WGK * 16 == BK, "k split must divide the step");
@@ -502,6 +524,7 @@ __device__ __forceinline__ void gemm_async_tile(
     constexpr int CA = BM * (BK / 8) / NT, CB = BN * (BK / 8) / NT;      // 16-byte pieces per thread and stage
     constexpr int STAGE = (BM + BN) * BK;                                 // elements
     __shared__ __attribute__((aligned(16))) bf16_t lds[NS * STAGE];
+    __shared__ __attribute__((aligned(16))) char strip[AHEAD_STRIP];
 
     const int nblk = tiles_m * tiles_n;
     // `block_id` as the hardware deals it (round-robin over the XCDs) or already renumbered
@@ -631,6 +654,7 @@ __device__ __forceinline__ void gemm_async_tile(
         for (int u = 0; u < SPS; ++u)
             if (SPS == 1 || kt + u < KT) { compute(cur); advance(cur); }
     }
+    touch_ahead(ahead, wave, NT / 64, lane, lds_address(strip));
 
     const int cb0 = j0 + wn0;
     // the operand tiles in LDS are dead once every wavefront has left the k loop; each
@@ -812,13 +836,14 @@ __device__ __forceinline__ void gemm_ring_tile(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, const bf16_t* __restrict__ bias,
     const bf16_t* __restrict__ R, void* __restrict__ C, bf16_t* __restrict__ C2, int m, int n, int k, int lda,
     int ldb, int epi, int epi_flag, int res_types, int tiles_m, int tiles_n, int group_m, int block_id,
-    float* __restrict__ bsum = nullptr, bool xcd_remap = true, int col0 = 0) {
+    float* __restrict__ bsum = nullptr, bool xcd_remap = true, int col0 = 0, const Ahead& ahead = {nullptr, 0}) {
     constexpr int NT = WGM * WGN * WGK * 64, NS = WGK == 1 ? 2 : BM * BN > 128 * 128 ? 3 : 4;
     constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16, HM = TM / 2;      // 16x16 tiles per wavefront
     constexpr int CA = BM * (RK / 8) / NT, CB = BN * (RK / 8) / NT, CS = CA + CB;     // 16-byte pieces per thread and stage
     constexpr unsigned STAGE = (BM + BN) * RK * 2, ABYTES = BM * RK * 2;
     constexpr int LDS_EPI = NT / 64 * EpiSlab<TN / 2>::FLOATS * 4, LDS_RING = NS * (int)STAGE;
     __shared__ __attribute__((aligned(1024))) char lds[LDS_RING > LDS_EPI ? LDS_RING : LDS_EPI];
+    __shared__ __attribute__((aligned(16))) char strip[AHEAD_STRIP];
 
     const int nblk = tiles_m * tiles_n;
     const int xcd = block_id & 7, local = block_id >> 3;
@@ -1091,6 +1116,7 @@ __device__ __forceinline__ void gemm_ring_tile(
         steps(std::false_type{});
     }
 #undef CHIMERA_C
+    touch_ahead(ahead, wave, NT / 64, lane, lds_address(strip));
 
     const int cb0 = j0 + wn0;
     auto put_col_sums = [&](const float* v) {
@@ -1173,9 +1199,9 @@ template <int BM, int BN, int WGM, int WGN, int WGK, bool A_KC, bool B_KC>
 __global__ __launch_bounds__(WGM* WGN * WGK * 64, 2) void gemm_bf16_ring_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, const bf16_t* __restrict__ bias,
     const bf16_t* __restrict__ R, void* __restrict__ C, bf16_t* __restrict__ C2, int m, int n, int k, int lda,
-    int ldb, int epi, int epi_flag, int res_types, int tiles_m, int tiles_n, int group_m, int col0) {
+    int ldb, int epi, int epi_flag, int res_types, int tiles_m, int tiles_n, int group_m, int col0, Ahead ahead) {
     gemm_ring_tile<BM, BN, WGM, WGN, WGK, A_KC, B_KC, -1>(A, B, bias, R, C, C2, m, n, k, lda, ldb, epi, epi_flag, res_types,
-                                                          tiles_m, tiles_n, group_m, (int)blockIdx.x, nullptr, true, col0);
+                                                          tiles_m, tiles_n, group_m, (int)blockIdx.x, nullptr, true, col0, ahead);
 }
 
 // A long contraction with few output tiles, cut along k: workgroups [s * tiles, (s+1) * tiles) (numbered so
@@ -1212,9 +1238,10 @@ template <int BM, int BN, int WGM, int WGN, int WGK, int NS, int SPS, bool A_KC,
 __global__ __launch_bounds__(WGM* WGN * WGK * 64) void gemm_bf16_async_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, const bf16_t* __restrict__ bias,
     const bf16_t* __restrict__ R, void* __restrict__ C, bf16_t* __restrict__ C2, int m, int n, int k, int lda,
-    int ldb, int epi, int epi_flag, int res_types, int tiles_m, int tiles_n, int group_m) {
+    int ldb, int epi, int epi_flag, int res_types, int tiles_m, int tiles_n, int group_m, Ahead ahead) {
     gemm_async_tile<BM, BN, WGM, WGN, WGK, NS, SPS, A_KC, B_KC, -1>(A, B, bias, R, C, C2, m, n, k, lda, ldb, epi, epi_flag,
-                                                                res_types, tiles_m, tiles_n, group_m, (int)blockIdx.x);
+                                                                res_types, tiles_m, tiles_n, group_m, (int)blockIdx.x, nullptr,
+                                                                true, ahead);
 }
 
 // Several products C_p (float) += A_p B_p of one launch: same contraction length and operand
@@ -1232,6 +1259,7 @@ struct GemmGroup {
     int first[GROUP_MAX + 1];
     int count, k;
     int overwrite;               // results replace C and bsum instead of being added
+    Ahead ahead;
 };
 
 // The product of a group launch that this workgroup belongs to, and its tile's number inside the
@@ -1255,7 +1283,7 @@ __global__ __launch_bounds__(WGM* WGN * WGK * 64, 2) void gemm_bf16_ring_group_k
     gemm_ring_tile<BM, BN, WGM, WGN, WGK, false, false, EPI_ACCUM_F32>(
         grp.a[p], grp.b[p], nullptr, nullptr, grp.c[p], nullptr, grp.m[p], grp.n[p], grp.k, grp.lda[p], grp.ldb[p],
         EPI_ACCUM_F32, grp.overwrite, 0, grp.tiles_m[p], grp.tiles_n[p], grp.group_m[p], gid - grp.first[p], grp.bsum[p],
-        false);
+        false, 0, grp.ahead);
 }
 
 template <int BM, int BN, int WGM, int WGN, int WGK, int NS, int SPS, bool A_KC, bool B_KC>
@@ -1265,7 +1293,7 @@ __global__ __launch_bounds__(WGM* WGN * WGK * 64) void gemm_bf16_async_group_ker
     gemm_async_tile<BM, BN, WGM, WGN, WGK, NS, SPS, A_KC, B_KC, EPI_ACCUM_F32>(
         grp.a[p], grp.b[p], nullptr, nullptr, grp.c[p], nullptr, grp.m[p], grp.n[p], grp.k, grp.lda[p], grp.ldb[p],
         EPI_ACCUM_F32, grp.overwrite, 0, grp.tiles_m[p], grp.tiles_n[p], grp.group_m[p], gid - grp.first[p], grp.bsum[p],
-        false);
+        false, grp.ahead);
 }
 
 // A launch of 256x256 tiles runs in rounds of NUM_CUS tiles, and a last round with few tiles
@@ -1319,6 +1347,8 @@ struct TileChoice { int bm, bn, splits; };
 // erf form (0: tanh form); for the float-accumulate epilogue 1 makes the result replace C (and
 // the column sums replace bsum) instead of being added, which a single product never asks for.
 inline int epilogue_flag(const GemmArgs& g) { return g.epilogue == EPI_ACCUM_F32 ? 0 : g.gelu_erf; }
+
+inline Ahead ahead_of(const GemmArgs& g) { return {(const char*)g.ahead, (unsigned)g.ahead_bytes}; }
 
 // Tuning aids, read from the environment once (first use) and changeable through
 // chimera_gemm_tuning(): a forced tile ("256x256", "128x128" or "256x256x<splits>" in
@@ -1427,7 +1457,7 @@ int launch_async(const GemmArgs& g, hipStream_t s) {
     hipLaunchKernelGGL((gemm_bf16_async_kernel<BM, BN, WGM, WGN, WGK, NS, SPS, AKC, BKC>), grid, block, 0, s,                   \
                        (const bf16_t*)g.a, (const bf16_t*)g.b, (const bf16_t*)g.bias, (const bf16_t*)g.r, g.c,        \
                        (bf16_t*)g.c2, g.m, g.n, g.k, g.lda, g.ldb, g.epilogue, epilogue_flag(g),                            \
-                       (g.r_f32 ? 1 : 0) | (g.c_f32 ? 2 : 0), tm, tn, gm)
+                       (g.r_f32 ? 1 : 0) | (g.c_f32 ? 2 : 0), tm, tn, gm, ahead_of(g))
     if (g.a_kc && !g.b_kc) CHIMERA_GEMM_LAUNCH(true, false);
     else if (g.a_kc && g.b_kc) CHIMERA_GEMM_LAUNCH(true, true);
     else CHIMERA_GEMM_LAUNCH(false, false);
@@ -1446,7 +1476,7 @@ int launch_ring(const GemmArgs& g, hipStream_t s, int col0 = 0, int cols256 = 0)
     hipLaunchKernelGGL((gemm_bf16_ring_kernel<BM, BN, WGM, WGN, WGK, AKC, BKC>), grid, block, 0, s,                     \
                        (const bf16_t*)g.a, (const bf16_t*)g.b, (const bf16_t*)g.bias, (const bf16_t*)g.r, g.c,        \
                        (bf16_t*)g.c2, g.m, g.n, g.k, g.lda, g.ldb, g.epilogue, epilogue_flag(g),                            \
-                       (g.r_f32 ? 1 : 0) | (g.c_f32 ? 2 : 0), tm, tn, gm, col0)
+                       (g.r_f32 ? 1 : 0) | (g.c_f32 ? 2 : 0), tm, tn, gm, col0, ahead_of(g))
     if (g.a_kc && !g.b_kc) CHIMERA_GEMM_LAUNCH(true, false);
     else if (g.a_kc && g.b_kc) CHIMERA_GEMM_LAUNCH(true, true);
     else CHIMERA_GEMM_LAUNCH(false, false);
@@ -1546,6 +1576,7 @@ int gemm_mfma_bf16(const GemmArgs& g, void* stream) {
                 const size_t m0 = (size_t)(tm - b) * 256;
                 const size_t csz = (g.epilogue == EPI_ACCUM_F32 || g.c_f32) ? 4 : 2;
                 GemmArgs head = g, tail = g;
+                head.ahead = nullptr; head.ahead_bytes = 0;
                 head.m = (int)m0;
                 tail.m = g.m - (int)m0;
                 tail.a = (const char*)g.a + (g.a_kc ? m0 * g.lda : m0) * 2;
@@ -1657,6 +1688,7 @@ int launch_group_tiled(int count, const GemmArgs* g, float* const* bsum, int ove
     }
     for (int i = 0; i < count; ++i) grp.group_m[i] = raster_group(grp.tiles_m[i], grp.tiles_n[i], (tiles + 7) / 8, tile, tile);
     for (int i = count; i <= GROUP_MAX; ++i) grp.first[i] = tiles;
+    grp.ahead = ahead_of(g[count - 1]);
     if (tile == 256) return launch_group_ring<256, 256, 2, 4, 1>(grp, stream);
     if (tile == 64) return tiles <= NUM_CUS ? launch_group<64, 64, 2, 2, 2, 8, 2>(grp, stream, first) : launch_group<64, 64, 1, 2, 2, 4>(grp, stream, first);
     // two workgroups per CU or the k-sliced 8-wavefront form

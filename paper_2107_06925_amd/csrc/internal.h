@@ -62,6 +62,7 @@ struct GemmArgs {
     int epilogue;
     int gelu_erf;
     int beside;                         // work of other streams shares the chip with this launch
+    const void* ahead; size_t ahead_bytes;   // what the next product reads from HBM (null: nothing), below 4 GiB: a hint (bf16 matrix-core path)
     void* ws;                           // optional split-K workspace (bf16 matrix-core path), may be null
     size_t ws_bytes;
 };

@@ -192,3 +192,11 @@ def test_deferred_zeroing_of_gradients():
         twice = [{k: 2 * v for k, v in layer.items()} for layer in gr]
         compare_grads(st.read_grads(), twice, L, H, dtype, "dtype %d ref %s" % (dtype, ref))
         st.close()
+
+
+# Stages whose weights, gradients and stash exceed the memory-side cache: every product touches the next one's
+# weights.  Few workgroups with many touches each, ranges that are no whole number of touches, the last weights of the
+# buffer; then more workgroups than touches.  Same bounds as above.
+@pytest.mark.parametrize("hidden, heads, seq, mb", [(2056, 257, 33, 1), (2304, 18, 130, 2), (1856, 29, 700, 2)])
+def test_stage_of_more_weights_than_the_cache(hidden, heads, seq, mb):
+    test_stage_forward_backward((1, hidden, heads, seq, mb, b.BF16, True, False, False, 1.0))
