@@ -294,6 +294,9 @@ int chimera_worker_bind(chimera_stage* down_stage, chimera_stage* up_stage);
  * creates up to four streams and launches a few tiny kernels to see that they have
  * queues of their own (one or two milliseconds); where too few are found, a later
  * replay looks again.
+ * Of small launches a replay beside each other is recorded into HIP graphs the second time
+ * the same stages replay the same schedule with nothing bound or set anew in between (some
+ * 2 us a launch), and goes out as those graphs from then on; they live with the stage of pipeline 0.
  * Beside another stage a bf16 product may take other tiles, which add the same terms
  * in another order: a replay repeated under the same conditions gives the same bits,
  * one that takes turns may differ from it by the rounding of float sums. */

@@ -1355,7 +1355,7 @@ inline Ahead ahead_of(const GemmArgs& g) { return {(const char*)g.ahead, (unsign
 // CHIMERA_GEMM_TILE) and the form of the LDS-DMA kernels (CHIMERA_GEMM_ASYNC: "0" = the
 // register-staged kernels, "4k" = the k-sliced 128x128 form always, "2" = never).
 enum AsyncMode { ASYNC_AUTO = 0, ASYNC_OFF = 1, ASYNC_KSLICED = 2, ASYNC_PLAIN = 3 };
-struct Tuning { TileChoice forced{0, 0, 0}; int async_mode = ASYNC_AUTO; };
+struct Tuning { TileChoice forced{0, 0, 0}; int async_mode = ASYNC_AUTO; unsigned long long version = 0; };
 Tuning& tuning() {
     static Tuning t = [] {
         Tuning v;
@@ -1768,7 +1768,10 @@ int gemm_mfma_set_tuning(int bm, int bn, int splits, int async_mode) {
     Tuning& t = tuning();
     t.forced = TileChoice{bm, bn, splits};
     t.async_mode = async_mode;
+    ++t.version;
     return CHIMERA_OK;
 }
+
+unsigned long long gemm_mfma_tuning_version() { return tuning().version; }
 
 }  // namespace chimera

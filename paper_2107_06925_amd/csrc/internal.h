@@ -93,6 +93,7 @@ int gemm_mfma_group_plan(int count, const GemmArgs* g, GemmGroupPlan* plan);
 int gemm_mfma_group_launch_head(const GemmGroupPlan& plan, float* const* bsum, int overwrite, void* stream);
 int gemm_mfma_group_launch_tail(const GemmGroupPlan& plan, int overwrite, void* stream);
 int gemm_mfma_set_tuning(int bm, int bn, int splits, int async_mode);
+unsigned long long gemm_mfma_tuning_version();   // changes with every gemm_mfma_set_tuning
 const char* gemm_mfma_last_group_kernel();   // instantiation(s) of the last grouped launch on this thread
 size_t gemm_mfma_workspace_bytes(int m, int n, int splits);
 size_t gemm_mfma_workspace_need(int m, int n, int k);   // bytes the tile heuristic wants for this shape (0 = none)

@@ -7,6 +7,7 @@
 
 #include <algorithm>
 #include <array>
+#include <atomic>
 #include <bit>
 #include <cstdio>
 #include <cstring>
@@ -69,11 +70,32 @@ static void prof_collect() {
     g_prof.recs.clear();
 }
 
+// A worker's replay as graphs, one chain of launches per lane.  `key` holds everything that the launches depend on (see
+// replay_key); the first replay under a key launches its kernels one by one, the second records them, and later ones launch the graphs.
+struct ReplayPlan {
+    std::vector<uint64_t> key;
+    std::vector<std::pair<int, hipGraphExec_t>> lanes;     // lane, its chain
+    bool refused = false;                                  // could not be recorded: launched one by one for good
+    void drop() {
+        for (auto& l : lanes) (void)hipGraphExecDestroy(l.second);
+        lanes.clear(); key.clear(); refused = false;
+    }
+    ~ReplayPlan() { drop(); }
+};
+
+static uint64_t next_stage_uid() {
+    static std::atomic<uint64_t> n{0};
+    return ++n;
+}
+
 }  // namespace chimera
 
 using namespace chimera;
 
 struct chimera_stage {
+    const uint64_t uid = next_stage_uid();
+    uint64_t version = 0;             // counts changes of what the stage's launches depend on: buffers, stream, io
+    ReplayPlan replay;                // of the last worker whose pipeline 0 this stage serves; replays end idle, so never in use outside one
     int L, H, heads, S, B, dtype;
     int M, d;
     size_t esz;
@@ -620,6 +642,59 @@ void make_lanes(Worker& wk, int want) {
     if ((int)wk.lanes.size() < want) wk.lanes_wait = wk.lanes_backoff = std::min(2 * wk.lanes_backoff + 1, 1023);
     else wk.lanes_backoff = 0;
 }
+// A replay in lanes of small launches goes out as one graph per lane from its third time on (the second records it: some
+// 2 us a launch, once).  A launch with arguments costs the host 2.7 to 3.5 us (they are written to device memory and read back), which is as long
+// as a small kernel runs; in a graph they are in place (132 launches: 16 us).  Measured, one by one -> graphs: two-block
+// stages of 128-wide float blocks at 128 tokens (124 launches) 529 -> 449 us, of 256-wide bf16 blocks at 256 tokens (264) 944 -> 900, of 512
+// at 512 733 -> 675, six of 256 at 2048 1107 -> 1007, four of 1024 at 1024 3100 -> 2970, two of 768 at 1024 (0.6e9) 2.27 -> 2.26 ms; beyond, the
+// kernels are longer than their launches (bert48, 4.3e9: 1 %).
+constexpr double GRAPH_WORK = 1 << 30;       // rows x hidden^2 of one micro-batch
+bool replay_in_graphs(const chimera_stage* st) { return (double)st->M * st->H * st->H <= GRAPH_WORK; }
+
+// Records what `launch` enqueues on the lanes as one graph each.  False (and never tried again under this key) if that fails; the stages
+// are then as before.
+template <typename F> bool record_replay(Worker& wk, ReplayPlan& plan, unsigned lanes_taken, const std::vector<chimera_stage*>& stages, F&& launch) {
+    std::vector<char> pending;
+    for (const chimera_stage* st : stages) pending.push_back(st && st->grads_pending_zero);
+    std::vector<std::pair<int, hipGraph_t>> graphs;
+    bool ok = true;
+    for (int l = 0; l < (int)wk.lanes.size() && ok; ++l)
+        if (lanes_taken >> l & 1) {
+            ok = hipStreamBeginCapture(wk.lanes[l], hipStreamCaptureModeRelaxed) == hipSuccess;
+            if (ok) graphs.push_back({l, nullptr});
+        }
+    if (ok) ok = launch() == CHIMERA_OK;
+    for (auto& g : graphs) ok = (hipStreamEndCapture(wk.lanes[g.first], &g.second) == hipSuccess && g.second) && ok;
+    for (auto& g : graphs) {
+        hipGraphExec_t exec = nullptr;
+        if (ok && (ok = hipGraphInstantiate(&exec, g.second, nullptr, nullptr, 0) == hipSuccess)) plan.lanes.push_back({g.first, exec});
+        if (g.second) (void)hipGraphDestroy(g.second);
+    }
+    if (ok) return true;
+    (void)hipGetLastError();
+    for (auto& l : plan.lanes) (void)hipGraphExecDestroy(l.second);
+    plan.lanes.clear();
+    plan.refused = true;
+    for (size_t i = 0; i < stages.size(); ++i)
+        if (stages[i]) {
+            stages[i]->grads_pending_zero = pending[i];
+            stages[i]->in_flight.clear(); stages[i]->halves_done.clear();
+            std::fill(stages[i]->slot_used.begin(), stages[i]->slot_used.end(), 0);
+        }
+    return false;
+}
+
+// All that the launches of a replay in lanes depend on: the schedule's parameters, the lanes, each stage with the version of its buffers and
+// io, whether its gradients are to be read as zero, and the products' tuning.
+std::vector<uint64_t> replay_key(std::initializer_list<uint64_t> schedule, const std::vector<chimera_stage*>& stages) {
+    std::vector<uint64_t> key(schedule);
+    key.push_back(gemm_mfma_tuning_version());
+    for (const chimera_stage* st : stages) {
+        key.push_back(st ? st->uid : 0);
+        if (st) { key.push_back(st->version); key.push_back(st->grads_pending_zero); }
+    }
+    return key;
+}
 }  // namespace
 
 // ----------------------------------------------------------------------- ABI
@@ -689,6 +764,8 @@ int chimera_stage_bind(chimera_stage* st, const void* d_weights, float* d_grads,
     if (((uintptr_t)d_weights | (uintptr_t)d_grads | (uintptr_t)d_stash | (uintptr_t)d_workspace) & 255)
         return fail(CHIMERA_EINVAL, "device buffers must be 256-byte aligned");
     if (!st->in_flight.empty()) return fail(CHIMERA_ESTATE, "cannot rebind with micro-batches in flight");
+    ++st->version;
+    st->replay.drop();
     st->weights = (const char*)d_weights; st->grads = d_grads; st->stash = (char*)d_stash; st->ws = (char*)d_workspace;
     st->slots = stash_slots; st->stream = (hipStream_t)hip_stream;
     st->grads_pending_zero = false;
@@ -716,6 +793,7 @@ int chimera_stage_set_io(chimera_stage* st, int mb, const void* d_x_in, void* d_
     if (((uintptr_t)d_x_in | (uintptr_t)d_y_out | (uintptr_t)d_dy_in | (uintptr_t)d_dx_out) & 15)
         return fail(CHIMERA_EINVAL, "io buffers must be 16-byte aligned");
     if (st->in_flight.count(mb)) return fail(CHIMERA_ESTATE, "micro-batch %d is in flight", mb);
+    ++st->version;
     st->io[mb] = chimera_stage::IO{d_x_in, d_y_out, d_dy_in, d_dx_out};
     return CHIMERA_OK;
 }
@@ -932,24 +1010,50 @@ int chimera_run_worker_pipes(int algo, int rank, int D, int N, int f) {
         l.st->have_side = false;
         l.st->beside = true;
     }
-    for (size_t i = 0; i < ops.size() && !rc; ++i) {
-        const Op& o = ops[i];
-        chimera_stage* st = wk.pipes[o.pipe];
-        if (wk.timing) (void)hipEventRecord(ev[2 * i], st->stream);
-        switch (o.kind) {
-            case CHIMERA_OP_F: rc = chimera_fwd_slot(st, o.mb, o.slot); break;
-            case CHIMERA_OP_F2: rc = chimera_fwd_slot(wk.fwd2[o.pipe], o.mb, 0); break;
-            case CHIMERA_OP_B:
-                // after a doubled forward nothing was kept: run the forward again, then the backward
-                if (!st->in_flight.count(o.mb)) rc = chimera_fwd_slot(st, o.mb, -1);
-                if (!rc) rc = chimera_bwd(st, o.mb);
-                break;
-            case CHIMERA_OP_BH0: rc = chimera_bwd_half(st, o.mb, 0); break;
-            case CHIMERA_OP_BH1: rc = chimera_bwd_half(st, o.mb, 1); break;
-            default: rc = fail(CHIMERA_EINVAL, "unknown op kind %d", o.kind);
+    auto launch_ops = [&] {
+        for (size_t i = 0; i < ops.size() && !rc; ++i) {
+            const Op& o = ops[i];
+            chimera_stage* st = wk.pipes[o.pipe];
+            if (wk.timing) (void)hipEventRecord(ev[2 * i], st->stream);
+            switch (o.kind) {
+                case CHIMERA_OP_F: rc = chimera_fwd_slot(st, o.mb, o.slot); break;
+                case CHIMERA_OP_F2: rc = chimera_fwd_slot(wk.fwd2[o.pipe], o.mb, 0); break;
+                case CHIMERA_OP_B:
+                    // after a doubled forward nothing was kept: run the forward again, then the backward
+                    if (!st->in_flight.count(o.mb)) rc = chimera_fwd_slot(st, o.mb, -1);
+                    if (!rc) rc = chimera_bwd(st, o.mb);
+                    break;
+                case CHIMERA_OP_BH0: rc = chimera_bwd_half(st, o.mb, 0); break;
+                case CHIMERA_OP_BH1: rc = chimera_bwd_half(st, o.mb, 1); break;
+                default: rc = fail(CHIMERA_EINVAL, "unknown op kind %d", o.kind);
+            }
+            if (wk.timing) (void)hipEventRecord(ev[2 * i + 1], st->stream);
         }
-        if (wk.timing) (void)hipEventRecord(ev[2 * i + 1], st->stream);
+        return rc;
+    };
+    ReplayPlan& plan = wk.pipes[0]->replay;
+    bool done = false;
+    if (!on_lane.empty() && !rc && std::all_of(on_lane.begin(), on_lane.end(), [](const OnLane& l) { return replay_in_graphs(l.st); })) {
+        int dev = 0;
+        (void)hipGetDevice(&dev);
+        std::vector<chimera_stage*> used;
+        for (int p = 0; p < pipes; ++p)
+            for (chimera_stage* st : stages_of(p)) used.push_back(runs[p] ? st : nullptr);
+        std::vector<uint64_t> key = replay_key({(uint64_t)algo, (uint64_t)rank, (uint64_t)D, (uint64_t)N, (uint64_t)f, (uint64_t)lanes, (uint64_t)dev}, used);
+        if (plan.key != key) {
+            plan.drop();
+            plan.key = std::move(key);
+        } else if (!plan.refused) {
+            if (plan.lanes.empty() && !record_replay(wk, plan, lanes_taken, used, launch_ops)) rc = CHIMERA_OK;     // launched one by one below
+            for (size_t i = 0; i < plan.lanes.size() && !rc; ++i) {
+                const hipError_t e = hipGraphLaunch(plan.lanes[i].second, wk.lanes[plan.lanes[i].first]);
+                if (e != hipSuccess) rc = fail(CHIMERA_EDEVICE, "worker replay: %s", hipGetErrorString(e));
+            }
+            done = !plan.lanes.empty();
+            if (done) for (chimera_stage* st : used) if (st && st->keep) st->grads_pending_zero = false;
+        }
     }
+    if (!done) (void)launch_ops();
     wk.enqueue_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_start).count();
     // lanes join the streams the stages were bound to
     for (OnLane& l : on_lane) {

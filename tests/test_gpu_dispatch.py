@@ -427,3 +427,55 @@ def _stage(dtype, hidden, heads, seq, microbatch, causal=True):
     compare_grads(st.read_grads(), gr, 2, hidden, dtype)
     assert_close(to_np(y), wy, dtype, "y")
     assert_close(to_np(dx), wdx, dtype, "dx")
+
+
+# A worker of small launches replays from graphs from its third replay on: new contents of the same buffers, gradients overwritten or
+# accumulated, io set anew and another schedule in between give what a worker gives whose launches always go out one by one.
+@pytest.mark.parametrize("dtype, hidden, heads, seq, mb", [(b.F32, 128, 4, 64, 2), (b.BF16, 256, 4, 96, 2)])
+def test_worker_replays_from_graphs(dtype, hidden, heads, seq, mb):
+    import torch
+    tdt, M, D = (torch.float32 if dtype == b.F32 else torch.bfloat16), seq * mb, 4
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    rn = lambda *s, std=1.0: torch.empty(s, dtype=tdt, device="cuda").normal_(0.0, std, generator=gen)
+    workers = []
+    for overlap in (True, False):
+        stages = [b.Stage(2, hidden, heads, seq, mb, dtype, stash_slots=4, overlap=overlap) for _ in range(2)]
+        workers.append((stages, {}))
+    for i in range(2):
+        workers[0][0][i].weights.copy_(rn(workers[0][0][i].weights.numel(), std=0.05))
+        workers[1][0][i].weights.copy_(workers[0][0][i].weights)
+        for st in (workers[0][0][i], workers[1][0][i]):
+            st.grads.zero_()
+
+    def set_io():
+        for stages, io in workers:
+            for g in range(2 * D):
+                x, dy = torch.zeros(M, hidden, dtype=tdt, device="cuda"), torch.zeros(M, hidden, dtype=tdt, device="cuda")
+                io[g] = (x, dy) + tuple(stages[0 if g % D < D // 2 else 1].set_io(g, x, dy))
+
+    set_io()
+    #           N, gradients zeroed first, io set anew
+    for step, (N, zero, anew) in enumerate([(4, 1, 0), (4, 1, 0), (4, 1, 0), (4, 1, 0), (4, 0, 0), (4, 0, 0), (4, 0, 0), (8, 1, 0), (8, 1, 0),
+                                            (8, 1, 1), (8, 1, 0), (8, 1, 0), (4, 1, 0), (8, 1, 0), (8, 1, 0), (8, 1, 0)]):
+        print("replay", dtype, step, flush=True)
+        if anew:
+            set_io()
+        for g in range(2 * D):
+            x, dy = rn(M, hidden), rn(M, hidden)
+            for _, io in workers:
+                io[g][0].copy_(x), io[g][1].copy_(dy), io[g][2].zero_(), io[g][3].zero_()
+        torch.cuda.synchronize()
+        for stages, _ in workers:
+            if zero:
+                for st in stages:
+                    st.zero_grads()
+            b.chimera_worker_bind_pipes(stages)
+            b.chimera_run_worker_pipes(b.DIRECT, 1, D, N)
+        for g in range(N):
+            assert torch.equal(workers[0][1][g][2], workers[1][1][g][2]) and torch.equal(workers[0][1][g][3], workers[1][1][g][3]), (step, g)
+            assert workers[0][1][g][2].abs().sum() > 0
+        for i in range(2):
+            assert torch.equal(workers[0][0][i].grads, workers[1][0][i].grads), (step, i)
+    for stages, _ in workers:
+        for st in stages:
+            st.close()
