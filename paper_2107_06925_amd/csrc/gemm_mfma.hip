@@ -204,10 +204,33 @@ template <> struct Raw8<float> {
 // (16 in a row for a 128-row wavefront tile: as long as a short k loop).  So the pieces of the
 // next DEPTH bands are requested before the current band is worked on: all bands when the
 // elements have 2 bytes, two bands when they are floats (registers).
+//
+// A wavefront with a single band (64x64 tiles) asks for all of it, bias included, before its k loop (EpiAhead): a round trip less at the
+// end of a short launch.  With the residual, 256 x 256 x 1024 6.9 -> 6.35 us, 400 x 320 x 1280 7.7 -> 7.25; bias 256 x 768 x 256
+// 4.4 -> 4.15.
+template <int TN> struct EpiAhead {
+    static constexpr int CPR = TN * 4, RPP = 64 / CPR, NP = 32 / RPP;
+    uint4 bias, q[NP][2];
+    __device__ __forceinline__ void request(int row_base, int col_base, int m, int n, const bf16_t* b, const bf16_t* r, const void* c,
+                                            int epi, int epi_flag, int res_types, int lane) {
+        const int pr = lane / CPR, lcol = min(col_base + lane % CPR * 8, n - 8);
+        if (epi == EPI_BIAS || epi == EPI_BIAS_GELU || epi == EPI_BIAS_RESIDUAL) bias = *reinterpret_cast<const uint4*>(b + lcol);
+        const bool f32 = epi == EPI_ACCUM_F32 || (epi == EPI_BIAS_RESIDUAL && (res_types & 1));
+        if (epi != EPI_BIAS_RESIDUAL && epi != EPI_DGELU && !(epi == EPI_ACCUM_F32 && !epi_flag)) return;
+        const char* src = epi == EPI_ACCUM_F32 ? (const char*)c : (const char*)r;
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            const size_t at = (size_t)min(row_base + j * RPP + pr, m - 1) * n + lcol;
+            q[j][0] = *reinterpret_cast<const uint4*>(src + at * (f32 ? 4 : 2));
+            if (f32) q[j][1] = *reinterpret_cast<const uint4*>(src + at * 4 + 16);
+        }
+    }
+};
 template <int EPI, bool RF32, bool CF32, int TM, int TN, typename Acc>
 __device__ __forceinline__ void epilogue(const Acc& acc, float* slab, int row_base, int col_base, int m,
                                          int n, const bf16_t* __restrict__ bias, const bf16_t* __restrict__ R,
-                                         void* __restrict__ c, bf16_t* __restrict__ C2, int epi_flag, int lane) {
+                                         void* __restrict__ c, bf16_t* __restrict__ C2, int epi_flag, int lane,
+                                         const EpiAhead<TN>* pre = nullptr) {
     constexpr int WN = EpiSlab<TN>::WN, STRIDE = EpiSlab<TN>::STRIDE;
     constexpr int CPR = WN / 8;                // 8-column pieces per row
     constexpr int RPP = 64 / CPR;              // rows covered by the 64 lanes at once
@@ -236,15 +259,24 @@ __device__ __forceinline__ void epilogue(const Acc& acc, float* slab, int row_ba
     float bv[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) bv[e] = 0.f;
-    if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU || EPI == EPI_BIAS_RESIDUAL)
-        if (gcol < n) load8(bias + gcol, bv);
-    if constexpr (READS)
-        if (reads) {
+    if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU || EPI == EPI_BIAS_RESIDUAL) {
+        if (pre) Raw8<bf16_t>{pre->bias}.unpack(bv);
+        else if (gcol < n) load8(bias + gcol, bv);
+    }
+    if constexpr (READS) {
+        if (pre) {
+#pragma unroll
+            for (int j = 0; j < NP; ++j) {
+                if constexpr (READS_F32) { ahead[0][j].lo = __builtin_bit_cast(float4, pre->q[j][0]); ahead[0][j].hi = __builtin_bit_cast(float4, pre->q[j][1]); }
+                else ahead[0][j].q = pre->q[j][0];
+            }
+        } else if (reads) {
             request(0, std::integral_constant<int, 0>{});
             if constexpr (DEPTH > 1 && TM > 1) request(1, std::integral_constant<int, 1 % DEPTH>{});
             if constexpr (DEPTH > 2 && TM > 2) request(2, std::integral_constant<int, 2 % DEPTH>{});
             if constexpr (DEPTH > 3 && TM > 3) request(3, std::integral_constant<int, 3 % DEPTH>{});
         }
+    }
     static_assert(TM <= 4, "at most four bands per wavefront");
     auto band = [&](auto a_c) {
         constexpr int a = decltype(a_c)::value;
@@ -471,6 +503,13 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_kernel(
 #undef CHIMERA_EPI
 }
 
+template <int N, typename F> __device__ __forceinline__ void static_for(F&& f) {
+    if constexpr (N > 0) {
+        static_for<N - 1>(f);
+        f(std::integral_constant<int, N - 1>{});
+    }
+}
+
 // ---------------------------------------------------------------- async variant
 // Same tiles, same LDS layouts, same MFMA loop, but the tiles travel global -> LDS
 // without passing through registers (global_load_lds_dwordx4: lane i of a wavefront
@@ -579,6 +618,11 @@ __device__ __forceinline__ void gemm_async_tile(
         for (int it = 0; it < CB; ++it) { lds_dma16(gb[it], sb + it * NT * 16); gb[it] += step_b; }
     };
 
+    static_assert(WGK == 2 && TM <= 2, "one band of rows per wavefront in the epilogue");
+    EpiAhead<TN> pre;
+    if (TM > 1 || wk == 0)
+        pre.request(i0 + wm0 + (TM > 1 ? wk * 32 : 0), j0 + wn0, m, n, bias, R, C, ONLY_EPI >= 0 ? ONLY_EPI : epi, epi_flag, res_types, lane);
+
     f32x16 acc[TM][TN];
 #pragma unroll
     for (int a = 0; a < TM; ++a)
@@ -643,16 +687,62 @@ __device__ __forceinline__ void gemm_async_tile(
     }
     int cur = 0, nxt = NS - SPS;               // stage computed now / stage the next issue fills
     auto advance = [](int& st) { st = st + 1 == NS ? 0 : st + 1; };
-    for (int kt = 0; kt < KT; kt += SPS) {
-        // the SPS oldest outstanding stages must have landed; up to NS - 2 SPS younger ones may fly on
-        if (kt + NS - SPS <= KT) wait_vmcnt<(NS - 2 * SPS) * (CA + CB)>(); else wait_vmcnt<0>();
+    // Operands of SPS stages out of LDS first, then a request behind each MFMA: all wavefronts leave the barrier together, and
+    // a CU takes 16 clocks for each of their 16 to 32 requests, which reads behind them would wait for.  Requests first -> reads
+    // first, operands in the memory-side cache: 632 x 1600 x 6400 26.1 -> 22.5 us, 1024 x 640 x 2560 11.5 -> 10.7, 1264 x 1600 x 6400
+    // (two workgroups per CU) 42.9 -> 41.7.
+    auto iteration = [&](auto always_c, int kt) {
+        constexpr bool always = decltype(always_c)::value;
+        bf16x8 af[SPS][KSUB][TM], bfr[SPS][KSUB][TN];
+        int st = cur;
+#pragma unroll
+        for (int u = 0; u < SPS; ++u) {
+            const bf16_t* As = lds + st * STAGE;
+            advance(st);
+            if (!always && u && kt + u >= KT) break;
+#pragma unroll
+            for (int ks = 0; ks < KSUB; ++ks) {
+#pragma unroll
+                for (int a = 0; a < TM; ++a) af[u][ks][a] = read_frag<BM, A_KC>(As, wm0 + a * 32, wk * KSUB + ks, lane);
+#pragma unroll
+                for (int b = 0; b < TN; ++b) bfr[u][ks][b] = read_frag<BN, B_KC>(As + BM * BK, wn0 + b * 32, wk * KSUB + ks, lane);
+            }
+        }
+        cur = st;
+        __builtin_amdgcn_sched_barrier(0);
+        constexpr int REQ = SPS * (CA + CB), MM = SPS * KSUB * TM * TN, PER = (REQ + MM - 1) / MM;
+        static_for<MM>([&](auto i_c) {
+            constexpr int i = decltype(i_c)::value, u = i / (KSUB * TM * TN), ks = i / (TM * TN) % KSUB, a = i / TN % TM, b = i % TN;
+            if (always || u == 0 || kt + u < KT) {
+                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[u][ks][a], bfr[u][ks][b], acc[a][b], 0, 0, 0);
+                if constexpr (ONLY_EPI == EPI_ACCUM_F32 && a == 0)
+                    if (col_sums) cs[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, bfr[u][ks][b], cs[b], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            static_for<PER>([&](auto j_c) {
+                constexpr int r = i * PER + decltype(j_c)::value, ru = r / (CA + CB), it = r % (CA + CB);
+                if constexpr (r < REQ)
+                    if (always || kt + NS - SPS + ru < KT) {
+                        const unsigned to = lds0 + (unsigned)(nxt * STAGE) * 2u + (unsigned)wave * 1024u;
+                        if constexpr (it < CA) { lds_dma16(ga[it], to + it * NT * 16); ga[it] += step_a; }
+                        else { lds_dma16(gb[it - CA], to + BM * BK * 2 + (it - CA) * NT * 16); gb[it - CA] += step_b; }
+                        if constexpr (it == CA + CB - 1) advance(nxt);
+                    }
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    int kt = 0;
+    for (; kt + NS <= KT; kt += SPS) {
+        // the SPS oldest outstanding stages must have landed; NS - 2 SPS younger ones may fly on
+        wait_vmcnt<(NS - 2 * SPS) * (CA + CB)>();
         __syncthreads();                       // every wavefront's part of this step is in LDS; the previous one is consumed
-#pragma unroll
-        for (int u = 0; u < SPS; ++u)
-            if (kt + NS - SPS + u < KT) { issue(nxt); advance(nxt); }
-#pragma unroll
-        for (int u = 0; u < SPS; ++u)
-            if (SPS == 1 || kt + u < KT) { compute(cur); advance(cur); }
+        iteration(std::true_type{}, 0);
+    }
+    for (; kt < KT; kt += SPS) {
+        if (kt + NS - SPS <= KT) wait_vmcnt<(NS - 2 * SPS) * (CA + CB)>(); else wait_vmcnt<0>();
+        __syncthreads();
+        iteration(std::false_type{}, kt);
     }
     touch_ahead(ahead, wave, NT / 64, lane, lds_address(strip));
 
@@ -663,7 +753,7 @@ __device__ __forceinline__ void gemm_async_tile(
     __syncthreads();
     float* slab = reinterpret_cast<float*>(lds) + (size_t)(tid >> 6) * EpiSlab<TN>::FLOATS;
     auto finish = [&]<int TMO>(const f32x16 (&out)[TMO][TN], int rb0) {
-#define CHIMERA_EPI(E, RF, CF) epilogue<E, RF, CF, TMO, TN>(Acc32<TMO, TN>{out}, slab, rb0, cb0, m, n, bias, R, C, C2, epi_flag, lane)
+#define CHIMERA_EPI(E, RF, CF) epilogue<E, RF, CF, TMO, TN>(Acc32<TMO, TN>{out}, slab, rb0, cb0, m, n, bias, R, C, C2, epi_flag, lane, &pre)
         if constexpr (ONLY_EPI == EPI_ACCUM_F32) { CHIMERA_EPI(EPI_ACCUM_F32, false, false); return; }
         switch (epi) {
             case EPI_NONE: CHIMERA_EPI(EPI_NONE, false, false); break;
@@ -824,13 +914,6 @@ __device__ __forceinline__ int rkswz(int k) { return (k & 3) | ((k >> 1) & 4); }
 __device__ __forceinline__ void lds_dma16_s(const void* sbase, unsigned voff, unsigned lds_base) {
     asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "{m0}"(lds_base) : "memory");
 }
-template <int N, typename F> __device__ __forceinline__ void static_for(F&& f) {
-    if constexpr (N > 0) {
-        static_for<N - 1>(f);
-        f(std::integral_constant<int, N - 1>{});
-    }
-}
-
 template <int BM, int BN, int WGM, int WGN, int WGK, bool A_KC, bool B_KC, int ONLY_EPI>
 __device__ __forceinline__ void gemm_ring_tile(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, const bf16_t* __restrict__ bias,
