@@ -37,104 +37,61 @@ __global__ __launch_bounds__(EDGE_THREADS) void embed_fwd_kernel(const int* __re
     }
 }
 
-// ---- embedding backward: one launch, two kinds of workgroups.
+// ---- embedding backward: one launch, three kinds of workgroups.
 //
 // Position table, dwpe[p] += sum over the sequences of dx[b*S + p], b ascending: one 16-byte piece
 // of a row per thread, eight sequences' pieces requested at a time.
 //
 // Token table, dwte[v] += sum of dx[t] over the positions t with token v.  Workgroup w owns the
-// tokens v with v mod EMB_OWNERS = w: every table row has one owner, so the sums need no atomics, and their
-// order is fixed by the positions alone.  Per window of EMB_WINDOW positions the workgroup
+// tokens v with v mod owners = w: every table row has one owner, so the sums need no atomics, and their
+// order is fixed by the positions alone.  Frequent tokens (more than EMB_HOT positions hold v mod EMB_BUCKETS) have owners of their
+// own: one CU reads some 64 bytes a nanosecond, and a frequent word's rows are many.  Workgroup (w, s) of those owns columns
+// [s, s + 1) * EMB_LANES * V of the frequent tokens with v mod hot_classes = w.  A workgroup
 //   1. lists its positions in ascending order (one ballot per 64 positions),
 //   2. finds the first entry of every distinct token in the list (a "head"),
-//   3. gives each head to one wavefront, which walks the list 64 entries at a time (ballot of
+//   3. gives each head and 64 pieces of its row to one wavefront, which walks the list 64 entries at a time (ballot of
 //      "same token") and adds the rows in ascending order, several in flight;
-//   4. shares tokens with more than EMB_HOT entries among its eight wavefronts instead (wavefront k
-//      takes entries 8k..8k+7 of every 64; the partial rows are added in wavefront order): a frequent
-//      word would otherwise be one wavefront's serial chain of row loads.
+//   4. or, for frequent tokens, shares each among 32 groups of lanes, the k-th of which takes the k-th, (k + 32)-th, ...
+//      position; the partial rows are added in a fixed tree.
+// A list holds EMB_LIST entries; a workgroup that owns more positions goes through them EMB_LIST positions at a time.
 // What bounds it is latency (list, row, table row: a few dependent round trips), so there are
 // enough workgroups that a wavefront seldom has more than one or two tokens.  (One workgroup per
-// position, each scanning all tokens through LDS, took 301 us at 4096 positions x 1024 columns.)
+// position, each scanning all tokens through LDS, took 301 us at 4096 positions x 1024 columns.)  With frequent tokens shared by
+// the wavefronts of their owner, whole rows each, and windows of 4096 positions, ids spread over the logarithm of the
+// vocabulary: 4096 x 1024 of 50304 35.6 -> 16.9 us (float 67 -> 18.7), 16384 x 2048 of 65536 244 -> 90, 16384 x 256 of 30000
+// 73 -> 57, 1000 x 776 of 5000 11.7 -> 9.3; every second position the same token, 4096 x 1024, 179 -> 35.
+// owners: 1024 x 1024 and 512 x 512 of them at 2048 tokens of 1600 columns 14.5 -> 11.2 us, at 4096 x 1024 16.9 -> 18.4,
+// at 8192 x 512 25.8 -> 34.  Classes of frequent tokens: 16 -> 32 at 16384 x 2048 112 -> 89, at 4096 x 1024 (float) 18.7 -> 20.6.
 constexpr int EMB_THREADS = 512, EMB_WAVES = EMB_THREADS / WAVE;
-constexpr int EMB_WINDOW = 4096;
+constexpr int EMB_LIST = 2048;
 constexpr int EMB_HOT = 16;
-constexpr int EMB_OWNERS = 1024;          // workgroups that share the token table (a power of two)
+constexpr int EMB_OWNERS_MIN = 64, EMB_OWNERS_MAX = 1024;       // workgroups that share the token table (powers of two)
+constexpr int EMB_HOT_CLASSES_MIN = 8, EMB_HOT_CLASSES_MAX = 32, EMB_BUCKETS = 16384;       // powers of two
+constexpr int EMB_LANES = 16, EMB_GROUPS = EMB_THREADS / EMB_LANES, EMB_FLY = 4;       // lanes of a group (256 bytes of a row); rows in flight
 typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));     // gradient tables need not be 16-byte aligned
 struct EmbedLds {
-    int tok[EMB_WINDOW];                  // owned tokens of the window, in position order
-    unsigned short pos[EMB_WINDOW];       // their positions within the window
-    unsigned short head[EMB_WINDOW];      // list index of the first entry of every distinct token
-    int counts[EMB_WAVES + 1];
+    int tok[EMB_LIST];                    // owned tokens, in position order
+    int pos[EMB_LIST];                    // their positions
+    unsigned short head[EMB_LIST];        // list index of the first entry of every distinct token
+    unsigned short same[EMB_LIST];        // list indices of one frequent token
+    int seen[EMB_BUCKETS / EMB_HOT_CLASSES_MIN];       // positions of the class's tokens, by bucket
+    float part[EMB_WAVES][EMB_LANES * 8]; // partial rows of a frequent token
+    int counts[EMB_WAVES];
     int heads;
 };
 
-template <typename T, int MAXC> struct EmbedRow {
-    static constexpr int V = Elem<T>::VEC, FLY = MAXC <= 2 ? 8 : 4;      // rows in flight
-    float a[MAXC][V];
-    __device__ __forceinline__ void zero() {
-#pragma unroll
-        for (int i = 0; i < MAXC; ++i)
-#pragma unroll
-            for (int e = 0; e < V; ++e) a[i][e] = 0.f;
-    }
-    // adds the rows pos[j] of the entries j in `mask`, ascending
-    __device__ __forceinline__ void add_rows(const T* __restrict__ dx, const unsigned short* pos, unsigned long long mask, int nchunk,
-                                             int H, int lane) {
-        while (mask) {
-            uint4 q[FLY][MAXC];
-            bool ok[FLY];
-#pragma unroll
-            for (int u = 0; u < FLY; ++u) {
-                ok[u] = mask != 0;
-                const int j = ok[u] ? __ffsll((long long)mask) - 1 : 0;
-                mask &= mask - 1;
-                const T* row = dx + (size_t)pos[j] * H;
-                if (ok[u])
-#pragma unroll
-                    for (int i = 0; i < MAXC; ++i)
-                        if (lane + i * WAVE < nchunk) q[u][i] = *reinterpret_cast<const uint4*>(row + (lane + i * WAVE) * V);
-            }
-#pragma unroll
-            for (int u = 0; u < FLY; ++u)
-                if (ok[u])
-#pragma unroll
-                    for (int i = 0; i < MAXC; ++i)
-                        if (lane + i * WAVE < nchunk) {
-                            float v[V];
-                            load_vec<T>(reinterpret_cast<const T*>(&q[u][i]), v);
-#pragma unroll
-                            for (int e = 0; e < V; ++e) a[i][e] += v[e];
-                        }
-        }
-    }
-    __device__ __forceinline__ void add_to(float* __restrict__ out, int nchunk, int lane) const {
-#pragma unroll
-        for (int i = 0; i < MAXC; ++i)
-            if (lane + i * WAVE < nchunk) {
-                float* o = out + (size_t)(lane + i * WAVE) * V;
-#pragma unroll
-                for (int e = 0; e < V; e += 4) {
-                    f32x4_u t = *reinterpret_cast<const f32x4_u*>(o + e);
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) t[k] += a[i][e + k];
-                    *reinterpret_cast<f32x4_u*>(o + e) = t;
-                }
-            }
-    }
-};
-
-template <typename T, int MAXC>
+template <typename T>
 __global__ __launch_bounds__(EMB_THREADS) void embed_bwd_kernel(const int* __restrict__ tokens, const T* __restrict__ dx,
                                                                 float* __restrict__ dwte, float* __restrict__ dwpe, int M, int S,
-                                                                int H, int vocab) {
+                                                                int H, int vocab, int owners, int hot_classes, int slices) {
     constexpr int V = Elem<T>::VEC;
-    extern __shared__ __attribute__((aligned(16))) char emb_smem[];
-    EmbedLds& sm = *reinterpret_cast<EmbedLds*>(emb_smem);
-    float* hot_row = reinterpret_cast<float*>(emb_smem + sizeof(EmbedLds));       // [H]
+    __shared__ __attribute__((aligned(16))) EmbedLds sm;
     const int tid = threadIdx.x, lane = tid % WAVE, wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
     const int nchunk = H / V;
-    if ((int)blockIdx.x >= EMB_OWNERS) {                            // position table
-        const size_t i = (size_t)(blockIdx.x - EMB_OWNERS) * EMB_THREADS + tid;
+    const int hot_wgs = hot_classes * slices;
+    const bool hot = (int)blockIdx.x < hot_wgs;
+    if ((int)blockIdx.x >= hot_wgs + owners) {                  // position table
+        const size_t i = (size_t)(blockIdx.x - hot_wgs - owners) * EMB_THREADS + tid;
         if (i >= (size_t)S * nchunk) return;
         const T* src = dx + i * V;                              // position p = i / nchunk of sequence 0
         const size_t stride = (size_t)S * H;
@@ -165,39 +122,90 @@ __global__ __launch_bounds__(EMB_THREADS) void embed_bwd_kernel(const int* __res
         }
         return;
     }
-    const int mine = (int)blockIdx.x;
-    for (int w0 = 0; w0 < M; w0 += EMB_WINDOW) {
-        // 1. the window's owned positions, ascending: wavefront k looks at positions [k, k+1) * 512
-        constexpr int GROUPS = EMB_WINDOW / EMB_WAVES / WAVE;
-        int tok[GROUPS];
-        unsigned long long own[GROUPS];
-        int n_wave = 0;
-        const int p0 = wave * (EMB_WINDOW / EMB_WAVES);
+    const int mine = hot ? (int)blockIdx.x / slices : (int)blockIdx.x - hot_wgs, classes = hot ? hot_classes : owners;      // (powers of two)
+    // of a frequent token's row: this group's lanes, and the lane's 16-byte piece
+    const int group = tid / EMB_LANES, slice = hot ? (int)blockIdx.x % slices : 0, piece = slice * EMB_LANES + lane % EMB_LANES;
+    auto add_row = [](float (&a)[V], const uint4& q) {
+        float x[V];
+        load_vec<T>(reinterpret_cast<const T*>(&q), x);
 #pragma unroll
-        for (int i = 0; i < GROUPS; ++i) {
-            const int t = w0 + p0 + i * WAVE + lane;
-            tok[i] = t < M ? min(max(tokens[t], 0), vocab - 1) : -1;        // ids outside the table are clamped, never followed
+        for (int e = 0; e < V; ++e) a[e] += x[e];
+    };
+    // 512 positions at a time, 64 per load; ids outside the table are clamped, never followed
+    constexpr int LOADS = EMB_THREADS / WAVE;
+    int tok[LOADS];
+    auto load_tokens = [&](int from, int end) {
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) {
+            const int t = from + i * WAVE + lane;
+            tok[i] = t < end ? min(max(tokens[t], 0), vocab - 1) : -1;
         }
+    };
+    auto bucket = [&](int v) { return (v & (EMB_BUCKETS - 1)) / classes; };
+    auto in_class = [&](int v) { return v >= 0 && (v & (classes - 1)) == mine; };
+    // positions of the class by bucket; whether one is frequent
+    auto count_buckets = [&] {
+        for (int i = tid; i < EMB_BUCKETS / classes; i += EMB_THREADS) sm.seen[i] = 0;
+        __syncthreads();
+        bool frequent = false;
+        for (int from = wave * EMB_THREADS; from < M; from += EMB_WAVES * EMB_THREADS) {
+            load_tokens(from, M);
 #pragma unroll
-        for (int i = 0; i < GROUPS; ++i) {
-            own[i] = __ballot(tok[i] >= 0 && (tok[i] & (EMB_OWNERS - 1)) == mine);
-            n_wave += __popcll(own[i]);
+            for (int i = 0; i < LOADS; ++i)
+                if (in_class(tok[i])) frequent |= atomicAdd(&sm.seen[bucket(tok[i])], 1) >= EMB_HOT;
+        }
+        return __syncthreads_or(frequent) != 0;
+    };
+    if (hot && !count_buckets()) return;
+    bool by_bucket = hot;                                       // the list leaves out what the other kind owns
+    auto owned = [&](int v) { return in_class(v) && (!by_bucket || (sm.seen[bucket(v)] > EMB_HOT) == hot); };
+    // Wavefront k looks at the k-th eighth of positions [w0, w0 + size).  Counts what is owned there, and everywhere.
+    int at = 0;
+    auto count_owned = [&](int w0, int size) {
+        const int each = ((size + EMB_WAVES - 1) / EMB_WAVES + WAVE - 1) / WAVE * WAVE, end = min(w0 + min((wave + 1) * each, size), M);
+        int n_wave = 0;
+        for (int from = w0 + wave * each; from < end; from += EMB_THREADS) {
+            load_tokens(from, end);
+#pragma unroll
+            for (int i = 0; i < LOADS; ++i) n_wave += __popcll(__ballot(owned(tok[i])));
         }
         if (lane == 0) sm.counts[wave] = n_wave;
         __syncthreads();                                        // also: the previous window's list and number of heads are no longer read
         if (tid == 0) sm.heads = 0;                             // counted up behind the next barrier
-        int at = 0, n = 0;
+        int n = 0;
+        at = 0;
 #pragma unroll
         for (int k = 0; k < EMB_WAVES; ++k) { const int c = sm.counts[k]; at += k < wave ? c : 0; n += c; }
-        n = __builtin_amdgcn_readfirstlane(n);
+        return __builtin_amdgcn_readfirstlane(n);
+    };
+    int window = M, n = count_owned(0, M);
+    const bool several = n > EMB_LIST;
+    if (several) {
+        window = EMB_LIST;
+        if (!hot) { (void)count_buckets(); by_bucket = true; }
+    }
+    for (int w0 = 0; w0 < M; w0 += window) {
+        // 1. the window's owned positions, ascending
+        if (several) {
+            __syncthreads();                                    // the counts have been read
+            n = count_owned(w0, window);
+        }
+        {
+            const int each = ((window + EMB_WAVES - 1) / EMB_WAVES + WAVE - 1) / WAVE * WAVE, end = min(w0 + min((wave + 1) * each, window), M);
+            for (int from = w0 + wave * each; from < end; from += EMB_THREADS) {
+                if (each > EMB_THREADS) load_tokens(from, end);         // else they are still there
 #pragma unroll
-        for (int i = 0; i < GROUPS; ++i) {
-            if ((own[i] >> lane) & 1) {
-                const int j = at + __popcll(own[i] & ((1ull << lane) - 1));
-                sm.tok[j] = tok[i];
-                sm.pos[j] = (unsigned short)(p0 + i * WAVE + lane);
+                for (int i = 0; i < LOADS; ++i) {
+                    const bool own = owned(tok[i]);
+                    const unsigned long long m = __ballot(own);
+                    if (own) {
+                        const int j = at + __popcll(m & ((1ull << lane) - 1));
+                        sm.tok[j] = tok[i];
+                        sm.pos[j] = from + i * WAVE + lane;
+                    }
+                    at += __popcll(m);
+                }
             }
-            at += __popcll(own[i]);
         }
         __syncthreads();
         if (n == 0) continue;
@@ -218,45 +226,91 @@ __global__ __launch_bounds__(EMB_THREADS) void embed_bwd_kernel(const int* __res
         }
         __syncthreads();
         const int heads = __builtin_amdgcn_readfirstlane(sm.heads);
-        const T* wdx = dx + (size_t)w0 * H;
-        EmbedRow<T, MAXC> row;
-        // 3. one wavefront per token
-        for (int hd = wave; hd < heads; hd += EMB_WAVES) {
-            const int first = __builtin_amdgcn_readfirstlane((int)sm.head[hd]), v = __builtin_amdgcn_readfirstlane(sm.tok[first]);
-            int count = 0;
-            for (int g = first & ~(WAVE - 1); g < n; g += WAVE) count += __popcll(__ballot(g + lane < n && sm.tok[min(g + lane, n - 1)] == v));
-            if (count > EMB_HOT) continue;
-            row.zero();
-            for (int g = first & ~(WAVE - 1); g < n; g += WAVE)
-                row.add_rows(wdx, sm.pos + g, __ballot(g + lane < n && sm.tok[min(g + lane, n - 1)] == v), nchunk, H, lane);
-            row.add_to(dwte + (size_t)v * H, nchunk, lane);
-        }
-        // 4. frequent tokens: all wavefronts (n > EMB_HOT is uniform, and so is every count)
-        if (n > EMB_HOT)
+        auto matches = [&](int from, int v, int mask) { return __ballot(from + lane < n && ((sm.tok[min(from + lane, n - 1)] ^ v) & mask) == 0); };     // of 64 entries
+        // 4. frequent tokens: all groups
+        if (hot) {
             for (int hd = 0; hd < heads; ++hd) {
                 const int first = __builtin_amdgcn_readfirstlane((int)sm.head[hd]), v = __builtin_amdgcn_readfirstlane(sm.tok[first]);
                 int count = 0;
-                for (int g = first & ~(WAVE - 1); g < n; g += WAVE) count += __popcll(__ballot(g + lane < n && sm.tok[min(g + lane, n - 1)] == v));
-                if (count <= EMB_HOT) continue;
-                row.zero();
-                for (int g = first & ~(WAVE - 1); g < n; g += WAVE)
-                    row.add_rows(wdx, sm.pos + g, __ballot(g + lane < n && sm.tok[min(g + lane, n - 1)] == v) & (0xffull << (8 * wave)), nchunk, H, lane);
-                for (int k = 0; k < EMB_WAVES; ++k) {
-                    if (wave == k)
-#pragma unroll
-                        for (int i = 0; i < MAXC; ++i)
-                            if (lane + i * WAVE < nchunk) {
-                                float* o = hot_row + (lane + i * WAVE) * V;
-#pragma unroll
-                                for (int e = 0; e < V; ++e) {
-                                    row.a[i][e] += k ? o[e] : 0.f;
-                                    o[e] = row.a[i][e];
-                                }
-                            }
-                    __syncthreads();
+                for (int g = first & ~(WAVE - 1); g < n; g += WAVE) {
+                    const unsigned long long m = matches(g, v, -1);
+                    if (g / WAVE % EMB_WAVES == wave && ((m >> lane) & 1)) sm.same[count + __popcll(m & ((1ull << lane) - 1))] = (unsigned short)(g + lane);
+                    count += __popcll(m);
                 }
-                if (wave == EMB_WAVES - 1) row.add_to(dwte + (size_t)v * H, nchunk, lane);
+                __syncthreads();
+                const T* src = dx + (size_t)min(piece, nchunk - 1) * V;
+                float a[V];
+#pragma unroll
+                for (int e = 0; e < V; ++e) a[e] = 0.f;
+                for (int i = group; i < count; i += EMB_GROUPS * EMB_FLY) {
+                    uint4 q[EMB_FLY];
+#pragma unroll
+                    for (int u = 0; u < EMB_FLY; ++u)
+                        q[u] = *reinterpret_cast<const uint4*>(src + (size_t)sm.pos[sm.same[min(i + u * EMB_GROUPS, count - 1)]] * H);
+#pragma unroll
+                    for (int u = 0; u < EMB_FLY; ++u)
+                        if (i + u * EMB_GROUPS < count) add_row(a, q[u]);
+                }
+#pragma unroll
+                for (int e = 0; e < V; ++e) {                   // the wavefront's four groups
+                    a[e] += __shfl_xor(a[e], 16, WAVE);
+                    a[e] += __shfl_xor(a[e], 32, WAVE);
+                    if (lane < EMB_LANES) sm.part[wave][lane * V + e] = a[e];
+                }
+                __syncthreads();                                // also: this token's indices are no longer read
+                const int col = slice * EMB_LANES * V + tid;
+                if (tid < EMB_LANES * V && col < H) {
+                    float sum = 0.f;
+#pragma unroll
+                    for (int k = 0; k < EMB_WAVES; ++k) sum += sm.part[k][tid];
+                    dwte[(size_t)v * H + col] += sum;           // (partial rows are written anew behind the next token's first barrier)
+                }
             }
+            continue;
+        }
+        // 3. one wavefront per token and 64 pieces of its row
+        const int parts = (nchunk + WAVE - 1) / WAVE;
+        for (int task = wave; task < heads * parts; task += EMB_WAVES) {
+            const int first = __builtin_amdgcn_readfirstlane((int)sm.head[task / parts]), v = __builtin_amdgcn_readfirstlane(sm.tok[first]);
+            if (!by_bucket && n > EMB_HOT) {                    // a frequent token?  (the list holds all of its bucket)
+                int count = 0;
+                for (int g = 0; g < n; g += WAVE) count += __popcll(matches(g, v, EMB_BUCKETS - 1));
+                if (count > EMB_HOT) continue;
+            }
+            const int at_piece = task % parts * WAVE + lane;
+            const size_t col = (size_t)min(at_piece, nchunk - 1) * V;
+            float* out = dwte + (size_t)v * H + col;
+            f32x4_u sum[V / 4];
+#pragma unroll
+            for (int e = 0; e < V / 4; ++e) sum[e] = *reinterpret_cast<const f32x4_u*>(out + 4 * e);
+            float a[V];
+#pragma unroll
+            for (int e = 0; e < V; ++e) a[e] = 0.f;
+            for (int g = first & ~(WAVE - 1); g < n; g += WAVE) {
+                unsigned long long m = matches(g, v, -1);
+                while (m) {
+                    uint4 q[EMB_FLY];
+                    int rows = 0;
+#pragma unroll
+                    for (int u = 0; u < EMB_FLY; ++u)
+                        if (m) {
+                            q[u] = *reinterpret_cast<const uint4*>(dx + (size_t)sm.pos[g + __ffsll((long long)m) - 1] * H + col);
+                            m &= m - 1;
+                            rows = u + 1;
+                        }
+#pragma unroll
+                    for (int u = 0; u < EMB_FLY; ++u)
+                        if (u < rows) add_row(a, q[u]);
+                }
+            }
+            if (at_piece < nchunk)
+#pragma unroll
+                for (int e = 0; e < V / 4; ++e) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) sum[e][k] += a[4 * e + k];
+                    *reinterpret_cast<f32x4_u*>(out + 4 * e) = sum[e];
+                }
+        }
     }
 }
 
@@ -468,22 +522,20 @@ int chimera_op_embedding_bwd(int dtype, int tokens, int seq, int hidden, int voc
     const int vec = dtype == CHIMERA_F32 ? 4 : 8;
     if (hidden / vec > 2 * EDGE_THREADS) return fail(CHIMERA_EINVAL, "hidden=%d too wide for the embedding backward (max %d)", hidden, 2 * EDGE_THREADS * vec);
     hipStream_t s = (hipStream_t)hip_stream;
-    const int per_lane = (hidden / vec + WAVE - 1) / WAVE;
-    const size_t pieces = (size_t)seq * (hidden / vec), lds = sizeof(EmbedLds) + (size_t)hidden * sizeof(float);
-    const dim3 grid(EMB_OWNERS + (unsigned)((pieces + EMB_THREADS - 1) / EMB_THREADS)), block(EMB_THREADS);
-#define EMBED_BWD(T, C)                                                                                                \
-    hipLaunchKernelGGL((embed_bwd_kernel<T, C>), grid, block, lds, s, d_tokens, (const T*)d_dx, d_dwte, d_dwpe, tokens, seq, \
-                       hidden, vocab)
-#define EMBED_BWD_T(T)                                                                                                 \
-    do {                                                                                                               \
-        if (per_lane <= 1) EMBED_BWD(T, 1);                                                                            \
-        else if (per_lane <= 2) EMBED_BWD(T, 2);                                                                       \
-        else if (per_lane <= 4) EMBED_BWD(T, 4);                                                                       \
-        else EMBED_BWD(T, 8);                                                                                          \
-    } while (0)
-    if (dtype == CHIMERA_F32) EMBED_BWD_T(float); else EMBED_BWD_T(bf16_t);
-#undef EMBED_BWD_T
-#undef EMBED_BWD
+    const size_t pieces = (size_t)seq * (hidden / vec);
+    // the workgroups of frequent tokens, which may take longest, go first
+    const int slices = (hidden / vec + EMB_LANES - 1) / EMB_LANES;
+    int hot_classes = tokens > EMB_HOT ? EMB_HOT_CLASSES_MAX : 0;
+    while (hot_classes > EMB_HOT_CLASSES_MIN && hot_classes * slices > (tokens > 4096 ? 512 : 256)) hot_classes /= 2;
+    int owners = EMB_OWNERS_MAX;
+    while (owners > EMB_OWNERS_MIN && owners * 4 > tokens) owners /= 2;          // four positions each
+    const dim3 grid(hot_classes * slices + owners + (unsigned)((pieces + EMB_THREADS - 1) / EMB_THREADS)), block(EMB_THREADS);
+    if (dtype == CHIMERA_F32)
+        hipLaunchKernelGGL(embed_bwd_kernel<float>, grid, block, 0, s, d_tokens, (const float*)d_dx, d_dwte, d_dwpe, tokens, seq, hidden,
+                           vocab, owners, hot_classes, slices);
+    else
+        hipLaunchKernelGGL(embed_bwd_kernel<bf16_t>, grid, block, 0, s, d_tokens, (const bf16_t*)d_dx, d_dwte, d_dwpe, tokens, seq, hidden,
+                           vocab, owners, hot_classes, slices);
     CHIMERA_LAUNCH_CHECK("embedding backward");
     return CHIMERA_OK;
 }

@@ -173,3 +173,32 @@ def test_edge_argument_errors():
         b.chimera_head_loss(y, tok, y[0], y[0], wh, 1.0, torch.zeros_like(y), torch.zeros(16, device="cuda"),
                             torch.zeros(16, device="cuda"), torch.zeros_like(wh), torch.zeros(1, device="cuda"), workspace=small)
     assert e.value.code == b.ENOMEM
+
+
+# Token lists of the embedding backward: one token everywhere, every second position, more positions of one owner's tokens than a
+# list holds, frequent tokens beside rare ones of the same bucket, rows that end inside a slice.  Integers, so that float sums are exact.
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("tokens,hidden,vocab,kind", [
+    (17, 8, 5, "same"), (2049, 136, 70000, "same"), (4096, 264, 1000, "padding"), (5000, 136, 40000, "owner"), (6144, 72, 40000, "bucket"),
+    (16384, 128, 3000, "log"), (4097, 1032, 50304, "log"), (600, 2048, 40, "log")])
+def test_embedding_backward_lists(tokens, hidden, vocab, kind, dtype):
+    import torch
+    print("embedding backward lists", tokens, hidden, vocab, kind, dtype, flush=True)
+    rng = np.random.default_rng(tokens)
+    ids = np.minimum(np.exp(rng.random(tokens) * np.log(vocab)).astype(np.int64) - 1, vocab - 1).clip(0)
+    if kind == "same":
+        ids[:] = 3
+    elif kind == "padding":
+        ids[::2] = 1
+    elif kind == "owner":
+        ids = rng.integers(0, vocab // 1024, tokens) * 1024 + 5
+    elif kind == "bucket":
+        ids[::3], ids[1::700] = 7, 7 + 16384
+    ids = ids.astype(np.int32)
+    dx = rng.integers(-4, 5, (tokens, hidden)).astype(np.float32)
+    dwte, dwpe = torch.ones((vocab, hidden), device="cuda"), torch.zeros((1, hidden), device="cuda")
+    b.chimera_op_embedding_bwd(torch.from_numpy(ids).cuda(), 1, to_dev(dx, dtype), dwte, dwpe)
+    want = np.ones((vocab, hidden), np.float32)
+    np.add.at(want, ids, dx)
+    assert np.array_equal(dwte.cpu().numpy(), want)
+    assert np.array_equal(dwpe.cpu().numpy()[0], dx.sum(0))
