@@ -6,7 +6,7 @@
 // One workgroup computes a tile of the output; its wavefronts own parts of it as a grid of MFMA
 // tiles whose accumulators never leave the registers.  Three kernels, by size (choose_tile):
 //   gemm_ring_tile    256x256, 256x128 and 128x128 tiles on v_mfma_f32_16x16x32_bf16
-//   gemm_async_tile   64x64 tiles on v_mfma_f32_32x32x16_bf16, a ring of k steps
+//   gemm_async_tile   32x32 to 128x64 tiles on v_mfma_f32_32x32x16_bf16, a ring of k steps
 //   gemm_bf16_kernel  the register-staged form: split-K and shapes on request
 // The k loop moves BK = 64 at a time through LDS, the next steps in flight.  What follows on
 // LDS layouts is the latter two's; gemm_ring_tile's own differ in their exchanges and are described there.
@@ -57,8 +57,9 @@ __device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ (row & 7
 
 typedef bf16_t bf16x4 __attribute__((ext_vector_type(4)));
 
-// The XOR of k-row k's 32-byte column blocks in a [BK][ROWS] tile (rows of 128 bytes have only four).
-template <int ROWS> __device__ __forceinline__ int kswz(int k) { return ROWS == 64 ? k & 2 : (k & 3) << 1; }
+// The XOR of k-row k's 32-byte column blocks in a [BK][ROWS] tile (rows of 128 bytes have only four; four rows of 64 bytes
+// are all banks as they are).
+template <int ROWS> __device__ __forceinline__ int kswz(int k) { return ROWS == 32 ? 0 : ROWS == 64 ? k & 2 : (k & 3) << 1; }
 // LDS element offset of the 16-byte chunk `ic` (8 rows) of k-row `k` in a [BK][ROWS] tile
 template <int ROWS> __device__ __forceinline__ int mc_off(int k, int ic) {
     return k * ROWS + (((ic >> 1) ^ kswz<ROWS>(k)) << 4) + ((ic & 1) << 3);
@@ -618,7 +619,7 @@ __device__ __forceinline__ void gemm_async_tile(
         for (int it = 0; it < CB; ++it) { lds_dma16(gb[it], sb + it * NT * 16); gb[it] += step_b; }
     };
 
-    static_assert(WGK == 2 && TM <= 2, "one band of rows per wavefront in the epilogue");
+    static_assert(TM == 1 || (WGK == 2 && TM == 2), "one band of rows per wavefront in the epilogue");
     EpiAhead<TN> pre;
     if (TM > 1 || wk == 0)
         pre.request(i0 + wm0 + (TM > 1 ? wk * 32 : 0), j0 + wn0, m, n, bias, R, C, ONLY_EPI >= 0 ? ONLY_EPI : epi, epi_flag, res_types, lane);
@@ -779,37 +780,44 @@ __device__ __forceinline__ void gemm_async_tile(
                 if (col < n) bsum[col] = epi_flag ? v[b] : bsum[col] + v[b];
             }
     };
-    static_assert(WGK == 2, "two wavefronts per block");
     if constexpr (TM == 1) {
-        // As below, but there is only one band of rows: the second wavefront hands it over and is done.
-        static_assert(WGK == 2 && sizeof(lds) >= (size_t)WGM * WGN * TN * 4 * 64 * sizeof(float4) + BN * sizeof(float), "LDS too small");
-        float4* xch = reinterpret_cast<float4*>(lds) + (size_t)wmn * TN * 4 * 64 + lane;
-        float* xcs = reinterpret_cast<float*>(reinterpret_cast<float4*>(lds) + (size_t)WGM * WGN * TN * 4 * 64) + wn0;
-        if (wk == 1) {
+        // The wavefronts of a block hold partial sums of it, one per k slice; there is one band of rows only: the first wavefront adds what
+        // the others hand over through LDS, in their order, and finishes it.
+        static_assert(sizeof(lds) >= (size_t)WGM * WGN * (WGK - 1) * TN * 4 * 64 * sizeof(float4) + (WGK - 1) * BN * sizeof(float), "LDS too small");
+        constexpr int PER_WAVE = TN * 4 * 64;
+        float4* xch = reinterpret_cast<float4*>(lds) + (size_t)wmn * PER_WAVE + lane;
+        float* xcs = reinterpret_cast<float*>(reinterpret_cast<float4*>(lds) + (size_t)WGM * WGN * (WGK - 1) * PER_WAVE) + wn0;
+        if (wk > 0) {
             if constexpr (ONLY_EPI == EPI_ACCUM_F32)
                 if (col_sums && lane < 32)
 #pragma unroll
-                    for (int b = 0; b < TN; ++b) xcs[b * 32 + lane] = cs[b][0];
+                    for (int b = 0; b < TN; ++b) xcs[(wk - 1) * BN + b * 32 + lane] = cs[b][0];
 #pragma unroll
             for (int b = 0; b < TN; ++b)
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    xch[(b * 4 + q) * 64] = make_float4(acc[0][b][4 * q], acc[0][b][4 * q + 1], acc[0][b][4 * q + 2], acc[0][b][4 * q + 3]);
+                    xch[(size_t)(wk - 1) * WGM * WGN * PER_WAVE + (b * 4 + q) * 64] = make_float4(acc[0][b][4 * q], acc[0][b][4 * q + 1], acc[0][b][4 * q + 2], acc[0][b][4 * q + 3]);
         }
         __syncthreads();
         if (wk == 0) {
 #pragma unroll
-            for (int b = 0; b < TN; ++b)
+            for (int w = 0; w < WGK - 1; ++w)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float4 v = xch[(b * 4 + q) * 64];
-                    acc[0][b][4 * q] += v.x; acc[0][b][4 * q + 1] += v.y; acc[0][b][4 * q + 2] += v.z; acc[0][b][4 * q + 3] += v.w;
-                }
+                for (int b = 0; b < TN; ++b)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const float4 v = xch[(size_t)w * WGM * WGN * PER_WAVE + (b * 4 + q) * 64];
+                        acc[0][b][4 * q] += v.x; acc[0][b][4 * q + 1] += v.y; acc[0][b][4 * q + 2] += v.z; acc[0][b][4 * q + 3] += v.w;
+                    }
             if constexpr (ONLY_EPI == EPI_ACCUM_F32)
                 if (col_sums) {
                     float v[TN];
 #pragma unroll
-                    for (int b = 0; b < TN; ++b) v[b] = cs[b][0] + (lane < 32 ? xcs[b * 32 + lane] : 0.f);
+                    for (int b = 0; b < TN; ++b) {
+                        v[b] = cs[b][0];
+#pragma unroll
+                        for (int w = 0; w < WGK - 1; ++w) v[b] += lane < 32 ? xcs[w * BN + b * 32 + lane] : 0.f;
+                    }
                     put_col_sums(v);
                 }
         }
@@ -1471,6 +1479,21 @@ bool far_operand(const GemmArgs& g) {
 // 632 x 4800 x 1600 (190, 750) 17.7 -> 23.9, 1264 x 2400 x 6400 (190, 760) 60.6 -> 82.9.
 bool small_tiles(long tiles64) { return tiles64 <= 2 * NUM_CUS && tuning().async_mode == ASYNC_AUTO; }
 
+// The tile of such a product: the largest with which it still has a tile for every CU or nearly so.  A CU takes 60 to 90 bytes a
+// nanosecond, so what bounds a small output's k loop is what its few workgroups have to read, (bm + bn) a step each; once
+// the chip is full a larger tile reads less in all.  Measured, 64x64 -> 32x32: 256 x 256 x 256 3.74 -> 3.30 us, x 1024 5.5 -> 3.9,
+// 400 x 320 x 1280 6.2 -> 4.2, 128 x 1600 x 6400 (200 tiles) 20.1 -> 11.8, 512 x 512 x 2048 (256) 8.2 -> 5.0; 32x64: 1024 x 512 x 2048
+// (256) 8.8 -> 7.1 (32x32 8.4), 333 x 776 x 3104 13.7 -> 10.9 (12.4), 400 x 960 x 320 3.9 -> 3.7 (4.0).
+// 64x64, two per CU -> 128x64: 1264 x 1600 x 6400 (250) 46.7 -> 39.5, x 1600 13.9 -> 12.1, 1024 x 2048 x 2048 (256) 16.6 -> 14.2,
+// 2048 x 768 x 3072 21.5 -> 17.2, 512 x 3072 x 1024 10.7 -> 9.3; beside another stage 10.6 -> 11.1 each at k = 1600, 13.3 -> 12.6 at 2048.
+TileChoice small_tile(const GemmArgs& g) {
+    auto fits = [&](int bm, int bn) { return (long)((g.m + bm - 1) / bm) * ((g.n + bn - 1) / bn) <= NUM_CUS; };
+    if (fits(32, 32)) return {32, 32, 1};
+    if (fits(32, 64)) return {32, 64, 1};
+    if (!fits(64, 64) && fits(128, 64) && (!g.beside || g.k >= 2048)) return {128, 64, 1};
+    return {64, 64, 1};
+}
+
 // 256x128 tiles for a product that shares the chip with another stage's: it should then take little of the
 // chip's time, not little time.  Alone it is slower than 128x128, whose tiles are twice as many (4096 x 1024 x
 // 4096 40 -> 56 us, 2048 x 1600 x 6400 57 -> 82), but it spends a third fewer CU-microseconds, a quarter less
@@ -1508,7 +1531,7 @@ TileChoice choose_tile(const GemmArgs& g) {
     // (measured at 2048 x 4800 x 1600: 152 tiles of 256x256 on 256 CUs take 42 us, 608 of 128x128 48 us)
     if (t256 >= 144) return {256, 256, 1};
     if (wide_tiles(g)) return {256, 128, 1};
-    if (small_tiles((long)((g.m + 63) / 64) * ((g.n + 63) / 64))) return {64, 64, 1};
+    if (small_tiles((long)((g.m + 63) / 64) * ((g.n + 63) / 64))) return small_tile(g);
     return {128, 128, 1};
 }
 
@@ -1629,7 +1652,7 @@ int gemm_mfma_bf16(const GemmArgs& g, void* stream) {
     hipStream_t s = (hipStream_t)stream;
     const bool far = far_operand(g);
     TileChoice t = choose_tile(g);
-    if (far && (t.bm == 64 || t.bm != t.bn)) t = {128, 128, 1};
+    if (far && (t.bm < 128 || t.bm != t.bn)) t = {128, 128, 1};
     if (t.splits > 1 && (size_t)((g.m + 255) / 256) * ((g.n + 255) / 256) * sizeof(unsigned) > SPLITK_COUNTER_BYTES)
         return fail(CHIMERA_EINVAL, "too many tiles for split-K");
     // 128x128 tiles: with one workgroup per CU, a workgroup of 4 wavefronts leaves one wavefront
@@ -1674,6 +1697,8 @@ int gemm_mfma_bf16(const GemmArgs& g, void* stream) {
             return launch_ring<256, 256, 2, 4, 1>(g, s);
         }
         if (t.bm == 256) return launch_ring<256, 128, 2, 2, 2>(g, s);
+        if (t.bm == 128 && t.bn == 64) return launch_async<128, 64, 2, 2, 2, 6, 2>(g, s);
+        if (t.bm == 32) return t.bn == 32 ? launch_async<32, 32, 1, 1, 4, 8, 2>(g, s) : launch_async<32, 64, 1, 2, 2, 8, 2>(g, s);
         if (t.bm == 64) {
             // one tile per CU at most: all of LDS for one workgroup, an eight-stage ring walked two stages per
             // barrier by two wavefronts per SIMD (256 x 256 x 1024: 6.7 -> 6.1 us; 632 x 1600 x 6400: 28.4 -> 25.4)
