@@ -1486,7 +1486,9 @@ bool small_tiles(long tiles64) { return tiles64 <= 2 * NUM_CUS && tuning().async
 // (256) 8.8 -> 7.1 (32x32 8.4), 333 x 776 x 3104 13.7 -> 10.9 (12.4), 400 x 960 x 320 3.9 -> 3.7 (4.0).
 // 64x64, two per CU -> 128x64: 1264 x 1600 x 6400 (250) 46.7 -> 39.5, x 1600 13.9 -> 12.1, 1024 x 2048 x 2048 (256) 16.6 -> 14.2,
 // 2048 x 768 x 3072 21.5 -> 17.2, 512 x 3072 x 1024 10.7 -> 9.3; beside another stage 10.6 -> 11.1 each at k = 1600, 13.3 -> 12.6 at 2048.
+// (Weight gradients stay on 64x64 tiles, so that one alone has the bits of one in a group.)
 TileChoice small_tile(const GemmArgs& g) {
+    if (!g.a_kc) return {64, 64, 1};
     auto fits = [&](int bm, int bn) { return (long)((g.m + bm - 1) / bm) * ((g.n + bn - 1) / bn) <= NUM_CUS; };
     if (fits(32, 32)) return {32, 32, 1};
     if (fits(32, 64)) return {32, 64, 1};
@@ -1566,7 +1568,8 @@ int launch_async(const GemmArgs& g, hipStream_t s) {
                        (g.r_f32 ? 1 : 0) | (g.c_f32 ? 2 : 0), tm, tn, gm, ahead_of(g))
     if (g.a_kc && !g.b_kc) CHIMERA_GEMM_LAUNCH(true, false);
     else if (g.a_kc && g.b_kc) CHIMERA_GEMM_LAUNCH(true, true);
-    else CHIMERA_GEMM_LAUNCH(false, false);
+    else if constexpr (BM == 64 && BN == 64) CHIMERA_GEMM_LAUNCH(false, false);
+    else return fail(CHIMERA_EINVAL, "no %dx%d tile for weight gradients", BM, BN);
 #undef CHIMERA_GEMM_LAUNCH
     CHIMERA_LAUNCH_CHECK("bf16 gemm (async)");
     return CHIMERA_OK;

@@ -479,3 +479,31 @@ def test_worker_replays_from_graphs(dtype, hidden, heads, seq, mb):
     for stages, _ in workers:
         for st in stages:
             st.close()
+
+
+# bf16 products on 32x32, 32x64 and 128x64 tiles: a single row or tile, the last and first sizes of each form (256 tiles), k below one step,
+# with a remainder, and around the lengths of the rings
+@pytest.mark.parametrize("m,n,k", [(1, 8, 8), (32, 32, 64), (33, 40, 520), (512, 512, 72), (512, 520, 584), (100, 1600, 1032),
+                                   (1024, 512, 448), (1000, 520, 200), (1264, 1600, 136), (2048, 1024, 456), (2040, 1032, 328), (1100, 1800, 392)])
+@pytest.mark.parametrize("layout", ["fwd", "dgrad"])
+def test_bf16_small_output_tiles(m, n, k, layout):
+    test_bf16_small_gemm(m, n, k, layout)
+
+
+# ... with every epilogue, ragged rows and columns
+@pytest.mark.parametrize("m,n,k", [(45, 72, 200), (333, 776, 136), (1100, 1448, 192)])
+def test_bf16_small_output_epilogues(m, n, k):
+    import torch
+    print("bf16 gemm epilogues", m, n, k, flush=True)
+    A, B, bias, R = _rand((m, k), 1, b.BF16), _rand((k, n), 2, b.BF16, 0.05), _rand((n,), 3, b.BF16), _rand((m, n), 4, b.BF16)
+    z = A.astype(np.float64) @ B.astype(np.float64)
+    gelu = lambda u: 0.5 * u * (1 + np.tanh(np.sqrt(2 / np.pi) * (u + 0.044715 * u ** 3)))
+    dgelu = lambda u: (gelu(u + 1e-5) - gelu(u - 1e-5)) / 2e-5
+    dA, dB, dBT, dbias, dR = (to_dev(t, b.BF16) for t in (A, B, B.T, bias, R))
+    c, c2 = torch.empty((m, n), device="cuda", dtype=torch.bfloat16), torch.empty((m, n), device="cuda", dtype=torch.bfloat16)
+    for epi, b_kc, want in ((b.EPI_BIAS, 0, z + bias), (b.EPI_BIAS_GELU, 0, z + bias), (b.EPI_BIAS_RESIDUAL, 0, z + bias + R),
+                            (b.EPI_DGELU, 1, z * dgelu(R.astype(np.float64)))):
+        b.chimera_op_gemm(dA, dBT if b_kc else dB, c, m, n, k, 1, b_kc, epi, dbias, dR, c2)
+        assert_close(to_np(c), want, b.BF16, "epilogue %d" % epi)
+        if epi == b.EPI_BIAS_GELU:
+            assert_close(to_np(c2), gelu(z + bias), b.BF16, "gelu")
