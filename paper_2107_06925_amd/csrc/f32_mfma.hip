@@ -9,13 +9,14 @@
 // k-contiguous operand then delivers four instructions' values with one 16-byte read; an operand
 // whose other index is contiguous delivers them as four 4-byte reads of 32 neighbouring values.
 //
-// Two forms:
+// Three forms:
 //  - tiles of 64x64, 8 wavefronts, k in steps of 32 through LDS.  A 64-clock instruction needs 8 bytes
 //    from LDS per lane at most, so LDS and L2 are far from their limits and the matrix pipes set the
 //    time, once the loads and LDS reads of the next steps are under way during the current one.
 //  - small outputs: one 32x32 tile per workgroup, the k range dealt over 4 or 8 wavefronts, operands
 //    straight from memory into registers, one exchange in LDS at the end.  Such a product is bound
-//    by its chain of latencies (launch, load, exchange, store), which this keeps to one of each.
+//    by its chain of latencies (launch, load, exchange, store), which this keeps to one of each;
+//  - the smallest outputs: the same with 16x16 tiles, which four times as many CUs read the operands of.
 #include "device.h"
 
 #include <algorithm>
@@ -74,6 +75,36 @@ __device__ __forceinline__ void finish(const F32Product& p, int flag, int row, i
         if constexpr (EPI == EPI_BIAS_GELU) p.c2[idx + e] = w[e];
     }
 }
+
+// The same for four columns whose other operands are asked for before the k loop: a round trip less at the end of a short launch.
+struct F32Ahead {
+    f32x4 bias, r;
+    template <int EPI> __device__ __forceinline__ void request(const F32Product& p, int flag, int row, int col) {
+        const size_t idx = (size_t)row * p.n + col;
+        // n is a multiple of 4, but C, R and the bias need not be aligned to 16 bytes
+        typedef f32x4 __attribute__((aligned(4))) f32x4_u;
+        if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU || EPI == EPI_BIAS_RESIDUAL) bias = *reinterpret_cast<const f32x4_u*>(p.bias + col);
+        if constexpr (EPI == EPI_BIAS_RESIDUAL || EPI == EPI_DGELU) r = *reinterpret_cast<const f32x4_u*>(p.r + idx);
+        if constexpr (EPI == EPI_ACCUM_F32) { r = f32x4{0.f, 0.f, 0.f, 0.f}; if (!flag) r = *reinterpret_cast<const f32x4_u*>(p.c + idx); }
+    }
+    template <int EPI> __device__ __forceinline__ void finish(const F32Product& p, int flag, int row, int col, const f32x4& acc) const {
+        const size_t idx = (size_t)row * p.n + col;
+        float v[4], w[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            v[e] = acc[e];
+            if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU || EPI == EPI_BIAS_RESIDUAL) v[e] += bias[e];
+            if constexpr (EPI == EPI_BIAS_RESIDUAL || EPI == EPI_ACCUM_F32) v[e] += r[e];
+            if constexpr (EPI == EPI_BIAS_GELU) w[e] = gelu_f(v[e], flag);
+            if constexpr (EPI == EPI_DGELU) v[e] *= gelu_grad_f(r[e], flag);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            p.c[idx + e] = v[e];
+            if constexpr (EPI == EPI_BIAS_GELU) p.c2[idx + e] = w[e];
+        }
+    }
+};
 
 // ------------------------------------------------------------------ tile form
 // LDS layout of an operand tile of ROWS rows: [ROWS][BK + 4] (k-contiguous) or [BK][ROWS + 8].  Both
@@ -335,7 +366,78 @@ __global__ __launch_bounds__(NW* WAVE) void gemm_f32_small_kernel(F32Launch L) {
     }
 }
 
-enum Form { TILE64, SMALL };
+// The smallest outputs: one 16x16 tile per workgroup on v_mfma_f32_16x16x4_f32 (lane group l/16 holds contraction values
+// 4(l/16)..+3 of a group of 16, instruction j the j-th of each), k dealt over the wavefronts 32 at a time, operands straight
+// from memory.  What such a launch waits for is what one CU reads (60 to 90 bytes a nanosecond) and a wavefront's chain of matrix
+// instructions: both are half, or a quarter, of a 32x32 tile's.
+template <int NW, bool A_KC, bool B_KC, int EPI>
+__global__ __launch_bounds__(NW* WAVE) void gemm_f32_tiny_kernel(F32Launch L) {
+    __shared__ __attribute__((aligned(16))) float red[NW][16 * 16];
+    int tile_m, tile_n;
+    const F32Product& p = tile_of(L, tile_m, tile_n);
+    const int m = p.m, n = p.n, K = p.k, lda = p.lda, ldb = p.ldb;
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row = min(tile_m * 16 + l16, m - 1), col = min(tile_n * 16 + l16, n - 1);
+    // thread t finishes four columns of one row
+    const int orow = tile_m * 16 + (tid >> 2), ocol = tile_n * 16 + (tid & 3) * 4;
+    const bool finishes = tid < 64 && orow < m && ocol < n;
+    F32Ahead ahead;
+    if (finishes) ahead.request<EPI>(p, L.flag, orow, ocol);
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    f32x4 fa[2][2], fb[2][2];
+    // values 16 i + 4 g .. + 3 of 32 from k0 on (beyond K: the last ones, masked later)
+    auto load = [&](f32x4 (&v)[2], const float* __restrict__ base, bool kc, int ld, int r, int k0) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int k = k0 + 16 * i + 4 * g;
+            if (kc) v[i] = *reinterpret_cast<const f32x4*>(base + (size_t)r * ld + min(k, K - 4));
+            else
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[i][j] = base[(size_t)min(k + j, K - 1) * ld + r];
+        }
+    };
+    auto fetch = [&](int s, int k0) { load(fa[s], p.a, A_KC, lda, row, k0); load(fb[s], p.b, B_KC, ldb, col, k0); };
+    auto work = [&](int s, int k0) {
+        if (k0 + 32 > K)                                          // uniform: the last slice only
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (k0 + 16 * i + 4 * g + j >= K) { fa[s][i][j] = 0.f; fb[s][i][j] = 0.f; }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[s][i][j], fb[s][i][j], acc, 0, 0, 0);
+    };
+    const int k_first = wave * 32, k_step = NW * 32;
+    if (k_first < K) {
+        fetch(0, k_first);
+        for (int k0 = k_first; k0 < K; k0 += 2 * k_step) {
+            if (k0 + k_step < K) fetch(1, k0 + k_step);
+            work(0, k0);
+            if (k0 + k_step >= K) break;
+            if (k0 + 2 * k_step < K) fetch(0, k0 + 2 * k_step);
+            work(1, k0 + k_step);
+        }
+    }
+    // partial tiles meet in LDS, added in wavefront order
+#pragma unroll
+    for (int r = 0; r < 4; ++r) red[wave][(4 * g + r) * 16 + l16] = acc[r];
+    __syncthreads();
+    if (finishes) {
+        f32x4 s = *reinterpret_cast<const f32x4*>(&red[0][tid * 4]);
+#pragma unroll
+        for (int w = 1; w < NW; ++w) s += *reinterpret_cast<const f32x4*>(&red[w][tid * 4]);
+        ahead.finish<EPI>(p, L.flag, orow, ocol, s);
+    }
+}
+
+enum Form { TILE64, SMALL, TINY };
+
+// Up to two 16x16 tiles per CU take the tiny form.  32x32 -> 16x16: 128 x 384 x 128 3.2 -> 2.4 us, 128 x 128 x 512 (64 tiles) 5.8 -> 3.3 with
+// residual, 6.6 -> 3.9 A B^T, 256 x 256 x 1024 (256) 10.5 -> 5.7, 300 x 320 x 1280 (380) 12.6 -> 10.7, 512 x 256 x 256 (512) 4.2 -> 3.4,
+// x 1024 10.6 -> 9.2.
+constexpr long TINY_TILES = 2 * NUM_CUS;
 
 // Form of a launch.  Up to half a 64x64 tile per CU the small form's 32x32 tiles spread the work
 // further (512 x 1024 x 1024, 128 tiles: 20 against 23 us; 300 x 640 x 640, 50 tiles: 9.6 against 16);
@@ -348,9 +450,10 @@ Form choose_form(int count, const GemmArgs* g) {
     return t64 <= NUM_CUS / 2 ? SMALL : TILE64;
 }
 
+
 template <bool A_KC, bool B_KC, int EPI>
 void launch_form(F32Launch& L, Form form, hipStream_t s) {
-    const int tile = form == TILE64 ? 64 : 32;
+    const int tile = form == TILE64 ? 64 : form == SMALL ? 32 : 16;
     L.total = 0;
     int kmax = 0;
     for (int i = 0; i < L.count; ++i) {
@@ -363,7 +466,12 @@ void launch_form(F32Launch& L, Form form, hipStream_t s) {
     }
     const dim3 grid(L.total);
     if (form == TILE64) hipLaunchKernelGGL((gemm_f32_tile_kernel<A_KC, B_KC, EPI>), grid, dim3(8 * WAVE), 0, s, L);
-    else if (kmax <= 256) hipLaunchKernelGGL((gemm_f32_small_kernel<4, A_KC, B_KC, EPI>), grid, dim3(4 * WAVE), 0, s, L);
+    else if (form == TINY) {
+        if constexpr (A_KC) {                                     // (weight gradients go in groups, which are larger)
+            if (kmax <= 128) hipLaunchKernelGGL((gemm_f32_tiny_kernel<4, A_KC, B_KC, EPI>), grid, dim3(4 * WAVE), 0, s, L);
+            else hipLaunchKernelGGL((gemm_f32_tiny_kernel<8, A_KC, B_KC, EPI>), grid, dim3(8 * WAVE), 0, s, L);
+        }
+    } else if (kmax <= 256) hipLaunchKernelGGL((gemm_f32_small_kernel<4, A_KC, B_KC, EPI>), grid, dim3(4 * WAVE), 0, s, L);
     else hipLaunchKernelGGL((gemm_f32_small_kernel<8, A_KC, B_KC, EPI>), grid, dim3(8 * WAVE), 0, s, L);
 }
 
@@ -407,7 +515,8 @@ int gemm_f32(const GemmArgs& g, void* stream) {
     F32Launch L{};
     L.count = 1; L.epi = g.epilogue; L.flag = g.epilogue == EPI_ACCUM_F32 ? 0 : g.gelu_erf;
     L.p[0] = product_of(g);
-    const Form form = choose_form(1, &g);
+    Form form = choose_form(1, &g);
+    if (g.a_kc && (long)((g.m + 15) / 16) * ((g.n + 15) / 16) <= TINY_TILES) form = TINY;
     hipStream_t s = (hipStream_t)stream;
     if (!g.a_kc) return launch_epi<false, false>(L, form, s);
     return g.b_kc ? launch_epi<true, true>(L, form, s) : launch_epi<true, false>(L, form, s);

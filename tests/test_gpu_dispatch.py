@@ -507,3 +507,26 @@ def test_bf16_small_output_epilogues(m, n, k):
         assert_close(to_np(c), want, b.BF16, "epilogue %d" % epi)
         if epi == b.EPI_BIAS_GELU:
             assert_close(to_np(c2), gelu(z + bias), b.BF16, "gelu")
+
+
+# float products on 16x16 tiles: one row, edges of tiles, the last size of the form (512 tiles) and the first beyond it, k below a slice, with a
+# remainder, and around the turns of 4 and 8 wavefronts; every epilogue, results and residual at an odd offset
+@pytest.mark.parametrize("m,n,k", [(1, 8, 8), (16, 16, 32), (17, 24, 40), (250, 128, 128), (33, 40, 136), (256, 256, 264),
+                                   (512, 256, 520), (513, 256, 104), (72, 1816, 296)])
+def test_float_smallest_outputs(m, n, k):
+    import torch
+    print("float gemm smallest", m, n, k, flush=True)
+    A, B, bias, R = _rand((m, k), 1, b.F32), _rand((k, n), 2, b.F32, 0.05), _rand((n,), 3, b.F32), _rand((m, n), 4, b.F32)
+    z = A.astype(np.float64) @ B.astype(np.float64)
+    gelu = lambda u: 0.5 * u * (1 + np.tanh(np.sqrt(2 / np.pi) * (u + 0.044715 * u ** 3)))
+    dgelu = lambda u: (gelu(u + 1e-5) - gelu(u - 1e-5)) / 2e-5
+    odd = lambda a: torch.from_numpy(np.concatenate([[0.0], a.ravel()]).astype(np.float32)).cuda()[1:].view(a.shape)
+    dA, dB, dBT, dbias, dR = to_dev(A, b.F32), to_dev(B, b.F32), to_dev(np.ascontiguousarray(B.T), b.F32), odd(bias), odd(R)
+    for epi, b_kc, want in ((b.EPI_NONE, 1, z), (b.EPI_NONE, 0, z), (b.EPI_BIAS, 0, z + bias), (b.EPI_BIAS_GELU, 0, z + bias),
+                            (b.EPI_BIAS_RESIDUAL, 0, z + bias + R), (b.EPI_DGELU, 1, z * dgelu(R.astype(np.float64)))):
+        c, c2 = odd(np.zeros((m, n))), odd(np.zeros((m, n)))
+        b.chimera_op_gemm(dA, dBT if b_kc else dB, c, m, n, k, 1, b_kc, epi, dbias, dR, c2)
+        # sums of k float products of size 0.05: well below 1e-5 of the largest
+        assert np.max(np.abs(to_np(c) - want)) <= 1e-5 * np.max(np.abs(want)), "epilogue %d" % epi
+        if epi == b.EPI_BIAS_GELU:
+            assert_close(to_np(c2), gelu(z + bias), b.F32, "gelu")
