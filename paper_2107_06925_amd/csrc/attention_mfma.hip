@@ -102,6 +102,11 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& v, int first) {
 }
 
 __device__ __forceinline__ float xor32(float v) { return __shfl_xor(v, 32, WAVE); }
+// maximum over lanes l and l ^ 32 without a trip through LDS
+__device__ __forceinline__ float max32(float v) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
 
 // ------------------------------------------------------------------- forward
 // Which 128-row tile (by rank: 0 = the one with the most work under the causal mask), head and
@@ -137,6 +142,15 @@ inline unsigned attn_grid(const AttnArgs& a) {
 // (contraction over the head dimension), V with the transposing read (contraction over keys).
 // Rows beyond the sequence are fetched from its last row (finite data): their scores are
 // masked, so they contribute exact zeros.
+//
+// A step is a serial chain per wavefront (scores, row maximum, exponentials, P V) with four
+// wavefronts per SIMD at most (two at head dim 128) to cover it, so its length bounds the kernel.
+// The two halves of a row's keys lie in lanes l and l ^ 32: their maxima meet through max32 (a
+// register swap, where a lane exchange through LDS waits for the LDS queue), and each half's sum
+// stays in its lane until the keys are done (both halves rescale by the same factor).  Measured
+// against two LDS exchanges per step: 2 x 1024 rows of 25 heads of 64 causal 19.8 -> 17.9 us, 632
+// rows 12.3 -> 11.3 us, 2048 rows of 16 heads of 128 45.0 -> 41.8 us, 8 x 512 rows of 16 heads of
+// 64 15.8 -> 15.3 us.
 template <int D, bool CAUSAL>
 __global__ __launch_bounds__(NT) void attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx,
                                                       float* __restrict__ lse, int S, int heads, int batch,
@@ -171,7 +185,7 @@ __global__ __launch_bounds__(NT) void attn_fwd_kernel(const bf16_t* __restrict__
     for (int t = 0; t < OT; ++t)
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[t][r] = 0.f;
-    float m = NEG_BIG, lsum = 0.f;
+    float m = NEG_BIG, lsum = 0.f;          // lsum: over this lane's half of the keys
 
     // one step of the key loop; the LDS buffer index is a compile-time constant so that every LDS
     // address is the lane's base plus an immediate
@@ -213,8 +227,7 @@ __global__ __launch_bounds__(NT) void attn_fwd_kernel(const bf16_t* __restrict__
             for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kt][r]);
-            mx = fmaxf(mx, xor32(mx)) * scale_log2e;
-            const float m_new = fmaxf(m, mx);
+            const float m_new = fmaxf(m, max32(mx) * scale_log2e);
             float rs = 0.f;
 #pragma unroll
             for (int kt = 0; kt < 2; ++kt)
@@ -225,7 +238,6 @@ __global__ __launch_bounds__(NT) void attn_fwd_kernel(const bf16_t* __restrict__
                     s[kt][r] = p;
                     rs += p;
                 }
-            rs += xor32(rs);
             // the accumulators only need rescaling when some row's maximum moved
             if (__builtin_amdgcn_ballot_w64(m_new != m)) {
                 const float alpha = __builtin_amdgcn_exp2f(m - m_new);
@@ -251,6 +263,7 @@ __global__ __launch_bounds__(NT) void attn_fwd_kernel(const bf16_t* __restrict__
         if (t + 1 < ntiles) step(t + 1, std::integral_constant<int, 1>{});
     }
 
+    lsum += xor32(lsum);
     if (qrow < S) {
         const float inv = 1.0f / lsum;
         bf16_t* out = ctx + ((size_t)b * S + qrow) * H + h * d;
