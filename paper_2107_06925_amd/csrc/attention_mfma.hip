@@ -108,6 +108,12 @@ __device__ __forceinline__ float max32(float v) {
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
+// sum over four neighbouring lanes
+__device__ __forceinline__ float quad_sum(float v) {
+    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xb1, 0xf, 0xf, true));
+    return v + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4e, 0xf, 0xf, true));
+}
+
 // ------------------------------------------------------------------- forward
 // Which 128-row tile (by rank: 0 = the one with the most work under the causal mask), head and
 // sequence a workgroup of the 1-D grid takes; false for the padding workgroups.  Workgroup ids
@@ -295,9 +301,10 @@ template <int D> struct AttnBwdLds {
     float lse2[2][64], dl[2][64];
 };
 
-template <int D, bool CAUSAL>
+template <int D, bool CAUSAL, bool FORM_DELTA>
 __device__ __forceinline__ void attn_bwd_dkv_role(AttnBwdLds<D>& sm, int bid, const bf16_t* __restrict__ qkv,
-                                                  const bf16_t* __restrict__ dctx, const float* __restrict__ lse,
+                                                  const bf16_t* __restrict__ dctx, const bf16_t* __restrict__ ctx,
+                                                  const float* __restrict__ lse,
                                                   const float* __restrict__ delta, bf16_t* __restrict__ dqkv, int S,
                                                   int heads, int batch, int d, float scale) {
     constexpr int KS = D / 16, OT = D / 32;
@@ -322,13 +329,26 @@ __device__ __forceinline__ void attn_bwd_dkv_role(AttnBwdLds<D>& sm, int bid, co
     const int qt0 = CAUSAL ? j0 / 64 : 0;
     const int ntiles = (S + 63) / 64;
     float stat = 0.f;                      // lse (threads 0..63) or delta (threads 64..127) of the next tile
+    // FORM_DELTA: a query's delta comes from four neighbouring threads, each with a quarter of its row of dO and O
+    constexpr int DP = FORM_DELTA ? D / 32 : 1;
+    const int dq_row = tid >> 2, dq_col = (tid & 3) * (D / 4);
+    bf16x8 od[DP], oc[DP];
     auto fetch = [&](int t, int buf) {
         const int i0 = t * 64;
         dma_utile<D>(base, ld, i0, S - 1, d, qs0 + buf * TILE_BYTES, wave, lane);
         dma_utile<D>(dOg, H, i0, S - 1, d, os0 + buf * TILE_BYTES, wave, lane);
-        if (tid < 128) {
+        if (tid < (FORM_DELTA ? 64 : 128)) {
             const int i = i0 + (tid & 63);
             stat = i < S ? (tid < 64 ? lse[stat0 + i] * LOG2E : delta[stat0 + i]) : 0.f;
+        }
+        if constexpr (FORM_DELTA) {
+            const size_t at = (size_t)(i0 + dq_row) * H + dq_col;
+#pragma unroll
+            for (int j = 0; j < DP; ++j) {
+                const bool ok = i0 + dq_row < S && dq_col + 8 * j < d;
+                od[j] = load_frag(dOg + at + 8 * j, ok);
+                oc[j] = load_frag(ctx + ((size_t)b * S * H + h * d) + at + 8 * j, ok);
+            }
         }
     };
     fetch(qt0, 0);
@@ -350,7 +370,16 @@ __device__ __forceinline__ void attn_bwd_dkv_role(AttnBwdLds<D>& sm, int bid, co
         const int i0 = t * 64;
         wait_vmcnt<0>();                   // this wavefront's share of tile t (and its statistics) has arrived
         if (tid < 64) lse2[buf][tid] = stat;
-        else if (tid < 128) dl[buf][tid - 64] = stat;
+        else if (!FORM_DELTA && tid < 128) dl[buf][tid - 64] = stat;
+        if constexpr (FORM_DELTA) {
+            float v = 0.f;
+#pragma unroll
+            for (int j = 0; j < DP; ++j)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v += (float)od[j][e] * (float)oc[j][e];
+            v = quad_sum(v);
+            if ((tid & 3) == 0) dl[buf][dq_row] = v;
+        }
         __syncthreads();                   // tile t complete in LDS; tile t-1 consumed by everyone
         if (t + 1 < ntiles) fetch(t + 1, buf ^ 1);
         const bf16_t* Qt = Qs[buf];
@@ -575,18 +604,18 @@ __global__ __launch_bounds__(NT) void attn_delta_kernel(const bf16_t* __restrict
 // Both backward kernels in one launch: workgroups come in groups of 8 (one per XCD), the groups
 // alternate between the dK/dV role and the dQ role, and a workgroup's number within its role keeps
 // its id mod 8, so that a (sequence, head) pair's tiles of both roles meet in one L2.  The two
-// roles are independent (delta comes from attn_delta_kernel), so with few pairs - where one role
-// alone leaves the chip half empty and its longest causal tile sets the time - each fills the
-// other's gaps.
-template <int D, bool CAUSAL>
+// roles are independent (delta comes from attn_delta_kernel, or with FORM_DELTA each forms its
+// own), so with few pairs - where one role alone leaves the chip half empty and its longest causal
+// tile sets the time - each fills the other's gaps.
+template <int D, bool CAUSAL, bool FORM_DELTA>
 __global__ __launch_bounds__(NT) void attn_bwd_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx,
-                                                      const float* __restrict__ lse, const float* __restrict__ delta,
+                                                      const bf16_t* __restrict__ ctx, const float* __restrict__ lse, float* __restrict__ delta,
                                                       bf16_t* __restrict__ dqkv, int S, int heads, int batch, int d, float scale) {
     __shared__ __attribute__((aligned(16))) AttnBwdLds<D> sm;
     const int blk = (int)blockIdx.x;
     const int role = (blk >> 3) & 1, bid = ((blk >> 4) << 3) | (blk & 7);
-    if (role == 0) attn_bwd_dkv_role<D, CAUSAL>(sm, bid, qkv, dctx, lse, delta, dqkv, S, heads, batch, d, scale);
-    else attn_bwd_dq_role<D, CAUSAL, false>(sm, bid, qkv, dctx, nullptr, lse, const_cast<float*>(delta), dqkv, S, heads, batch, d, scale);
+    if (role == 0) attn_bwd_dkv_role<D, CAUSAL, FORM_DELTA>(sm, bid, qkv, dctx, ctx, lse, delta, dqkv, S, heads, batch, d, scale);
+    else attn_bwd_dq_role<D, CAUSAL, FORM_DELTA>(sm, bid, qkv, dctx, ctx, lse, delta, dqkv, S, heads, batch, d, scale);
 }
 
 // The roles as launches of their own, dQ first (it forms delta): for many pairs, where each role
@@ -606,7 +635,7 @@ __global__ __launch_bounds__(NT) void attn_bwd_dkv_kernel(const bf16_t* __restri
                                                           bf16_t* __restrict__ dqkv, int S, int heads, int batch, int d,
                                                           float scale) {
     __shared__ __attribute__((aligned(16))) AttnBwdLds<D> sm;
-    attn_bwd_dkv_role<D, CAUSAL>(sm, (int)blockIdx.x, qkv, dctx, lse, delta, dqkv, S, heads, batch, d, scale);
+    attn_bwd_dkv_role<D, CAUSAL, false>(sm, (int)blockIdx.x, qkv, dctx, nullptr, lse, delta, dqkv, S, heads, batch, d, scale);
 }
 
 // ctx in the forward (which has no dctx), ctx, dctx and dqkv in the backward
@@ -659,13 +688,23 @@ int attention_bwd_mfma(const AttnArgs& a, void* stream) {
     // Few (sequence, head) pairs: one launch with both roles (measured: 448 workgroups per role
     // 58 -> 53 us, 256 per role at head dim 128 149 -> 119 us; 512 and more per role are faster apart).
     const bool merged = attn_grid(a) <= 480;
+    // With both roles in one launch the dK/dV role can form the deltas it needs itself, once per tile of keys, where
+    // attn_delta_kernel is a launch of its own and a wait for it.  That pays while the chip has room beside the
+    // workgroups (one per CU and role) and a query meets few tiles: head dim 64, 2 x 128 rows of 4 heads 9.6 -> 7.6 us,
+    // 2 x 200 of 5 12.9 -> 11.3, 2 x 632 of 25 (250 workgroups) 25.6 -> 24.1, 896 of 25 28.7 -> 28.2, but 3 x 768 of 16
+    // (288) 42.6 -> 43.5 and 2 x 1024 of 25 (448) 71.5 -> 76.2 with two such calls at a time.  At head dim 128, one
+    // wavefront per SIMD: 2 x 128 rows of 8 15.6 -> 14.2, 2 x 256 20.7 -> 19.7, but 2 x 512 32.0 -> 32.5 us.
+    const bool own = merged && (a.head_dim <= 64 ? attn_grid(a) <= 256 && a.seq <= 1024 : a.seq <= 256);
 #define ATTN_BWD(D, C)                                                                                              \
     do {                                                                                                            \
-        if (merged) {                                                                                               \
+        if (own) {                                                                                                  \
+            hipLaunchKernelGGL((attn_bwd_kernel<D, C, true>), grid2, block, 0, s, (const bf16_t*)a.qkv, (const bf16_t*)a.dctx, \
+                               (const bf16_t*)a.ctx, a.lse, a.delta, (bf16_t*)a.dqkv, a.seq, a.heads, a.batch, a.head_dim, scale); \
+        } else if (merged) {                                                                                        \
             hipLaunchKernelGGL((attn_delta_kernel<D>), dgrid, block, 0, s, (const bf16_t*)a.dctx, (const bf16_t*)a.ctx, \
                                a.delta, a.seq, a.heads, a.batch, a.head_dim);                                                   \
-            hipLaunchKernelGGL((attn_bwd_kernel<D, C>), grid2, block, 0, s, (const bf16_t*)a.qkv, (const bf16_t*)a.dctx, \
-                               a.lse, a.delta, (bf16_t*)a.dqkv, a.seq, a.heads, a.batch, a.head_dim, scale);                     \
+            hipLaunchKernelGGL((attn_bwd_kernel<D, C, false>), grid2, block, 0, s, (const bf16_t*)a.qkv, (const bf16_t*)a.dctx, \
+                               (const bf16_t*)a.ctx, a.lse, a.delta, (bf16_t*)a.dqkv, a.seq, a.heads, a.batch, a.head_dim, scale); \
         } else {                                                                                                    \
             hipLaunchKernelGGL((attn_bwd_dq_kernel<D, C>), grid, block, 0, s, (const bf16_t*)a.qkv, (const bf16_t*)a.dctx, \
                                (const bf16_t*)a.ctx, a.lse, a.delta, (bf16_t*)a.dqkv, a.seq, a.heads, a.batch, a.head_dim, scale); \

@@ -265,6 +265,15 @@ def test_bf16_attention_head_dims(batch, seq, heads, d, causal):
     _attention(b.BF16, batch, seq, heads, d, causal)
 
 
+# bf16 backward at both sides of the lines where the dK/dV role forms the row sums of dO * O itself: sequence lengths around its
+# 64-row tiles and the last served one, workgroups per role of 256 and the next, partly filled quarters of a row
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("batch,seq,heads,d", [(1, 1, 1, 64), (2, 63, 3, 24), (1, 129, 2, 64), (2, 191, 2, 56), (1, 1024, 2, 64), (1, 1025, 2, 64),
+                                               (8, 129, 16, 64), (8, 129, 17, 64), (1, 256, 3, 128), (1, 257, 3, 128), (2, 65, 3, 104)])
+def test_bf16_attention_row_sums(batch, seq, heads, d, causal):
+    _attention(b.BF16, batch, seq, heads, d, causal)
+
+
 # results and gradients at addresses that wide accesses cannot take: served at head dimensions other than 64 and 128, refused there
 @pytest.mark.parametrize("d,served", [(40, True), (96, True), (64, False), (128, False)])
 @pytest.mark.parametrize("shifted", ["ctx", "dctx", "dqkv"])
