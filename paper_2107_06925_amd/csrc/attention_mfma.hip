@@ -294,6 +294,11 @@ __global__ __launch_bounds__(NT) void attn_fwd_kernel(const bf16_t* __restrict__
 // work on the current one; each 32-query half of a tile is finished (scores to dK/dV) before
 // the next starts, which keeps the live score registers at 32.  Rows beyond the sequence
 // repeat its last row; their P is masked to zero.
+// The dP products start at -delta (its LDS copy is negated) where they started at zero: that
+// is the subtraction without an instruction per score, and at head dim 128, whose accumulators
+// and fragments exceed the 256 registers that vector instructions reach, fewer copies to the
+// others: both roles together 2048 rows of 16 heads of 128 causal 111.7 -> 98.4 us, 2 x 1024 of
+// 16 105.4 -> 94.1, 4 x 333 of 6 26.4 -> 24.1; 8 x 512 of 16 of 64 47.9 -> 47.2.
 // LDS of one backward workgroup: two tensors x two stages of [64][D] tiles, and (dK/dV role) the
 // statistics of a tile's 64 queries.
 template <int D> struct AttnBwdLds {
@@ -339,7 +344,7 @@ __device__ __forceinline__ void attn_bwd_dkv_role(AttnBwdLds<D>& sm, int bid, co
         dma_utile<D>(dOg, H, i0, S - 1, d, os0 + buf * TILE_BYTES, wave, lane);
         if (tid < (FORM_DELTA ? 64 : 128)) {
             const int i = i0 + (tid & 63);
-            stat = i < S ? (tid < 64 ? lse[stat0 + i] * LOG2E : delta[stat0 + i]) : 0.f;
+            stat = i < S ? (tid < 64 ? lse[stat0 + i] * LOG2E : -delta[stat0 + i]) : 0.f;
         }
         if constexpr (FORM_DELTA) {
             const size_t at = (size_t)(i0 + dq_row) * H + dq_col;
@@ -378,7 +383,7 @@ __device__ __forceinline__ void attn_bwd_dkv_role(AttnBwdLds<D>& sm, int bid, co
 #pragma unroll
                 for (int e = 0; e < 8; ++e) v += (float)od[j][e] * (float)oc[j][e];
             v = quad_sum(v);
-            if ((tid & 3) == 0) dl[buf][dq_row] = v;
+            if ((tid & 3) == 0) dl[buf][dq_row] = -v;
         }
         __syncthreads();                   // tile t complete in LDS; tile t-1 consumed by everyone
         if (t + 1 < ntiles) fetch(t + 1, buf ^ 1);
@@ -391,7 +396,12 @@ __device__ __forceinline__ void attn_bwd_dkv_role(AttnBwdLds<D>& sm, int bid, co
             for (int it = 0; it < 2; ++it) {
                 f32x16 p, dp;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) { p[r] = 0.f; dp[r] = 0.f; }
+                for (int r4 = 0; r4 < 4; ++r4) {                       // 4 consecutive queries; dP starts at -delta
+                    const float4 d4 = *reinterpret_cast<const float4*>(&dl[buf][it * 32 + 8 * r4 + 4 * g]);
+                    const float dv4[4] = {d4.x, d4.y, d4.z, d4.w};
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) { p[r4 * 4 + c] = 0.f; dp[r4 * 4 + c] = dv4[c]; }
+                }
 #pragma unroll
                 for (int kk = 0; kk < KS; ++kk) {
                     p = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_us<D>(Qt, it * 32 + l32, kk, g), kf[kk], p, 0, 0, 0);
@@ -401,13 +411,11 @@ __device__ __forceinline__ void attn_bwd_dkv_role(AttnBwdLds<D>& sm, int bid, co
                 for (int r4 = 0; r4 < 4; ++r4) {
                     const int il = it * 32 + 8 * r4 + 4 * g;       // 4 consecutive queries
                     const float4 l4 = *reinterpret_cast<const float4*>(&lse2[buf][il]);
-                    const float4 d4 = *reinterpret_cast<const float4*>(&dl[buf][il]);
-                    const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dv4[4] = {d4.x, d4.y, d4.z, d4.w};
+                    const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
 #pragma unroll
                     for (int c = 0; c < 4; ++c) {
                         const int r = r4 * 4 + c;
                         p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(p[r], c2, -lv[c]));     // hardware exp2
-                        dp[r] -= dv4[c];
                     }
                 }
                 if (edge) {                               // wavefront-uniform: only tiles on an edge mask
@@ -531,8 +539,9 @@ __device__ __forceinline__ void attn_bwd_dq_role(AttnBwdLds<D>& sm, int bid, con
 #pragma unroll
             for (int kt = 0; kt < 2; ++kt) {
                 f32x16 p, dp;
+                // at head dim 64 sixteen registers of -delta cost the third wavefront per SIMD (170 for 152)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) { p[r] = 0.f; dp[r] = 0.f; }
+                for (int r = 0; r < 16; ++r) { p[r] = 0.f; dp[r] = D > 64 ? -my_dl : 0.f; }
 #pragma unroll
                 for (int kk = 0; kk < KS; ++kk) {
                     p = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_us<D>(Kt, kt * 32 + l32, kk, g), qf[kk], p, 0, 0, 0);
@@ -548,7 +557,7 @@ __device__ __forceinline__ void attn_bwd_dq_role(AttnBwdLds<D>& sm, int bid, con
                     }
                 }
 #pragma unroll
-                for (int r = 0; r < 16; ++r) dp[r] = p[r] * (dp[r] - my_dl);
+                for (int r = 0; r < 16; ++r) dp[r] = p[r] * (D > 64 ? dp[r] : dp[r] - my_dl);
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {
                     const bf16x8 dsf = pack8(dp, j * 8);
@@ -690,10 +699,11 @@ int attention_bwd_mfma(const AttnArgs& a, void* stream) {
     const bool merged = attn_grid(a) <= 480;
     // With both roles in one launch the dK/dV role can form the deltas it needs itself, once per tile of keys, where
     // attn_delta_kernel is a launch of its own and a wait for it.  That pays while the chip has room beside the
-    // workgroups (one per CU and role) and a query meets few tiles: head dim 64, 2 x 128 rows of 4 heads 9.6 -> 7.6 us,
-    // 2 x 200 of 5 12.9 -> 11.3, 2 x 632 of 25 (250 workgroups) 25.6 -> 24.1, 896 of 25 28.7 -> 28.2, but 3 x 768 of 16
-    // (288) 42.6 -> 43.5 and 2 x 1024 of 25 (448) 71.5 -> 76.2 with two such calls at a time.  At head dim 128, one
-    // wavefront per SIMD: 2 x 128 rows of 8 15.6 -> 14.2, 2 x 256 20.7 -> 19.7, but 2 x 512 32.0 -> 32.5 us.
+    // workgroups (one per CU and role) and a query meets few tiles: head dim 64, 2 x 128 rows of 4 heads 9.5 -> 7.6 us,
+    // 2 x 200 of 5 13.0 -> 11.3, 896 of 25 (224 workgroups) 28.7 -> 28.2, with two such calls at a time 37.4 -> 36.4;
+    // 2 x 632 of 25 (280) 26.6 -> 24.3 but 37.2 -> 38.8, 3 x 768 of 16 (288) 29.6 -> 28.1 but 41.4 -> 42.7, 2 x 1024 of
+    // 25 (448) 72.8 -> 75.7.  At head dim 128, one wavefront per SIMD: 2 x 128 rows of 8 14.7 -> 13.2, 2 x 256 19.1 -> 18.0,
+    // but 2 x 512 28.7 -> 29.4 us.
     const bool own = merged && (a.head_dim <= 64 ? attn_grid(a) <= 256 && a.seq <= 1024 : a.seq <= 256);
 #define ATTN_BWD(D, C)                                                                                              \
     do {                                                                                                            \
