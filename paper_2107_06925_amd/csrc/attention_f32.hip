@@ -171,7 +171,7 @@ __global__ __launch_bounds__(NT) void attn_fwd_f32_kernel(const float* __restric
         float mx = s[0];
 #pragma unroll
         for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
-        mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE)) * scale_log2e;
+        mx = max32(mx) * scale_log2e;
         const float m_new = fmaxf(m, mx), alpha = __builtin_amdgcn_exp2f(m - m_new);
         float rs = 0.f;
 #pragma unroll
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(NT) void attn_fwd_f32_kernel(const float* __restric
             s[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], scale_log2e, -m_new));
             rs += s[r];
         }
-        lsum = lsum * alpha + (rs + __shfl_xor(rs, 32, WAVE));
+        lsum = lsum * alpha + sum32(rs);
         m = m_new;
 #pragma unroll
         for (int t = 0; t < OT; ++t)
@@ -232,7 +232,7 @@ __device__ __forceinline__ void dq_role(float* lds, int bid, const float* __rest
     for (int i = 0; i < D / 8; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) delta += dO.v[i][j] * o.v[i][j];
-    delta += __shfl_xor(delta, 32, WAVE);
+    delta = sum32(delta);
     f32x16 dq[OT];
 #pragma unroll
     for (int t = 0; t < OT; ++t)
@@ -303,7 +303,7 @@ __device__ __forceinline__ void dkv_role(float* lds, int bid, const float* __res
         for (int i = 0; i < D / 8; ++i)
 #pragma unroll
             for (int j = 0; j < 4; ++j) delta += dO.v[i][j] * o.v[i][j];
-        delta += __shfl_xor(delta, 32, WAVE);
+        delta = sum32(delta);
         f32x16 p = dot_rows<D>(q, k), dp = dot_rows<D>(dO, v);
         const bool edge = i0 + TILE > S || (CAUSAL && i0 < j0 + TILE - 1);
 #pragma unroll

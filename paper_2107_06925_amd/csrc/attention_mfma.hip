@@ -101,17 +101,10 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& v, int first) {
     return o;
 }
 
-__device__ __forceinline__ float xor32(float v) { return __shfl_xor(v, 32, WAVE); }
-// maximum over lanes l and l ^ 32 without a trip through LDS
-__device__ __forceinline__ float max32(float v) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-
 // sum over four neighbouring lanes
 __device__ __forceinline__ float quad_sum(float v) {
-    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xb1, 0xf, 0xf, true));
-    return v + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4e, 0xf, 0xf, true));
+    v += dpp<0xb1>(v);
+    return v + dpp<0x4e>(v);
 }
 
 // ------------------------------------------------------------------- forward
@@ -269,7 +262,7 @@ __global__ __launch_bounds__(NT) void attn_fwd_kernel(const bf16_t* __restrict__
         if (t + 1 < ntiles) step(t + 1, std::integral_constant<int, 1>{});
     }
 
-    lsum += xor32(lsum);
+    lsum = sum32(lsum);
     if (qrow < S) {
         const float inv = 1.0f / lsum;
         bf16_t* out = ctx + ((size_t)b * S + qrow) * H + h * d;
@@ -514,7 +507,7 @@ __device__ __forceinline__ void attn_bwd_dq_role(AttnBwdLds<D>& sm, int bid, con
 #pragma unroll
             for (int e = 0; e < 8; ++e) my_dl += (float)of[kk][e] * (float)cf[e];
         }
-        my_dl += xor32(my_dl);
+        my_dl = sum32(my_dl);
         if (g == 0 && qrow < S) delta[stat0 + qrow] = my_dl;
     } else {
         my_dl = qrow < S ? delta[stat0 + qrow] : 0.f;

@@ -64,16 +64,30 @@ template <typename T, int V> __device__ __forceinline__ void store_elems(T* p, c
     for (int i = 0; i < V; i += PER) store_vec<T>(p + i, in + i);
 }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, WAVE);
-    return v;
+// f(v, v of lane l ^ o) in every lane for o = 32, and for o = 32, 16, 8, 4, 2, 1 in turn (a reduction over the wavefront),
+// without LDS: a swap of register halves or rows pairs lanes 32 and 16 apart, and once lanes 8 (4) apart agree, a rotation of
+// a row of sixteen by 8 (4) is the exchange.  Through LDS each exchange is a round trip, six in a chain per reduction: LayerNorm
+// forward of 256 x 256 bf16 2.37 -> 2.03 us, 1024 x 640 2.72 -> 2.38, 4096 x 1024 4.32 -> 4.10.  All lanes have to be active.
+template <typename F> __device__ __forceinline__ float fold32(float v, F f) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return f(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, WAVE));
-    return v;
+template <int CTRL> __device__ __forceinline__ float dpp(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
 }
+template <typename F> __device__ __forceinline__ float wave_fold(float v, F f) {
+    v = fold32(v, f);
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = f(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    v = f(v, dpp<0x128>(v));            // row_ror:8
+    v = f(v, dpp<0x124>(v));            // row_ror:4
+    v = f(v, dpp<0x4e>(v));             // quad_perm [2,3,0,1]
+    return f(v, dpp<0xb1>(v));          // quad_perm [1,0,3,2]
+}
+__device__ __forceinline__ float sum32(float v) { return fold32(v, [](float a, float b) { return a + b; }); }
+__device__ __forceinline__ float max32(float v) { return fold32(v, [](float a, float b) { return fmaxf(a, b); }); }
+__device__ __forceinline__ float wave_sum(float v) { return wave_fold(v, [](float a, float b) { return a + b; }); }
+__device__ __forceinline__ float wave_max(float v) { return wave_fold(v, [](float a, float b) { return fmaxf(a, b); }); }
 
 // GeLU, tanh form: 0.5 u (1 + tanh z), z = sqrt(2/pi) (u + 0.044715 u^3); erf form: u Phi(u).
 // 0.5 (1 + tanh z) is the logistic function of 2z, which needs one hardware exp2 and one

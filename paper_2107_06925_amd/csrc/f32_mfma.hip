@@ -247,7 +247,7 @@ __global__ __launch_bounds__(8 * WAVE) void gemm_f32_tile_kernel(F32Launch L) {
 #pragma unroll
         for (int r = 0; r < R; ++r) xch[(wave * R + r) * WAVE + lane] = wk ? acc[0][0][r] : acc[0][0][R + r];
         if (col_sums) {
-            cs[0] += __shfl_xor(cs[0], 32, WAVE);
+            cs[0] = sum32(cs[0]);
             if (wk && g == 0) xcs[wn0 + l32] = cs[0];
         }
         __syncthreads();
@@ -344,7 +344,7 @@ __global__ __launch_bounds__(NW* WAVE) void gemm_f32_small_kernel(F32Launch L) {
     const bool col_sums = EPI == EPI_ACCUM_F32 && p.bsum && tile_m == 0;
     if constexpr (EPI == EPI_ACCUM_F32)
         if (col_sums) {
-            cs += __shfl_xor(cs, 32, WAVE);
+            cs = sum32(cs);
             if (g == 0) red_cs[wave][l32] = cs;
         }
     __syncthreads();
