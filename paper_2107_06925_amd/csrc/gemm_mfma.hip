@@ -1486,13 +1486,18 @@ bool small_tiles(long tiles64) { return tiles64 <= 2 * NUM_CUS && tuning().async
 // (256) 8.8 -> 7.1 (32x32 8.4), 333 x 776 x 3104 13.7 -> 10.9 (12.4), 400 x 960 x 320 3.9 -> 3.7 (4.0).
 // 64x64, two per CU -> 128x64: 1264 x 1600 x 6400 (250) 46.7 -> 39.5, x 1600 13.9 -> 12.1, 1024 x 2048 x 2048 (256) 16.6 -> 14.2,
 // 2048 x 768 x 3072 21.5 -> 17.2, 512 x 3072 x 1024 10.7 -> 9.3; beside another stage 10.6 -> 11.1 each at k = 1600, 13.3 -> 12.6 at 2048.
+// Beside another stage the tiles below 64x64 may take half of the CUs: they read more in all, and what one stage's tiles take the
+// other's do without.  Replays of two stages with the limit at all CUs -> at half: two blocks of 512 at 1024 tokens 1409 -> 1371 us
+// (64x64 tiles throughout: 1398), of 512 at 512 1259 -> 1238, of 1024 at 128 1483 -> 1443 and at 256 1728 -> 1684, of 1600 at 128 2610 -> 2538; of 256 at
+// 256, whose products need 64 to 192 such tiles, 859 -> 857 (at three quarters of the CUs 853).
 // (Weight gradients stay on 64x64 tiles, so that one alone has the bits of one in a group.)
 TileChoice small_tile(const GemmArgs& g) {
     if (!g.a_kc) return {64, 64, 1};
-    auto fits = [&](int bm, int bn) { return (long)((g.m + bm - 1) / bm) * ((g.n + bn - 1) / bn) <= NUM_CUS; };
-    if (fits(32, 32)) return {32, 32, 1};
-    if (fits(32, 64)) return {32, 64, 1};
-    if (!fits(64, 64) && fits(128, 64) && (!g.beside || g.k >= 2048)) return {128, 64, 1};
+    auto fits = [&](int bm, int bn, int cus) { return (long)((g.m + bm - 1) / bm) * ((g.n + bn - 1) / bn) <= cus; };
+    const int few = g.beside ? NUM_CUS / 2 : NUM_CUS;
+    if (fits(32, 32, few)) return {32, 32, 1};
+    if (fits(32, 64, few)) return {32, 64, 1};
+    if (!fits(64, 64, NUM_CUS) && fits(128, 64, NUM_CUS) && (!g.beside || g.k >= 2048)) return {128, 64, 1};
     return {64, 64, 1};
 }
 
