@@ -44,16 +44,16 @@ __global__ __launch_bounds__(EDGE_THREADS) void embed_fwd_kernel(const int* __re
 //
 // Token table, dwte[v] += sum of dx[t] over the positions t with token v.  Workgroup w owns the
 // tokens v with v mod owners = w: every table row has one owner, so the sums need no atomics, and their
-// order is fixed by the positions alone.  Frequent tokens (more than EMB_HOT positions hold v mod EMB_BUCKETS) have owners of their
-// own: one CU reads some 64 bytes a nanosecond, and a frequent word's rows are many.  Workgroup (w, s) of those owns columns
-// [s, s + 1) * EMB_LANES * V of the frequent tokens with v mod hot_classes = w.  A workgroup
+// order is fixed by the positions alone.  Frequent tokens (more than embed_hot_from positions hold v mod EMB_BUCKETS)
+// have owners of their own: one CU reads some 64 bytes a nanosecond, and a frequent word's rows are many.  Workgroup (w, s) of those
+// owns columns [s, s + 1) * EMB_LANES * V of the frequent tokens with v mod hot_classes = w.  A workgroup
 //   1. lists its positions in ascending order (one ballot per 64 positions),
 //   2. finds the first entry of every distinct token in the list (a "head"),
 //   3. gives each head and 64 pieces of its row to one wavefront, which walks the list 64 entries at a time (ballot of
 //      "same token") and adds the rows in ascending order, several in flight;
 //   4. or, for frequent tokens, shares each among 32 groups of lanes, the k-th of which takes the k-th, (k + 32)-th, ...
 //      position; the partial rows are added in a fixed tree.
-// A list holds EMB_LIST entries; a workgroup that owns more positions goes through them EMB_LIST positions at a time.
+// A list holds EMB_LIST entries; a workgroup that owns more goes through the positions in windows that about fill it.
 // What bounds it is latency (list, row, table row: a few dependent round trips), so there are
 // enough workgroups that a wavefront seldom has more than one or two tokens.  (One workgroup per
 // position, each scanning all tokens through LDS, took 301 us at 4096 positions x 1024 columns.)  With frequent tokens shared by
@@ -62,9 +62,14 @@ __global__ __launch_bounds__(EDGE_THREADS) void embed_fwd_kernel(const int* __re
 // 73 -> 57, 1000 x 776 of 5000 11.7 -> 9.3; every second position the same token, 4096 x 1024, 179 -> 35.
 // owners: 1024 x 1024 and 512 x 512 of them at 2048 tokens of 1600 columns 14.5 -> 11.2 us, at 4096 x 1024 16.9 -> 18.4,
 // at 8192 x 512 25.8 -> 34.  Classes of frequent tokens: 16 -> 32 at 16384 x 2048 112 -> 89, at 4096 x 1024 (float) 18.7 -> 20.6.
+// Frequent beyond 16 positions and windows of EMB_LIST positions -> beyond one in 256, 16 to 32 at least, and full lists: uniform ids
+// 4096 x 1024 of 256 21.7 -> 11.5, 16384 x 1024 of 1000 77 -> 45, 262144 x 256 of 30000 8430 -> 577; logarithmic ids 32768 x 1024 of 50304
+// 344 -> 112, 131072 x 1024 2270 -> 530.  With one in 128 524288 x 512 takes 2610 us for 2100, with one in 512 131072 x 1024 593 for 530; with 32 for
+// 16 384 x 1024 of 2000 10.0 for 8.9, with 16 for 32 4096 x 256 of 2000 16.6 for 13.7.
 constexpr int EMB_THREADS = 512, EMB_WAVES = EMB_THREADS / WAVE;
 constexpr int EMB_LIST = 2048;
-constexpr int EMB_HOT = 16;
+constexpr int EMB_HOT_MIN = 16;
+inline int embed_hot_from(int tokens) { return std::max(std::clamp(tokens / 64, EMB_HOT_MIN, 32), tokens / 256); }
 constexpr int EMB_OWNERS_MIN = 64, EMB_OWNERS_MAX = 1024;       // workgroups that share the token table (powers of two)
 constexpr int EMB_HOT_CLASSES_MIN = 8, EMB_HOT_CLASSES_MAX = 32, EMB_BUCKETS = 16384;       // powers of two
 constexpr int EMB_LANES = 16, EMB_GROUPS = EMB_THREADS / EMB_LANES, EMB_FLY = 4;       // lanes of a group (256 bytes of a row); rows in flight
@@ -80,10 +85,11 @@ struct EmbedLds {
     int heads;
 };
 
+// Three workgroups per CU: at 81 registers (two) 8192 x 768 bf16 takes 34.8 us instead of 28.2.
 template <typename T>
-__global__ __launch_bounds__(EMB_THREADS) void embed_bwd_kernel(const int* __restrict__ tokens, const T* __restrict__ dx,
+__global__ __launch_bounds__(EMB_THREADS, 6) void embed_bwd_kernel(const int* __restrict__ tokens, const T* __restrict__ dx,
                                                                 float* __restrict__ dwte, float* __restrict__ dwpe, int M, int S,
-                                                                int H, int vocab, int owners, int hot_classes, int slices) {
+                                                                int H, int vocab, int owners, int hot_classes, int slices, int hot_from) {
     constexpr int V = Elem<T>::VEC;
     __shared__ __attribute__((aligned(16))) EmbedLds sm;
     const int tid = threadIdx.x, lane = tid % WAVE, wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
@@ -152,13 +158,13 @@ __global__ __launch_bounds__(EMB_THREADS) void embed_bwd_kernel(const int* __res
             load_tokens(from, M);
 #pragma unroll
             for (int i = 0; i < LOADS; ++i)
-                if (in_class(tok[i])) frequent |= atomicAdd(&sm.seen[bucket(tok[i])], 1) >= EMB_HOT;
+                if (in_class(tok[i])) frequent |= atomicAdd(&sm.seen[bucket(tok[i])], 1) >= hot_from;
         }
         return __syncthreads_or(frequent) != 0;
     };
     if (hot && !count_buckets()) return;
     bool by_bucket = hot;                                       // the list leaves out what the other kind owns
-    auto owned = [&](int v) { return in_class(v) && (!by_bucket || (sm.seen[bucket(v)] > EMB_HOT) == hot); };
+    auto owned = [&](int v) { return in_class(v) && (!by_bucket || (sm.seen[bucket(v)] > hot_from) == hot); };
     // Wavefront k looks at the k-th eighth of positions [w0, w0 + size).  Counts what is owned there, and everywhere.
     int at = 0;
     auto count_owned = [&](int w0, int size) {
@@ -179,17 +185,30 @@ __global__ __launch_bounds__(EMB_THREADS) void embed_bwd_kernel(const int* __res
         return __builtin_amdgcn_readfirstlane(n);
     };
     int window = M, n = count_owned(0, M);
-    const bool several = n > EMB_LIST;
-    if (several) {
-        window = EMB_LIST;
-        if (!hot) { (void)count_buckets(); by_bucket = true; }
+    if (n > EMB_LIST && !hot) {                                 // too many even without the frequent tokens?
+        (void)count_buckets();
+        by_bucket = true;
+        n = count_owned(0, M);
     }
-    for (int w0 = 0; w0 < M; w0 += window) {
-        // 1. the window's owned positions, ascending
-        if (several) {
+    int w0 = 0;
+    // a window of which the list should be nearly full, by what the last one had (EMB_LIST positions always fit)
+    auto fitting = [&] {
+        const float even = (float)window * (EMB_LIST * 0.875f) / (float)max(n, 1);
+        return __builtin_amdgcn_readfirstlane(min(M - w0, max(EMB_LIST, (int)min(even, (float)M))));
+    };
+    auto next_window = [&] {
+        w0 += window;
+        if (w0 >= M) return;
+        window = fitting();
+        n = count_owned(w0, window);
+    };
+    for (; w0 < M; next_window()) {
+        while (n > EMB_LIST) {                                  // (uniform)
+            window = fitting();
             __syncthreads();                                    // the counts have been read
             n = count_owned(w0, window);
         }
+        // 1. the window's owned positions, ascending
         {
             const int each = ((window + EMB_WAVES - 1) / EMB_WAVES + WAVE - 1) / WAVE * WAVE, end = min(w0 + min((wave + 1) * each, window), M);
             for (int from = w0 + wave * each; from < end; from += EMB_THREADS) {
@@ -272,10 +291,10 @@ __global__ __launch_bounds__(EMB_THREADS) void embed_bwd_kernel(const int* __res
         const int parts = (nchunk + WAVE - 1) / WAVE;
         for (int task = wave; task < heads * parts; task += EMB_WAVES) {
             const int first = __builtin_amdgcn_readfirstlane((int)sm.head[task / parts]), v = __builtin_amdgcn_readfirstlane(sm.tok[first]);
-            if (!by_bucket && n > EMB_HOT) {                    // a frequent token?  (the list holds all of its bucket)
+            if (!by_bucket && n > hot_from) {                    // a frequent token?  (the list holds all of its bucket)
                 int count = 0;
                 for (int g = 0; g < n; g += WAVE) count += __popcll(matches(g, v, EMB_BUCKETS - 1));
-                if (count > EMB_HOT) continue;
+                if (count > hot_from) continue;
             }
             const int at_piece = task % parts * WAVE + lane;
             const size_t col = (size_t)min(at_piece, nchunk - 1) * V;
@@ -525,17 +544,18 @@ int chimera_op_embedding_bwd(int dtype, int tokens, int seq, int hidden, int voc
     const size_t pieces = (size_t)seq * (hidden / vec);
     // the workgroups of frequent tokens, which may take longest, go first
     const int slices = (hidden / vec + EMB_LANES - 1) / EMB_LANES;
-    int hot_classes = tokens > EMB_HOT ? EMB_HOT_CLASSES_MAX : 0;
+    const int hot_from = embed_hot_from(tokens);
+    int hot_classes = tokens > hot_from ? EMB_HOT_CLASSES_MAX : 0;
     while (hot_classes > EMB_HOT_CLASSES_MIN && hot_classes * slices > (tokens > 4096 ? 512 : 256)) hot_classes /= 2;
     int owners = EMB_OWNERS_MAX;
     while (owners > EMB_OWNERS_MIN && owners * 4 > tokens) owners /= 2;          // four positions each
     const dim3 grid(hot_classes * slices + owners + (unsigned)((pieces + EMB_THREADS - 1) / EMB_THREADS)), block(EMB_THREADS);
     if (dtype == CHIMERA_F32)
         hipLaunchKernelGGL(embed_bwd_kernel<float>, grid, block, 0, s, d_tokens, (const float*)d_dx, d_dwte, d_dwpe, tokens, seq, hidden,
-                           vocab, owners, hot_classes, slices);
+                           vocab, owners, hot_classes, slices, hot_from);
     else
         hipLaunchKernelGGL(embed_bwd_kernel<bf16_t>, grid, block, 0, s, d_tokens, (const bf16_t*)d_dx, d_dwte, d_dwpe, tokens, seq, hidden,
-                           vocab, owners, hot_classes, slices);
+                           vocab, owners, hot_classes, slices, hot_from);
     CHIMERA_LAUNCH_CHECK("embedding backward");
     return CHIMERA_OK;
 }
