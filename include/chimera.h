@@ -335,6 +335,9 @@ int chimera_worker_last_enqueue_ms(double* h_ms);
 /* The number of streams on which the last chimera_run_worker* ran its stages beside each
  * other; 1: the stages took turns. */
 int chimera_worker_last_lanes(int* h_lanes);
+/* How the last chimera_run_worker* went out: 0 launch by launch, 1 recorded into HIP graphs and
+ * launched as those, 2 as graphs recorded by an earlier replay. */
+int chimera_worker_last_replay(int* h_how);
 
 /* Per-kernel-class timing of everything the stages launch while enabled: a HIP
  * event pair brackets every launch (this slows the replay a little, and the stages of a

@@ -11,6 +11,7 @@ OK, EINVAL, ENOMEM, ESTATE, EDEVICE = 0, -1, -2, -3, -4
 F32, BF16 = 0, 1
 DIRECT, GPIPE, ONE_F_ONE_B, DOUBLING, HALVING = 0, 1, 2, 3, 4
 OP_F, OP_B, OP_F2, OP_BH0, OP_BH1 = 0, 1, 2, 3, 4
+REPLAY_LAUNCHES, REPLAY_RECORDED, REPLAY_GRAPHS = 0, 1, 2
 OPT_CAUSAL, OPT_GELU, OPT_KERNELS, OPT_OVERLAP, OPT_KEEP = 0, 1, 2, 3, 4
 EPI_NONE, EPI_BIAS, EPI_BIAS_GELU, EPI_BIAS_RESIDUAL, EPI_DGELU, EPI_ACCUM_F32 = range(6)
 
@@ -70,6 +71,7 @@ _SIGNATURES = {
     "chimera_model_select": (_i, [_i, _i, C.c_int64, C.c_double, C.c_double, C.c_double, _i, _i, _p, _p, _p]),
     "chimera_worker_last_enqueue_ms": (_i, [_p]),
     "chimera_worker_last_lanes": (_i, [_p]),
+    "chimera_worker_last_replay": (_i, [_p]),
     "chimera_op_gemm_workspace_bytes": (_sz, [_i, _i, _i]),
     "chimera_op_gemm_tuning": (_i, [_i, _i, _i, _i]),
     "chimera_op_gemm_group_last_kernel": (C.c_char_p, []),
@@ -331,6 +333,12 @@ def chimera_worker_last_enqueue_ms():
 def chimera_worker_last_lanes():
     v = C.c_int(0)
     check(lib().chimera_worker_last_lanes(C.byref(v)))
+    return v.value
+
+
+def chimera_worker_last_replay():
+    v = C.c_int(0)
+    check(lib().chimera_worker_last_replay(C.byref(v)))
     return v.value
 
 

@@ -574,6 +574,7 @@ struct Worker {
     int lanes_device = -1;
     int lanes_wait = 0, lanes_backoff = 0;    // replays until more lanes are looked for again; doubles with every failure
     int lanes_used = 1;                       // by the last replay
+    int replayed = 0;                         // how the last replay went out (chimera_worker_last_replay)
 } g_worker;
 
 // The worker's lanes: at most MAX_LANES streams for the whole process, made by the first replay that can use
@@ -1033,6 +1034,7 @@ int chimera_run_worker_pipes(int algo, int rank, int D, int N, int f) {
     };
     ReplayPlan& plan = wk.pipes[0]->replay;
     bool done = false;
+    wk.replayed = 0;
     if (!on_lane.empty() && !rc && std::all_of(on_lane.begin(), on_lane.end(), [](const OnLane& l) { return replay_in_graphs(l.st); })) {
         int dev = 0;
         (void)hipGetDevice(&dev);
@@ -1044,12 +1046,14 @@ int chimera_run_worker_pipes(int algo, int rank, int D, int N, int f) {
             plan.drop();
             plan.key = std::move(key);
         } else if (!plan.refused) {
-            if (plan.lanes.empty() && !record_replay(wk, plan, lanes_taken, used, launch_ops)) rc = CHIMERA_OK;     // launched one by one below
+            const bool record = plan.lanes.empty();
+            if (record && !record_replay(wk, plan, lanes_taken, used, launch_ops)) rc = CHIMERA_OK;     // launched one by one below
             for (size_t i = 0; i < plan.lanes.size() && !rc; ++i) {
                 const hipError_t e = hipGraphLaunch(plan.lanes[i].second, wk.lanes[plan.lanes[i].first]);
                 if (e != hipSuccess) rc = fail(CHIMERA_EDEVICE, "worker replay: %s", hipGetErrorString(e));
             }
             done = !plan.lanes.empty();
+            if (done) wk.replayed = record ? 1 : 2;
             if (done) for (chimera_stage* st : used) if (st && st->keep) st->grads_pending_zero = false;
         }
     }
@@ -1112,6 +1116,12 @@ int chimera_worker_last_enqueue_ms(double* h_ms) {
 int chimera_worker_last_lanes(int* h_lanes) {
     if (!h_lanes) return fail(CHIMERA_EINVAL, "h_lanes is NULL");
     *h_lanes = g_worker.lanes_used;
+    return CHIMERA_OK;
+}
+
+int chimera_worker_last_replay(int* h_how) {
+    if (!h_how) return fail(CHIMERA_EINVAL, "h_how is NULL");
+    *h_how = g_worker.replayed;
     return CHIMERA_OK;
 }
 

@@ -464,9 +464,12 @@ def test_worker_replays_from_graphs(dtype, hidden, heads, seq, mb):
                 io[g] = (x, dy) + tuple(stages[0 if g % D < D // 2 else 1].set_io(g, x, dy))
 
     set_io()
-    #           N, gradients zeroed first, io set anew
-    for step, (N, zero, anew) in enumerate([(4, 1, 0), (4, 1, 0), (4, 1, 0), (4, 1, 0), (4, 0, 0), (4, 0, 0), (4, 0, 0), (8, 1, 0), (8, 1, 0),
-                                            (8, 1, 1), (8, 1, 0), (8, 1, 0), (4, 1, 0), (8, 1, 0), (8, 1, 0), (8, 1, 0)]):
+    one_by_one, recorded, graphs = b.REPLAY_LAUNCHES, b.REPLAY_RECORDED, b.REPLAY_GRAPHS
+    #           N, gradients zeroed first, io set anew, how it goes out
+    for step, (N, zero, anew, how) in enumerate([
+            (4, 1, 0, one_by_one), (4, 1, 0, recorded), (4, 1, 0, graphs), (4, 1, 0, graphs), (4, 0, 0, one_by_one), (4, 0, 0, recorded),
+            (4, 0, 0, graphs), (8, 1, 0, one_by_one), (8, 1, 0, recorded), (8, 1, 1, one_by_one), (8, 1, 0, recorded), (8, 1, 0, graphs),
+            (4, 1, 0, one_by_one), (8, 1, 0, one_by_one), (8, 1, 0, recorded), (8, 1, 0, graphs)]):
         print("replay", dtype, step, flush=True)
         if anew:
             set_io()
@@ -481,6 +484,8 @@ def test_worker_replays_from_graphs(dtype, hidden, heads, seq, mb):
                     st.zero_grads()
             b.chimera_worker_bind_pipes(stages)
             b.chimera_run_worker_pipes(b.DIRECT, 1, D, N)
+            beside = stages is workers[0][0]
+            assert (b.chimera_worker_last_lanes(), b.chimera_worker_last_replay()) == ((2, how) if beside else (1, one_by_one)), step
         for g in range(N):
             assert torch.equal(workers[0][1][g][2], workers[1][1][g][2]) and torch.equal(workers[0][1][g][3], workers[1][1][g][3]), (step, g)
             assert workers[0][1][g][2].abs().sum() > 0
@@ -489,6 +494,70 @@ def test_worker_replays_from_graphs(dtype, hidden, heads, seq, mb):
     for stages, _ in workers:
         for st in stages:
             st.close()
+
+
+# Replays from graphs against replays of the same worker launch by launch, bit for bit, up to the largest launches that are recorded: doubled forwards and
+# the backwards that recompute them, halved backwards, four pipelines, weight gradients one by one (their zero fill is recorded).  A change of the
+# products' tuning (to what it is) makes a replay go out launch by launch again.
+@pytest.mark.parametrize("algo,f,rank,dtype,hidden,heads,seq,mb,reference", [
+    (b.DIRECT, 1, 1, b.BF16, 1024, 16, 256, 4, False), (b.DOUBLING, 1, 1, b.BF16, 320, 5, 200, 2, False), (b.DOUBLING, 1, 0, b.F32, 128, 4, 64, 2, False),
+    (b.HALVING, 1, 2, b.BF16, 640, 10, 128, 2, False), (b.DIRECT, 2, 3, b.BF16, 256, 4, 128, 2, False), (b.DIRECT, 2, 1, b.F32, 128, 4, 40, 1, False),
+    (b.DIRECT, 1, 0, b.BF16, 128, 4, 40, 1, True)])
+def test_graphs_of_every_schedule(algo, f, rank, dtype, hidden, heads, seq, mb, reference):
+    import torch
+    print("graphs", algo, f, rank, dtype, hidden, seq, mb, reference, flush=True)
+    tdt, M, D, N = (torch.float32 if dtype == b.F32 else torch.bfloat16), seq * mb, 4, 8
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    rn = lambda *s, std=1.0: torch.empty(s, dtype=tdt, device="cuda").normal_(0.0, std, generator=gen)
+    need = b.stash_slots_needed_pipes(algo, D, N, f, rank)
+    kw = dict(reference_kernels=reference)
+    stages = [b.Stage(2, hidden, heads, seq, mb, dtype, stash_slots=max(n, 1), **kw) for n in need]
+    for st in stages:
+        st.weights.copy_(rn(st.weights.numel(), std=0.05))
+    x, dy, y, dx = rn(N, M, hidden), rn(N, M, hidden), torch.zeros(N, M, hidden, dtype=tdt, device="cuda"), torch.zeros(N, M, hidden, dtype=tdt, device="cuda")
+    y2 = torch.zeros_like(y)
+    doubled = [b.Stage(2, hidden, heads, seq, 2 * mb, dtype, keep=False, share_weights_of=st, **kw) for st in stages] if algo == b.DOUBLING else []
+    io = lambda st, mb_, *t: b.check(b.lib().chimera_stage_set_io(st.handle, mb_, *[b._ptr(v) for v in t]))
+    for o in b.chimera_schedule_pipes(algo, D, N, f, rank):
+        if o.kind == b.OP_F2:
+            io(doubled[o.pipe], o.mb, x[o.mb:o.mb + 2], y2[o.mb:o.mb + 2], x[o.mb:o.mb + 2], y2[o.mb:o.mb + 2])
+        else:
+            io(stages[o.pipe], o.mb, x[o.mb], y[o.mb], dy[o.mb], dx[o.mb])
+
+    def replay(how, zero):
+        for t in (y, dx, y2):
+            t.zero_()
+        if zero:
+            for st in stages:
+                st.zero_grads()
+        b.chimera_worker_bind_pipes(stages)
+        if doubled:
+            b.chimera_worker_bind_doubling(*doubled)
+        torch.cuda.synchronize()
+        b.chimera_run_worker_pipes(algo, rank, D, N, f)
+        assert b.chimera_worker_last_lanes() >= 2 and b.chimera_worker_last_replay() == how
+        assert all(float(t.float().abs().sum()) > 0 for t in (y2 if doubled else y, dx))
+        return [t.clone() for t in [y, dx, y2] + [st.grads for st in stages]]
+
+    for zero in (True, False):
+        b.check(b.lib().chimera_op_gemm_tuning(0, 0, 0, 0))
+        got = {}
+        for i, how in enumerate((b.REPLAY_LAUNCHES, b.REPLAY_RECORDED, b.REPLAY_GRAPHS, b.REPLAY_GRAPHS)):
+            if i == 3:
+                x.copy_(rn(N, M, hidden)), dy.copy_(rn(N, M, hidden))
+            if not zero:
+                for st in stages:
+                    st.grads.fill_(0.25)
+            got[i] = replay(how, zero)
+        b.check(b.lib().chimera_op_gemm_tuning(0, 0, 0, 0))
+        if not zero:
+            for st in stages:
+                st.grads.fill_(0.25)
+        got[4] = replay(b.REPLAY_LAUNCHES, zero)
+        for i, j in ((1, 0), (2, 0), (3, 4)):
+            assert all(torch.equal(p, q) for p, q in zip(got[i], got[j])), (zero, i)
+    for st in doubled + stages:
+        st.close()
 
 
 # bf16 products on 32x32, 32x64 and 128x64 tiles: a single row or tile, the last and first sizes of each form (256 tiles), k below one step,
