@@ -133,7 +133,7 @@ struct chimera_stage {
     bool use_side = false;            // the running backward uses it
     bool beside = false;              // a replay runs this stage beside another one
 
-    struct IO { const void* x; void* y; const void* dy; void* dx; };
+    struct IO { const void* x; void* y; const void* dy; void* dx; bool operator==(const IO&) const = default; };
     std::unordered_map<int, IO> io;
     std::unordered_map<int, int> in_flight;   // micro-batch -> slot
     std::unordered_map<int, int> halves_done; // micro-batch -> halves of its backward already run
@@ -794,8 +794,11 @@ int chimera_stage_set_io(chimera_stage* st, int mb, const void* d_x_in, void* d_
     if (((uintptr_t)d_x_in | (uintptr_t)d_y_out | (uintptr_t)d_dy_in | (uintptr_t)d_dx_out) & 15)
         return fail(CHIMERA_EINVAL, "io buffers must be 16-byte aligned");
     if (st->in_flight.count(mb)) return fail(CHIMERA_ESTATE, "micro-batch %d is in flight", mb);
+    const chimera_stage::IO io{d_x_in, d_y_out, d_dy_in, d_dx_out};
+    auto known = st->io.find(mb);
+    if (known != st->io.end() && known->second == io) return CHIMERA_OK;       // what was recorded stays valid
     ++st->version;
-    st->io[mb] = chimera_stage::IO{d_x_in, d_y_out, d_dy_in, d_dx_out};
+    st->io[mb] = io;
     return CHIMERA_OK;
 }
 
