@@ -295,8 +295,10 @@ int chimera_worker_bind(chimera_stage* down_stage, chimera_stage* up_stage);
  * queues of their own (one or two milliseconds); where too few are found, a later
  * replay looks again.
  * Of small launches a replay beside each other is recorded into HIP graphs the second time
- * the same stages replay the same schedule with nothing bound or set anew in between (some
- * 2 us a launch), and goes out as those graphs from then on; they live with the stage of pipeline 0.
+ * the same stages replay the same schedule, with gradients zeroed before it or not, on the same
+ * buffers and io (some 2 us a launch), and goes out as those graphs from then on.  They live with
+ * the stage of pipeline 0, which keeps the four that were used last, until it is bound anew or
+ * destroyed; other buffers or io on any of the stages make them void.
  * Beside another stage a bf16 product may take other tiles, which add the same terms
  * in another order: a replay repeated under the same conditions gives the same bits,
  * one that takes turns may differ from it by the rounding of float sums. */

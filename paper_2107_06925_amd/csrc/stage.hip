@@ -11,6 +11,7 @@
 #include <bit>
 #include <cstdio>
 #include <cstring>
+#include <list>
 #include <unordered_map>
 #include <vector>
 
@@ -72,16 +73,17 @@ static void prof_collect() {
 
 // A worker's replay as graphs, one chain of launches per lane.  `key` holds everything that the launches depend on (see
 // replay_key); the first replay under a key launches its kernels one by one, the second records them, and later ones launch the graphs.
+// Gradient accumulation alternates between two keys (gradients overwritten or added to), a change of N or of the schedule adds its own, so a few
+// plans are kept, the one used last in front.
 struct ReplayPlan {
-    std::vector<uint64_t> key;
+    const std::vector<uint64_t> key;
     std::vector<std::pair<int, hipGraphExec_t>> lanes;     // lane, its chain
     bool refused = false;                                  // could not be recorded: launched one by one for good
-    void drop() {
-        for (auto& l : lanes) (void)hipGraphExecDestroy(l.second);
-        lanes.clear(); key.clear(); refused = false;
-    }
-    ~ReplayPlan() { drop(); }
+    explicit ReplayPlan(std::vector<uint64_t> k) : key(std::move(k)) {}
+    ReplayPlan(const ReplayPlan&) = delete;
+    ~ReplayPlan() { for (auto& l : lanes) (void)hipGraphExecDestroy(l.second); }
 };
+constexpr size_t MAX_PLANS = 4;
 
 static uint64_t next_stage_uid() {
     static std::atomic<uint64_t> n{0};
@@ -95,7 +97,7 @@ using namespace chimera;
 struct chimera_stage {
     const uint64_t uid = next_stage_uid();
     uint64_t version = 0;             // counts changes of what the stage's launches depend on: buffers, stream, io
-    ReplayPlan replay;                // of the last worker whose pipeline 0 this stage serves; replays end idle, so never in use outside one
+    std::list<ReplayPlan> replays;    // of the workers whose pipeline 0 this stage serves; replays end idle, so never in use outside one
     int L, H, heads, S, B, dtype;
     int M, d;
     size_t esz;
@@ -685,16 +687,32 @@ template <typename F> bool record_replay(Worker& wk, ReplayPlan& plan, unsigned 
     return false;
 }
 
-// All that the launches of a replay in lanes depend on: the schedule's parameters, the lanes, each stage with the version of its buffers and
-// io, whether its gradients are to be read as zero, and the products' tuning.
-std::vector<uint64_t> replay_key(std::initializer_list<uint64_t> schedule, const std::vector<chimera_stage*>& stages) {
-    std::vector<uint64_t> key(schedule);
-    key.push_back(gemm_mfma_tuning_version());
-    for (const chimera_stage* st : stages) {
-        key.push_back(st ? st->uid : 0);
-        if (st) { key.push_back(st->version); key.push_back(st->grads_pending_zero); }
-    }
+// All that the launches of a replay in lanes depend on: the products' tuning, the schedule's parameters, the lanes, each stage with the version of
+// its buffers and io and whether its gradients are to be read as zero.
+constexpr size_t KEY_HEAD = 8, KEY_STAGE = 3;
+std::vector<uint64_t> replay_key(const std::array<uint64_t, KEY_HEAD - 1>& schedule, const std::vector<chimera_stage*>& stages) {
+    std::vector<uint64_t> key{gemm_mfma_tuning_version()};
+    key.insert(key.end(), schedule.begin(), schedule.end());
+    for (const chimera_stage* st : stages) key.insert(key.end(), {st ? st->uid : 0, st ? st->version : 0, st ? st->grads_pending_zero : 0ull});
     return key;
+}
+// No replay can have key `old` any more once one has `now`: the tuning, or the buffers or io of a stage of both, have changed.
+bool outlived(const std::vector<uint64_t>& old, const std::vector<uint64_t>& now) {
+    bool gone = old[0] != now[0];
+    for (size_t i = KEY_HEAD; i < std::min(old.size(), now.size()); i += KEY_STAGE) gone = gone || (old[i] == now[i] && old[i + 1] != now[i + 1]);
+    return gone;
+}
+// The plan of `key`, in front of the list, and whether an earlier replay had that key.
+std::pair<ReplayPlan*, bool> find_plan(std::list<ReplayPlan>& plans, std::vector<uint64_t> key) {
+    auto it = std::find_if(plans.begin(), plans.end(), [&](const ReplayPlan& p) { return p.key == key; });
+    const bool known = it != plans.end();
+    if (known) plans.splice(plans.begin(), plans, it);
+    else {
+        plans.remove_if([&](const ReplayPlan& p) { return outlived(p.key, key); });
+        while (plans.size() >= MAX_PLANS) plans.pop_back();
+        plans.emplace_front(std::move(key));
+    }
+    return {&plans.front(), known};
 }
 }  // namespace
 
@@ -766,7 +784,7 @@ int chimera_stage_bind(chimera_stage* st, const void* d_weights, float* d_grads,
         return fail(CHIMERA_EINVAL, "device buffers must be 256-byte aligned");
     if (!st->in_flight.empty()) return fail(CHIMERA_ESTATE, "cannot rebind with micro-batches in flight");
     ++st->version;
-    st->replay.drop();
+    st->replays.clear();
     st->weights = (const char*)d_weights; st->grads = d_grads; st->stash = (char*)d_stash; st->ws = (char*)d_workspace;
     st->slots = stash_slots; st->stream = (hipStream_t)hip_stream;
     st->grads_pending_zero = false;
@@ -1035,7 +1053,6 @@ int chimera_run_worker_pipes(int algo, int rank, int D, int N, int f) {
         }
         return rc;
     };
-    ReplayPlan& plan = wk.pipes[0]->replay;
     bool done = false;
     wk.replayed = 0;
     if (!on_lane.empty() && !rc && std::all_of(on_lane.begin(), on_lane.end(), [](const OnLane& l) { return replay_in_graphs(l.st); })) {
@@ -1044,18 +1061,16 @@ int chimera_run_worker_pipes(int algo, int rank, int D, int N, int f) {
         std::vector<chimera_stage*> used;
         for (int p = 0; p < pipes; ++p)
             for (chimera_stage* st : stages_of(p)) used.push_back(runs[p] ? st : nullptr);
-        std::vector<uint64_t> key = replay_key({(uint64_t)algo, (uint64_t)rank, (uint64_t)D, (uint64_t)N, (uint64_t)f, (uint64_t)lanes, (uint64_t)dev}, used);
-        if (plan.key != key) {
-            plan.drop();
-            plan.key = std::move(key);
-        } else if (!plan.refused) {
-            const bool record = plan.lanes.empty();
-            if (record && !record_replay(wk, plan, lanes_taken, used, launch_ops)) rc = CHIMERA_OK;     // launched one by one below
-            for (size_t i = 0; i < plan.lanes.size() && !rc; ++i) {
-                const hipError_t e = hipGraphLaunch(plan.lanes[i].second, wk.lanes[plan.lanes[i].first]);
+        const auto [plan, known] = find_plan(wk.pipes[0]->replays, replay_key({(uint64_t)algo, (uint64_t)rank, (uint64_t)D, (uint64_t)N, (uint64_t)f,
+                                                                               (uint64_t)lanes, (uint64_t)dev}, used));
+        if (known && !plan->refused) {
+            const bool record = plan->lanes.empty();
+            if (record && !record_replay(wk, *plan, lanes_taken, used, launch_ops)) rc = CHIMERA_OK;     // launched one by one below
+            for (size_t i = 0; i < plan->lanes.size() && !rc; ++i) {
+                const hipError_t e = hipGraphLaunch(plan->lanes[i].second, wk.lanes[plan->lanes[i].first]);
                 if (e != hipSuccess) rc = fail(CHIMERA_EDEVICE, "worker replay: %s", hipGetErrorString(e));
             }
-            done = !plan.lanes.empty();
+            done = !plan->lanes.empty();
             if (done) wk.replayed = record ? 1 : 2;
             if (done) for (chimera_stage* st : used) if (st && st->keep) st->grads_pending_zero = false;
         }

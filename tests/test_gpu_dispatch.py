@@ -469,7 +469,8 @@ def test_worker_replays_from_graphs(dtype, hidden, heads, seq, mb):
     for step, (N, zero, anew, how) in enumerate([
             (4, 1, 0, one_by_one), (4, 1, 0, recorded), (4, 1, 0, graphs), (4, 1, 0, graphs), (4, 0, 0, one_by_one), (4, 0, 0, recorded),
             (4, 0, 0, graphs), (8, 1, 0, one_by_one), (8, 1, 0, recorded), (8, 1, 1, one_by_one), (8, 1, 0, recorded), (8, 1, 0, graphs),
-            (4, 1, 0, one_by_one), (8, 1, 0, one_by_one), (8, 1, 0, recorded), (8, 1, 0, graphs)]):
+            (4, 1, 0, one_by_one), (8, 1, 0, graphs), (4, 1, 0, recorded), (8, 0, 0, one_by_one), (4, 1, 0, graphs), (8, 0, 0, recorded),
+            (4, 0, 0, one_by_one), (8, 0, 0, graphs), (8, 1, 0, graphs), (4, 0, 0, recorded), (4, 0, 0, graphs), (4, 1, 0, graphs)]):
         print("replay", dtype, step, flush=True)
         if anew:
             set_io()

@@ -130,6 +130,33 @@ assert how == [0, 1, 2, 2], how
 io(s[0], 0)
 assert replay(s) == 0
 """,
+    "gradients accumulated": r"""
+s = worker()
+assert [replay(s, z=z) for z in [1, 0, 0] * 4] == [0, 0, 1] + [1, 2, 2] + [2, 2, 2] * 2
+assert count("captures") == 4 and count("graphs_alive") == 4
+s = worker()
+assert [replay(s, z=z) for z in [1, 0] * 4] == [0, 0] + [1, 1] + [2, 2] * 2
+""",
+    "schedules in turn": r"""
+s = worker(N=16)
+assert [replay(s, N=n) for n in [4, 8, 12] * 3] == [0] * 3 + [1] * 3 + [2] * 3
+assert count("graphs_alive") == 6
+# more than are kept: never recorded, the graphs of what is not used any more given back
+assert [replay(s, N=n, z=z) for n, z in [(4, 0), (8, 0), (12, 0), (16, 0), (16, 1)] * 3] == [0] * 15
+assert count("graphs_alive") == 0
+assert [replay(s, N=16) for _ in range(3)] == [1, 2, 2]
+""",
+    "outlived plans": r"""
+s = worker(N=8)
+assert [replay(s, N=n) for n in [4, 4, 8, 8]] == [0, 1, 0, 1] and count("graphs_alive") == 4
+io(s[1], 0)                                                    # every recording of this stage is void
+assert replay(s) == 0 and count("graphs_alive") == 0
+assert [replay(s) for _ in range(2)] == [1, 2] and count("graphs_alive") == 2
+b.check(L.chimera_op_gemm_tuning(0, 0, 0, 0))
+assert [replay(s) for _ in range(3)] == [0, 1, 2] and count("graphs_alive") == 2
+b.check(L.chimera_stage_bind(s[0].handle, *s[0].buffers))
+assert count("graphs_alive") == 0 and [replay(s) for _ in range(3)] == [0, 1, 2]
+""",
 }
 
 
