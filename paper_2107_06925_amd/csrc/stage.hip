@@ -78,6 +78,7 @@ static void prof_collect() {
 struct ReplayPlan {
     const std::vector<uint64_t> key;
     std::vector<std::pair<int, hipGraphExec_t>> lanes;     // lane, its chain
+    std::vector<char> pending_zero;                        // of every stage, once the chains have run
     bool refused = false;                                  // could not be recorded: launched one by one for good
     explicit ReplayPlan(std::vector<uint64_t> k) : key(std::move(k)) {}
     ReplayPlan(const ReplayPlan&) = delete;
@@ -654,11 +655,16 @@ void make_lanes(Worker& wk, int want) {
 constexpr double GRAPH_WORK = 1 << 30;       // rows x hidden^2 of one micro-batch
 bool replay_in_graphs(const chimera_stage* st) { return (double)st->M * st->H * st->H <= GRAPH_WORK; }
 
+std::vector<char> pending_zero(const std::vector<chimera_stage*>& stages) {
+    std::vector<char> out;
+    for (const chimera_stage* st : stages) out.push_back(st && st->grads_pending_zero);
+    return out;
+}
+
 // Records what `launch` enqueues on the lanes as one graph each.  False (and never tried again under this key) if that fails; the stages
 // are then as before.
 template <typename F> bool record_replay(Worker& wk, ReplayPlan& plan, unsigned lanes_taken, const std::vector<chimera_stage*>& stages, F&& launch) {
-    std::vector<char> pending;
-    for (const chimera_stage* st : stages) pending.push_back(st && st->grads_pending_zero);
+    const std::vector<char> pending = pending_zero(stages);
     std::vector<std::pair<int, hipGraph_t>> graphs;
     bool ok = true;
     for (int l = 0; l < (int)wk.lanes.size() && ok; ++l)
@@ -673,6 +679,7 @@ template <typename F> bool record_replay(Worker& wk, ReplayPlan& plan, unsigned 
         if (ok && (ok = hipGraphInstantiate(&exec, g.second, nullptr, nullptr, 0) == hipSuccess)) plan.lanes.push_back({g.first, exec});
         if (g.second) (void)hipGraphDestroy(g.second);
     }
+    plan.pending_zero = pending_zero(stages);
     if (ok) return true;
     (void)hipGetLastError();
     for (auto& l : plan.lanes) (void)hipGraphExecDestroy(l.second);
@@ -1065,14 +1072,22 @@ int chimera_run_worker_pipes(int algo, int rank, int D, int N, int f) {
                                                                                (uint64_t)lanes, (uint64_t)dev}, used));
         if (known && !plan->refused) {
             const bool record = plan->lanes.empty();
+            const std::vector<char> pending = pending_zero(used);
             if (record && !record_replay(wk, *plan, lanes_taken, used, launch_ops)) rc = CHIMERA_OK;     // launched one by one below
+            unsigned launched = 0;
             for (size_t i = 0; i < plan->lanes.size() && !rc; ++i) {
                 const hipError_t e = hipGraphLaunch(plan->lanes[i].second, wk.lanes[plan->lanes[i].first]);
                 if (e != hipSuccess) rc = fail(CHIMERA_EDEVICE, "worker replay: %s", hipGetErrorString(e));
+                else launched |= 1u << plan->lanes[i].first;
             }
             done = !plan->lanes.empty();
-            if (done) wk.replayed = record ? 1 : 2;
-            if (done) for (chimera_stage* st : used) if (st && st->keep) st->grads_pending_zero = false;
+            if (done) {
+                wk.replayed = record ? 1 : 2;
+                // a zeroing is done where its chain has gone out (two stages per pipeline in `used`)
+                for (size_t i = 0; i < used.size(); ++i)
+                    if (used[i]) used[i]->grads_pending_zero = launched >> (i / 2 % lanes) & 1 ? plan->pending_zero[i] : pending[i];
+                if (rc) wk.pipes[0]->replays.pop_front();
+            }
         }
     }
     if (!done) (void)launch_ops();

@@ -146,6 +146,27 @@ assert [replay(s, N=n, z=z) for n, z in [(4, 0), (8, 0), (12, 0), (16, 0), (16, 
 assert count("graphs_alive") == 0
 assert [replay(s, N=16) for _ in range(3)] == [1, 2, 2]
 """,
+    "failed launches": r"""
+fail = C.c_int.in_dll(fake, "fake_fail_graph_launch")
+def refused(s, nth, z=True):
+    fail.value = nth
+    try:
+        replay(s, z=z)
+    except b.ChimeraError as e:
+        assert e.code == b.EDEVICE
+        return True
+s = worker()
+for before in (1, 2, 3):                                       # while recording, and from graphs
+    # the first lane's graph is refused: neither stage's zeroing has been done; the second's: that stage's has not
+    for nth, left in ((1, (True, True)), (2, (False, True))):
+        assert [replay(s) for _ in range(before)] == [0, 1, 2][:before]
+        assert refused(s, nth)
+        assert tuple(fills(st) > 0 for st in s) == left, (before, nth)
+        assert count("graphs_alive") == 0                      # recorded again, from the start
+# nothing to zero: nothing is left to zero
+assert [replay(s, z=False) for _ in range(2)] == [0, 1] and refused(s, 1, z=False)
+assert [fills(st) for st in s] == [0, 0]
+""",
     "outlived plans": r"""
 s = worker(N=8)
 assert [replay(s, N=n) for n in [4, 4, 8, 8]] == [0, 1, 0, 1] and count("graphs_alive") == 4
