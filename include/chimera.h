@@ -299,6 +299,8 @@ int chimera_worker_bind(chimera_stage* down_stage, chimera_stage* up_stage);
  * buffers and io (some 2 us a launch), and goes out as those graphs from then on.  They live with
  * the stage of pipeline 0, which keeps the four that were used last, until it is bound anew or
  * destroyed; other buffers or io on any of the stages make them void.
+ * EDEVICE, with nothing done, while one of the stages' streams is under capture: a replay ends
+ * with a wait, which a capture does not allow.
  * Beside another stage a bf16 product may take other tiles, which add the same terms
  * in another order: a replay repeated under the same conditions gives the same bits,
  * one that takes turns may differ from it by the rounding of float sums. */

@@ -985,6 +985,15 @@ int chimera_run_worker_pipes(int algo, int rank, int D, int N, int f) {
         if ((o.kind == CHIMERA_OP_BH0 || o.kind == CHIMERA_OP_BH1) && (st->B % 2))
             return fail(CHIMERA_EINVAL, "a micro-batch of %d sequences cannot be halved", st->B);
     }
+    // A replay waits for the streams, which a stream under capture cannot: refused before anything has been enqueued, recorded or counted as done.
+    auto capturing = [](const chimera_stage* st) {
+        hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+        if (!st) return false;
+        if (hipStreamIsCapturing(st->stream, &status) != hipSuccess) (void)hipGetLastError();
+        return status != hipStreamCaptureStatusNone;
+    };
+    if (std::any_of(wk.pipes.begin(), wk.pipes.end(), capturing) || std::any_of(std::begin(wk.fwd2), std::end(wk.fwd2), capturing))
+        return fail(CHIMERA_EDEVICE, "worker replay: %s", hipGetErrorString(hipErrorStreamCaptureUnsupported));
     std::vector<hipEvent_t> ev;
     if (wk.timing) {
         ev.resize(ops.size() * 2);

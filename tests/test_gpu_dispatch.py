@@ -561,6 +561,42 @@ def test_graphs_of_every_schedule(algo, f, rank, dtype, hidden, heads, seq, mb, 
         st.close()
 
 
+# A replay while its stages' stream is under capture is refused; the capture goes on, and so do the graphs of the worker.
+def test_replay_under_capture():
+    import torch
+    home, graph, x = torch.cuda.Stream(), torch.cuda.CUDAGraph(), torch.zeros(64, device="cuda")
+    stages = [b.Stage(1, 128, 2, 64, 1, b.BF16, stash_slots=2, stream=home) for _ in range(2)]
+    for st in stages:
+        st.weights.normal_(0, 0.02)
+        for mb in range(2):
+            t = torch.randn(64, 128, device="cuda").bfloat16()
+            st.set_io(mb, t, t)
+    torch.cuda.synchronize()
+    b.chimera_worker_bind_pipes(stages)
+
+    def replay():
+        for st in stages:
+            st.zero_grads()
+        b.chimera_run_worker(0, 2, 2)
+        return b.chimera_worker_last_replay()
+
+    assert [replay() for _ in range(2)] == [b.REPLAY_LAUNCHES, b.REPLAY_RECORDED]
+    want = [st.grads.clone() for st in stages]
+    with torch.cuda.graph(graph, stream=home):
+        x.add_(1)
+        with pytest.raises(b.ChimeraError) as e:
+            replay()
+        x.add_(1)
+    assert e.value.code == b.EDEVICE
+    assert replay() == b.REPLAY_GRAPHS and all(torch.equal(st.grads, w) for st, w in zip(stages, want))
+    for i in range(1, 4):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert float(x.min()) == float(x.max()) == 2.0 * i
+    for st in stages:
+        st.close()
+
+
 # bf16 products on 32x32, 32x64 and 128x64 tiles: a single row or tile, the last and first sizes of each form (256 tiles), k below one step,
 # with a remainder, and around the lengths of the rings
 @pytest.mark.parametrize("m,n,k", [(1, 8, 8), (32, 32, 64), (33, 40, 520), (512, 512, 72), (512, 520, 584), (100, 1600, 1032),

@@ -167,6 +167,26 @@ for before in (1, 2, 3):                                       # while recording
 assert [replay(s, z=False) for _ in range(2)] == [0, 1] and refused(s, 1, z=False)
 assert [fills(st) for st in s] == [0, 0]
 """,
+    "caller's capture": r"""
+home = 0x5000
+s = worker(stream=home)
+assert [replay(s) for _ in range(2)] == [0, 1]
+def refused(z):
+    before = [count(n) for n in ("launches", "captures", "graph_launches", "waits")]
+    fake.fake_caller_capture(C.c_void_p(home), 1)
+    try:
+        replay(s, z=z)
+        return False
+    except b.ChimeraError as e:
+        assert e.code == b.EDEVICE
+    finally:
+        fake.fake_caller_capture(C.c_void_p(home), 0)
+    return [count(n) for n in ("launches", "captures", "graph_launches", "waits")] == before
+assert refused(True) and [replay(s) for _ in range(2)] == [2, 2]
+assert refused(False) and [replay(s, z=False) for _ in range(3)] == [0, 1, 2]
+zero(s)
+assert refused(False) and [fills(st) > 0 for st in s] == [True, True]
+""",
     "outlived plans": r"""
 s = worker(N=8)
 assert [replay(s, N=n) for n in [4, 4, 8, 8]] == [0, 1, 0, 1] and count("graphs_alive") == 4
