@@ -539,7 +539,9 @@ template <int N, typename F> __device__ __forceinline__ void static_for(F&& f) {
 // than not (gpt2-1p3b-n32 97.8 -> 99.4 ms, gpt2-deep 50.2 -> 51.2).
 struct Ahead { const char* p; unsigned bytes; };
 constexpr unsigned AHEAD_PIECE = 64 * 128, AHEAD_STRIP = 256;
-__device__ __forceinline__ void touch_ahead(const Ahead& ahead, int wave, int waves, int lane, unsigned strip) {
+__device__ __forceinline__ void touch_ahead(const Ahead& ahead, int wave, int waves, int lane) {
+    __shared__ __attribute__((aligned(16))) char lines[AHEAD_STRIP];
+    const unsigned strip = lds_address(lines);
     // pieces beyond the range repeat its last word
     for (size_t at = ((size_t)blockIdx.x * waves + wave) * AHEAD_PIECE; at < ahead.bytes; at += (size_t)gridDim.x * waves * AHEAD_PIECE) {
         const unsigned off = min((unsigned)at + (unsigned)lane * 128u, ahead.bytes - 4u);
@@ -564,7 +566,6 @@ __device__ __forceinline__ void gemm_async_tile(
     constexpr int CA = BM * (BK / 8) / NT, CB = BN * (BK / 8) / NT;      // 16-byte pieces per thread and stage
     constexpr int STAGE = (BM + BN) * BK;                                 // elements
     __shared__ __attribute__((aligned(16))) bf16_t lds[NS * STAGE];
-    __shared__ __attribute__((aligned(16))) char strip[AHEAD_STRIP];
 
     const int nblk = tiles_m * tiles_n;
     // `block_id` as the hardware deals it (round-robin over the XCDs) or already renumbered
@@ -745,7 +746,7 @@ __device__ __forceinline__ void gemm_async_tile(
         __syncthreads();
         iteration(std::false_type{}, kt);
     }
-    touch_ahead(ahead, wave, NT / 64, lane, lds_address(strip));
+    if constexpr (ONLY_EPI < 0) touch_ahead(ahead, wave, NT / 64, lane);       // weight gradients and split products precede no product
 
     const int cb0 = j0 + wn0;
     // the operand tiles in LDS are dead once every wavefront has left the k loop; each
@@ -934,7 +935,6 @@ __device__ __forceinline__ void gemm_ring_tile(
     constexpr unsigned STAGE = (BM + BN) * RK * 2, ABYTES = BM * RK * 2;
     constexpr int LDS_EPI = NT / 64 * EpiSlab<TN / 2>::FLOATS * 4, LDS_RING = NS * (int)STAGE;
     __shared__ __attribute__((aligned(1024))) char lds[LDS_RING > LDS_EPI ? LDS_RING : LDS_EPI];
-    __shared__ __attribute__((aligned(16))) char strip[AHEAD_STRIP];
 
     const int nblk = tiles_m * tiles_n;
     const int xcd = block_id & 7, local = block_id >> 3;
@@ -1207,7 +1207,7 @@ __device__ __forceinline__ void gemm_ring_tile(
         steps(std::false_type{});
     }
 #undef CHIMERA_C
-    touch_ahead(ahead, wave, NT / 64, lane, lds_address(strip));
+    if constexpr (ONLY_EPI < 0) touch_ahead(ahead, wave, NT / 64, lane);       // weight gradients and split products precede no product
 
     const int cb0 = j0 + wn0;
     auto put_col_sums = [&](const float* v) {
@@ -1350,7 +1350,6 @@ struct GemmGroup {
     int first[GROUP_MAX + 1];
     int count, k;
     int overwrite;               // results replace C and bsum instead of being added
-    Ahead ahead;
 };
 
 // The product of a group launch that this workgroup belongs to, and its tile's number inside the
@@ -1374,7 +1373,7 @@ __global__ __launch_bounds__(WGM* WGN * WGK * 64, 2) void gemm_bf16_ring_group_k
     gemm_ring_tile<BM, BN, WGM, WGN, WGK, false, false, EPI_ACCUM_F32>(
         grp.a[p], grp.b[p], nullptr, nullptr, grp.c[p], nullptr, grp.m[p], grp.n[p], grp.k, grp.lda[p], grp.ldb[p],
         EPI_ACCUM_F32, grp.overwrite, 0, grp.tiles_m[p], grp.tiles_n[p], grp.group_m[p], gid - grp.first[p], grp.bsum[p],
-        false, 0, grp.ahead);
+        false);
 }
 
 template <int BM, int BN, int WGM, int WGN, int WGK, int NS, int SPS, bool A_KC, bool B_KC>
@@ -1384,7 +1383,7 @@ __global__ __launch_bounds__(WGM* WGN * WGK * 64) void gemm_bf16_async_group_ker
     gemm_async_tile<BM, BN, WGM, WGN, WGK, NS, SPS, A_KC, B_KC, EPI_ACCUM_F32>(
         grp.a[p], grp.b[p], nullptr, nullptr, grp.c[p], nullptr, grp.m[p], grp.n[p], grp.k, grp.lda[p], grp.ldb[p],
         EPI_ACCUM_F32, grp.overwrite, 0, grp.tiles_m[p], grp.tiles_n[p], grp.group_m[p], gid - grp.first[p], grp.bsum[p],
-        false, grp.ahead);
+        false);
 }
 
 // A launch of 256x256 tiles runs in rounds of NUM_CUS tiles, and a last round with few tiles
@@ -1684,7 +1683,9 @@ int gemm_mfma_bf16(const GemmArgs& g, void* stream) {
                 // columns in the same way: wide outputs of few tile rows (1024 x 50304 x 4096, 788 tiles:
                 // three full rounds and 20 tiles: 482 -> 386 + 41 us)
                 const int col0 = (tn - bc) * 256;
-                if (int rc = launch_ring<256, 256, 2, 4, 1>(g, s, 0, tn - bc)) return rc;
+                GemmArgs head = g;
+                head.ahead = nullptr; head.ahead_bytes = 0;
+                if (int rc = launch_ring<256, 256, 2, 4, 1>(head, s, 0, tn - bc)) return rc;
                 if ((long)((g.m + 127) / 128) * ((g.n - col0 + 127) / 128) <= NUM_CUS) return launch_ring<128, 128, 2, 2, 2>(g, s, col0);
                 return launch_ring<128, 128, 2, 2, 1>(g, s, col0);
             }
@@ -1807,7 +1808,6 @@ int launch_group_tiled(int count, const GemmArgs* g, float* const* bsum, int ove
     }
     for (int i = 0; i < count; ++i) grp.group_m[i] = raster_group(grp.tiles_m[i], grp.tiles_n[i], (tiles + 7) / 8, tile, tile);
     for (int i = count; i <= GROUP_MAX; ++i) grp.first[i] = tiles;
-    grp.ahead = ahead_of(g[count - 1]);
     if (tile == 256) return launch_group_ring<256, 256, 2, 4, 1>(grp, stream);
     if (tile == 64) return tiles <= NUM_CUS ? launch_group<64, 64, 2, 2, 2, 8, 2>(grp, stream, first) : launch_group<64, 64, 1, 2, 2, 4>(grp, stream, first);
     // two workgroups per CU or the k-sliced 8-wavefront form
