@@ -450,9 +450,9 @@ Form choose_form(int count, const GemmArgs* g) {
     return t64 <= NUM_CUS / 2 ? SMALL : TILE64;
 }
 
-
 template <bool A_KC, bool B_KC, int EPI>
-void launch_form(F32Launch& L, Form form, hipStream_t s) {
+int launch_form(F32Launch& L, Form form, hipStream_t s) {
+    if (!A_KC && form == TINY) return fail(CHIMERA_EINVAL, "no 16x16 tile for weight gradients");       // (those go in groups, which are larger)
     const int tile = form == TILE64 ? 64 : form == SMALL ? 32 : 16;
     L.total = 0;
     int kmax = 0;
@@ -467,26 +467,26 @@ void launch_form(F32Launch& L, Form form, hipStream_t s) {
     const dim3 grid(L.total);
     if (form == TILE64) hipLaunchKernelGGL((gemm_f32_tile_kernel<A_KC, B_KC, EPI>), grid, dim3(8 * WAVE), 0, s, L);
     else if (form == TINY) {
-        if constexpr (A_KC) {                                     // (weight gradients go in groups, which are larger)
+        if constexpr (A_KC) {
             if (kmax <= 128) hipLaunchKernelGGL((gemm_f32_tiny_kernel<4, A_KC, B_KC, EPI>), grid, dim3(4 * WAVE), 0, s, L);
             else hipLaunchKernelGGL((gemm_f32_tiny_kernel<8, A_KC, B_KC, EPI>), grid, dim3(8 * WAVE), 0, s, L);
         }
     } else if (kmax <= 256) hipLaunchKernelGGL((gemm_f32_small_kernel<4, A_KC, B_KC, EPI>), grid, dim3(4 * WAVE), 0, s, L);
     else hipLaunchKernelGGL((gemm_f32_small_kernel<8, A_KC, B_KC, EPI>), grid, dim3(8 * WAVE), 0, s, L);
+    CHIMERA_LAUNCH_CHECK("float gemm");
+    return CHIMERA_OK;
 }
 
 template <bool A_KC, bool B_KC>
 int launch_epi(F32Launch& L, Form form, hipStream_t s) {
     switch (L.epi) {
-        case EPI_NONE: launch_form<A_KC, B_KC, EPI_NONE>(L, form, s); break;
-        case EPI_BIAS: launch_form<A_KC, B_KC, EPI_BIAS>(L, form, s); break;
-        case EPI_BIAS_GELU: launch_form<A_KC, B_KC, EPI_BIAS_GELU>(L, form, s); break;
-        case EPI_BIAS_RESIDUAL: launch_form<A_KC, B_KC, EPI_BIAS_RESIDUAL>(L, form, s); break;
-        case EPI_DGELU: launch_form<A_KC, B_KC, EPI_DGELU>(L, form, s); break;
-        default: launch_form<A_KC, B_KC, EPI_ACCUM_F32>(L, form, s); break;
+        case EPI_NONE: return launch_form<A_KC, B_KC, EPI_NONE>(L, form, s);
+        case EPI_BIAS: return launch_form<A_KC, B_KC, EPI_BIAS>(L, form, s);
+        case EPI_BIAS_GELU: return launch_form<A_KC, B_KC, EPI_BIAS_GELU>(L, form, s);
+        case EPI_BIAS_RESIDUAL: return launch_form<A_KC, B_KC, EPI_BIAS_RESIDUAL>(L, form, s);
+        case EPI_DGELU: return launch_form<A_KC, B_KC, EPI_DGELU>(L, form, s);
+        default: return launch_form<A_KC, B_KC, EPI_ACCUM_F32>(L, form, s);
     }
-    CHIMERA_LAUNCH_CHECK("float gemm");
-    return CHIMERA_OK;
 }
 
 F32Product product_of(const GemmArgs& g) {
@@ -534,9 +534,7 @@ int gemm_f32_group(int count, const GemmArgs* g, float* const* bsum, int overwri
     F32Launch L{};
     L.count = count; L.epi = EPI_ACCUM_F32; L.flag = overwrite ? 1 : 0;
     for (int i = 0; i < count; ++i) { L.p[i] = product_of(g[i]); L.p[i].bsum = bsum ? bsum[i] : nullptr; }
-    launch_form<false, false, EPI_ACCUM_F32>(L, choose_form(count, g), (hipStream_t)stream);
-    CHIMERA_LAUNCH_CHECK("float gemm group");
-    return CHIMERA_OK;
+    return launch_form<false, false, EPI_ACCUM_F32>(L, choose_form(count, g), (hipStream_t)stream);
 }
 
 }  // namespace chimera
