@@ -181,7 +181,7 @@ def test_edge_argument_errors():
 @pytest.mark.parametrize("tokens,hidden,vocab,kind", [
     (17, 8, 5, "same"), (2049, 136, 70000, "same"), (4096, 264, 1000, "padding"), (5000, 136, 40000, "owner"), (6144, 72, 40000, "bucket"),
     (16384, 128, 3000, "log"), (4097, 1032, 50304, "log"), (600, 2048, 40, "log"),
-    (4096, 64, 125, "uniform"), (8193, 64, 250, "uniform"), (70000, 40, 30000, "dense"), (70001, 24, 90, "uniform")])
+    (463, 24, 900, "log"), (65, 192, 3, "uniform"), (4096, 64, 125, "uniform"), (8193, 64, 250, "uniform"), (70000, 40, 30000, "dense"), (70001, 24, 90, "uniform")])
 def test_embedding_backward_lists(tokens, hidden, vocab, kind, dtype):
     import torch
     print("embedding backward lists", tokens, hidden, vocab, kind, dtype, flush=True)
