@@ -676,7 +676,7 @@ __device__ __forceinline__ void gemm_async_tile(
         load_tile<BN, NT, B_KC>(rb, B, ldb, j0, n, KT * BK, k, tid);
 #pragma unroll
         for (int st = 0; st < NS - SPS; ++st)
-            if (st < KT) issue(st);
+            if (st < KT) [[likely]] issue(st);
         bf16_t* last = lds + (NS - 1) * STAGE;             // the stage that the first issue of the loop fills
         store_tile<BM, NT, A_KC>(ra, last, tid);
         store_tile<BN, NT, B_KC>(rb, last + BM * BK, tid);
@@ -685,23 +685,23 @@ __device__ __forceinline__ void gemm_async_tile(
     } else {
 #pragma unroll
         for (int st = 0; st < NS - SPS; ++st)
-            if (st < KT) issue(st);
+            if (st < KT) [[likely]] issue(st);
     }
     int cur = 0, nxt = NS - SPS;               // stage computed now / stage the next issue fills
     auto advance = [](int& st) { st = st + 1 == NS ? 0 : st + 1; };
     // Operands of SPS stages out of LDS first, then a request behind each MFMA: all wavefronts leave the barrier together, and
     // a CU takes 16 clocks for each of their 16 to 32 requests, which reads behind them would wait for.  Requests first -> reads
     // first, operands in the memory-side cache: 632 x 1600 x 6400 26.1 -> 22.5 us, 1024 x 640 x 2560 11.5 -> 10.7, 1264 x 1600 x 6400
-    // (two workgroups per CU) 42.9 -> 41.7.
-    auto iteration = [&](auto always_c, int kt) {
-        constexpr bool always = decltype(always_c)::value;
+    // (two workgroups per CU) 42.9 -> 41.7.  The last steps, which have nothing left to request, and all of a k loop shorter than the
+    // ring, leave the order to the compiler: with it fixed there too, and every instruction behind a condition, k = 192 to 768 takes 3 to 5 %
+    // longer (A B^T 1280 x 768 x 320 4.68 -> 4.50 us, A B 1088 x 1088 x 512 6.32 -> 6.05).
+    auto iteration = [&] {
         bf16x8 af[SPS][KSUB][TM], bfr[SPS][KSUB][TN];
         int st = cur;
 #pragma unroll
         for (int u = 0; u < SPS; ++u) {
             const bf16_t* As = lds + st * STAGE;
             advance(st);
-            if (!always && u && kt + u >= KT) break;
 #pragma unroll
             for (int ks = 0; ks < KSUB; ++ks) {
 #pragma unroll
@@ -715,21 +715,18 @@ __device__ __forceinline__ void gemm_async_tile(
         constexpr int REQ = SPS * (CA + CB), MM = SPS * KSUB * TM * TN, PER = (REQ + MM - 1) / MM;
         static_for<MM>([&](auto i_c) {
             constexpr int i = decltype(i_c)::value, u = i / (KSUB * TM * TN), ks = i / (TM * TN) % KSUB, a = i / TN % TM, b = i % TN;
-            if (always || u == 0 || kt + u < KT) {
-                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[u][ks][a], bfr[u][ks][b], acc[a][b], 0, 0, 0);
-                if constexpr (ONLY_EPI == EPI_ACCUM_F32 && a == 0)
-                    if (col_sums) cs[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, bfr[u][ks][b], cs[b], 0, 0, 0);
-            }
+            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[u][ks][a], bfr[u][ks][b], acc[a][b], 0, 0, 0);
+            if constexpr (ONLY_EPI == EPI_ACCUM_F32 && a == 0)
+                if (col_sums) cs[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, bfr[u][ks][b], cs[b], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
             static_for<PER>([&](auto j_c) {
-                constexpr int r = i * PER + decltype(j_c)::value, ru = r / (CA + CB), it = r % (CA + CB);
-                if constexpr (r < REQ)
-                    if (always || kt + NS - SPS + ru < KT) {
-                        const unsigned to = lds0 + (unsigned)(nxt * STAGE) * 2u + (unsigned)wave * 1024u;
-                        if constexpr (it < CA) { lds_dma16(ga[it], to + it * NT * 16); ga[it] += step_a; }
-                        else { lds_dma16(gb[it - CA], to + BM * BK * 2 + (it - CA) * NT * 16); gb[it - CA] += step_b; }
-                        if constexpr (it == CA + CB - 1) advance(nxt);
-                    }
+                constexpr int r = i * PER + decltype(j_c)::value, it = r % (CA + CB);
+                if constexpr (r < REQ) {
+                    const unsigned to = lds0 + (unsigned)(nxt * STAGE) * 2u + (unsigned)wave * 1024u;
+                    if constexpr (it < CA) { lds_dma16(ga[it], to + it * NT * 16); ga[it] += step_a; }
+                    else { lds_dma16(gb[it - CA], to + BM * BK * 2 + (it - CA) * NT * 16); gb[it - CA] += step_b; }
+                    if constexpr (it == CA + CB - 1) advance(nxt);
+                }
             });
             __builtin_amdgcn_sched_barrier(0);
         });
@@ -739,14 +736,20 @@ __device__ __forceinline__ void gemm_async_tile(
         // the SPS oldest outstanding stages must have landed; NS - 2 SPS younger ones may fly on
         wait_vmcnt<(NS - 2 * SPS) * (CA + CB)>();
         __syncthreads();                       // every wavefront's part of this step is in LDS; the previous one is consumed
-        iteration(std::true_type{}, 0);
+        iteration();
     }
     for (; kt < KT; kt += SPS) {
         if (kt + NS - SPS <= KT) wait_vmcnt<(NS - 2 * SPS) * (CA + CB)>(); else wait_vmcnt<0>();
         __syncthreads();
-        iteration(std::false_type{}, kt);
+#pragma unroll
+        for (int u = 0; u < SPS - 1; ++u)
+            if (kt + NS - SPS + u < KT) { issue(nxt); advance(nxt); }
+#pragma unroll
+        for (int u = 0; u < SPS; ++u)
+            if (u == 0 || kt + u < KT) { compute(cur); advance(cur); }
     }
-    if constexpr (ONLY_EPI < 0) touch_ahead(ahead, wave, NT / 64, lane);       // weight gradients and split products precede no product
+    if constexpr (ONLY_EPI < 0)
+        if (ahead.bytes) [[unlikely]] touch_ahead(ahead, wave, NT / 64, lane);       // weight gradients and split products precede no product
 
     const int cb0 = j0 + wn0;
     // the operand tiles in LDS are dead once every wavefront has left the k loop; each
