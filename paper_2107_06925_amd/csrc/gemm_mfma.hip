@@ -1488,8 +1488,9 @@ bool small_tiles(long tiles64) { return tiles64 <= 2 * NUM_CUS && tuning().async
 // (256) 8.8 -> 7.1 (32x32 8.4), 333 x 776 x 3104 13.7 -> 10.9 (12.4), 400 x 960 x 320 3.9 -> 3.7 (4.0).
 // 64x64, two per CU -> 128x64: 1264 x 1600 x 6400 (250) 46.7 -> 39.5, x 1600 13.9 -> 12.1, 1024 x 2048 x 2048 (256) 16.6 -> 14.2,
 // 2048 x 768 x 3072 21.5 -> 17.2, 512 x 3072 x 1024 10.7 -> 9.3; beside another stage 10.6 -> 11.1 each at k = 1600, 13.3 -> 12.6 at 2048.
-// With the GeLU derivative, whose epilogue is the longest, from k = 640 on: 1024 x 2048 x 192 7 % slower, x 320 5, x 512 2, x 640 4 % faster, x 1024 4; other
-// epilogues 3 % either way below k = 512.
+// From k = 128 on: at 64 and 96 it is 1 to 5 % slower (1152 x 1280 x 64 A B 4.21 -> 4.44 us, A B^T 4.27 -> 4.40), at 128 as fast, from 256 on 3 to
+// 13 % faster.  With the GeLU derivative, whose epilogue is the longest, from 640 on: x 192 2 to 3 % slower, x 512 1 to 2, x 640 as fast, x 768
+// 2 to 4 % faster.
 // Beside another stage the tiles below 64x64 may take half of the CUs: they read more in all, and what one stage's tiles take the
 // other's do without.  Replays of two stages with the limit at all CUs -> at half: two blocks of 512 at 1024 tokens 1409 -> 1371 us
 // (64x64 tiles throughout: 1398), of 512 at 512 1259 -> 1238, of 1024 at 128 1483 -> 1443 and at 256 1728 -> 1684, of 1600 at 128 2610 -> 2538; of 256 at
@@ -1501,7 +1502,7 @@ TileChoice small_tile(const GemmArgs& g) {
     const int few = g.beside ? NUM_CUS / 2 : NUM_CUS;
     if (fits(32, 32, few)) return {32, 32, 1};
     if (fits(32, 64, few)) return {32, 64, 1};
-    const int long_k = g.beside ? 2048 : g.epilogue == EPI_DGELU ? 640 : 0;
+    const int long_k = g.beside ? 2048 : g.epilogue == EPI_DGELU ? 640 : 128;
     if (!fits(64, 64, NUM_CUS) && fits(128, 64, NUM_CUS) && g.k >= long_k) return {128, 64, 1};
     return {64, 64, 1};
 }

@@ -607,7 +607,8 @@ def test_bf16_small_output_tiles(m, n, k, layout):
 
 
 # ... with every epilogue, ragged rows and columns
-@pytest.mark.parametrize("m,n,k", [(45, 72, 200), (333, 776, 136), (1100, 1448, 192), (1100, 1448, 640)])
+@pytest.mark.parametrize("m,n,k", [(45, 72, 200), (333, 776, 136), (1100, 1448, 120), (1100, 1448, 192),
+                                   (1100, 1448, 328), (1100, 1448, 640)])
 def test_bf16_small_output_epilogues(m, n, k):
     import torch
     print("bf16 gemm epilogues", m, n, k, flush=True)
