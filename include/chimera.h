@@ -479,7 +479,7 @@ int chimera_op_embedding_fwd(int dtype, int tokens, int seq, int hidden, int voc
                              const int32_t* d_tokens, const void* d_wte, const void* d_wpe,
                              void* d_x, void* hip_stream);
 /* dwte[v] += sum of dx[t] over the positions t with token[t] = v (ascending t, in partial sums
- * of a fixed order where a token is frequent or there are more than 4096 positions),
+ * of a fixed order where a token is frequent or there are more than 2048 positions),
  * dwpe[p] += sum of dx[b*seq + p] over the sequences b (ascending); both float. */
 int chimera_op_embedding_bwd(int dtype, int tokens, int seq, int hidden, int vocab,
                              const int32_t* d_tokens, const void* d_dx,
