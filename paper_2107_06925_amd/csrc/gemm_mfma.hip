@@ -621,8 +621,11 @@ __device__ __forceinline__ void gemm_async_tile(
     };
 
     static_assert(TM == 1 || (WGK == 2 && TM == 2), "one band of rows per wavefront in the epilogue");
+    // With two workgroups on a CU each hides the other's last trip, and these requests hold back the first operands.  Without them A^T B 1472 x 1280 x 512
+    // 7.56 -> 7.24 us, groups of 12 x 384^2 x 1024 10.36 -> 9.97, A B^T with the GeLU derivative 1088 x 1088 x 192 5.54 -> 5.39; but A B x 64 4.2 -> 4.4.
+    constexpr bool EPI_AHEAD = SPS > 1 || (A_KC && !B_KC);
     EpiAhead<TN> pre;
-    if (TM > 1 || wk == 0)
+    if (EPI_AHEAD && (TM > 1 || wk == 0))
         pre.request(i0 + wm0 + (TM > 1 ? wk * 32 : 0), j0 + wn0, m, n, bias, R, C, ONLY_EPI >= 0 ? ONLY_EPI : epi, epi_flag, res_types, lane);
 
     f32x16 acc[TM][TN];
@@ -758,7 +761,7 @@ __device__ __forceinline__ void gemm_async_tile(
     __syncthreads();
     float* slab = reinterpret_cast<float*>(lds) + (size_t)(tid >> 6) * EpiSlab<TN>::FLOATS;
     auto finish = [&]<int TMO>(const f32x16 (&out)[TMO][TN], int rb0) {
-#define CHIMERA_EPI(E, RF, CF) epilogue<E, RF, CF, TMO, TN>(Acc32<TMO, TN>{out}, slab, rb0, cb0, m, n, bias, R, C, C2, epi_flag, lane, &pre)
+#define CHIMERA_EPI(E, RF, CF) epilogue<E, RF, CF, TMO, TN>(Acc32<TMO, TN>{out}, slab, rb0, cb0, m, n, bias, R, C, C2, epi_flag, lane, EPI_AHEAD ? &pre : nullptr)
         if constexpr (ONLY_EPI == EPI_ACCUM_F32) { CHIMERA_EPI(EPI_ACCUM_F32, false, false); return; }
         switch (epi) {
             case EPI_NONE: CHIMERA_EPI(EPI_NONE, false, false); break;
