@@ -137,26 +137,32 @@ __device__ __forceinline__ bf16x8 read_frag(const bf16_t* lds, int r0, int kk, i
     }
 }
 
-// Epilogue of one wavefront.  Accumulator register r of lane l holds
-// C[8*(r/4) + 4*(l/32) + r%4][l%32] of its 32x32 tile: one column per lane, which
-// would mean 2-byte global accesses.  So each 32-row band of the wavefront's
-// tile goes through a wavefront-private LDS slab ([32][WN + 8] floats, the
-// padding keeps the two lane halves on different banks) and comes back as 8
-// consecutive columns per lane; bias, residual, GeLU operands and the results
-// then move in 16-byte pieces, 128 contiguous bytes per 8 lanes.
+// Epilogue of one wavefront.  The matrix instructions get B's rows as their first operand, so a lane's accumulators are runs of
+// four consecutive columns of one row of C (row l%32 of a 32x32 tile, columns 8q + 4(l/32) + 0..3; row l%16 of a 16x16 tile,
+// columns 4(l/16) + 0..3).  Each 32-row band of the wavefront's tile goes through a wavefront-private LDS slab ([32][WN] floats)
+// and comes back as 8 consecutive columns per lane; bias, residual, GeLU operands and the results then move in 16-byte pieces,
+// 128 contiguous bytes per 8 lanes.  16-byte chunk c of row r sits at c ^ flip(r): both the writes (16 rows, one chunk each) and
+// the reads (whole rows, every other chunk) put a pass of 16 lanes on all banks.  With A's rows first (one column per lane, written float
+// by float) and rows padded by 32 bytes instead, half of the slabs' LDS cycles were conflicts, 4096 clocks of a 256x256 tile: 4096 x 3072 x 1024
+// 28.4 -> 27.7 us, 2048 x 6400 x 1600 with GeLU 48.3 -> 47.3, 1264 x 4800 x 1600 24.6 -> 24.1, 400 x 1280 x 320 with GeLU 4.87 -> 4.70,
+// 512 x 2048 x 512 5.68 -> 5.52; the float accumulate is bound by HBM and as fast as before.
 template <int TN> struct EpiSlab {
-    static constexpr int WN = TN * 32, STRIDE = WN + 8, FLOATS = 32 * STRIDE;
+    static constexpr int WN = TN * 32, FLOATS = 32 * WN;
+    static_assert(TN == 1 || TN == 2, "rows of 32 or 64 floats");
+    static __device__ __forceinline__ int flip(int row) { return TN == 1 ? (row >> 1) & 7 : row & 15; }
+    static __device__ __forceinline__ float* at(float* slab, int row, int chunk) { return slab + row * WN + ((chunk ^ flip(row)) << 2); }
 };
-// Writers of one 32-row band of accumulators into a slab: 32x32 tiles, and 16x16 tiles (column l%16, rows
-// 4(l/16) + r).
+// Writers of one 32-row band of accumulators into a slab: 32x32 tiles, and 16x16 tiles.
 template <int TM, int TN> struct Acc32 {
     const f32x16 (&acc)[TM][TN];
     template <int BAND> __device__ __forceinline__ void put(float* slab, int lane) const {
-        const int l32 = lane & 31, lhi = lane >> 5;
 #pragma unroll
         for (int b = 0; b < TN; ++b)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) slab[(8 * (r >> 2) + 4 * lhi + (r & 3)) * EpiSlab<TN>::STRIDE + b * 32 + l32] = acc[BAND][b][r];
+            for (int q = 0; q < 4; ++q) {
+                const f32x16& t = acc[BAND][b];
+                *reinterpret_cast<f32x4*>(EpiSlab<TN>::at(slab, lane & 31, 8 * b + 2 * q + (lane >> 5))) = f32x4{t[4 * q], t[4 * q + 1], t[4 * q + 2], t[4 * q + 3]};
+            }
     }
 };
 template <int TM, int TN> struct Acc16 {
@@ -166,9 +172,7 @@ template <int TM, int TN> struct Acc16 {
         for (int a = 0; a < 2; ++a)
 #pragma unroll
             for (int b = 0; b < 2 * TN; ++b)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    slab[(16 * a + 4 * (lane >> 4) + r) * EpiSlab<TN>::STRIDE + b * 16 + (lane & 15)] = acc[BAND * 2 + a][b][r];
+                *reinterpret_cast<f32x4*>(EpiSlab<TN>::at(slab, 16 * a + (lane & 15), 4 * b + (lane >> 4))) = acc[BAND * 2 + a][b];
     }
 };
 
@@ -232,7 +236,7 @@ __device__ __forceinline__ void epilogue(const Acc& acc, float* slab, int row_ba
                                          int n, const bf16_t* __restrict__ bias, const bf16_t* __restrict__ R,
                                          void* __restrict__ c, bf16_t* __restrict__ C2, int epi_flag, int lane,
                                          const EpiAhead<TN>* pre = nullptr) {
-    constexpr int WN = EpiSlab<TN>::WN, STRIDE = EpiSlab<TN>::STRIDE;
+    constexpr int WN = EpiSlab<TN>::WN;
     constexpr int CPR = WN / 8;                // 8-column pieces per row
     constexpr int RPP = 64 / CPR;              // rows covered by the 64 lanes at once
     constexpr int NP = 32 / RPP;               // passes per band of 32 rows
@@ -290,8 +294,8 @@ __device__ __forceinline__ void epilogue(const Acc& acc, float* slab, int row_ba
             const int lr = j * RPP + pr;
             const int grow = row_base + a * 32 + lr;
             float v[8];
-            load_vec<float>(slab + lr * STRIDE + pc, v);
-            load_vec<float>(slab + lr * STRIDE + pc + 4, v + 4);
+            load_vec<float>(EpiSlab<TN>::at(slab, lr, pc / 4), v);
+            load_vec<float>(EpiSlab<TN>::at(slab, lr, pc / 4 + 1), v + 4);
             float rv[8];
             if constexpr (READS) {
                 if (reads) ahead[SLOT][j].unpack(rv);
@@ -399,7 +403,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_kernel(
             for (int a = 0; a < TM; ++a)
 #pragma unroll
                 for (int b = 0; b < TN; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[a], bfr[b], acc[a][b], 0, 0, 0);
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[b], af[a], acc[a][b], 0, 0, 0);
         }
     };
     auto fetch = [&](Staged<BM, NT, A_KC>& ra, Staged<BN, NT, B_KC>& rb, int kt) {
@@ -665,7 +669,7 @@ __device__ __forceinline__ void gemm_async_tile(
             for (int a = 0; a < TM; ++a)
 #pragma unroll
                 for (int b = 0; b < TN; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[a], bfr[b], acc[a][b], 0, 0, 0);
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[b], af[a], acc[a][b], 0, 0, 0);
             if constexpr (ONLY_EPI == EPI_ACCUM_F32)
                 if (col_sums)
 #pragma unroll
@@ -718,7 +722,7 @@ __device__ __forceinline__ void gemm_async_tile(
         constexpr int REQ = SPS * (CA + CB), MM = SPS * KSUB * TM * TN, PER = (REQ + MM - 1) / MM;
         static_for<MM>([&](auto i_c) {
             constexpr int i = decltype(i_c)::value, u = i / (KSUB * TM * TN), ks = i / (TM * TN) % KSUB, a = i / TN % TM, b = i % TN;
-            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[u][ks][a], bfr[u][ks][b], acc[a][b], 0, 0, 0);
+            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[u][ks][b], af[u][ks][a], acc[a][b], 0, 0, 0);
             if constexpr (ONLY_EPI == EPI_ACCUM_F32 && a == 0)
                 if (col_sums) cs[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, bfr[u][ks][b], cs[b], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
@@ -1065,7 +1069,7 @@ __device__ __forceinline__ void gemm_ring_tile(
         constexpr bool sums = decltype(sums_c)::value;
         static_for<HM * TN>([&](auto i_c) {
             constexpr int i = decltype(i_c)::value, a = half * HM + i / TN, b = i % TN;
-            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[a], fb[set][b], acc[a][b], 0, 0, 0);
+            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[set][b], fa[a], acc[a][b], 0, 0, 0);
             if constexpr (sums && a == 0) cs[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, fb[set][b], cs[b], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
             between(i_c);
