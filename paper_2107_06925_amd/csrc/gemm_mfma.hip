@@ -35,6 +35,8 @@
 // that the tiles in flight on one XCD share operand panels in its L2.
 #include "device.h"
 
+#include <algorithm>
+#include <climits>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -51,6 +53,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int BK = 64;
 constexpr int GROUP_M = 8;       // tile rows per raster group
 constexpr int NUM_CUS = 256;     // compute units of an MI355X
+constexpr int XCDS = 8, PER_XCD = NUM_CUS / XCDS;
 constexpr size_t SPLITK_COUNTER_BYTES = 4096;
 
 __device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ (row & 7) ^ ((row >> 3) & 7); }
@@ -930,21 +933,27 @@ __device__ __forceinline__ int rswz(int r) { return (r >> 1) & 7; }
 // block in rows 8g..8g+3 of four lane groups g.
 __device__ __forceinline__ int rkswz(int k) { return (k & 3) | ((k >> 1) & 4); }
 
+// Buffers of a tile in LDS (its epilogue's slabs take their place): the kernel owns them, so that one kernel can hold several tile sizes.
+template <int BM, int BN, int WGM, int WGN, int WGK> struct RingLds {
+    static constexpr int STAGES = WGK == 1 ? 2 : BM * BN > 128 * 128 ? 3 : 4, STAGE = (BM + BN) * RK * 2;
+    static constexpr int EPILOGUE = WGM * WGN * WGK * EpiSlab<BN / WGN / 32>::FLOATS * 4, RING = STAGES * STAGE;
+    static constexpr int BYTES = RING > EPILOGUE ? RING : EPILOGUE;
+};
+
 __device__ __forceinline__ void lds_dma16_s(const void* sbase, unsigned voff, unsigned lds_base) {
     asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "{m0}"(lds_base) : "memory");
 }
 template <int BM, int BN, int WGM, int WGN, int WGK, bool A_KC, bool B_KC, int ONLY_EPI>
 __device__ __forceinline__ void gemm_ring_tile(
-    const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, const bf16_t* __restrict__ bias,
+    char* lds, const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, const bf16_t* __restrict__ bias,
     const bf16_t* __restrict__ R, void* __restrict__ C, bf16_t* __restrict__ C2, int m, int n, int k, int lda,
     int ldb, int epi, int epi_flag, int res_types, int tiles_m, int tiles_n, int group_m, int block_id,
     float* __restrict__ bsum = nullptr, bool xcd_remap = true, int col0 = 0, const Ahead& ahead = {nullptr, 0}) {
-    constexpr int NT = WGM * WGN * WGK * 64, NS = WGK == 1 ? 2 : BM * BN > 128 * 128 ? 3 : 4;
+    using Lds = RingLds<BM, BN, WGM, WGN, WGK>;
+    constexpr int NT = WGM * WGN * WGK * 64, NS = Lds::STAGES;
     constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16, HM = TM / 2;      // 16x16 tiles per wavefront
     constexpr int CA = BM * (RK / 8) / NT, CB = BN * (RK / 8) / NT, CS = CA + CB;     // 16-byte pieces per thread and stage
-    constexpr unsigned STAGE = (BM + BN) * RK * 2, ABYTES = BM * RK * 2;
-    constexpr int LDS_EPI = NT / 64 * EpiSlab<TN / 2>::FLOATS * 4, LDS_RING = NS * (int)STAGE;
-    __shared__ __attribute__((aligned(1024))) char lds[LDS_RING > LDS_EPI ? LDS_RING : LDS_EPI];
+    constexpr unsigned STAGE = Lds::STAGE, ABYTES = BM * RK * 2;
 
     const int nblk = tiles_m * tiles_n;
     const int xcd = block_id & 7, local = block_id >> 3;
@@ -1262,7 +1271,7 @@ __device__ __forceinline__ void gemm_ring_tile(
         // it hands the other half to its partner through LDS and adds what the partner hands over.
         static_assert(WGK == 2 && TM % 4 == 0, "bands of 32 rows");
         constexpr int PER_WAVE = HM * TN * 64;                   // 16 bytes each
-        static_assert(sizeof(lds) >= NT / 64 * PER_WAVE * 16 + BN * sizeof(float), "LDS too small for the exchange");
+        static_assert(Lds::BYTES >= NT / 64 * PER_WAVE * 16 + BN * (int)sizeof(float), "LDS too small for the exchange");
         f32x4* xch = reinterpret_cast<f32x4*>(lds);
         float* xcs = reinterpret_cast<float*>(xch + NT / 64 * PER_WAVE) + wn0;
         if constexpr (ONLY_EPI == EPI_ACCUM_F32)
@@ -1301,7 +1310,8 @@ __global__ __launch_bounds__(WGM* WGN * WGK * 64, 2) void gemm_bf16_ring_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, const bf16_t* __restrict__ bias,
     const bf16_t* __restrict__ R, void* __restrict__ C, bf16_t* __restrict__ C2, int m, int n, int k, int lda,
     int ldb, int epi, int epi_flag, int res_types, int tiles_m, int tiles_n, int group_m, int col0, Ahead ahead) {
-    gemm_ring_tile<BM, BN, WGM, WGN, WGK, A_KC, B_KC, -1>(A, B, bias, R, C, C2, m, n, k, lda, ldb, epi, epi_flag, res_types,
+    __shared__ __attribute__((aligned(1024))) char lds[RingLds<BM, BN, WGM, WGN, WGK>::BYTES];
+    gemm_ring_tile<BM, BN, WGM, WGN, WGK, A_KC, B_KC, -1>(lds, A, B, bias, R, C, C2, m, n, k, lda, ldb, epi, epi_flag, res_types,
                                                           tiles_m, tiles_n, group_m, (int)blockIdx.x, nullptr, true, col0, ahead);
 }
 
@@ -1316,8 +1326,9 @@ __global__ __launch_bounds__(WGM* WGN * WGK * 64, 2) void gemm_bf16_ring_split_k
     const int xcd = (int)blockIdx.x & 7, local = (int)blockIdx.x >> 3;
     const int pid = xcd * (total >> 3) + min(xcd, total & 7) + local;
     const int split = pid / tiles, k0 = split * k_per;
+    __shared__ __attribute__((aligned(1024))) char lds[RingLds<BM, BN, WGM, WGN, WGK>::BYTES];
     gemm_ring_tile<BM, BN, WGM, WGN, WGK, true, true, EPI_ACCUM_F32>(
-        A + k0, B + k0, nullptr, nullptr, slabs + (size_t)split * m * n, nullptr, m, n, min(k_per, k - k0), lda, ldb,
+        lds, A + k0, B + k0, nullptr, nullptr, slabs + (size_t)split * m * n, nullptr, m, n, min(k_per, k - k0), lda, ldb,
         EPI_ACCUM_F32, 1, 0, tiles_m, tiles_n, group_m, pid % tiles, nullptr, false);
 }
 
@@ -1380,8 +1391,9 @@ template <int BM, int BN, int WGM, int WGN, int WGK>
 __global__ __launch_bounds__(WGM* WGN * WGK * 64, 2) void gemm_bf16_ring_group_kernel(GemmGroup grp) {
     int gid;
     const int p = group_product(grp, gid);
+    __shared__ __attribute__((aligned(1024))) char lds[RingLds<BM, BN, WGM, WGN, WGK>::BYTES];
     gemm_ring_tile<BM, BN, WGM, WGN, WGK, false, false, EPI_ACCUM_F32>(
-        grp.a[p], grp.b[p], nullptr, nullptr, grp.c[p], nullptr, grp.m[p], grp.n[p], grp.k, grp.lda[p], grp.ldb[p],
+        lds, grp.a[p], grp.b[p], nullptr, nullptr, grp.c[p], nullptr, grp.m[p], grp.n[p], grp.k, grp.lda[p], grp.ldb[p],
         EPI_ACCUM_F32, grp.overwrite, 0, grp.tiles_m[p], grp.tiles_n[p], grp.group_m[p], gid - grp.first[p], grp.bsum[p],
         false);
 }
@@ -1396,6 +1408,60 @@ __global__ __launch_bounds__(WGM* WGN * WGK * 64) void gemm_bf16_async_group_ker
         false);
 }
 
+// The same on tiles of several sizes in one launch.  An entry is the tiles of one size of one product, a phase the entries of all products
+// that are begun together.  Of every 256 tiles of a phase an XCD takes 32 neighbours, so that the tiles in flight share operand panels in
+// its L2 and, between the XCDs, in the memory-side cache (one range of the whole phase per XCD: block of 2048 at k = 512 121 -> 128 us, of
+// 1920 at 2048 204 -> 220; one range of each product's tiles: block of 1280 at 2048 104 -> 128).
+enum TileForm { TILE_256, TILE_128x256, TILE_256x128, TILE_128 };
+constexpr int MIXED_MAX = 4 * GROUP_MAX;
+struct MixedEntry {
+    const bf16_t *a, *b;
+    float *c, *bsum;
+    int m, n, lda, ldb, tiles_m, tiles_n, group_m, col0;
+    int form;
+};
+constexpr int MIXED_PHASES = 3;
+struct MixedPhase {
+    int first, tiles;                // its tiles
+    int local;                       // number, within an XCD, of its first workgroup
+    int skew;                        // the XCD that takes the first of the tiles that eight do not divide
+};
+struct MixedGroup {
+    MixedPhase phase[MIXED_PHASES];
+    int first[MIXED_MAX];            // number of an entry's first tile, all laid end to end (INT_MAX behind the last entry)
+    int count, k, overwrite;
+    MixedEntry e[MIXED_MAX];
+};
+
+__global__ __launch_bounds__(512, 2) void gemm_bf16_mixed_group_kernel(MixedGroup grp) {
+    __shared__ __attribute__((aligned(1024))) char lds[RingLds<256, 128, 2, 2, 2>::BYTES];
+    static_assert(RingLds<256, 256, 2, 4, 1>::BYTES <= sizeof(lds) && RingLds<128, 256, 1, 4, 2>::BYTES <= sizeof(lds) &&
+                  RingLds<128, 128, 2, 2, 2>::BYTES <= sizeof(lds), "the largest of them");
+    const int local = (int)blockIdx.x >> 3, h = local >= grp.phase[2].local ? 2 : local >= grp.phase[1].local ? 1 : 0;
+    const MixedPhase& p = grp.phase[h];
+    const int slot = ((int)blockIdx.x - p.skew) & 7, at = local - p.local, rounds = p.tiles / NUM_CUS, rest = p.tiles % NUM_CUS;
+    int gid = p.first + at / PER_XCD * NUM_CUS + slot * PER_XCD + at % PER_XCD;
+    if (at >= rounds * PER_XCD) {
+        const int last = at - rounds * PER_XCD;
+        if (last >= rest / XCDS + (slot < rest % XCDS ? 1 : 0)) return;
+        gid = p.first + rounds * NUM_CUS + slot * (rest / XCDS) + min(slot, rest % XCDS) + last;
+    }
+    int i = 0;
+#pragma unroll
+    for (int j = 1; j < MIXED_MAX; ++j)
+        if (gid >= grp.first[j]) i = j;
+    const MixedEntry& e = grp.e[i];
+    const int tile = gid - grp.first[i];
+#define CHIMERA_MIXED(...)                                                                                                  \
+    gemm_ring_tile<__VA_ARGS__, false, false, EPI_ACCUM_F32>(lds, e.a, e.b, nullptr, nullptr, e.c, nullptr, e.m, e.n, grp.k, \
+        e.lda, e.ldb, EPI_ACCUM_F32, grp.overwrite, 0, e.tiles_m, e.tiles_n, e.group_m, tile, e.bsum, false, e.col0)
+    if (e.form == TILE_256) CHIMERA_MIXED(256, 256, 2, 4, 1);
+    else if (e.form == TILE_128x256) CHIMERA_MIXED(128, 256, 1, 4, 2);
+    else if (e.form == TILE_256x128) CHIMERA_MIXED(256, 128, 2, 2, 2);
+    else CHIMERA_MIXED(128, 128, 2, 2, 2);
+#undef CHIMERA_MIXED
+}
+
 // A launch of 256x256 tiles runs in rounds of NUM_CUS tiles, and a last round with few tiles
 // costs as much as a full one.  The products here can be cut along m without touching the data
 // (row bands of A and C are just pointer offsets), so the last `b` bands of 256 rows may go to a
@@ -1403,19 +1469,18 @@ __global__ __launch_bounds__(WGM* WGN * WGK * 64) void gemm_bf16_async_group_ker
 // of 128x128 tiles (a quarter of the flops) counts 0.45.  Measured, launch included: 0.36 to 0.39 of a 256x256
 // round at one tile per CU (k = 1600: 18.4 against 49.5 us A B, 24.5 against 68 A^T B), 0.34 each of two rounds
 // at two per CU; the rest stands for what an estimate in whole rounds leaves out.  Returns the b
-// that minimises it (0: leave the product whole); `other` = 256x256 tiles of the launch that do
-// not belong to this product.  Columns are counted by the same rule with rows and columns exchanged.
-int bands_to_peel(long other, int tm, int tn, int n, double* cost = nullptr) {
+// that minimises it (0: leave the product whole).  Columns are counted by the same rule with rows and columns exchanged.
+int bands_to_peel(int tm, int tn, int n, double* cost) {
     const int tn128 = (n + 127) / 128;
     auto rounds = [](long tiles) { return (double)((tiles + NUM_CUS - 1) / NUM_CUS); };
-    const double whole = rounds(other + (long)tm * tn);
+    const double whole = rounds((long)tm * tn);
     int best_b = 0;
     double best = whole - 0.25;                                  // a split must pay for its second launch
     for (int b = 1; b < tm; ++b) {
-        const double est = rounds(other + (long)(tm - b) * tn) + 0.45 * rounds((long)b * 2 * tn128);
+        const double est = rounds((long)(tm - b) * tn) + 0.45 * rounds((long)b * 2 * tn128);
         if (est < best) { best = est; best_b = b; }
     }
-    if (cost) *cost = best;
+    *cost = best;
     return best_b;
 }
 
@@ -1612,29 +1677,25 @@ int launch_ring(const GemmArgs& g, hipStream_t s, int col0 = 0, int cols256 = 0)
     return CHIMERA_OK;
 }
 
-// Name of the kernel instantiation(s) the last grouped launch on this thread went to (for reports).
-thread_local char g_last_group_kernel[192] = "";
-void note_group_kernel(bool first, const char* name) {
-    char* dst = g_last_group_kernel;
-    const size_t used = first ? 0 : std::strlen(dst);
-    std::snprintf(dst + used, sizeof g_last_group_kernel - used, "%s%s", used ? " + " : "", name);
-}
+// Name of the kernel instantiation the last grouped launch on this thread went to (for reports).
+thread_local char g_last_group_kernel[96] = "";
+void note_group_kernel(const char* name) { std::snprintf(g_last_group_kernel, sizeof g_last_group_kernel, "%s", name); }
 
 template <int BM, int BN, int WGM, int WGN, int WGK>
-int launch_group_ring(const GemmGroup& grp, hipStream_t s, bool first = true) {
+int launch_group_ring(const GemmGroup& grp, hipStream_t s) {
     char name[96];
     std::snprintf(name, sizeof name, "gemm_bf16_ring_group_kernel<%d,%d,%d,%d,%d>", BM, BN, WGM, WGN, WGK);
-    note_group_kernel(first, name);
+    note_group_kernel(name);
     hipLaunchKernelGGL((gemm_bf16_ring_group_kernel<BM, BN, WGM, WGN, WGK>), dim3(grp.first[grp.count]), dim3(WGM * WGN * WGK * 64), 0, s, grp);
     CHIMERA_LAUNCH_CHECK("bf16 gemm group");
     return CHIMERA_OK;
 }
 
 template <int BM, int BN, int WGM, int WGN, int WGK, int NS, int SPS = 1>
-int launch_group(const GemmGroup& grp, hipStream_t s, bool first = true) {
+int launch_group(const GemmGroup& grp, hipStream_t s) {
     char name[96];
     std::snprintf(name, sizeof name, "gemm_bf16_async_group_kernel<%d,%d,%d,%d,%d,%d,%d,false,false>", BM, BN, WGM, WGN, WGK, NS, SPS);
-    note_group_kernel(first, name);
+    note_group_kernel(name);
     const dim3 grid(grp.first[grp.count]), block(WGM * WGN * WGK * 64);
     hipLaunchKernelGGL((gemm_bf16_async_group_kernel<BM, BN, WGM, WGN, WGK, NS, SPS, false, false>), grid, block, 0, s, grp);
     CHIMERA_LAUNCH_CHECK("bf16 gemm group");
@@ -1688,8 +1749,8 @@ int gemm_mfma_bf16(const GemmArgs& g, void* stream) {
         if (t.bm == 256 && t.bn == 256) {
             const int tm = (g.m + 255) / 256, tn = (g.n + 255) / 256;
             double by_rows = 0, by_columns = 0;
-            const int b = forced_tile().bm ? 0 : bands_to_peel(0, tm, tn, g.n, &by_rows);
-            const int bc = forced_tile().bm ? 0 : bands_to_peel(0, tn, tm, g.m, &by_columns);
+            const int b = forced_tile().bm ? 0 : bands_to_peel(tm, tn, g.n, &by_rows);
+            const int bc = forced_tile().bm ? 0 : bands_to_peel(tn, tm, g.m, &by_columns);
             if (bc > 0 && by_columns < by_rows && g.n - (tn - bc) * 256 >= 8) {
                 // columns in the same way: wide outputs of few tile rows (1024 x 50304 x 4096, 788 tiles:
                 // three full rounds and 20 tiles: 482 -> 386 + 41 us)
@@ -1804,8 +1865,93 @@ bool gemm_mfma_group_supports(int count, const GemmArgs* g) {
 }
 
 namespace {
-int launch_group_tiled(int count, const GemmArgs* g, float* const* bsum, int overwrite, int tile, hipStream_t stream,
-                       bool first = true) {
+// A group on tiles of 256x256, its remainders of up to 128 rows or columns on halves of them, begun first, and what full rounds leave
+// over on quarters or halves, begun last.  Against 256x256 tiles throughout, with the last row bands of one product in a launch of
+// 128x128 tiles of its own: blocks of 1280, 1344, 1408, 1600 and 1792 at 2048 tokens 106 -> 101, 132 -> 114, 137 -> 123, 169 -> 157 and 207 -> 191 us;
+// of 1024, 1536 and 2048, which have neither remainders nor a rest, within 1 %.  gpt2-1p3b-n32 96.0 -> 93.6 ms.
+// (1) A remainder costs a half tile, not a whole one: a block of 1600 needs 450 + 82 halves instead of 532.
+// (2) All workgroups of a launch that starts with one size reach their epilogues together, and the chip then waits for HBM: 256 tiles of += x 64
+// take 25.5 us, 16 take 10.7.  Halves first put CUs out of step, and give CUs to the other lane of a replay at other times than the
+// rest: halves first -> last gpt2-1p3b-n32 94.2 -> 96.1 ms, six blocks of 1600 at 632 tokens, forward and backward, 1665 -> 1706 us.  Halving
+// whole tiles for it does not pay: a half takes 0.6 of a tile's time (2048 wide, 128 of 768 halved 222 -> 235 us).
+// (3) Up to 64 tiles beyond full rounds take a round of quarters, 0.38 of one of 256x256; more of them a round of halves where these and
+// the remainders' fit into one.
+int launch_group_mixed(int count, const GemmArgs* g, float* const* bsum, int overwrite, bool smaller, hipStream_t stream) {
+    int fm[GROUP_MAX], fn[GROUP_MAX], cut[GROUP_MAX] = {};      // tile rows and columns of 256x256, tile rows cut smaller
+    long full = 0, half = 0;
+    for (int i = 0; i < count; ++i) {
+        const int rm = g[i].m % 256, rn = g[i].n % 256;
+        fm[i] = g[i].m / 256 + (rm > (smaller ? 128 : 0));
+        fn[i] = g[i].n / 256 + (rn > (smaller ? 128 : 0));
+        full += (long)fm[i] * fn[i];
+        if (fm[i] * 256 < g[i].m) half += (g[i].n + 255) / 256;
+        if (fn[i] * 256 < g[i].n) half += fm[i];
+    }
+    const long over = smaller && full + half > NUM_CUS ? (full + half) % NUM_CUS : 0;
+    const bool quarters = 4 * over <= NUM_CUS;
+    const long left = full % NUM_CUS;                        // of the whole tiles alone
+    const bool fill = smaller && !quarters && full > NUM_CUS && half + 2 * left <= NUM_CUS;
+    long todo = fill ? left : over <= full && (quarters || (over > half && 2 * over <= NUM_CUS)) ? over : 0;
+    while (todo > 0) {
+        int best = -1;
+        long got = 0;
+        for (int i = 0; i < count; ++i) {
+            if (fm[i] == cut[i] || !fn[i]) continue;
+            const long t = std::min<long>(fm[i] - cut[i], (todo + fn[i] - 1) / fn[i]) * fn[i];
+            if (best < 0 || std::labs(t - todo) < std::labs(got - todo)) { best = i; got = t; }
+        }
+        if (best < 0) break;
+        cut[best] += (int)(got / fn[best]);
+        todo -= got;
+    }
+    MixedGroup grp{};
+    grp.k = g[0].k; grp.overwrite = overwrite ? 1 : 0;
+    std::fill(std::begin(grp.first), std::end(grp.first), INT_MAX);
+    int tiles = 0;
+    auto put = [&](int i, int form, int row0, int rows, int col0, int cols) {
+        if (rows <= 0 || cols <= 0) return;
+        const int bm = form == TILE_128x256 || form == TILE_128 ? 128 : 256, bn = form == TILE_256x128 || form == TILE_128 ? 128 : 256;
+        MixedEntry& e = grp.e[grp.count++];
+        e.a = (const bf16_t*)g[i].a + row0;                      // A is [k, m]
+        e.b = (const bf16_t*)g[i].b;
+        e.c = (float*)g[i].c + (size_t)row0 * g[i].n;
+        e.bsum = bsum && row0 == 0 ? bsum[i] : nullptr;
+        e.m = rows; e.n = g[i].n; e.lda = g[i].lda; e.ldb = g[i].ldb; e.col0 = col0;
+        e.tiles_m = (rows + bm - 1) / bm; e.tiles_n = (cols + bn - 1) / bn;
+        e.form = form; grp.first[&e - grp.e] = tiles;
+        tiles += e.tiles_m * e.tiles_n;
+    };
+    int local = 0;
+    auto close = [&](int h) {                                    // the entries put since the last call are phase h
+        MixedPhase& p = grp.phase[h];
+        p.first = h ? grp.phase[h - 1].first + grp.phase[h - 1].tiles : 0;
+        p.tiles = tiles - p.first; p.local = local; p.skew = p.first % XCDS;
+        local += (p.tiles + XCDS - 1) / XCDS;
+        for (int i = 0; i < grp.count; ++i) {
+            MixedEntry& e = grp.e[i];
+            if (grp.first[i] < p.first) continue;
+            const int bm = e.form == TILE_128x256 || e.form == TILE_128 ? 128 : 256, bn = e.form == TILE_256x128 || e.form == TILE_128 ? 128 : 256;
+            e.group_m = raster_group(e.tiles_m, e.tiles_n, std::min((p.tiles + XCDS - 1) / XCDS, PER_XCD), bm, bn);
+        }
+    };
+    // rows [0, whole) on 256x256 tiles, then those cut smaller, then the remainder; columns [0, cols) and their remainder
+    auto whole = [&](int i) { return std::min((fm[i] - cut[i]) * 256, g[i].m); };
+    auto rows = [&](int i) { return std::min(fm[i] * 256, g[i].m); };
+    auto cols = [&](int i) { return std::min(fn[i] * 256, g[i].n); };
+    for (int i = 0; i < count; ++i) put(i, TILE_128x256, rows(i), g[i].m - rows(i), 0, g[i].n);
+    for (int i = 0; i < count; ++i) put(i, TILE_256x128, 0, rows(i), cols(i), g[i].n - cols(i));
+    close(0);
+    for (int i = 0; i < count; ++i) put(i, TILE_256, 0, whole(i), 0, cols(i));
+    close(1);
+    for (int i = 0; i < count; ++i) put(i, quarters ? TILE_128 : TILE_128x256, whole(i), rows(i) - whole(i), 0, cols(i));
+    close(2);
+    note_group_kernel("gemm_bf16_mixed_group_kernel");
+    hipLaunchKernelGGL(gemm_bf16_mixed_group_kernel, dim3(local * XCDS), dim3(512), 0, stream, grp);
+    CHIMERA_LAUNCH_CHECK("bf16 gemm group");
+    return CHIMERA_OK;
+}
+
+int launch_group_tiled(int count, const GemmArgs* g, float* const* bsum, int overwrite, int tile, hipStream_t stream) {
     GemmGroup grp{};
     grp.count = count; grp.k = g[0].k; grp.overwrite = overwrite ? 1 : 0;
     int tiles = 0;
@@ -1819,73 +1965,32 @@ int launch_group_tiled(int count, const GemmArgs* g, float* const* bsum, int ove
     }
     for (int i = 0; i < count; ++i) grp.group_m[i] = raster_group(grp.tiles_m[i], grp.tiles_n[i], (tiles + 7) / 8, tile, tile);
     for (int i = count; i <= GROUP_MAX; ++i) grp.first[i] = tiles;
-    if (tile == 256) return launch_group_ring<256, 256, 2, 4, 1>(grp, stream);
-    if (tile == 64) return tiles <= NUM_CUS ? launch_group<64, 64, 2, 2, 2, 8, 2>(grp, stream, first) : launch_group<64, 64, 1, 2, 2, 4>(grp, stream, first);
+    if (tile == 64) return tiles <= NUM_CUS ? launch_group<64, 64, 2, 2, 2, 8, 2>(grp, stream) : launch_group<64, 64, 1, 2, 2, 4>(grp, stream);
     // two workgroups per CU or the k-sliced 8-wavefront form
     const int mode = tuning().async_mode;
     const bool ksplit = mode != ASYNC_AUTO ? mode == ASYNC_KSLICED : tiles <= NUM_CUS;
-    if (ksplit) return launch_group_ring<128, 128, 2, 2, 2>(grp, stream, first);
-    return launch_group_ring<128, 128, 2, 2, 1>(grp, stream, first);
+    if (ksplit) return launch_group_ring<128, 128, 2, 2, 2>(grp, stream);
+    return launch_group_ring<128, 128, 2, 2, 1>(grp, stream);
 }
 }  // namespace
 
-// Decides how a group goes out: tile size, and whether the last row bands of one product leave
-// as a second launch with 128x128 tiles (a nearly empty last round of 256x256 tiles).
-int gemm_mfma_group_plan(int count, const GemmArgs* g, GemmGroupPlan* plan) {
-    if (!plan) return fail(CHIMERA_EINVAL, "plan is NULL");
+int gemm_mfma_bf16_group(int count, const GemmArgs* g, float* const* bsum, int overwrite, void* stream) {
     if (!gemm_mfma_group_supports(count, g))
         return fail(CHIMERA_EINVAL, "bf16 gemm group: 1..%d float-accumulating products with index-contiguous operands, "
                     "one contraction length", GROUP_MAX);
-    static_assert(GROUP_MAX == sizeof(plan->head) / sizeof(plan->head[0]), "plan size");
-    plan->count = count; plan->has_tail = 0; plan->tail_of = -1;
-    for (int i = 0; i < count; ++i) plan->head[i] = g[i];
     // tile choice as for single products: 256x256 once such tiles occupy most of the chip, else
     // 128x128.  (192 tiles of 256x256 on 256 CUs beat 768 tiles of 128x128: they pull half the
     // bytes from L2 into LDS, which is what limits these kernels, and the CUs they leave free
     // serve the launches of the other stream.)
-    long t256 = 0;
-    for (int i = 0; i < count; ++i) t256 += (long)((g[i].m + 255) / 256) * ((g[i].n + 255) / 256);
-    const TileChoice forced = forced_tile();
-    long t64 = 0;
-    for (int i = 0; i < count; ++i) t64 += (long)((g[i].m + 63) / 64) * ((g[i].n + 63) / 64);
-    plan->tile = forced.bm == 256 || forced.bm == 128 ? forced.bm
-                 : t256 >= 160 ? 256 : small_tiles(t64) ? 64 : 128;
-    if (plan->tile != 256 || forced.bm) return CHIMERA_OK;
-    // a nearly empty last round: the last row bands of one product go to a 128x128 launch
-    int best_p = -1, best_b = 0;
-    double best_rounds = 1e30;
-    for (int p = 0; p < count; ++p) {
-        const int tm = (g[p].m + 255) / 256, tn = (g[p].n + 255) / 256;
-        const int b = bands_to_peel(t256 - (long)tm * tn, tm, tn, g[p].n);
-        if (!b || g[p].m - (tm - b) * 256 < 8) continue;
-        const double est = (double)((t256 - (long)b * tn + NUM_CUS - 1) / NUM_CUS) + 0.45 * (double)(((long)b * 2 * ((g[p].n + 127) / 128) + NUM_CUS - 1) / NUM_CUS);
-        if (est < best_rounds) { best_rounds = est; best_p = p; best_b = b; }
+    long t256 = 0, t64 = 0;
+    for (int i = 0; i < count; ++i) {
+        t256 += (long)((g[i].m + 255) / 256) * ((g[i].n + 255) / 256);
+        t64 += (long)((g[i].m + 63) / 64) * ((g[i].n + 63) / 64);
     }
-    if (best_p < 0) return CHIMERA_OK;
-    const size_t m0 = (size_t)((g[best_p].m + 255) / 256 - best_b) * 256;
-    plan->head[best_p].m = (int)m0;
-    plan->tail = g[best_p];
-    plan->tail.m = g[best_p].m - (int)m0;
-    plan->tail.a = (const char*)plan->tail.a + m0 * 2;                      // A is [k, m]: the band starts m0 columns in
-    plan->tail.c = (char*)plan->tail.c + m0 * plan->tail.n * sizeof(float);
-    plan->has_tail = 1; plan->tail_of = best_p;
-    return CHIMERA_OK;
-}
-
-int gemm_mfma_group_launch_head(const GemmGroupPlan& plan, float* const* bsum, int overwrite, void* stream) {
-    return launch_group_tiled(plan.count, plan.head, bsum, overwrite, plan.tile, (hipStream_t)stream);
-}
-
-int gemm_mfma_group_launch_tail(const GemmGroupPlan& plan, int overwrite, void* stream) {
-    if (!plan.has_tail) return CHIMERA_OK;
-    return launch_group_tiled(1, &plan.tail, nullptr, overwrite, 128, (hipStream_t)stream, false);   // the column sums come from the head
-}
-
-int gemm_mfma_bf16_group(int count, const GemmArgs* g, float* const* bsum, int overwrite, void* stream) {
-    GemmGroupPlan plan;
-    if (int rc = gemm_mfma_group_plan(count, g, &plan)) return rc;
-    if (int rc = gemm_mfma_group_launch_head(plan, bsum, overwrite, stream)) return rc;
-    return gemm_mfma_group_launch_tail(plan, overwrite, stream);
+    const int forced = forced_tile().bm;
+    const int tile = forced == 256 || forced == 128 ? forced : t256 >= 160 ? 256 : small_tiles(t64) ? 64 : 128;
+    if (tile == 256) return launch_group_mixed(count, g, bsum, overwrite, forced == 0, (hipStream_t)stream);
+    return launch_group_tiled(count, g, bsum, overwrite, tile, (hipStream_t)stream);
 }
 
 const char* gemm_mfma_last_group_kernel() { return g_last_group_kernel; }

@@ -269,26 +269,11 @@ int linear_wgrad(chimera_stage* st, int m, int n, int k, const void* x, const vo
 bool wgrad_group_ok(const chimera_stage* st, const GemmArgs (&g)[4]) {
     return st->kernels == 0 && (st->dtype == CHIMERA_BF16 ? gemm_mfma_group_supports(4, g) : gemm_f32_group_supports(4, g));
 }
-// One or two launches (the second takes the last row bands of one product on smaller tiles),
-// each timed as a class of its own so that a class is one kernel.
 int wgrad_group(chimera_stage* st, const GemmArgs (&g)[4], float* const (&db)[4], int overwrite, hipStream_t stream) {
-    if (st->dtype == CHIMERA_F32) {
-        double flop = 0;
-        for (int i = 0; i < 4; ++i) flop += 2.0 * g[i].m * g[i].n * g[i].k;
-        ProfScope prof(PC_GEMM_WGRAD, flop, stream);
-        return gemm_f32_group(4, g, db, overwrite, stream);
-    }
-    GemmGroupPlan plan;
-    TRY(gemm_mfma_group_plan(4, g, &plan));
     double flop = 0;
-    for (int i = 0; i < plan.count; ++i) flop += 2.0 * plan.head[i].m * plan.head[i].n * plan.head[i].k;
-    {
-        ProfScope prof(PC_GEMM_WGRAD, flop, stream);
-        TRY(gemm_mfma_group_launch_head(plan, db, overwrite, stream));
-    }
-    if (!plan.has_tail) return CHIMERA_OK;
-    ProfScope prof(PC_GEMM_WGRAD_TAIL, 2.0 * plan.tail.m * plan.tail.n * plan.tail.k, stream);
-    return gemm_mfma_group_launch_tail(plan, overwrite, stream);
+    for (int i = 0; i < 4; ++i) flop += 2.0 * g[i].m * g[i].n * g[i].k;
+    ProfScope prof(PC_GEMM_WGRAD, flop, stream);
+    return st->dtype == CHIMERA_F32 ? gemm_f32_group(4, g, db, overwrite, stream) : gemm_mfma_bf16_group(4, g, db, overwrite, stream);
 }
 
 // Performs a zeroing that chimera_stage_zero_grads deferred.

@@ -412,6 +412,30 @@ def test_bf16_groups(k, shapes):
         assert_close(to_np(bs) - 0.25, wb, b.BF16)
 
 
+# groups on tiles of several sizes: remainders of 64 and 8 rows and columns on half tiles, what a full round leaves over on quarters
+# (44 and 20 tiles) or halves (128), a product that is one half tile high; accumulating (column sums too) and overwriting
+@pytest.mark.parametrize("k", [64, 192, 320])
+@pytest.mark.parametrize("shapes", [[(5120, 1280), (1280, 5120), (1280, 1280), (1280, 3840)], [(6400, 1600), (1600, 6400), (1600, 1600), (1600, 4800)],
+                                    [(5376, 1344), (1344, 5376), (1344, 1344), (1344, 4032)], [(4104, 4104), (72, 2056), (2056, 72)]])
+def test_bf16_groups_of_mixed_tiles(k, shapes):
+    import torch
+    print("bf16 mixed group", k, shapes, flush=True)
+    gen = torch.Generator().manual_seed(k)
+    probs, sums, want = [], [], []
+    for m, n in shapes:
+        X, Y = (torch.randn((k, c), generator=gen).to(torch.bfloat16) for c in (m, n))
+        probs.append((X.cuda(), Y.cuda(), torch.full((m, n), float("nan"), device="cuda")))
+        sums.append(torch.full((n,), float("nan"), device="cuda"))
+        want.append((X.double().T @ Y.double(), Y.double().sum(0)))
+    for passes, overwrite in ((1, True), (2, False)):
+        b.chimera_op_gemm_group_accumulate(probs, k, sums, overwrite=overwrite)
+        for (_, _, c), bs, (wc, wb) in zip(probs, sums, want):
+            # exact products of bf16 numbers, summed in float: k roundings of sums of the order of sqrt(k), once more when added
+            tol = 2.0 ** -24 * k * passes * 8
+            assert float((c.cpu().double() / passes - wc).abs().max()) <= tol * float(wc.abs().max())
+            assert float((bs.cpu().double() / passes - wb).abs().max()) <= tol * float(wb.abs().max())
+
+
 # token counts that are no multiple of the contraction steps, and gradients that start from anything
 @pytest.mark.parametrize("dtype,hidden,heads,seq,microbatch", [(b.F32, 64, 2, 75, 1), (b.F32, 136, 2, 37, 3), (b.F32, 256, 4, 130, 2),
                                                                  (b.BF16, 128, 2, 75, 1), (b.BF16, 136, 1, 37, 3), (b.BF16, 560, 7, 99, 1),
