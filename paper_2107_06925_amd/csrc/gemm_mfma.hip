@@ -179,6 +179,9 @@ template <int TM, int TN> struct Acc16 {
     }
 };
 
+// `epi_flag` of the float accumulate: the result replaces C, which is not read; C passes the caches by.
+enum { ACCUM_OVERWRITE = 1, ACCUM_ONCE = 2 };
+
 __device__ __forceinline__ void load8(const bf16_t* p, float* o) { load_vec<bf16_t>(p, o); }
 __device__ __forceinline__ void load8(const float* p, float* o) { load_vec<float>(p, o); load_vec<float>(p + 4, o + 4); }
 __device__ __forceinline__ void store8(bf16_t* p, const float* v) { store_vec<bf16_t>(p, v); }
@@ -190,6 +193,7 @@ template <typename T> struct Raw8;
 template <> struct Raw8<bf16_t> {
     uint4 q;
     __device__ __forceinline__ void load(const bf16_t* p) { q = *reinterpret_cast<const uint4*>(p); }
+    __device__ __forceinline__ void load_once(const bf16_t* p) { load(p); }
     __device__ __forceinline__ void unpack(float* o) const {
         const unsigned w[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
@@ -200,6 +204,10 @@ template <> struct Raw8<float> {
     float4 lo, hi;
     __device__ __forceinline__ void load(const float* p) {
         lo = *reinterpret_cast<const float4*>(p); hi = *reinterpret_cast<const float4*>(p + 4);
+    }
+    __device__ __forceinline__ void load_once(const float* p) {
+        lo = __builtin_bit_cast(float4, __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p)));
+        hi = __builtin_bit_cast(float4, __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p + 4)));
     }
     __device__ __forceinline__ void unpack(float* o) const {
         o[0] = lo.x; o[1] = lo.y; o[2] = lo.z; o[3] = lo.w; o[4] = hi.x; o[5] = hi.y; o[6] = hi.z; o[7] = hi.w;
@@ -224,7 +232,7 @@ template <int TN> struct EpiAhead {
         const int pr = lane / CPR, lcol = min(col_base + lane % CPR * 8, n - 8);
         if (epi == EPI_BIAS || epi == EPI_BIAS_GELU || epi == EPI_BIAS_RESIDUAL) bias = *reinterpret_cast<const uint4*>(b + lcol);
         const bool f32 = epi == EPI_ACCUM_F32 || (epi == EPI_BIAS_RESIDUAL && (res_types & 1));
-        if (epi != EPI_BIAS_RESIDUAL && epi != EPI_DGELU && !(epi == EPI_ACCUM_F32 && !epi_flag)) return;
+        if (epi != EPI_BIAS_RESIDUAL && epi != EPI_DGELU && !(epi == EPI_ACCUM_F32 && !(epi_flag & ACCUM_OVERWRITE))) return;
         const char* src = epi == EPI_ACCUM_F32 ? (const char*)c : (const char*)r;
 #pragma unroll
         for (int j = 0; j < NP; ++j) {
@@ -251,7 +259,7 @@ __device__ __forceinline__ void epilogue(const Acc& acc, float* slab, int row_ba
     float* Cf = (float*)c;
     const int pr = lane / CPR, pc = (lane % CPR) * 8;
     const int gcol = col_base + pc;
-    const bool reads = READS && !(EPI == EPI_ACCUM_F32 && epi_flag);      // an overwriting accumulate reads nothing
+    const bool reads = READS && !(EPI == EPI_ACCUM_F32 && (epi_flag & ACCUM_OVERWRITE));      // an overwriting accumulate reads nothing
     const RT* Rsrc = EPI == EPI_ACCUM_F32 ? reinterpret_cast<const RT*>(c) : reinterpret_cast<const RT*>(R);
     // pieces outside the matrix are requested from its last row / last piece (never used)
     const int lcol = min(gcol, n - 8);
@@ -261,7 +269,9 @@ __device__ __forceinline__ void epilogue(const Acc& acc, float* slab, int row_ba
 #pragma unroll
         for (int j = 0; j < NP; ++j) {
             const int grow = min(row_base + a * 32 + j * RPP + pr, m - 1);
-            ahead[SLOT][j].load(Rsrc + (size_t)grow * n + lcol);
+            const RT* from = Rsrc + (size_t)grow * n + lcol;
+            if (EPI == EPI_ACCUM_F32 && (epi_flag & ACCUM_ONCE)) ahead[SLOT][j].load_once(from);
+            else ahead[SLOT][j].load(from);
         }
     };
     float bv[8];
@@ -343,7 +353,12 @@ __device__ __forceinline__ void epilogue(const Acc& acc, float* slab, int row_ba
             } else {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) v[e] += rv[e];    // rv = 0 when the result replaces C
-                store8(Cf + idx, v);
+                if (epi_flag & ACCUM_ONCE) {
+                    __builtin_nontemporal_store(f32x4{v[0], v[1], v[2], v[3]}, reinterpret_cast<f32x4*>(Cf + idx));
+                    __builtin_nontemporal_store(f32x4{v[4], v[5], v[6], v[7]}, reinterpret_cast<f32x4*>(Cf + idx + 4));
+                } else {
+                    store8(Cf + idx, v);
+                }
             }
         }
         __builtin_amdgcn_wave_barrier();                      // all lanes have read the slab before it is rewritten
@@ -791,7 +806,7 @@ __device__ __forceinline__ void gemm_async_tile(
 #pragma unroll
             for (int b = 0; b < TN; ++b) {
                 const int col = cb0 + b * 32 + lane;
-                if (col < n) bsum[col] = epi_flag ? v[b] : bsum[col] + v[b];
+                if (col < n) bsum[col] = (epi_flag & ACCUM_OVERWRITE) ? v[b] : bsum[col] + v[b];
             }
     };
     if constexpr (TM == 1) {
@@ -1233,7 +1248,7 @@ __device__ __forceinline__ void gemm_ring_tile(
 #pragma unroll
         for (int b = 0; b < TN; ++b) {
             const int col = cb0 + b * 16 + lane;
-            if (lane < 16 && col < n) bsum[col] = epi_flag ? v[b] : bsum[col] + v[b];
+            if (lane < 16 && col < n) bsum[col] = (epi_flag & ACCUM_OVERWRITE) ? v[b] : bsum[col] + v[b];
         }
     };
     float* slab = reinterpret_cast<float*>(lds) + (size_t)wave * EpiSlab<TN / 2>::FLOATS;
@@ -1429,7 +1444,7 @@ struct MixedPhase {
 struct MixedGroup {
     MixedPhase phase[MIXED_PHASES];
     int first[MIXED_MAX];            // number of an entry's first tile, all laid end to end (INT_MAX behind the last entry)
-    int count, k, overwrite;
+    int count, k, flags;             // flags: ACCUM_*
     MixedEntry e[MIXED_MAX];
 };
 
@@ -1454,7 +1469,7 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_mixed_group_kernel(MixedGrou
     const int tile = gid - grp.first[i];
 #define CHIMERA_MIXED(...)                                                                                                  \
     gemm_ring_tile<__VA_ARGS__, false, false, EPI_ACCUM_F32>(lds, e.a, e.b, nullptr, nullptr, e.c, nullptr, e.m, e.n, grp.k, \
-        e.lda, e.ldb, EPI_ACCUM_F32, grp.overwrite, 0, e.tiles_m, e.tiles_n, e.group_m, tile, e.bsum, false, e.col0)
+        e.lda, e.ldb, EPI_ACCUM_F32, grp.flags, 0, e.tiles_m, e.tiles_n, e.group_m, tile, e.bsum, false, e.col0)
     if (e.form == TILE_256) CHIMERA_MIXED(256, 256, 2, 4, 1);
     else if (e.form == TILE_128x256) CHIMERA_MIXED(128, 256, 1, 4, 2);
     else if (e.form == TILE_256x128) CHIMERA_MIXED(256, 128, 2, 2, 2);
@@ -1509,8 +1524,8 @@ int raster_group(int tiles_m, int tiles_n, int per_xcd, int bm, int bn) {
 struct TileChoice { int bm, bn, splits; };
 
 // The kernels' `epi_flag` argument modifies the epilogue: for the GeLU epilogues 1 selects the
-// erf form (0: tanh form); for the float-accumulate epilogue 1 makes the result replace C (and
-// the column sums replace bsum) instead of being added, which a single product never asks for.
+// erf form (0: tanh form); for the float-accumulate epilogue it holds ACCUM_* flags, none in a single product
+// (ACCUM_OVERWRITE: the column sums replace bsum too).
 inline int epilogue_flag(const GemmArgs& g) { return g.epilogue == EPI_ACCUM_F32 ? 0 : g.gelu_erf; }
 
 inline Ahead ahead_of(const GemmArgs& g) { return {(const char*)g.ahead, (unsigned)g.ahead_bytes}; }
@@ -1905,7 +1920,7 @@ int launch_group_mixed(int count, const GemmArgs* g, float* const* bsum, int ove
         todo -= got;
     }
     MixedGroup grp{};
-    grp.k = g[0].k; grp.overwrite = overwrite ? 1 : 0;
+    grp.k = g[0].k; grp.flags = (overwrite ? ACCUM_OVERWRITE : 0) | (g[0].c_once ? ACCUM_ONCE : 0);
     std::fill(std::begin(grp.first), std::end(grp.first), INT_MAX);
     int tiles = 0;
     auto put = [&](int i, int form, int row0, int rows, int col0, int cols) {

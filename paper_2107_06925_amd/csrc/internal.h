@@ -63,6 +63,7 @@ struct GemmArgs {
     int gelu_erf;
     int beside;                         // work of other streams shares the chip with this launch
     const void* ahead; size_t ahead_bytes;   // what the next product reads from HBM (null: nothing), below 4 GiB: a hint (bf16 matrix-core path)
+    int c_once;                         // EPI_ACCUM_F32 in a group: C is next read when it will have left the memory-side cache (a hint)
     void* ws;                           // optional split-K workspace (bf16 matrix-core path), may be null
     size_t ws_bytes;
 };
