@@ -335,7 +335,7 @@ __device__ __forceinline__ void epilogue(const Acc& acc, float* slab, int row_ba
 #pragma unroll
                     for (int e = 0; e < 8; ++e) g[e] = gelu_f(v[e], 0);
                 }
-                store8(C + idx, v);
+                if (C) store8(C + idx, v);                    // null: nobody reads it
                 store8(C2 + idx, g);
             } else if constexpr (EPI == EPI_BIAS_RESIDUAL) {
 #pragma unroll
@@ -1527,6 +1527,9 @@ struct TileChoice { int bm, bn, splits; };
 // erf form (0: tanh form); for the float-accumulate epilogue it holds ACCUM_* flags, none in a single product
 // (ACCUM_OVERWRITE: the column sums replace bsum too).
 inline int epilogue_flag(const GemmArgs& g) { return g.epilogue == EPI_ACCUM_F32 ? 0 : g.gelu_erf; }
+// A forward that keeps nothing leaves out u, half of what the first product of an MLP writes: six blocks of 1600 at 1264 tokens
+// 775 -> 761 us, bert48 with doubled forwards 52.1 -> 51.4 ms.
+inline void* result(const GemmArgs& g) { return g.epilogue == EPI_BIAS_GELU && g.c_unused ? nullptr : g.c; }
 
 inline Ahead ahead_of(const GemmArgs& g) { return {(const char*)g.ahead, (unsigned)g.ahead_bytes}; }
 
@@ -1643,7 +1646,7 @@ int launch_layout(const GemmArgs& g, int splits, hipStream_t s) {
     float* slabs = g.ws ? (float*)((char*)g.ws + SPLITK_COUNTER_BYTES) : nullptr;
 #define CHIMERA_GEMM_LAUNCH(AKC, BKC)                                                                              \
     hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WGM, WGN, PF, AKC, BKC>), grid, block, 0, s, (const bf16_t*)g.a,  \
-                       (const bf16_t*)g.b, (const bf16_t*)g.bias, (const bf16_t*)g.r, g.c, (bf16_t*)g.c2, g.m, g.n, \
+                       (const bf16_t*)g.b, (const bf16_t*)g.bias, (const bf16_t*)g.r, result(g), (bf16_t*)g.c2, g.m, g.n, \
                        g.k, g.lda, g.ldb, g.epilogue, epilogue_flag(g), (g.r_f32 ? 1 : 0) | (g.c_f32 ? 2 : 0), tm, tn,    \
                        splits, slabs, arrivals)
     if (g.a_kc && !g.b_kc) CHIMERA_GEMM_LAUNCH(true, false);
@@ -1661,7 +1664,7 @@ int launch_async(const GemmArgs& g, hipStream_t s) {
     const int gm = raster_group(tm, tn, (tm * tn + 7) / 8, BM, BN);
 #define CHIMERA_GEMM_LAUNCH(AKC, BKC)                                                                                \
     hipLaunchKernelGGL((gemm_bf16_async_kernel<BM, BN, WGM, WGN, WGK, NS, SPS, AKC, BKC>), grid, block, 0, s,                   \
-                       (const bf16_t*)g.a, (const bf16_t*)g.b, (const bf16_t*)g.bias, (const bf16_t*)g.r, g.c,        \
+                       (const bf16_t*)g.a, (const bf16_t*)g.b, (const bf16_t*)g.bias, (const bf16_t*)g.r, result(g), \
                        (bf16_t*)g.c2, g.m, g.n, g.k, g.lda, g.ldb, g.epilogue, epilogue_flag(g),                            \
                        (g.r_f32 ? 1 : 0) | (g.c_f32 ? 2 : 0), tm, tn, gm, ahead_of(g))
     if (g.a_kc && !g.b_kc) CHIMERA_GEMM_LAUNCH(true, false);
@@ -1681,7 +1684,7 @@ int launch_ring(const GemmArgs& g, hipStream_t s, int col0 = 0, int cols256 = 0)
     const int gm = raster_group(tm, tn, (tm * tn + 7) / 8, BM, BN);
 #define CHIMERA_GEMM_LAUNCH(AKC, BKC)                                                                                \
     hipLaunchKernelGGL((gemm_bf16_ring_kernel<BM, BN, WGM, WGN, WGK, AKC, BKC>), grid, block, 0, s,                     \
-                       (const bf16_t*)g.a, (const bf16_t*)g.b, (const bf16_t*)g.bias, (const bf16_t*)g.r, g.c,        \
+                       (const bf16_t*)g.a, (const bf16_t*)g.b, (const bf16_t*)g.bias, (const bf16_t*)g.r, result(g), \
                        (bf16_t*)g.c2, g.m, g.n, g.k, g.lda, g.ldb, g.epilogue, epilogue_flag(g),                            \
                        (g.r_f32 ? 1 : 0) | (g.c_f32 ? 2 : 0), tm, tn, gm, col0, ahead_of(g))
     if (g.a_kc && !g.b_kc) CHIMERA_GEMM_LAUNCH(true, false);

@@ -63,7 +63,9 @@ struct GemmArgs {
     int gelu_erf;
     int beside;                         // work of other streams shares the chip with this launch
     const void* ahead; size_t ahead_bytes;   // what the next product reads from HBM (null: nothing), below 4 GiB: a hint (bf16 matrix-core path)
-    int c_once;                         // EPI_ACCUM_F32 in a group: C is next read when it will have left the memory-side cache (a hint)
+    // Hints to the bf16 matrix-core path.  c_once: C of a group's EPI_ACCUM_F32 is next read when it will have left the memory-side
+    // cache; c_unused: nobody reads C of EPI_BIAS_GELU, which then keeps what it holds
+    int c_once, c_unused;
     void* ws;                           // optional split-K workspace (bf16 matrix-core path), may be null
     size_t ws_bytes;
 };

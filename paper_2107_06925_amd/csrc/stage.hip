@@ -243,6 +243,7 @@ int linear_fwd(chimera_stage* st, int m, int n, int k, const void* x, const void
     g.b = w; g.ldb = n; g.b_kc = 0;
     g.bias = bias; g.r = r; g.c = c; g.c2 = c2; g.epilogue = epi; g.gelu_erf = st->gelu_erf;
     g.r_f32 = r_f32; g.c_f32 = c_f32;
+    g.c_unused = !st->keep;
     return gemm(st, g, PC_GEMM_FWD, st->stream);
 }
 // dX[m,k] = dY[m,n] W^T, W stored [k, n]: contraction over n, contiguous in both.
