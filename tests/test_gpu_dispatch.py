@@ -393,6 +393,24 @@ def test_bf16_middle_tiles(m, n, k, layout):
     test_bf16_small_gemm(m, n, k, layout)
 
 
+# launches of several rounds: 256x256 tiles with a partly filled last round (561, 873 and 792 tiles), 128x128 tiles two per CU (572)
+@pytest.mark.parametrize("m,n,k", [(4104, 8200, 72), (2056, 24584, 64), (5640, 9216, 72), (2816, 3328, 72)])
+@pytest.mark.parametrize("layout", ["fwd", "dgrad", "wgrad"])
+def test_bf16_products_of_several_rounds(m, n, k, layout):
+    import torch
+    print("bf16 rounds", m, n, k, layout, flush=True)
+    a_kc, b_kc = {"fwd": (1, 0), "dgrad": (1, 1), "wgrad": (0, 0)}[layout]
+    gen = torch.Generator().manual_seed(m)
+    A, B = torch.randn((m, k), generator=gen).to(torch.bfloat16), torch.randn((k, n), generator=gen).to(torch.bfloat16)
+    want = A.double() @ B.double()
+    da, db = (A if a_kc else A.T.contiguous()).cuda(), (B.T.contiguous() if b_kc else B).cuda()
+    dc = torch.full((m, n), 0.0 if layout == "wgrad" else float("nan"), dtype=torch.float32 if layout == "wgrad" else torch.bfloat16, device="cuda")
+    b.chimera_op_gemm(da, db, dc, m, n, k, a_kc, b_kc, b.EPI_ACCUM_F32 if layout == "wgrad" else b.EPI_NONE)
+    # float sums of k exact products, and one rounding to bf16
+    tol = 2.0 ** -24 * k * 8 + (0 if layout == "wgrad" else 2.0 ** -8)
+    assert float((dc.cpu().double() - want).abs().max()) <= tol * float(want.abs().max())
+
+
 # grouped weight gradients with column sums on 256x256 tiles and on both forms of 128x128 tiles
 @pytest.mark.parametrize("k", [64, 128, 192, 320, 576])
 @pytest.mark.parametrize("shapes", [[(1032, 1544), (2056, 1032), (1032, 2312), (1032, 1288)], [(1032, 1544), (1032, 520)],
