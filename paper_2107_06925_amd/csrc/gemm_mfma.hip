@@ -1438,7 +1438,7 @@ __global__ __launch_bounds__(WGM* WGN * WGK * 64) void gemm_bf16_async_group_ker
 // its L2 and, between the XCDs, in the memory-side cache (one range of the whole phase per XCD: block of 2048 at k = 512 121 -> 128 us, of
 // 1920 at 2048 204 -> 220; one range of each product's tiles: block of 1280 at 2048 104 -> 128).
 enum TileForm { TILE_256, TILE_128x256, TILE_256x128, TILE_128 };
-constexpr int MIXED_MAX = 4 * GROUP_MAX;
+constexpr int MIXED_MAX = 5 * GROUP_MAX;
 struct MixedEntry {
     const bf16_t *a, *b;
     float *c, *bsum;
@@ -1730,6 +1730,102 @@ int launch_group(const GemmGroup& grp, hipStream_t s) {
     return CHIMERA_OK;
 }
 
+// A group on tiles of 256x256, its remainders of up to 128 rows or columns on halves of them, begun first, and what full rounds leave
+// over on quarters or halves, begun last.  Against 256x256 tiles throughout, with the last row bands of one product in a launch of
+// 128x128 tiles of its own: blocks of 1280, 1344, 1408, 1600 and 1792 at 2048 tokens 106 -> 101, 132 -> 114, 137 -> 123, 169 -> 157 and 207 -> 191 us;
+// of 1024, 1536 and 2048, which have neither remainders nor a rest, within 1 %.  gpt2-1p3b-n32 96.0 -> 93.6 ms.
+// (1) A remainder costs a half tile, not a whole one: a block of 1600 needs 450 + 82 halves instead of 532.
+// (2) All workgroups of a launch that starts with one size reach their epilogues together, and the chip then waits for HBM: 256 tiles of += x 64
+// take 25.5 us, 16 take 10.7.  Halves first put CUs out of step, and give CUs to the other lane of a replay at other times than the
+// rest: halves first -> last gpt2-1p3b-n32 94.2 -> 96.1 ms, six blocks of 1600 at 632 tokens, forward and backward, 1665 -> 1706 us.  Halving
+// whole tiles for it does not pay: a half takes 0.6 of a tile's time (2048 wide, 128 of 768 halved 222 -> 235 us).
+// (3) Up to 64 tiles beyond full rounds take a round of quarters, 0.38 of one of 256x256; more of them a round of halves where these and
+// the remainders' fit into one.
+int launch_group_mixed(int count, const GemmArgs* g, float* const* bsum, int overwrite, bool smaller, hipStream_t stream) {
+    int fm[GROUP_MAX], fn[GROUP_MAX], cut_m[GROUP_MAX] = {}, cut_n[GROUP_MAX] = {};      // tile rows and columns of 256x256, how many of each are cut smaller
+    long full = 0, half = 0;
+    for (int i = 0; i < count; ++i) {
+        const int rm = g[i].m % 256, rn = g[i].n % 256;
+        fm[i] = g[i].m / 256 + (rm > (smaller ? 128 : 0));
+        fn[i] = g[i].n / 256 + (rn > (smaller ? 128 : 0));
+        full += (long)fm[i] * fn[i];
+        if (fm[i] * 256 < g[i].m) half += (g[i].n + 255) / 256;
+        if (fn[i] * 256 < g[i].n) half += fm[i];
+    }
+    const long over = smaller && full + half > NUM_CUS ? (full + half) % NUM_CUS : 0;
+    const bool quarters = 4 * over <= NUM_CUS;
+    const long left = full % NUM_CUS;                        // of the whole tiles alone
+    const bool fill = smaller && !quarters && full > NUM_CUS && half + 2 * left <= NUM_CUS;
+    long todo = fill ? left : over <= full && (quarters || (over > half && 2 * over <= NUM_CUS)) ? over : 0;
+    const long most = quarters ? NUM_CUS / 4 : (NUM_CUS - (fill ? half : 0)) / 2;
+    while (todo > 0) {                                           // whole bands of rows or columns, as many tiles as come nearest
+        int best = -1;
+        bool by_rows = true;
+        long got = 0, bands = 0;
+        auto offer = [&](int i, bool rows, long left_over, long per) {
+            if (left_over <= 0 || per <= 0) return;
+            const long n = std::min(left_over, (todo + per - 1) / per), t = n * per;
+            if (t <= most && (best < 0 || std::labs(t - todo) < std::labs(got - todo))) { best = i; by_rows = rows; got = t; bands = n; }
+        };
+        for (int i = 0; i < count; ++i) {
+            offer(i, true, fm[i] - cut_m[i], fn[i] - cut_n[i]);
+            offer(i, false, fn[i] - cut_n[i], fm[i] - cut_m[i]);
+        }
+        if (best < 0) break;
+        (by_rows ? cut_m : cut_n)[best] += (int)bands;
+        todo -= got;
+    }
+    MixedGroup grp{};
+    grp.k = g[0].k; grp.flags = (overwrite ? ACCUM_OVERWRITE : 0) | (g[0].c_once ? ACCUM_ONCE : 0);
+    std::fill(std::begin(grp.first), std::end(grp.first), INT_MAX);
+    int tiles = 0;
+    auto put = [&](int i, int form, int row0, int rows, int col0, int cols) {
+        if (rows <= 0 || cols <= 0) return;
+        const int bm = form == TILE_128x256 || form == TILE_128 ? 128 : 256, bn = form == TILE_256x128 || form == TILE_128 ? 128 : 256;
+        MixedEntry& e = grp.e[grp.count++];
+        e.a = (const bf16_t*)g[i].a + row0;                      // A is [k, m]
+        e.b = (const bf16_t*)g[i].b;
+        e.c = (float*)g[i].c + (size_t)row0 * g[i].n;
+        e.bsum = bsum && row0 == 0 ? bsum[i] : nullptr;
+        e.m = rows; e.n = g[i].n; e.lda = g[i].lda; e.ldb = g[i].ldb; e.col0 = col0;
+        e.tiles_m = (rows + bm - 1) / bm; e.tiles_n = (cols + bn - 1) / bn;
+        e.form = form; grp.first[&e - grp.e] = tiles;
+        tiles += e.tiles_m * e.tiles_n;
+    };
+    int local = 0;
+    auto close = [&](int h) {                                    // the entries put since the last call are phase h
+        MixedPhase& p = grp.phase[h];
+        p.first = h ? grp.phase[h - 1].first + grp.phase[h - 1].tiles : 0;
+        p.tiles = tiles - p.first; p.local = local; p.skew = p.first % XCDS;
+        local += (p.tiles + XCDS - 1) / XCDS;
+        for (int i = 0; i < grp.count; ++i) {
+            MixedEntry& e = grp.e[i];
+            if (grp.first[i] < p.first) continue;
+            const int bm = e.form == TILE_128x256 || e.form == TILE_128 ? 128 : 256, bn = e.form == TILE_256x128 || e.form == TILE_128 ? 128 : 256;
+            e.group_m = raster_group(e.tiles_m, e.tiles_n, std::min((p.tiles + XCDS - 1) / XCDS, PER_XCD), bm, bn);
+        }
+    };
+    // rows [0, whole_m) of columns [0, whole_n) on 256x256 tiles, up to `rows` and `cols` cut smaller, then the remainders
+    auto rows = [&](int i) { return std::min(fm[i] * 256, g[i].m); };
+    auto cols = [&](int i) { return std::min(fn[i] * 256, g[i].n); };
+    auto whole_m = [&](int i) { return std::min((fm[i] - cut_m[i]) * 256, g[i].m); };
+    auto whole_n = [&](int i) { return std::min((fn[i] - cut_n[i]) * 256, g[i].n); };
+    for (int i = 0; i < count; ++i) put(i, TILE_128x256, rows(i), g[i].m - rows(i), 0, g[i].n);
+    for (int i = 0; i < count; ++i) put(i, TILE_256x128, 0, rows(i), cols(i), g[i].n - cols(i));
+    close(0);
+    for (int i = 0; i < count; ++i) put(i, TILE_256, 0, whole_m(i), 0, whole_n(i));
+    close(1);
+    for (int i = 0; i < count; ++i) {
+        put(i, quarters ? TILE_128 : TILE_128x256, whole_m(i), rows(i) - whole_m(i), 0, whole_n(i));
+        put(i, quarters ? TILE_128 : TILE_256x128, 0, rows(i), whole_n(i), cols(i) - whole_n(i));
+    }
+    close(2);
+    note_group_kernel("gemm_bf16_mixed_group_kernel");
+    hipLaunchKernelGGL(gemm_bf16_mixed_group_kernel, dim3(local * XCDS), dim3(512), 0, stream, grp);
+    CHIMERA_LAUNCH_CHECK("bf16 gemm group");
+    return CHIMERA_OK;
+}
+
 }  // namespace
 
 bool gemm_mfma_supports(const GemmArgs& g) {
@@ -1775,13 +1871,14 @@ int gemm_mfma_bf16(const GemmArgs& g, void* stream) {
     const bool can_async = t.splits == 1 && mode != ASYNC_OFF && !far;
     if (can_async) {
         if (t.bm == 256 && t.bn == 256) {
+            if (!g.a_kc && g.epilogue == EPI_ACCUM_F32) return launch_group_mixed(1, &g, nullptr, 0, forced_tile().bm == 0, s);
             const int tm = (g.m + 255) / 256, tn = (g.n + 255) / 256;
             double by_rows = 0, by_columns = 0;
             const int b = forced_tile().bm ? 0 : bands_to_peel(tm, tn, g.n, &by_rows);
             const int bc = forced_tile().bm ? 0 : bands_to_peel(tn, tm, g.m, &by_columns);
             if (bc > 0 && by_columns < by_rows && g.n - (tn - bc) * 256 >= 8) {
                 // columns in the same way: wide outputs of few tile rows (1024 x 50304 x 4096, 788 tiles:
-                // three full rounds and 20 tiles: 482 -> 386 + 41 us)
+                // three full rounds and 20 tiles: 386 -> 344 us)
                 const int col0 = (tn - bc) * 256;
                 GemmArgs head = g;
                 head.ahead = nullptr; head.ahead_bytes = 0;
@@ -1893,92 +1990,6 @@ bool gemm_mfma_group_supports(int count, const GemmArgs* g) {
 }
 
 namespace {
-// A group on tiles of 256x256, its remainders of up to 128 rows or columns on halves of them, begun first, and what full rounds leave
-// over on quarters or halves, begun last.  Against 256x256 tiles throughout, with the last row bands of one product in a launch of
-// 128x128 tiles of its own: blocks of 1280, 1344, 1408, 1600 and 1792 at 2048 tokens 106 -> 101, 132 -> 114, 137 -> 123, 169 -> 157 and 207 -> 191 us;
-// of 1024, 1536 and 2048, which have neither remainders nor a rest, within 1 %.  gpt2-1p3b-n32 96.0 -> 93.6 ms.
-// (1) A remainder costs a half tile, not a whole one: a block of 1600 needs 450 + 82 halves instead of 532.
-// (2) All workgroups of a launch that starts with one size reach their epilogues together, and the chip then waits for HBM: 256 tiles of += x 64
-// take 25.5 us, 16 take 10.7.  Halves first put CUs out of step, and give CUs to the other lane of a replay at other times than the
-// rest: halves first -> last gpt2-1p3b-n32 94.2 -> 96.1 ms, six blocks of 1600 at 632 tokens, forward and backward, 1665 -> 1706 us.  Halving
-// whole tiles for it does not pay: a half takes 0.6 of a tile's time (2048 wide, 128 of 768 halved 222 -> 235 us).
-// (3) Up to 64 tiles beyond full rounds take a round of quarters, 0.38 of one of 256x256; more of them a round of halves where these and
-// the remainders' fit into one.
-int launch_group_mixed(int count, const GemmArgs* g, float* const* bsum, int overwrite, bool smaller, hipStream_t stream) {
-    int fm[GROUP_MAX], fn[GROUP_MAX], cut[GROUP_MAX] = {};      // tile rows and columns of 256x256, tile rows cut smaller
-    long full = 0, half = 0;
-    for (int i = 0; i < count; ++i) {
-        const int rm = g[i].m % 256, rn = g[i].n % 256;
-        fm[i] = g[i].m / 256 + (rm > (smaller ? 128 : 0));
-        fn[i] = g[i].n / 256 + (rn > (smaller ? 128 : 0));
-        full += (long)fm[i] * fn[i];
-        if (fm[i] * 256 < g[i].m) half += (g[i].n + 255) / 256;
-        if (fn[i] * 256 < g[i].n) half += fm[i];
-    }
-    const long over = smaller && full + half > NUM_CUS ? (full + half) % NUM_CUS : 0;
-    const bool quarters = 4 * over <= NUM_CUS;
-    const long left = full % NUM_CUS;                        // of the whole tiles alone
-    const bool fill = smaller && !quarters && full > NUM_CUS && half + 2 * left <= NUM_CUS;
-    long todo = fill ? left : over <= full && (quarters || (over > half && 2 * over <= NUM_CUS)) ? over : 0;
-    while (todo > 0) {
-        int best = -1;
-        long got = 0;
-        for (int i = 0; i < count; ++i) {
-            if (fm[i] == cut[i] || !fn[i]) continue;
-            const long t = std::min<long>(fm[i] - cut[i], (todo + fn[i] - 1) / fn[i]) * fn[i];
-            if (best < 0 || std::labs(t - todo) < std::labs(got - todo)) { best = i; got = t; }
-        }
-        if (best < 0) break;
-        cut[best] += (int)(got / fn[best]);
-        todo -= got;
-    }
-    MixedGroup grp{};
-    grp.k = g[0].k; grp.flags = (overwrite ? ACCUM_OVERWRITE : 0) | (g[0].c_once ? ACCUM_ONCE : 0);
-    std::fill(std::begin(grp.first), std::end(grp.first), INT_MAX);
-    int tiles = 0;
-    auto put = [&](int i, int form, int row0, int rows, int col0, int cols) {
-        if (rows <= 0 || cols <= 0) return;
-        const int bm = form == TILE_128x256 || form == TILE_128 ? 128 : 256, bn = form == TILE_256x128 || form == TILE_128 ? 128 : 256;
-        MixedEntry& e = grp.e[grp.count++];
-        e.a = (const bf16_t*)g[i].a + row0;                      // A is [k, m]
-        e.b = (const bf16_t*)g[i].b;
-        e.c = (float*)g[i].c + (size_t)row0 * g[i].n;
-        e.bsum = bsum && row0 == 0 ? bsum[i] : nullptr;
-        e.m = rows; e.n = g[i].n; e.lda = g[i].lda; e.ldb = g[i].ldb; e.col0 = col0;
-        e.tiles_m = (rows + bm - 1) / bm; e.tiles_n = (cols + bn - 1) / bn;
-        e.form = form; grp.first[&e - grp.e] = tiles;
-        tiles += e.tiles_m * e.tiles_n;
-    };
-    int local = 0;
-    auto close = [&](int h) {                                    // the entries put since the last call are phase h
-        MixedPhase& p = grp.phase[h];
-        p.first = h ? grp.phase[h - 1].first + grp.phase[h - 1].tiles : 0;
-        p.tiles = tiles - p.first; p.local = local; p.skew = p.first % XCDS;
-        local += (p.tiles + XCDS - 1) / XCDS;
-        for (int i = 0; i < grp.count; ++i) {
-            MixedEntry& e = grp.e[i];
-            if (grp.first[i] < p.first) continue;
-            const int bm = e.form == TILE_128x256 || e.form == TILE_128 ? 128 : 256, bn = e.form == TILE_256x128 || e.form == TILE_128 ? 128 : 256;
-            e.group_m = raster_group(e.tiles_m, e.tiles_n, std::min((p.tiles + XCDS - 1) / XCDS, PER_XCD), bm, bn);
-        }
-    };
-    // rows [0, whole) on 256x256 tiles, then those cut smaller, then the remainder; columns [0, cols) and their remainder
-    auto whole = [&](int i) { return std::min((fm[i] - cut[i]) * 256, g[i].m); };
-    auto rows = [&](int i) { return std::min(fm[i] * 256, g[i].m); };
-    auto cols = [&](int i) { return std::min(fn[i] * 256, g[i].n); };
-    for (int i = 0; i < count; ++i) put(i, TILE_128x256, rows(i), g[i].m - rows(i), 0, g[i].n);
-    for (int i = 0; i < count; ++i) put(i, TILE_256x128, 0, rows(i), cols(i), g[i].n - cols(i));
-    close(0);
-    for (int i = 0; i < count; ++i) put(i, TILE_256, 0, whole(i), 0, cols(i));
-    close(1);
-    for (int i = 0; i < count; ++i) put(i, quarters ? TILE_128 : TILE_128x256, whole(i), rows(i) - whole(i), 0, cols(i));
-    close(2);
-    note_group_kernel("gemm_bf16_mixed_group_kernel");
-    hipLaunchKernelGGL(gemm_bf16_mixed_group_kernel, dim3(local * XCDS), dim3(512), 0, stream, grp);
-    CHIMERA_LAUNCH_CHECK("bf16 gemm group");
-    return CHIMERA_OK;
-}
-
 int launch_group_tiled(int count, const GemmArgs* g, float* const* bsum, int overwrite, int tile, hipStream_t stream) {
     GemmGroup grp{};
     grp.count = count; grp.k = g[0].k; grp.overwrite = overwrite ? 1 : 0;
