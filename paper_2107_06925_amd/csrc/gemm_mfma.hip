@@ -221,32 +221,96 @@ template <> struct Raw8<float> {
 // next DEPTH bands are requested before the current band is worked on: all bands when the
 // elements have 2 bytes, two bands when they are floats (registers).
 //
-// A wavefront with a single band (64x64 tiles) asks for all of it, bias included, before its k loop (EpiAhead): a round trip less at the
+// The small tiles ask for all of it, bias included, before their k loop (EpiAhead): a round trip less at the
 // end of a short launch.  With the residual, 256 x 256 x 1024 6.9 -> 6.35 us, 400 x 320 x 1280 7.7 -> 7.25; bias 256 x 768 x 256
 // 4.4 -> 4.15.
-template <int TN> struct EpiAhead {
-    static constexpr int CPR = TN * 4, RPP = 64 / CPR, NP = 32 / RPP;
-    uint4 bias, q[NP][2];
-    __device__ __forceinline__ void request(int row_base, int col_base, int m, int n, const bf16_t* b, const bf16_t* r, const void* c,
-                                            int epi, int epi_flag, int res_types, int lane) {
-        const int pr = lane / CPR, lcol = min(col_base + lane % CPR * 8, n - 8);
+template <int PIECES> struct EpiAhead {
+    uint4 bias, q[PIECES][2];
+    // 8 columns from col on of rows row, row + 16, ...
+    __device__ __forceinline__ void request(int row, int col, int m, int n, const bf16_t* b, const bf16_t* r, const void* c, int epi,
+                                            int epi_flag, int res_types) {
+        const int lcol = min(col, n - 8);
         if (epi == EPI_BIAS || epi == EPI_BIAS_GELU || epi == EPI_BIAS_RESIDUAL) bias = *reinterpret_cast<const uint4*>(b + lcol);
         const bool f32 = epi == EPI_ACCUM_F32 || (epi == EPI_BIAS_RESIDUAL && (res_types & 1));
         if (epi != EPI_BIAS_RESIDUAL && epi != EPI_DGELU && !(epi == EPI_ACCUM_F32 && !(epi_flag & ACCUM_OVERWRITE))) return;
         const char* src = epi == EPI_ACCUM_F32 ? (const char*)c : (const char*)r;
 #pragma unroll
-        for (int j = 0; j < NP; ++j) {
-            const size_t at = (size_t)min(row_base + j * RPP + pr, m - 1) * n + lcol;
+        for (int j = 0; j < PIECES; ++j) {
+            const size_t at = (size_t)min(row + j * 16, m - 1) * n + lcol;
             q[j][0] = *reinterpret_cast<const uint4*>(src + at * (f32 ? 4 : 2));
             if (f32) q[j][1] = *reinterpret_cast<const uint4*>(src + at * 4 + 16);
         }
     }
 };
+
+// Sums v of 8 consecutive elements of C from idx on, with their bias bv and what the epilogue reads besides (rv): finishes and stores them.
+template <int EPI, bool CF32>
+__device__ __forceinline__ void finish8(float* v, const float* bv, const float* rv, size_t idx, void* c, bf16_t* C2, int epi_flag) {
+    bf16_t* C = (bf16_t*)c;
+    float* Cf = (float*)c;
+    if constexpr (EPI == EPI_NONE) {
+        store8(C + idx, v);
+    } else if constexpr (EPI == EPI_BIAS) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += bv[e];
+        store8(C + idx, v);
+    } else if constexpr (EPI == EPI_BIAS_GELU) {
+        float g[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += bv[e];
+        if (epi_flag) {                               // one wavefront-uniform branch per piece, not per element
+#pragma unroll
+            for (int e = 0; e < 8; ++e) g[e] = gelu_f(v[e], 1);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) g[e] = gelu_f(v[e], 0);
+        }
+        if (C) store8(C + idx, v);                    // null: nobody reads it
+        store8(C2 + idx, g);
+    } else if constexpr (EPI == EPI_BIAS_RESIDUAL) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += bv[e] + rv[e];
+        if constexpr (CF32) store8(Cf + idx, v); else store8(C + idx, v);
+    } else if constexpr (EPI == EPI_DGELU) {
+        if (epi_flag) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] *= gelu_grad_f(rv[e], 1);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] *= gelu_grad_f(rv[e], 0);
+        }
+        store8(C + idx, v);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += rv[e];    // rv = 0 when the result replaces C
+        if (epi_flag & ACCUM_ONCE) {
+            __builtin_nontemporal_store(f32x4{v[0], v[1], v[2], v[3]}, reinterpret_cast<f32x4*>(Cf + idx));
+            __builtin_nontemporal_store(f32x4{v[4], v[5], v[6], v[7]}, reinterpret_cast<f32x4*>(Cf + idx + 4));
+        } else {
+            store8(Cf + idx, v);
+        }
+    }
+}
+// What a launch's epilogue is, as template arguments of `f`: f.operator()<EPI, R is float, C is float>()
+template <typename F> __device__ __forceinline__ void with_epilogue(int epi, int res_types, F&& f) {
+    switch (epi) {
+        case EPI_NONE: f.template operator()<EPI_NONE, false, false>(); break;
+        case EPI_BIAS: f.template operator()<EPI_BIAS, false, false>(); break;
+        case EPI_BIAS_GELU: f.template operator()<EPI_BIAS_GELU, false, false>(); break;
+        case EPI_BIAS_RESIDUAL:                    // res_types: bit 0 = R is float, bit 1 = C is float
+            if (res_types == 0) f.template operator()<EPI_BIAS_RESIDUAL, false, false>();
+            else if (res_types == 1) f.template operator()<EPI_BIAS_RESIDUAL, true, false>();
+            else if (res_types == 2) f.template operator()<EPI_BIAS_RESIDUAL, false, true>();
+            else f.template operator()<EPI_BIAS_RESIDUAL, true, true>();
+            break;
+        case EPI_DGELU: f.template operator()<EPI_DGELU, false, false>(); break;
+        default: f.template operator()<EPI_ACCUM_F32, false, false>(); break;
+    }
+}
 template <int EPI, bool RF32, bool CF32, int TM, int TN, typename Acc>
 __device__ __forceinline__ void epilogue(const Acc& acc, float* slab, int row_base, int col_base, int m,
                                          int n, const bf16_t* __restrict__ bias, const bf16_t* __restrict__ R,
-                                         void* __restrict__ c, bf16_t* __restrict__ C2, int epi_flag, int lane,
-                                         const EpiAhead<TN>* pre = nullptr) {
+                                         void* __restrict__ c, bf16_t* __restrict__ C2, int epi_flag, int lane) {
     constexpr int WN = EpiSlab<TN>::WN;
     constexpr int CPR = WN / 8;                // 8-column pieces per row
     constexpr int RPP = 64 / CPR;              // rows covered by the 64 lanes at once
@@ -255,8 +319,6 @@ __device__ __forceinline__ void epilogue(const Acc& acc, float* slab, int row_ba
     constexpr bool READS = EPI == EPI_BIAS_RESIDUAL || EPI == EPI_DGELU || EPI == EPI_ACCUM_F32;
     using RT = std::conditional_t<READS_F32, float, bf16_t>;
     constexpr int DEPTH = !READS ? 1 : (READS_F32 ? (TM < 2 ? TM : 2) : TM);
-    bf16_t* C = (bf16_t*)c;
-    float* Cf = (float*)c;
     const int pr = lane / CPR, pc = (lane % CPR) * 8;
     const int gcol = col_base + pc;
     const bool reads = READS && !(EPI == EPI_ACCUM_F32 && (epi_flag & ACCUM_OVERWRITE));      // an overwriting accumulate reads nothing
@@ -278,17 +340,10 @@ __device__ __forceinline__ void epilogue(const Acc& acc, float* slab, int row_ba
 #pragma unroll
     for (int e = 0; e < 8; ++e) bv[e] = 0.f;
     if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU || EPI == EPI_BIAS_RESIDUAL) {
-        if (pre) Raw8<bf16_t>{pre->bias}.unpack(bv);
-        else if (gcol < n) load8(bias + gcol, bv);
+        if (gcol < n) load8(bias + gcol, bv);
     }
     if constexpr (READS) {
-        if (pre) {
-#pragma unroll
-            for (int j = 0; j < NP; ++j) {
-                if constexpr (READS_F32) { ahead[0][j].lo = __builtin_bit_cast(float4, pre->q[j][0]); ahead[0][j].hi = __builtin_bit_cast(float4, pre->q[j][1]); }
-                else ahead[0][j].q = pre->q[j][0];
-            }
-        } else if (reads) {
+        if (reads) {
             request(0, std::integral_constant<int, 0>{});
             if constexpr (DEPTH > 1 && TM > 1) request(1, std::integral_constant<int, 1 % DEPTH>{});
             if constexpr (DEPTH > 2 && TM > 2) request(2, std::integral_constant<int, 2 % DEPTH>{});
@@ -317,49 +372,7 @@ __device__ __forceinline__ void epilogue(const Acc& acc, float* slab, int row_ba
                     for (int e = 0; e < 8; ++e) rv[e] = 0.f;
             }
             if (grow >= m || gcol >= n) continue;
-            const size_t idx = (size_t)grow * n + gcol;
-            if constexpr (EPI == EPI_NONE) {
-                store8(C + idx, v);
-            } else if constexpr (EPI == EPI_BIAS) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] += bv[e];
-                store8(C + idx, v);
-            } else if constexpr (EPI == EPI_BIAS_GELU) {
-                float g[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] += bv[e];
-                if (epi_flag) {                               // one wavefront-uniform branch per piece, not per element
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) g[e] = gelu_f(v[e], 1);
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) g[e] = gelu_f(v[e], 0);
-                }
-                if (C) store8(C + idx, v);                    // null: nobody reads it
-                store8(C2 + idx, g);
-            } else if constexpr (EPI == EPI_BIAS_RESIDUAL) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] += bv[e] + rv[e];
-                if constexpr (CF32) store8(Cf + idx, v); else store8(C + idx, v);
-            } else if constexpr (EPI == EPI_DGELU) {
-                if (epi_flag) {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) v[e] *= gelu_grad_f(rv[e], 1);
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) v[e] *= gelu_grad_f(rv[e], 0);
-                }
-                store8(C + idx, v);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] += rv[e];    // rv = 0 when the result replaces C
-                if (epi_flag & ACCUM_ONCE) {
-                    __builtin_nontemporal_store(f32x4{v[0], v[1], v[2], v[3]}, reinterpret_cast<f32x4*>(Cf + idx));
-                    __builtin_nontemporal_store(f32x4{v[4], v[5], v[6], v[7]}, reinterpret_cast<f32x4*>(Cf + idx + 4));
-                } else {
-                    store8(Cf + idx, v);
-                }
-            }
+            finish8<EPI, CF32>(v, bv, rv, (size_t)grow * n + gcol, c, C2, epi_flag);
         }
         __builtin_amdgcn_wave_barrier();                      // all lanes have read the slab before it is rewritten
         if constexpr (READS && a + DEPTH < TM)
@@ -509,21 +522,9 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_kernel(
     static_assert(sizeof(lds) >= (size_t)WGM * WGN * EpiSlab<TN>::FLOATS * sizeof(float), "LDS too small for the epilogue");
     __syncthreads();
     float* slab = reinterpret_cast<float*>(lds) + (size_t)(tid >> 6) * EpiSlab<TN>::FLOATS;
-#define CHIMERA_EPI(E, RF, CF) epilogue<E, RF, CF, TM, TN>(Acc32<TM, TN>{acc}, slab, rb0, cb0, m, n, bias, R, C, C2, epi_flag, lane)
-    switch (epi) {
-        case EPI_NONE: CHIMERA_EPI(EPI_NONE, false, false); break;
-        case EPI_BIAS: CHIMERA_EPI(EPI_BIAS, false, false); break;
-        case EPI_BIAS_GELU: CHIMERA_EPI(EPI_BIAS_GELU, false, false); break;
-        case EPI_BIAS_RESIDUAL:                    // res_types: bit 0 = R is float, bit 1 = C is float
-            if (res_types == 0) CHIMERA_EPI(EPI_BIAS_RESIDUAL, false, false);
-            else if (res_types == 1) CHIMERA_EPI(EPI_BIAS_RESIDUAL, true, false);
-            else if (res_types == 2) CHIMERA_EPI(EPI_BIAS_RESIDUAL, false, true);
-            else CHIMERA_EPI(EPI_BIAS_RESIDUAL, true, true);
-            break;
-        case EPI_DGELU: CHIMERA_EPI(EPI_DGELU, false, false); break;
-        default: CHIMERA_EPI(EPI_ACCUM_F32, false, false); break;
-    }
-#undef CHIMERA_EPI
+    with_epilogue(epi, res_types, [&]<int E, bool RF, bool CF>() {
+        epilogue<E, RF, CF, TM, TN>(Acc32<TM, TN>{acc}, slab, rb0, cb0, m, n, bias, R, C, C2, epi_flag, lane);
+    });
 }
 
 template <int N, typename F> __device__ __forceinline__ void static_for(F&& f) {
@@ -642,13 +643,17 @@ __device__ __forceinline__ void gemm_async_tile(
         for (int it = 0; it < CB; ++it) { lds_dma16(gb[it], sb + it * NT * 16); gb[it] += step_b; }
     };
 
-    static_assert(TM == 1 || (WGK == 2 && TM == 2), "one band of rows per wavefront in the epilogue");
+    // The wavefronts of a block of the tile hold partial sums of it, one per k slice; in the end each finishes its share of the rows, a lane
+    // 8 columns of rows row0, row0 + 16, ...
+    constexpr int SHARE = WM / WGK, PIECES = (SHARE + 15) / 16;
+    static_assert(TN == 1, "rows of 32 columns");
+    const int row0 = wk * SHARE + lane / 4, gcol = j0 + wn0 + lane % 4 * 8;
     // With two workgroups on a CU each hides the other's last trip, and these requests hold back the first operands.  Without them A^T B 1472 x 1280 x 512
     // 7.56 -> 7.24 us, groups of 12 x 384^2 x 1024 10.36 -> 9.97, A B^T with the GeLU derivative 1088 x 1088 x 192 5.54 -> 5.39; but A B x 64 4.2 -> 4.4.
     constexpr bool EPI_AHEAD = SPS > 1 || (A_KC && !B_KC);
-    EpiAhead<TN> pre;
-    if (EPI_AHEAD && (TM > 1 || wk == 0))
-        pre.request(i0 + wm0 + (TM > 1 ? wk * 32 : 0), j0 + wn0, m, n, bias, R, C, ONLY_EPI >= 0 ? ONLY_EPI : epi, epi_flag, res_types, lane);
+    EpiAhead<PIECES> pre;
+    auto ask = [&] { pre.request(i0 + wm0 + row0, gcol, m, n, bias, R, C, ONLY_EPI >= 0 ? ONLY_EPI : epi, epi_flag, res_types); };
+    if (EPI_AHEAD) ask();
 
     f32x16 acc[TM][TN];
 #pragma unroll
@@ -776,135 +781,61 @@ __device__ __forceinline__ void gemm_async_tile(
     if constexpr (ONLY_EPI < 0)
         if (ahead.bytes) [[unlikely]] touch_ahead(ahead, wave, NT / 64, lane);       // weight gradients and split products precede no product
 
-    const int cb0 = j0 + wn0;
-    // the operand tiles in LDS are dead once every wavefront has left the k loop; each
-    // wavefront then stages its output through its own slab there
-    static_assert(sizeof(lds) >= (size_t)(NT / 64) * EpiSlab<TN>::FLOATS * sizeof(float), "LDS too small for the epilogue");
+    if (!EPI_AHEAD) ask();
+    // The operand tiles in LDS are dead once every wavefront has left the k loop: each puts its sums there, and every one of a block adds, in
+    // the order of the k slices, and finishes its share.  With one of them (or each its half of 64 rows) finishing what it had taken from
+    // the others after a second trip through LDS -> so: 256 x 768 x 256 3.57 -> 3.37 us, 256 x 1024 x 256 with GeLU 4.02 -> 3.55, 400 x 320 x 1280
+    // 5.73 -> 5.43, 512 x 2048 x 512 5.56 -> 5.37, 1264 x 1600 x 1600 13.2 -> 12.5.
+    constexpr int BAND = EpiSlab<1>::FLOATS;
+    static_assert(sizeof(lds) >= ((size_t)(NT / 64) * TM * BAND + WGK * BN) * sizeof(float), "LDS too small for the sums");
     __syncthreads();
-    float* slab = reinterpret_cast<float*>(lds) + (size_t)(tid >> 6) * EpiSlab<TN>::FLOATS;
-    auto finish = [&]<int TMO>(const f32x16 (&out)[TMO][TN], int rb0) {
-#define CHIMERA_EPI(E, RF, CF) epilogue<E, RF, CF, TMO, TN>(Acc32<TMO, TN>{out}, slab, rb0, cb0, m, n, bias, R, C, C2, epi_flag, lane, EPI_AHEAD ? &pre : nullptr)
-        if constexpr (ONLY_EPI == EPI_ACCUM_F32) { CHIMERA_EPI(EPI_ACCUM_F32, false, false); return; }
-        switch (epi) {
-            case EPI_NONE: CHIMERA_EPI(EPI_NONE, false, false); break;
-            case EPI_BIAS: CHIMERA_EPI(EPI_BIAS, false, false); break;
-            case EPI_BIAS_GELU: CHIMERA_EPI(EPI_BIAS_GELU, false, false); break;
-            case EPI_BIAS_RESIDUAL:
-                if (res_types == 0) CHIMERA_EPI(EPI_BIAS_RESIDUAL, false, false);
-                else if (res_types == 1) CHIMERA_EPI(EPI_BIAS_RESIDUAL, true, false);
-                else if (res_types == 2) CHIMERA_EPI(EPI_BIAS_RESIDUAL, false, true);
-                else CHIMERA_EPI(EPI_BIAS_RESIDUAL, true, true);
-                break;
-            case EPI_DGELU: CHIMERA_EPI(EPI_DGELU, false, false); break;
-            default: CHIMERA_EPI(EPI_ACCUM_F32, false, false); break;
+    float* slabs = reinterpret_cast<float*>(lds);
+    float* xcs = slabs + NT / 64 * TM * BAND + wn0 + lane;
+    static_for<TM>([&](auto a_c) { Acc32<TM, 1>{acc}.template put<decltype(a_c)::value>(slabs + (wave * TM + decltype(a_c)::value) * BAND, lane); });
+    if constexpr (ONLY_EPI == EPI_ACCUM_F32)               // row 0 of a column-sum accumulator: register 0 of lanes 0..31
+        if (col_sums && lane < 32) xcs[wk * BN] = cs[0][0];
+    __syncthreads();
+    if constexpr (ONLY_EPI == EPI_ACCUM_F32)
+        if (col_sums && wk == 0 && lane < 32) {
+            float v = cs[0][0];
+#pragma unroll
+            for (int w = 1; w < WGK; ++w) v += xcs[w * BN];
+            const int col = j0 + wn0 + lane;
+            if (col < n) bsum[col] = (epi_flag & ACCUM_OVERWRITE) ? v : bsum[col] + v;
         }
-#undef CHIMERA_EPI
+    auto finish = [&]<int E, bool RF, bool CF>() {
+        constexpr bool READS_F32 = E == EPI_ACCUM_F32 || (E == EPI_BIAS_RESIDUAL && RF), READS = E == EPI_BIAS_RESIDUAL || E == EPI_DGELU || E == EPI_ACCUM_F32;
+        float bv[8];
+        if constexpr (E == EPI_BIAS || E == EPI_BIAS_GELU || E == EPI_BIAS_RESIDUAL) Raw8<bf16_t>{pre.bias}.unpack(bv);
+#pragma unroll
+        for (int j = 0; j < PIECES; ++j) {
+            const int r = row0 + j * 16, grow = i0 + wm0 + r;
+            float v[8];
+#pragma unroll
+            for (int w = 0; w < WGK; ++w) {
+                float* slab = slabs + ((w * WGM * WGN + wmn) * TM + r / 32) * BAND;
+                float u[8];
+                load_vec<float>(EpiSlab<1>::at(slab, r % 32, lane % 4 * 2), u);
+                load_vec<float>(EpiSlab<1>::at(slab, r % 32, lane % 4 * 2 + 1), u + 4);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = w ? v[e] + u[e] : u[e];
+            }
+            float rv[8];
+            if constexpr (READS_F32) {
+                const bool reads = !(E == EPI_ACCUM_F32 && (epi_flag & ACCUM_OVERWRITE));
+                if (reads) Raw8<float>{__builtin_bit_cast(float4, pre.q[j][0]), __builtin_bit_cast(float4, pre.q[j][1])}.unpack(rv);
+                else
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) rv[e] = 0.f;
+            } else if constexpr (READS) {
+                Raw8<bf16_t>{pre.q[j][0]}.unpack(rv);
+            }
+            if (grow < m && gcol < n) finish8<E, CF>(v, bv, rv, (size_t)grow * n + gcol, C, C2, epi_flag);
+        }
     };
-    // row 0 of a column-sum accumulator: register 0 of lanes 0..31
-    auto put_col_sums = [&](const float (&v)[TN]) {
-        if (lane < 32)
-#pragma unroll
-            for (int b = 0; b < TN; ++b) {
-                const int col = cb0 + b * 32 + lane;
-                if (col < n) bsum[col] = (epi_flag & ACCUM_OVERWRITE) ? v[b] : bsum[col] + v[b];
-            }
-    };
-    if constexpr (TM == 1) {
-        // The wavefronts of a block hold partial sums of it, one per k slice; there is one band of rows only: the first wavefront adds what
-        // the others hand over through LDS, in their order, and finishes it.
-        static_assert(sizeof(lds) >= (size_t)WGM * WGN * (WGK - 1) * TN * 4 * 64 * sizeof(float4) + (WGK - 1) * BN * sizeof(float), "LDS too small");
-        constexpr int PER_WAVE = TN * 4 * 64;
-        float4* xch = reinterpret_cast<float4*>(lds) + (size_t)wmn * PER_WAVE + lane;
-        float* xcs = reinterpret_cast<float*>(reinterpret_cast<float4*>(lds) + (size_t)WGM * WGN * (WGK - 1) * PER_WAVE) + wn0;
-        if (wk > 0) {
-            if constexpr (ONLY_EPI == EPI_ACCUM_F32)
-                if (col_sums && lane < 32)
-#pragma unroll
-                    for (int b = 0; b < TN; ++b) xcs[(wk - 1) * BN + b * 32 + lane] = cs[b][0];
-#pragma unroll
-            for (int b = 0; b < TN; ++b)
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    xch[(size_t)(wk - 1) * WGM * WGN * PER_WAVE + (b * 4 + q) * 64] = make_float4(acc[0][b][4 * q], acc[0][b][4 * q + 1], acc[0][b][4 * q + 2], acc[0][b][4 * q + 3]);
-        }
-        __syncthreads();
-        if (wk == 0) {
-#pragma unroll
-            for (int w = 0; w < WGK - 1; ++w)
-#pragma unroll
-                for (int b = 0; b < TN; ++b)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const float4 v = xch[(size_t)w * WGM * WGN * PER_WAVE + (b * 4 + q) * 64];
-                        acc[0][b][4 * q] += v.x; acc[0][b][4 * q + 1] += v.y; acc[0][b][4 * q + 2] += v.z; acc[0][b][4 * q + 3] += v.w;
-                    }
-            if constexpr (ONLY_EPI == EPI_ACCUM_F32)
-                if (col_sums) {
-                    float v[TN];
-#pragma unroll
-                    for (int b = 0; b < TN; ++b) {
-                        v[b] = cs[b][0];
-#pragma unroll
-                        for (int w = 0; w < WGK - 1; ++w) v[b] += lane < 32 ? xcs[w * BN + b * 32 + lane] : 0.f;
-                    }
-                    put_col_sums(v);
-                }
-        }
-        __syncthreads();                       // the exchange area becomes the slabs
-        if (wk == 0) finish(acc, i0 + wm0);
-    } else {
-        // Two wavefronts hold partial sums of the same WM x WN block (one per k slice).  Each
-        // keeps the upper or lower half of the rows: it hands the other half to its partner
-        // through LDS, adds what the partner hands over (one float addition per element, so the
-        // result does not depend on which wavefront adds), and finishes its half.
-        static_assert(WGK == 2 && TM % 2 == 0, "row halves");
-        constexpr int TMO = TM / 2;
-        constexpr int PER_WAVE = TMO * TN * 4 * 64;                      // float4 per wavefront
-        static_assert(sizeof(lds) >= (size_t)(NT / 64) * PER_WAVE * sizeof(float4), "LDS too small for the exchange");
-        float4* xch = reinterpret_cast<float4*>(lds);
-        // column sums of the two k slices meet behind the exchange area
-        float* xcs = reinterpret_cast<float*>(xch + (size_t)(NT / 64) * PER_WAVE) + wn0;
-        static_assert(sizeof(lds) >= (size_t)(NT / 64) * PER_WAVE * sizeof(float4) + BN * sizeof(float), "LDS too small");
-        if constexpr (ONLY_EPI == EPI_ACCUM_F32)
-            if (col_sums && wk == 1 && lane < 32)
-#pragma unroll
-                for (int b = 0; b < TN; ++b) xcs[b * 32 + lane] = cs[b][0];
-        float4* send = xch + (size_t)wave * PER_WAVE + lane;
-        const float4* recv = xch + (size_t)(wave ^ (WGM * WGN)) * PER_WAVE + lane;
-        f32x16 own[TMO][TN];
-#pragma unroll
-        for (int a = 0; a < TMO; ++a)
-#pragma unroll
-            for (int b = 0; b < TN; ++b) {
-                const f32x16 give = wk ? acc[a][b] : acc[TMO + a][b];
-                own[a][b] = wk ? acc[TMO + a][b] : acc[a][b];
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    send[((a * TN + b) * 4 + q) * 64] = make_float4(give[4 * q], give[4 * q + 1], give[4 * q + 2], give[4 * q + 3]);
-            }
-        __syncthreads();
-#pragma unroll
-        for (int a = 0; a < TMO; ++a)
-#pragma unroll
-            for (int b = 0; b < TN; ++b)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float4 v = recv[((a * TN + b) * 4 + q) * 64];
-                    own[a][b][4 * q] += v.x;
-                    own[a][b][4 * q + 1] += v.y;
-                    own[a][b][4 * q + 2] += v.z;
-                    own[a][b][4 * q + 3] += v.w;
-                }
-        if constexpr (ONLY_EPI == EPI_ACCUM_F32)
-            if (col_sums && wk == 0) {
-                float v[TN];
-#pragma unroll
-                for (int b = 0; b < TN; ++b) v[b] = cs[b][0] + (lane < 32 ? xcs[b * 32 + lane] : 0.f);
-                put_col_sums(v);
-            }
-        __syncthreads();                       // the exchange area becomes the slabs
-        finish(own, i0 + wm0 + wk * TMO * 32);
-    }
+    if (SHARE < 16 && lane >= SHARE * 4) return;
+    if constexpr (ONLY_EPI == EPI_ACCUM_F32) finish.template operator()<EPI_ACCUM_F32, false, false>();
+    else with_epilogue(epi, res_types, finish);
 }
 
 // ------------------------------------------------------------------ tiles of 128x128 and 256x256
@@ -1264,22 +1195,9 @@ __device__ __forceinline__ void gemm_ring_tile(
     float* slab = reinterpret_cast<float*>(lds) + (size_t)wave * EpiSlab<TN / 2>::FLOATS;
     auto finish = [&](const auto& out, auto rows_c, int rb0) {
         constexpr int TO = decltype(rows_c)::value;              // 32-row bands of this wavefront
-#define CHIMERA_EPI(E, RF, CF) epilogue<E, RF, CF, TO, TN / 2>(out, slab, rb0, cb0, m, n, bias, R, C, C2, epi_flag, lane)
-        if constexpr (ONLY_EPI == EPI_ACCUM_F32) { CHIMERA_EPI(EPI_ACCUM_F32, false, false); return; }
-        switch (epi) {
-            case EPI_NONE: CHIMERA_EPI(EPI_NONE, false, false); break;
-            case EPI_BIAS: CHIMERA_EPI(EPI_BIAS, false, false); break;
-            case EPI_BIAS_GELU: CHIMERA_EPI(EPI_BIAS_GELU, false, false); break;
-            case EPI_BIAS_RESIDUAL:
-                if (res_types == 0) CHIMERA_EPI(EPI_BIAS_RESIDUAL, false, false);
-                else if (res_types == 1) CHIMERA_EPI(EPI_BIAS_RESIDUAL, true, false);
-                else if (res_types == 2) CHIMERA_EPI(EPI_BIAS_RESIDUAL, false, true);
-                else CHIMERA_EPI(EPI_BIAS_RESIDUAL, true, true);
-                break;
-            case EPI_DGELU: CHIMERA_EPI(EPI_DGELU, false, false); break;
-            default: CHIMERA_EPI(EPI_ACCUM_F32, false, false); break;
-        }
-#undef CHIMERA_EPI
+        auto run = [&]<int E, bool RF, bool CF>() { epilogue<E, RF, CF, TO, TN / 2>(out, slab, rb0, cb0, m, n, bias, R, C, C2, epi_flag, lane); };
+        if constexpr (ONLY_EPI == EPI_ACCUM_F32) run.template operator()<EPI_ACCUM_F32, false, false>();
+        else with_epilogue(epi, res_types, run);
     };
     __syncthreads();                           // the buffers become the wavefronts' slabs
     if constexpr (WGK == 1) {
