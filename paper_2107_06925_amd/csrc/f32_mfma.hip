@@ -1,25 +1,20 @@
-// Float products on the CDNA4 matrix cores: v_mfma_f32_32x32x2_f32, full float operands and
-// accumulation (the chip's float matrix rate is 157 TFLOP/s, twice what an LDS-fed vector loop
-// reached of it and eight times the plain kernel).  Same three layouts and epilogues as the bf16
-// products.
+// Float products on the CDNA4 matrix cores, same three layouts and epilogues as the bf16 products.  Four forms:
+//  - tiles of 128x128 and 64x64 on the bf16 instructions, each float split into three bf16 numbers: six products where the float
+//    instruction makes one, at 16 times its rate;
+//  - small outputs: one 32x32 tile per workgroup on v_mfma_f32_32x32x2_f32, the k range dealt over 4 or 8 wavefronts, operands
+//    straight from memory into registers, one exchange in LDS at the end.  Such a product is bound
+//    by its chain of latencies (launch, load, exchange, store), which this keeps to one of each;
+//  - the smallest outputs: the same with 16x16 tiles, which four times as many CUs read the operands of.
 //
-// Per lane l the instruction takes ONE contraction value of row (column) l%32; which contraction
+// Per lane l the float instruction takes ONE contraction value of row (column) l%32; which contraction
 // index lane group g = l/32 holds is free as long as both operands agree.  Here the k range goes in
 // groups of 8: group g holds 4g..4g+3 and instruction j (0..3) contracts the pair (j, 4+j).  A
 // k-contiguous operand then delivers four instructions' values with one 16-byte read; an operand
 // whose other index is contiguous delivers them as four 4-byte reads of 32 neighbouring values.
-//
-// Three forms:
-//  - tiles of 64x64, 8 wavefronts, k in steps of 32 through LDS.  A 64-clock instruction needs 8 bytes
-//    from LDS per lane at most, so LDS and L2 are far from their limits and the matrix pipes set the
-//    time, once the loads and LDS reads of the next steps are under way during the current one.
-//  - small outputs: one 32x32 tile per workgroup, the k range dealt over 4 or 8 wavefronts, operands
-//    straight from memory into registers, one exchange in LDS at the end.  Such a product is bound
-//    by its chain of latencies (launch, load, exchange, store), which this keeps to one of each;
-//  - the smallest outputs: the same with 16x16 tiles, which four times as many CUs read the operands of.
 #include "device.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace chimera {
 
@@ -27,6 +22,7 @@ namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef bf16_t bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int NUM_CUS = 256;
 
@@ -55,6 +51,14 @@ __device__ __forceinline__ const F32Product& tile_of(const F32Launch& L, int& ti
     return p;
 }
 
+// One result whose other operands are there: the bias, and the residual, the GeLU's input or what the result is added to
+template <int EPI> __device__ __forceinline__ void finish_one(const F32Product& p, int flag, size_t idx, float v, float bias, float other) {
+    if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU || EPI == EPI_BIAS_RESIDUAL) v += bias;
+    if constexpr (EPI == EPI_BIAS_RESIDUAL || EPI == EPI_ACCUM_F32) v += other;
+    if constexpr (EPI == EPI_DGELU) v *= gelu_grad_f(other, flag);
+    p.c[idx] = v;
+    if constexpr (EPI == EPI_BIAS_GELU) p.c2[idx] = gelu_f(v, flag);
+}
 // N consecutive results of one row (columns col..col+N-1, inside the matrix)
 template <int EPI, int N>
 __device__ __forceinline__ void finish(const F32Product& p, int flag, int row, int col, const float* acc) {
@@ -106,177 +110,6 @@ struct F32Ahead {
     }
 };
 
-// ------------------------------------------------------------------ tile form
-// LDS layout of an operand tile of ROWS rows: [ROWS][BK + 4] (k-contiguous) or [BK][ROWS + 8].  Both
-// paddings make the fragment reads conflict-free on the 64 banks: 16 consecutive rows at a stride of
-// 20 or 36 words cover all banks with 4 words each; the two lane groups' rows 4g+j lie
-// 4 * (ROWS + 8) = 32 (mod 64) words apart.
-template <int ROWS, int BK, int NT, bool KC> struct OpTile {
-    static constexpr int STRIDE = KC ? BK + 4 : ROWS + 8, FLOATS = KC ? ROWS * STRIDE : BK * STRIDE;
-    static constexpr int N = ROWS * BK / 4 / NT;               // 16-byte pieces per thread and step
-    static_assert(N >= 1, "every thread moves a piece");
-    f32x4 v[N];
-    unsigned oks;                        // bit i: v[i] lies inside the matrix; the others become zeros only on
-                                         // their way to LDS (a select right behind the load would wait for it)
-    __device__ __forceinline__ void load(const float* __restrict__ base, int ld, int row0, int nrows, int k0, int K, int tid) {
-        oks = 0;
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const int c = tid + i * NT;
-            const int row = row0 + (KC ? c / (BK / 4) : c % (ROWS / 4) * 4), k = k0 + (KC ? c % (BK / 4) * 4 : c / (ROWS / 4));
-            const bool ok = row < nrows && k < K;
-            v[i] = *reinterpret_cast<const f32x4*>(base + (ok ? (KC ? (size_t)row * ld + k : (size_t)k * ld + row) : 0));
-            oks |= (ok ? 1u : 0u) << i;
-        }
-    }
-    __device__ __forceinline__ void store(float* lds, int tid) const {
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const int c = tid + i * NT;
-            const int off = KC ? c / (BK / 4) * STRIDE + c % (BK / 4) * 4 : c / (ROWS / 4) * STRIDE + c % (ROWS / 4) * 4;
-            const bool ok = (oks >> i) & 1;
-            *reinterpret_cast<f32x4*>(lds + off) = f32x4{ok ? v[i][0] : 0.f, ok ? v[i][1] : 0.f, ok ? v[i][2] : 0.f, ok ? v[i][3] : 0.f};
-        }
-    }
-    // the four values of row `row` and k group `grp` (of 8) that lane group g holds
-    static __device__ __forceinline__ f32x4 frag(const float* lds, int row, int grp, int g) {
-        if constexpr (KC) return *reinterpret_cast<const f32x4*>(lds + row * STRIDE + grp * 8 + 4 * g);
-        const float* q = lds + (grp * 8 + 4 * g) * STRIDE + row;
-        return f32x4{q[0], q[STRIDE], q[2 * STRIDE], q[3 * STRIDE]};
-    }
-};
-
-// Two wavefronts share a 32x32 block (TM = TN = 1), each with half of every k step: with one 64x64 tile per CU there
-// is otherwise one wavefront per SIMD, and nothing runs while it waits for a barrier or LDS.
-template <bool A_KC, bool B_KC, int EPI>
-__global__ __launch_bounds__(8 * WAVE) void gemm_f32_tile_kernel(F32Launch L) {
-    constexpr int BM = 64, BN = 64, BK = 32, WGK = 2, NT = 4 * WGK * WAVE, WM = BM / 2, WN = BN / 2, TM = WM / 32, TN = WN / 32, GRPS = BK / 8 / WGK;
-    using TA = OpTile<BM, BK, NT, A_KC>;
-    using TB = OpTile<BN, BK, NT, B_KC>;
-    __shared__ __attribute__((aligned(16))) float lds[3][TA::FLOATS + TB::FLOATS];
-    int tile_m, tile_n;
-    const F32Product& p = tile_of(L, tile_m, tile_n);
-    const int i0 = tile_m * BM, j0 = tile_n * BN, m = p.m, n = p.n, K = p.k, lda = p.lda, ldb = p.ldb;
-    const float* __restrict__ A = p.a;
-    const float* __restrict__ B = p.b;
-    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, g = lane >> 5, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wk = wave >> 2, wm0 = ((wave >> 1) & 1) * WM, wn0 = (wave & 1) * WN;
-
-    f32x16 acc[TM][TN];
-#pragma unroll
-    for (int a = 0; a < TM; ++a)
-#pragma unroll
-        for (int b = 0; b < TN; ++b)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
-    // column sums of B come from the fragments that the top wavefronts of the first tile row hold anyway
-    const bool col_sums = EPI == EPI_ACCUM_F32 && p.bsum && tile_m == 0 && wm0 == 0;
-    float cs[TN];
-#pragma unroll
-    for (int b = 0; b < TN; ++b) cs[b] = 0.f;
-
-    // Loads run in register sets three steps ahead of LDS (a step is 0.4 us of matrix work, a load that
-    // misses L2 takes twice that) and LDS two steps ahead of the matrix cores, in rings of three walked
-    // by an unrolled loop.  With LDS that far ahead the first fragments of the next step are read
-    // before the barrier that ends this one.
-    constexpr int NB = 3;
-    TA ra[NB];
-    TB rb[NB];
-    const int KT = (K + BK - 1) / BK;
-    auto fetch = [&](int u, int kt) {
-        ra[u].load(A, lda, i0, m, kt * BK, K, tid);
-        rb[u].load(B, ldb, j0, n, kt * BK, K, tid);
-    };
-    auto stash = [&](int u) {
-        ra[u].store(lds[u], tid);
-        rb[u].store(lds[u] + TA::FLOATS, tid);
-    };
-    f32x4 fa[2][TM], fb[2][TN];
-    auto read = [&](int s, int buf, int gi) {
-        const int grp = wk * GRPS + gi;
-#pragma unroll
-        for (int a = 0; a < TM; ++a) fa[s][a] = TA::frag(lds[buf], wm0 + a * 32 + l32, grp, g);
-#pragma unroll
-        for (int b = 0; b < TN; ++b) fb[s][b] = TB::frag(lds[buf] + TA::FLOATS, wn0 + b * 32 + l32, grp, g);
-    };
-#pragma unroll
-    for (int u = 0; u < NB; ++u)
-        if (u < KT) fetch(u, u);
-    stash(0);
-    if (1 < KT) stash(1);
-    if (3 < KT) fetch(0, 3);
-    if (4 < KT) fetch(1, 4);
-    __syncthreads();
-    read(0, 0, 0);
-    static_assert(GRPS % 2 == 0, "fragment set of a group at compile time");
-    for (int kt0 = 0; kt0 < KT; kt0 += NB) {
-#pragma unroll
-        for (int u = 0; u < NB; ++u) {
-            const int kt = kt0 + u;
-            if (kt >= KT) break;
-            if (kt + 2 < KT) stash((u + 2) % NB);            // its buffer was last read in step kt - 1
-            if (kt + 5 < KT) fetch((u + 2) % NB, kt + 5);
-#pragma unroll
-            for (int gi = 0; gi < GRPS; ++gi) {
-                const int s = gi & 1;
-                if (gi + 1 < GRPS) read(s ^ 1, u, gi + 1);
-                else if (kt + 1 < KT) read(s ^ 1, (u + 1) % NB, 0);
-                if constexpr (EPI == EPI_ACCUM_F32)
-                    if (col_sums)
-#pragma unroll
-                        for (int b = 0; b < TN; ++b) cs[b] += (fb[s][b][0] + fb[s][b][1]) + (fb[s][b][2] + fb[s][b][3]);
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-#pragma unroll
-                    for (int a = 0; a < TM; ++a)
-#pragma unroll
-                        for (int b = 0; b < TN; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[s][a][j], fb[s][b][j], acc[a][b], 0, 0, 0);
-            }
-            __syncthreads();                   // step kt + 2 is in LDS, and everyone is done with step kt
-        }
-    }
-    // Two wavefronts with partial sums of one block: each hands over one half of its registers and
-    // finishes the other (registers 0..7 or 8..15 of every 32x32 tile, i.e. 16 of its rows).
-    constexpr int R = 16 / WGK;
-    {
-        static_assert(TM == 1 && TN == 1, "one tile per wavefront");
-        static_assert(sizeof(lds) >= 8 * R * WAVE * sizeof(float) + BN * sizeof(float), "LDS too small for the exchange");
-        float* xch = &lds[0][0];
-        float* xcs = xch + 8 * R * WAVE;
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < R; ++r) xch[(wave * R + r) * WAVE + lane] = wk ? acc[0][0][r] : acc[0][0][R + r];
-        if (col_sums) {
-            cs[0] = sum32(cs[0]);
-            if (wk && g == 0) xcs[wn0 + l32] = cs[0];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const float other = xch[((wave ^ 4) * R + r) * WAVE + lane];
-            acc[0][0][r] = wk ? other + acc[0][0][R + r] : acc[0][0][r] + other;
-        }
-        if (col_sums && !wk) cs[0] += xcs[wn0 + l32];
-    }
-    // register r of lane l: row 8(r/4) + 4g + r%4, column l%32 - 128 contiguous bytes per half wavefront
-#pragma unroll
-    for (int b = 0; b < TN; ++b) {
-        const int col = j0 + wn0 + b * 32 + l32;
-        if (col >= n) continue;
-        if constexpr (EPI == EPI_ACCUM_F32)
-            if (col_sums && g == 0 && wk == 0) p.bsum[col] = L.flag ? cs[b] : p.bsum[col] + cs[b];
-#pragma unroll
-        for (int a = 0; a < TM; ++a)
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const int row = i0 + wm0 + a * 32 + wk * 16 + 8 * (r >> 2) + 4 * g + (r & 3);
-                const float v = acc[a][b][r];
-                if (row < m) finish<EPI, 1>(p, L.flag, row, col, &v);
-            }
-    }
-}
-
-// ----------------------------------------------------------------- small form
 // The 32 k values a wavefront takes at a time, of one operand row per lane: 16 registers.  Rows
 // beyond the matrix repeat its last one (their results are not stored); k beyond the range becomes
 // zero at use.
@@ -298,6 +131,400 @@ __device__ __forceinline__ void mask_slice(f32x4 (&v)[4], int k0, int K, int g) 
         for (int j = 0; j < 4; ++j) v[i][j] = k0 + 8 * i + 4 * g + j < K ? v[i][j] : 0.f;
 }
 
+// ------------------------------------------------------------------ tile forms
+// On the bf16 matrix instructions.  A float is the sum of three bf16 numbers: its upper 16 bits, the rest to nearest, and what that leaves
+// (8 + 8 + 8 bits), so a product of two floats is nine products of their parts.  The three smallest are left out: below 2^-22 of it,
+// 2^-25 as a rule, a rounding's size.  A bf16 instruction rounds once for 16 products where the float one rounds for every second:
+// against float64, relative 2-norm, k = 64, 256, 1024, 4096: 1.06e-7 -> 5.3e-8, 2.06e-7 -> 7.4e-8, 4.06e-7 -> 1.32e-7, 8.10e-7 -> 2.73e-7 (128x128 tiles, whose
+// sums are not halved: 9.2e-8, 1.86e-7, 3.95e-7).  The sums of the large parts' products and of the others are kept apart until the end.
+//
+// What bounds it: with two wavefronts on a SIMD matrix and vector instructions overlap by a third at best (8 of the former alone 140 ns, 64 of the
+// latter 148, both 202), and a 64x64 step of 32 k is 12 and 100 of them; LDS is busy 44 % of the time, without conflicts.  Against tiles of
+// v_mfma_f32_32x32x2_f32, which were bound by that instruction: 1024 x 1024 x 1024 A B 27.0 -> 21.3 us, A B^T 25.7 -> 20.5, A^T B 29.0 -> 21.5;
+// 1024 x 3072 x 1024 64.7 -> 50.6; 704 x 2816 x 704 33.2 -> 24.4; 1000 x 1000 x 104 6.5 -> 6.0; two steps of k are slower, 1024 x 1024 x 64
+// 4.84 -> 5.07.  Splitting in registers, a wavefront per k slice of a whole tile, was slower (2048^3 118 -> 161 us: no registers are left to load ahead).
+struct SplitBuf { bf16_t part[2][3][64][32]; };                // operand, part, row, k: one step
+// 16-byte chunk c (8 k values) of row r sits at c ^ bits of r: 16 rows of one chunk, as many of four rows, all fall on different banks
+__device__ __forceinline__ int split_chunk(int row, int c) { return c ^ ((row >> 2) & 3); }
+
+// The chunks a thread moves: 8 k values of one operand row in every step of BK.  Buffer loads: an address is a uniform base, which moves on
+// by a step, and an offset that stays the same; what lies beyond the operand's end reads as zero, as the k rows behind K of an
+// index-contiguous operand do.  (In a row of a k-contiguous one, others follow.)
+template <bool KC, int BK> struct SplitChunk {
+    const char* at;                       // the tile's first row, this step's first k
+    size_t step;
+    int ld, rows, left;                   // left: k values from this step on
+    unsigned off[KC ? 1 : 8];
+    __device__ __forceinline__ SplitChunk(const float* from, int ld, int row0, int nrows, int max_rows, int K, int row, int oct)
+        : at((const char*)(from + (KC ? (size_t)row0 * ld : row0))), step((KC ? (size_t)BK : (size_t)BK * ld) * 4), ld(ld), rows(min(nrows - row0, max_rows)), left(K) {
+        row = min(row, rows - 1);         // rows beyond the matrix repeat its last one: their results are not stored
+#pragma unroll
+        for (int j = 0; j < (KC ? 1 : 8); ++j) off[j] = (KC ? (unsigned)row * (unsigned)ld + oct * 8 : (unsigned)(oct * 8 + j) * (unsigned)ld + row) * 4u;
+    }
+    __device__ __forceinline__ void load(float (&v)[8]) {
+        const int elems = KC ? (rows - 1) * ld + left : min(left, BK) * ld;
+        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)at, 0, (int)(4u * max(elems, 0)), 0x00020000);
+        if constexpr (KC) {
+            const f32x4 lo = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off[0], 0, 0));
+            const f32x4 hi = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off[0] + 16, 0, 0));
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { v[j] = lo[j]; v[4 + j] = hi[j]; }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, off[j], 0, 0));
+        }
+        at += step; left -= BK;
+    }
+};
+constexpr int MAX_LD = 1 << 22;                                // 128 rows, or 32 k, of them stay below 2^31 bytes
+
+// Writes a chunk's parts, part p at `at` + p * PART; the upper parts' bits join `bits`.
+template <int PART> __device__ __forceinline__ void split_store(const float (&v)[8], bf16_t* at, unsigned& bits) {
+    typedef bf16_t bf16x2 __attribute__((ext_vector_type(2)));
+    unsigned w[3][4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const unsigned x = __float_as_uint(v[2 * j]), y = __float_as_uint(v[2 * j + 1]);
+        const float rx = v[2 * j] - __uint_as_float(x & 0xffff0000u), ry = v[2 * j + 1] - __uint_as_float(y & 0xffff0000u);
+        const unsigned mid = __builtin_bit_cast(unsigned, bf16x2{(bf16_t)rx, (bf16_t)ry});
+        const float lx = rx - __uint_as_float(mid << 16), ly = ry - __uint_as_float(mid & 0xffff0000u);
+        w[0][j] = __builtin_amdgcn_perm(y, x, 0x07060302u);      // upper halves
+        w[1][j] = mid;
+        w[2][j] = __builtin_amdgcn_perm(__float_as_uint(ly), __float_as_uint(lx), 0x07060302u);       // no more than eight bits are left
+    }
+    bits |= (w[0][0] | w[0][1]) | (w[0][2] | w[0][3]);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) *reinterpret_cast<uint4*>(at + p * PART) = make_uint4(w[p][0], w[p][1], w[p][2], w[p][3]);
+}
+// Numbers below 2^-95 only (all exponents' upper bits are zero), and not just zeros: the instructions have no bits left for their smallest parts
+__device__ __forceinline__ bool all_tiny(unsigned bits) { const unsigned b = (bits | bits >> 16) & 0x7fff; return b && b < 32u << 7; }
+
+// 8 wavefronts: two share a 32x32 block, each with half of every k step; four stage A's rows, four B's.
+template <bool A_KC, bool B_KC, int EPI>
+__global__ __launch_bounds__(8 * WAVE, 4) void gemm_f32_tile_kernel(F32Launch L) {
+    constexpr int BM = 64, BN = 64, BK = 32;
+    __shared__ __attribute__((aligned(16))) SplitBuf lds[2];
+    int tile_m, tile_n;
+    const F32Product& p = tile_of(L, tile_m, tile_n);
+    const int i0 = tile_m * BM, j0 = tile_n * BN, m = p.m, n = p.n, K = p.k, lda = p.lda, ldb = p.ldb;
+    const float* __restrict__ A = p.a;
+    const float* __restrict__ B = p.b;
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, g = lane >> 5, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wk = wave >> 2, wm0 = ((wave >> 1) & 1) * 32, wn0 = (wave & 1) * 32;
+
+    // Each thread stages one chunk a step.  Rows beyond the matrix repeat its last one (their results are not stored).
+    const bool stages_a = wave < 4;
+    constexpr bool GROUPED = EPI == EPI_ACCUM_F32 && !A_KC && !B_KC;        // only those have column sums
+    const bool col_sums = GROUPED && p.bsum && tile_m == 0;
+    constexpr int STEP = sizeof(SplitBuf) / sizeof(bf16_t), PART = 64 * BK;
+    constexpr int D = A_KC ? 2 : 4;                              // steps that loads run ahead
+    const int KT = (K + BK - 1) / BK;
+    float cs = 0.f;
+    unsigned bits = 0;
+    f32x16 acc, low;                                             // the large parts' products, and the others
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = low[r] = 0.f;
+    const bf16_t* const get_a = &lds[0].part[0][0][wm0 + l32][split_chunk(wm0 + l32, 2 * wk + g) * 8];
+    const bf16_t* const get_b = &lds[0].part[1][0][wn0 + l32][split_chunk(wn0 + l32, 2 * wk + g) * 8];
+    // register r of lane l: row 8(r/4) + 4g + r%4, column l%32 - 128 contiguous bytes per half wavefront
+    constexpr int R = 8;
+    const int col = j0 + wn0 + l32;
+    auto row_of = [&](int r) { return i0 + wm0 + wk * 16 + 8 * (r >> 2) + 4 * g + (r & 3); };
+    // what the epilogue reads is asked for behind the last requests of the loop
+    constexpr bool READS = EPI == EPI_BIAS_RESIDUAL || EPI == EPI_DGELU || EPI == EPI_ACCUM_F32;
+    float bias = 0.f, other[R];
+    auto ask = [&] {
+        const int c = min(col, n - 1);
+        if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU || EPI == EPI_BIAS_RESIDUAL) bias = p.bias[c];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            other[r] = 0.f;
+            if (READS && !(EPI == EPI_ACCUM_F32 && L.flag)) other[r] = (EPI == EPI_ACCUM_F32 ? p.c : p.r)[(size_t)min(row_of(r), m - 1) * n + c];
+        }
+    };
+    auto steps = [&](auto kc_c, auto sums_c, const float* __restrict__ from, int ld, int row0, int rows) {
+        constexpr bool KC = decltype(kc_c)::value, SUMS = decltype(sums_c)::value;
+        const int srow = KC ? (tid & 255) >> 2 : lane, oct = KC ? tid & 3 : wave & 3;
+        SplitChunk<KC, BK> chunk(from, ld, row0, rows, BM, K, srow, oct);
+        bf16_t* const put = &lds[0].part[stages_a ? 0 : 1][0][srow][split_chunk(srow, oct) * 8];
+        float v[D][8];
+        auto stash = [&](int u, int kt, auto last_c) {
+            if (KC && decltype(last_c)::value && kt * BK + BK > K)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) v[u][j] = kt * BK + oct * 8 + j < K ? v[u][j] : 0.f;
+            if (SUMS) cs += ((v[u][0] + v[u][1]) + (v[u][2] + v[u][3])) + ((v[u][4] + v[u][5]) + (v[u][6] + v[u][7]));
+            split_store<PART>(v[u], put + (u & 1) * STEP, bits);
+        };
+        auto multiply = [&](int buf) {
+            bf16x8 fa[3], fb[3];
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                fa[q] = *reinterpret_cast<const bf16x8*>(get_a + buf * STEP + q * PART);
+                fb[q] = *reinterpret_cast<const bf16x8*>(get_b + buf * STEP + q * PART);
+            }
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[0], fb[0], acc, 0, 0, 0);
+            low = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[0], fb[1], low, 0, 0, 0);
+            low = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[1], fb[0], low, 0, 0, 0);
+            low = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[1], fb[1], low, 0, 0, 0);
+            low = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[0], fb[2], low, 0, 0, 0);
+            low = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[2], fb[0], low, 0, 0, 0);
+        };
+        static_assert(D % 2 == 0, "buffer of a step at compile time");
+#pragma unroll
+        for (int u = 0; u < D; ++u) chunk.load(v[u]);
+        stash(0, 0, std::true_type{});
+        chunk.load(v[0]);
+        __syncthreads();
+        // A step multiplies one buffer while the next step's chunks, loaded D steps ago, go to the other.
+        int kt = 0;
+        for (; kt + D + 1 < KT; kt += D)
+#pragma unroll
+            for (int u = 0; u < D; ++u) {
+                multiply(u & 1);
+                stash((u + 1) % D, kt + u + 1, std::false_type{});
+                chunk.load(v[(u + 1) % D]);
+                __syncthreads();
+            }
+        ask();
+#pragma unroll
+        for (int u = 0; u <= D; ++u) {
+            if (kt + u >= KT) break;
+            multiply(u & 1);
+            if (kt + u + 1 < KT) stash((u + 1) % D, kt + u + 1, std::true_type{});
+            __syncthreads();
+        }
+        if (SUMS && !stages_a) reinterpret_cast<float*>(lds)[8 * 8 * WAVE + oct * BN + srow] = cs;      // behind the exchange of sums
+    };
+    auto roles = [&](auto sums_c) {
+        if constexpr (A_KC == B_KC) steps(std::bool_constant<A_KC>{}, sums_c, stages_a ? A : B, stages_a ? lda : ldb, stages_a ? i0 : j0, stages_a ? m : n);
+        else if (stages_a) steps(std::bool_constant<A_KC>{}, std::false_type{}, A, lda, i0, m);
+        else steps(std::bool_constant<B_KC>{}, std::false_type{}, B, ldb, j0, n);
+    };
+    if constexpr (GROUPED) {
+        if (col_sums) roles(std::true_type{});
+        else roles(std::false_type{});
+    } else roles(std::false_type{});
+    // Two wavefronts with partial sums of one block: each hands over one half of its registers and
+    // finishes the other (registers 0..7 or 8..15, i.e. 16 of its rows).
+    static_assert(sizeof(lds) >= (8 * R * WAVE + 4 * BN + 8) * sizeof(float), "LDS too small for the exchange");
+    float* xch = reinterpret_cast<float*>(lds);
+    float* xcs = xch + 8 * R * WAVE;
+    int* redo = reinterpret_cast<int*>(xcs + 4 * BN);
+    float out[R];
+    auto meet = [&] {
+#pragma unroll
+        for (int r = 0; r < R; ++r) xch[(wave * R + r) * WAVE + lane] = wk ? acc[r] : acc[R + r];
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const float sum = xch[((wave ^ 4) * R + r) * WAVE + lane];
+            out[r] = wk ? sum + acc[R + r] : acc[r] + sum;
+        }
+    };
+    // Parts of an infinity give NaN.  Tiles with such sums, or with tiny numbers, are formed again on the float instructions.
+    bool again = all_tiny(bits);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        acc[r] += low[r];
+        again |= !(fabsf(acc[r]) < INFINITY);
+    }
+    again = __any(again);
+    if (lane == 0) redo[wave] = again;
+    meet();
+    int any = 0;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) any |= redo[w];
+    if (any) {
+        const int row = min(i0 + wm0 + l32, m - 1), col = min(j0 + wn0 + l32, n - 1);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+        for (int k0 = wk * 32; k0 < K; k0 += 64) {
+            f32x4 fa[4], fb[4];
+            load_slice<A_KC>(fa, A, lda, row, k0, K, g);
+            load_slice<B_KC>(fb, B, ldb, col, k0, K, g);
+            if (k0 + 32 > K) { mask_slice(fa, k0, K, g); mask_slice(fb, k0, K, g); }
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][j], fb[i][j], acc, 0, 0, 0);
+        }
+        __syncthreads();                       // everyone has read what is written again
+        meet();
+    }
+    if constexpr (GROUPED)
+        if (col_sums && tid < BN && j0 + tid < n) {
+            const float sum = (xcs[tid] + xcs[BN + tid]) + (xcs[2 * BN + tid] + xcs[3 * BN + tid]);
+            float* o = p.bsum + j0 + tid;
+            *o = L.flag ? sum : *o + sum;
+        }
+    if (col >= n) return;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (row_of(r) < m) finish_one<EPI>(p, L.flag, (size_t)row_of(r) * n + col, out[r], bias, other[r]);
+}
+
+// Larger outputs: 128x128, 4 wavefronts of 64x64, two workgroups on a CU, each thread stages a chunk of either operand: half of the vector work and
+// of the LDS reads per matrix instruction.  Float instructions -> 64x64 -> this, A B: 2048^3 156 -> 121 -> 104 us, 2048 x 16384 x 512 319 -> 246 -> 193,
+// 4096 x 4096 x 1024 - -> 226 -> 178.  Loads four steps ahead need more registers than there are (2048^3 131).
+template <bool A_KC, bool B_KC, int EPI>
+__global__ __launch_bounds__(4 * WAVE, 2) void gemm_f32_wide_kernel(F32Launch L) {
+    constexpr int BM = 128, BN = 128, BK = 16, NT = 4 * WAVE, TM = 2, TN = 2, CPR = BK / 8;
+    constexpr int PART_A = BM * BK, PART_B = BN * BK, STEP = 3 * (PART_A + PART_B);
+    __shared__ __attribute__((aligned(16))) bf16_t lds[2 * STEP];
+    // 16-byte chunk c of row r sits at c ^ bits of r: 16 rows of one chunk, as many chunks of neighbouring rows, all fall on different banks
+    auto chunk = [](int row, int c) { return c ^ ((row >> 3) & 1); };
+    int tile_m, tile_n;
+    const F32Product& p = tile_of(L, tile_m, tile_n);
+    const int i0 = tile_m * BM, j0 = tile_n * BN, m = p.m, n = p.n, K = p.k;
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, g = lane >> 5, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm0 = (wave >> 1) * 64, wn0 = (wave & 1) * (BN / 2);
+    const int KT = (K + BK - 1) / BK;
+    unsigned bits_a = 0, bits_b = 0;
+    float cs = 0.f;
+    f32x16 acc[TM][TN], low[TM][TN];
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[a][b][r] = low[a][b][r] = 0.f;
+
+    constexpr bool GROUPED = EPI == EPI_ACCUM_F32 && !A_KC && !B_KC;        // only those have column sums
+    const bool col_sums = GROUPED && p.bsum && tile_m == 0;
+    static_assert(BM * CPR == NT && BN * CPR == NT, "a chunk of either operand per thread");
+    auto row_of = [&](bool kc) { return kc ? tid / CPR : tid % BM; };
+    auto oct_of = [&](bool kc) { return kc ? tid % CPR : __builtin_amdgcn_readfirstlane(tid / BM); };
+    SplitChunk<A_KC, BK> ca(p.a, p.lda, i0, m, BM, K, row_of(A_KC), oct_of(A_KC));
+    SplitChunk<B_KC, BK> cb(p.b, p.ldb, j0, n, BN, K, row_of(B_KC), oct_of(B_KC));
+    bf16_t* const put_a = lds + row_of(A_KC) * BK + chunk(row_of(A_KC), oct_of(A_KC)) * 8;
+    bf16_t* const put_b = lds + 3 * PART_A + row_of(B_KC) * BK + chunk(row_of(B_KC), oct_of(B_KC)) * 8;
+    constexpr int D = 2;                                         // steps that loads run ahead
+    float va[D][8], vb[D][8];
+    auto fetch = [&](int u) { ca.load(va[u]); cb.load(vb[u]); };
+    auto stash = [&](int u, int kt, auto last_c) {
+        if ((A_KC || B_KC) && decltype(last_c)::value && kt * BK + BK > K)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                if (A_KC && kt * BK + oct_of(true) * 8 + j >= K) va[u][j] = 0.f;
+                if (B_KC && kt * BK + oct_of(true) * 8 + j >= K) vb[u][j] = 0.f;
+            }
+        split_store<PART_A>(va[u], put_a + (u & 1) * STEP, bits_a);
+        split_store<PART_B>(vb[u], put_b + (u & 1) * STEP, bits_b);
+        const float* v = vb[u];
+        if (GROUPED) cs += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+    };
+    auto multiply = [&](int buf) {
+        bf16x8 fa[TM][3], fb[TN][3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+#pragma unroll
+            for (int a = 0; a < TM; ++a) {
+                const int row = wm0 + a * 32 + l32;
+                fa[a][q] = *reinterpret_cast<const bf16x8*>(lds + buf * STEP + q * PART_A + row * BK + chunk(row, g) * 8);
+            }
+#pragma unroll
+            for (int b = 0; b < TN; ++b) {
+                const int row = wn0 + b * 32 + l32;
+                fb[b][q] = *reinterpret_cast<const bf16x8*>(lds + buf * STEP + 3 * PART_A + q * PART_B + row * BK + chunk(row, g) * 8);
+            }
+        }
+        // B's rows first: a lane's sums are then four neighbouring columns of a row
+#pragma unroll
+        for (int a = 0; a < TM; ++a)
+#pragma unroll
+            for (int b = 0; b < TN; ++b) {
+                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[b][0], fa[a][0], acc[a][b], 0, 0, 0);
+                low[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[b][1], fa[a][0], low[a][b], 0, 0, 0);
+                low[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[b][0], fa[a][1], low[a][b], 0, 0, 0);
+                low[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[b][1], fa[a][1], low[a][b], 0, 0, 0);
+                low[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[b][2], fa[a][0], low[a][b], 0, 0, 0);
+                low[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[b][0], fa[a][2], low[a][b], 0, 0, 0);
+            }
+    };
+    static_assert(D % 2 == 0, "buffer of a step at compile time");
+#pragma unroll
+    for (int u = 0; u < D; ++u) fetch(u);
+    stash(0, 0, std::true_type{});
+    fetch(0);
+    __syncthreads();
+    int kt = 0;
+    for (; kt + D + 1 < KT; kt += D)
+#pragma unroll
+        for (int u = 0; u < D; ++u) {
+            multiply(u & 1);
+            stash((u + 1) % D, kt + u + 1, std::false_type{});
+            fetch((u + 1) % D);
+            __syncthreads();
+        }
+#pragma unroll
+    for (int u = 0; u <= D; ++u) {
+        if (kt + u >= KT) break;
+        multiply(u & 1);
+        if (kt + u + 1 < KT) stash((u + 1) % D, kt + u + 1, std::true_type{});
+        __syncthreads();
+    }
+    bool again = all_tiny(bits_a) || all_tiny(bits_b);           // as in gemm_f32_tile_kernel
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                acc[a][b][r] += low[a][b][r];
+                again |= !(fabsf(acc[a][b][r]) < INFINITY);
+            }
+    if (__syncthreads_or(again)) {
+#pragma unroll
+        for (int a = 0; a < TM; ++a)
+#pragma unroll
+            for (int b = 0; b < TN; ++b) {
+                const int row = min(i0 + wm0 + a * 32 + l32, m - 1), col = min(j0 + wn0 + b * 32 + l32, n - 1);
+                f32x16 sum;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) sum[r] = 0.f;
+                for (int k0 = 0; k0 < K; k0 += 32) {
+                    f32x4 fa[4], fb[4];
+                    load_slice<A_KC>(fa, p.a, p.lda, row, k0, K, g);
+                    load_slice<B_KC>(fb, p.b, p.ldb, col, k0, K, g);
+                    if (k0 + 32 > K) { mask_slice(fa, k0, K, g); mask_slice(fb, k0, K, g); }
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) sum = __builtin_amdgcn_mfma_f32_32x32x2f32(fb[i][j], fa[i][j], sum, 0, 0, 0);
+                }
+                acc[a][b] = sum;
+            }
+    }
+    if constexpr (GROUPED)
+        if (col_sums) {                                          // a column's chunks lie in NT / BN threads
+            float* xcs = reinterpret_cast<float*>(lds);
+            xcs[tid] = cs;
+            __syncthreads();
+            if (tid < BN && j0 + tid < n) {
+                float sum = xcs[B_KC ? tid * CPR : tid];
+#pragma unroll
+                for (int i = 1; i < NT / BN; ++i) sum += xcs[B_KC ? tid * CPR + i : tid + i * BN];
+                float* o = p.bsum + j0 + tid;
+                *o = L.flag ? sum : *o + sum;
+            }
+        }
+#pragma unroll
+    for (int a = 0; a < TM; ++a) {
+        const int row = i0 + wm0 + a * 32 + l32;
+#pragma unroll
+        for (int b = 0; b < TN; ++b)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int col = j0 + wn0 + b * 32 + 8 * q + 4 * g;
+                float v[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = acc[a][b][4 * q + e];
+                if (row < m && col < n) finish<EPI, 4>(p, L.flag, row, col, v);      // n is a multiple of 4
+            }
+    }
+}
+
+// ----------------------------------------------------------------- small form
 template <int NW, bool A_KC, bool B_KC, int EPI>
 __global__ __launch_bounds__(NW* WAVE) void gemm_f32_small_kernel(F32Launch L) {
     __shared__ __attribute__((aligned(16))) float red[NW][32 * 32];
@@ -432,28 +659,38 @@ __global__ __launch_bounds__(NW* WAVE) void gemm_f32_tiny_kernel(F32Launch L) {
     }
 }
 
-enum Form { TILE64, SMALL, TINY };
+enum Form { WIDE128, TILE64, SMALL, TINY };
 
 // Up to two 16x16 tiles per CU take the tiny form.  32x32 -> 16x16: 128 x 384 x 128 3.2 -> 2.4 us, 128 x 128 x 512 (64 tiles) 5.8 -> 3.3 with
 // residual, 6.6 -> 3.9 A B^T, 256 x 256 x 1024 (256) 10.5 -> 5.7, 300 x 320 x 1280 (380) 12.6 -> 10.7, 512 x 256 x 256 (512) 4.2 -> 3.4,
 // x 1024 10.6 -> 9.2.
 constexpr long TINY_TILES = 2 * NUM_CUS;
 
-// Form of a launch.  Up to half a 64x64 tile per CU the small form's 32x32 tiles spread the work
-// further (512 x 1024 x 1024, 128 tiles: 20 against 23 us; 300 x 640 x 640, 50 tiles: 9.6 against 16);
-// beyond that the tile form's shared operands win (1000 x 640 x 2560, 160 tiles: 53 against 66 us;
-// 1024 x 1024 x 4096, 256 tiles: 85 against 140 us, 101 TFLOP/s; 2048^3: 160 us, 107 TFLOP/s).  128x128
-// tiles were 5 % faster at 4096 x 4096 x 1024 k-contiguous and slower everywhere else.
+// Form of a launch.  Up to half a 64x64 tile per CU the small form's 32x32 tiles spread the work further (512 x 1024 x 1024, 128 tiles: 19 to 21 us;
+// 512 x 512 x 2048, 64 tiles: 19 against 30 to 47); beyond that the larger tiles' shared operands win (512 x 1536 x 512, 192 tiles: 10.7 to
+// 15.3 against 15.0 to 17.4; 1024 x 1024 x 4096, 256 tiles: 62 to 88 against 129 to 149).  A round of 128x128 tiles (one per CU) takes as long
+// as 3.5 of 64x64, each of several 3.25, and begins and ends more slowly: 64x64 -> 128x128, A B and A^T B, 1024 x 4096 x 512 36.5 -> 33.6 and 38.0 -> 38.3 us,
+// x 1024 65.0 -> 55.0 and 65.7 -> 61.3, x 256 21.6 -> 21.4 and 24.2 -> 27.1; 1280 x 3840 x 512 (300 tiles) 43.1 -> 43.9 and 45.2 -> 53.5;
+// 1280 x 5120 x 640 (400) 68.9 -> 56.9 and 70.9 -> 66.3; 4096 x 4096 x 256 76 -> 57 and 82 -> 77; A^T B 1024 x 4096 x 128 16.6 -> 20.7.
 Form choose_form(int count, const GemmArgs* g) {
-    long t64 = 0;
-    for (int i = 0; i < count; ++i) t64 += (long)((g[i].m + 63) / 64) * ((g[i].n + 63) / 64);
-    return t64 <= NUM_CUS / 2 ? SMALL : TILE64;
+    long t64 = 0, t128 = 0;
+    for (int i = 0; i < count; ++i) {
+        t64 += (long)((g[i].m + 63) / 64) * ((g[i].n + 63) / 64);
+        t128 += (long)((g[i].m + 127) / 128) * ((g[i].n + 127) / 128);
+    }
+    bool far = false;                                            // beyond a buffer load's offsets
+    for (int i = 0; i < count; ++i) far |= g[i].lda > MAX_LD || g[i].ldb > MAX_LD;
+    if (far || t64 <= NUM_CUS / 2) return SMALL;
+    const long rounds64 = (t64 + NUM_CUS - 1) / NUM_CUS, rounds128 = (t128 + NUM_CUS - 1) / NUM_CUS;
+    const bool sums = g[0].epilogue == EPI_ACCUM_F32;
+    if (rounds128 == 1) return rounds64 == 4 && g[0].k >= (sums ? 768 : 512) ? WIDE128 : TILE64;
+    return 3.25 * rounds128 < rounds64 && !(sums && g[0].k < 192) ? WIDE128 : TILE64;
 }
 
 template <bool A_KC, bool B_KC, int EPI>
 int launch_form(F32Launch& L, Form form, hipStream_t s) {
     if (!A_KC && form == TINY) return fail(CHIMERA_EINVAL, "no 16x16 tile for weight gradients");       // (those go in groups, which are larger)
-    const int tile = form == TILE64 ? 64 : form == SMALL ? 32 : 16;
+    const int tile = form == WIDE128 ? 128 : form == TILE64 ? 64 : form == SMALL ? 32 : 16;
     L.total = 0;
     int kmax = 0;
     for (int i = 0; i < L.count; ++i) {
@@ -465,7 +702,8 @@ int launch_form(F32Launch& L, Form form, hipStream_t s) {
         kmax = std::max(kmax, p.k);
     }
     const dim3 grid(L.total);
-    if (form == TILE64) hipLaunchKernelGGL((gemm_f32_tile_kernel<A_KC, B_KC, EPI>), grid, dim3(8 * WAVE), 0, s, L);
+    if (form == WIDE128) hipLaunchKernelGGL((gemm_f32_wide_kernel<A_KC, B_KC, EPI>), grid, dim3(4 * WAVE), 0, s, L);
+    else if (form == TILE64) hipLaunchKernelGGL((gemm_f32_tile_kernel<A_KC, B_KC, EPI>), grid, dim3(8 * WAVE), 0, s, L);
     else if (form == TINY) {
         if constexpr (A_KC) {
             if (kmax <= 128) hipLaunchKernelGGL((gemm_f32_tiny_kernel<4, A_KC, B_KC, EPI>), grid, dim3(4 * WAVE), 0, s, L);

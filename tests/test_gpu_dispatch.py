@@ -690,3 +690,65 @@ def test_float_smallest_outputs(m, n, k):
         assert np.max(np.abs(to_np(c) - want)) <= 1e-5 * np.max(np.abs(want)), "epilogue %d" % epi
         if epi == b.EPI_BIAS_GELU:
             assert_close(to_np(c2), gelu(z + bias), b.F32, "gelu")
+
+
+# float products on split operands, 64x64 tiles (the first three) and 128x128 tiles: ragged edges, fewer steps than are loaded ahead, k with a
+# remainder; every epilogue, results and residual at an odd offset; weight gradients
+@pytest.mark.parametrize("m,n,k", [(1032, 584, 8), (1001, 776, 72), (584, 1480, 200), (2600, 2600, 24), (2601, 2600, 232), (2040, 2040, 776)])
+def test_float_split_products(m, n, k):
+    import torch
+    print("float split", m, n, k, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(m)
+    odd = lambda *shape: torch.randn(1 + int(np.prod(shape)), generator=gen, device="cuda")[1:].view(shape)
+    A, B, bias, R = torch.randn((m, k), generator=gen, device="cuda"), torch.randn((k, n), generator=gen, device="cuda") * 0.05, odd(n), odd(m, n)
+    z, size = A.double() @ B.double(), A.double().abs() @ B.double().abs()
+    # of the sum of a product's absolute terms: 2^-22 for parts left out, a rounding for every 16 products and for the few sums at the end (and of the epilogue)
+    tol = size * (4 + k / 16 + 8) * 2.0 ** -24 + 2.0 ** -21
+    gelu = lambda u: 0.5 * u * (1 + torch.tanh(np.sqrt(2 / np.pi) * (u + 0.044715 * u ** 3)))
+    u = R.double().requires_grad_()
+    slope, = torch.autograd.grad(gelu(u).sum(), u)
+    for epi, b_kc, want in ((b.EPI_NONE, 1, z), (b.EPI_BIAS, 0, z + bias), (b.EPI_BIAS_GELU, 0, z + bias), (b.EPI_BIAS_RESIDUAL, 0, z + bias + R),
+                            (b.EPI_DGELU, 1, z * slope)):
+        c, c2 = odd(m, n), odd(m, n)
+        b.chimera_op_gemm(A, B.T.contiguous() if b_kc else B, c, m, n, k, 1, b_kc, epi, bias, R, c2)
+        # of the values added and of GeLU's derivative (up to 1.13, hardware exp2 and reciprocal) some roundings
+        assert bool(((c.double() - want).abs() <= 1.2 * tol + want.abs() * 2.0 ** -20).all()), "epilogue %d" % epi
+        if epi == b.EPI_BIAS_GELU:
+            assert_close(to_np(c2), to_np(gelu(want)), b.F32, "gelu")
+    m = m // 8 * 8
+    c = torch.full((m, n), 0.5, device="cuda")
+    b.chimera_op_gemm(A[:m].T.contiguous(), B, c, m, n, k, 0, 0, b.EPI_ACCUM_F32)
+    assert bool(((c.double() - 0.5 - z[:m]).abs() <= tol[:m]).all())
+
+
+# what a split has to keep: every bit of a float (times one, in all ranges of exponents), infinities, NaN, sums near the largest float; 64x64 and 128x128 tiles
+@pytest.mark.parametrize("n", [1024, 2048])
+@pytest.mark.parametrize("layout", ["fwd", "dgrad", "wgrad"])
+def test_float_split_ranges(n, layout):
+    import torch
+    print("float split ranges", n, layout, flush=True)
+    a_kc, b_kc = {"fwd": (1, 0), "dgrad": (1, 1), "wgrad": (0, 0)}[layout]
+
+    def product(A, B):
+        c = torch.zeros((n, n), device="cuda")
+        b.chimera_op_gemm(A if a_kc else A.T.contiguous(), B.T.contiguous() if b_kc else B, c, n, n, n, a_kc, b_kc,
+                          b.EPI_NONE if a_kc else b.EPI_ACCUM_F32)
+        return c
+
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    X, Y, one = torch.randn((n, n), generator=gen, device="cuda"), torch.randn((n, n), generator=gen, device="cuda"), torch.eye(n, device="cuda")
+    for scale in (1.0, torch.exp2(torch.randint(-70, 120, (n, n), generator=gen, device="cuda").float()), 2.0 ** -97, 2.0 ** -120, 5e37):       # the largest of n^2 normal numbers: below 6.8
+        assert torch.equal(product(X * scale, one), X * scale) and torch.equal(product(one, X * scale), X * scale)
+    tiny = product(X * 2.0 ** -118, Y * 2.0 ** 100).double() * 2.0 ** 18
+    assert float((tiny - X.double() @ Y.double()).norm() / (X.double() @ Y.double()).norm()) <= n * 2.0 ** -24
+    X[5, 7], X[900, 3], X[70, 1], X[70, 2] = float("inf"), float("nan"), 3.4e38, 3.4e38
+    Y[1, 40] = Y[2, 40] = 1.0
+    got, want = product(X, Y), X.double() @ Y.double()
+    assert torch.equal(got[5].double(), want[5]) and bool(got[900].isnan().all()) and float(got[70, 40]) == float("inf")
+    rest = [i for i in range(n) if i not in (5, 70, 900)]
+    assert float((got[rest].double() - want[rest]).abs().max()) <= n * 2.0 ** -24 * float(want[rest].abs().max())
+
+
+# a block whose grouped float weight gradients and bias gradients take 128x128 tiles, tokens with a remainder
+def test_float_stage_on_wide_tiles():
+    _stage(b.F32, 768, 12, 203, 1)
