@@ -905,7 +905,7 @@ __device__ __forceinline__ void gemm_ring_tile(
     char* lds, const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, const bf16_t* __restrict__ bias,
     const bf16_t* __restrict__ R, void* __restrict__ C, bf16_t* __restrict__ C2, int m, int n, int k, int lda,
     int ldb, int epi, int epi_flag, int res_types, int tiles_m, int tiles_n, int group_m, int block_id,
-    float* __restrict__ bsum = nullptr, bool xcd_remap = true, int col0 = 0, const Ahead& ahead = {nullptr, 0}) {
+    float* __restrict__ bsum = nullptr, bool xcd_remap = true, int col0 = 0, const Ahead& ahead = {nullptr, 0}, int band = 0) {
     using Lds = RingLds<BM, BN, WGM, WGN, WGK>;
     constexpr int NT = WGM * WGN * WGK * 64, NS = Lds::STAGES;
     constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16, HM = TM / 2;      // 16x16 tiles per wavefront
@@ -913,12 +913,17 @@ __device__ __forceinline__ void gemm_ring_tile(
     constexpr unsigned STAGE = Lds::STAGE, ABYTES = BM * RK * 2;
 
     const int nblk = tiles_m * tiles_n;
-    const int pid = xcd_remap ? dealt<Lds::PER_CU>(block_id, nblk) : block_id;
-    const int width = group_m * tiles_n;
+    int pid = xcd_remap ? dealt<Lds::PER_CU>(block_id, nblk) : block_id, first_n = 0, cols = tiles_n;
+    if (band) {                                // see raster_band
+        first_n = pid / (tiles_m * band) * band;
+        pid -= first_n * tiles_m;
+        cols = min(band, tiles_n - first_n);
+    }
+    const int width = group_m * cols;
     const int first_m = (pid / width) * group_m;
     const int gsz = min(tiles_m - first_m, group_m);
     const int tile_m = first_m + (pid % width) % gsz;
-    const int tile_n = (pid % width) / gsz;
+    const int tile_n = first_n + (pid % width) / gsz;
     const int i0 = tile_m * BM, j0 = col0 + tile_n * BN;
 
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
@@ -1252,10 +1257,10 @@ template <int BM, int BN, int WGM, int WGN, int WGK, bool A_KC, bool B_KC>
 __global__ __launch_bounds__(WGM* WGN * WGK * 64, 2) void gemm_bf16_ring_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, const bf16_t* __restrict__ bias,
     const bf16_t* __restrict__ R, void* __restrict__ C, bf16_t* __restrict__ C2, int m, int n, int k, int lda,
-    int ldb, int epi, int epi_flag, int res_types, int tiles_m, int tiles_n, int group_m, int col0, Ahead ahead) {
+    int ldb, int epi, int epi_flag, int res_types, int tiles_m, int tiles_n, int group_m, int band, int col0, Ahead ahead) {
     __shared__ __attribute__((aligned(1024))) char lds[RingLds<BM, BN, WGM, WGN, WGK>::BYTES];
     gemm_ring_tile<BM, BN, WGM, WGN, WGK, A_KC, B_KC, -1>(lds, A, B, bias, R, C, C2, m, n, k, lda, ldb, epi, epi_flag, res_types,
-                                                          tiles_m, tiles_n, group_m, (int)blockIdx.x, nullptr, true, col0, ahead);
+                                                          tiles_m, tiles_n, group_m, (int)blockIdx.x, nullptr, true, col0, ahead, band);
 }
 
 // A long contraction with few output tiles, cut along k: workgroups [s * tiles, (s+1) * tiles) (numbered so
@@ -1360,7 +1365,7 @@ constexpr int MIXED_MAX = 5 * GROUP_MAX;
 struct MixedEntry {
     const bf16_t *a, *b;
     float *c, *bsum;
-    int m, n, lda, ldb, tiles_m, tiles_n, group_m, col0;
+    int m, n, lda, ldb, tiles_m, tiles_n, group_m, band, col0;
     int form;
 };
 constexpr int MIXED_PHASES = 3;
@@ -1397,7 +1402,7 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_mixed_group_kernel(MixedGrou
     const int tile = gid - grp.first[i];
 #define CHIMERA_MIXED(...)                                                                                                  \
     gemm_ring_tile<__VA_ARGS__, false, false, EPI_ACCUM_F32>(lds, e.a, e.b, nullptr, nullptr, e.c, nullptr, e.m, e.n, grp.k, \
-        e.lda, e.ldb, EPI_ACCUM_F32, grp.flags, 0, e.tiles_m, e.tiles_n, e.group_m, tile, e.bsum, false, e.col0)
+        e.lda, e.ldb, EPI_ACCUM_F32, grp.flags, 0, e.tiles_m, e.tiles_n, e.group_m, tile, e.bsum, false, e.col0, Ahead{nullptr, 0}, e.band)
     if (e.form == TILE_256) CHIMERA_MIXED(256, 256, 2, 4, 1);
     else if (e.form == TILE_128x256) CHIMERA_MIXED(128, 256, 1, 4, 2);
     else if (e.form == TILE_256x128) CHIMERA_MIXED(256, 128, 2, 2, 2);
@@ -1447,6 +1452,20 @@ int raster_group(int tiles_m, int tiles_n, int per_xcd, int bm, int bn) {
         if (cost < best * 0.999) { best = cost; best_g = g; }
     }
     return best_g;
+}
+
+// Launches of several rounds whose B (`bytes`) the memory-side cache does not keep beside what else they move: tile columns per band.  All tile
+// rows of a band come before the next band, so that B comes from HBM once and not for every raster group, and the tiles of a round, which are
+// in flight together, are about as many rows as columns.  0: one band.  Without -> with, final layer forward and backward, 3339 tokens of
+// 1624, vocabulary 58632 (190 MB) 2308 -> 2282 us; 8192 of 2048, 65536 (268 MB) 5843 -> 5676; but 4096 of 1024, 50304 (103 MB) 1330 -> 1351, 4096 x
+// 8192 x 2048 (34 MB) 98.5 -> 100.8.
+constexpr size_t B_IN_CACHE = (size_t)128 << 20;
+int raster_band(int tiles_m, int tiles_n, int round, size_t bytes) {
+    if (tiles_m * tiles_n <= round || bytes <= B_IN_CACHE) return 0;
+    int side = 1;
+    while (side * side < round) ++side;
+    const int band = std::max(side, round / tiles_m);
+    return band < tiles_n ? band : 0;
 }
 
 struct TileChoice { int bm, bn, splits; };
@@ -1609,12 +1628,14 @@ template <int BM, int BN, int WGM, int WGN, int WGK>
 int launch_ring(const GemmArgs& g, hipStream_t s, int col0 = 0, int cols256 = 0) {
     const int tm = (g.m + BM - 1) / BM, tn = cols256 ? cols256 * (256 / BN) : (g.n - col0 + BN - 1) / BN;
     const dim3 grid(tm * tn), block(WGM * WGN * WGK * 64);
-    const int gm = raster_group(tm, tn, std::min((tm * tn + 7) / 8, PER_XCD * RingLds<BM, BN, WGM, WGN, WGK>::PER_CU), BM, BN);
+    constexpr int PER_CU = RingLds<BM, BN, WGM, WGN, WGK>::PER_CU;
+    const int band = raster_band(tm, tn, NUM_CUS * PER_CU, (size_t)g.n * g.k * sizeof(bf16_t));
+    const int gm = raster_group(tm, band ? band : tn, std::min((tm * tn + 7) / 8, PER_XCD * PER_CU), BM, BN);
 #define CHIMERA_GEMM_LAUNCH(AKC, BKC)                                                                                \
     hipLaunchKernelGGL((gemm_bf16_ring_kernel<BM, BN, WGM, WGN, WGK, AKC, BKC>), grid, block, 0, s,                     \
                        (const bf16_t*)g.a, (const bf16_t*)g.b, (const bf16_t*)g.bias, (const bf16_t*)g.r, result(g), \
                        (bf16_t*)g.c2, g.m, g.n, g.k, g.lda, g.ldb, g.epilogue, epilogue_flag(g),                            \
-                       (g.r_f32 ? 1 : 0) | (g.c_f32 ? 2 : 0), tm, tn, gm, col0, ahead_of(g))
+                       (g.r_f32 ? 1 : 0) | (g.c_f32 ? 2 : 0), tm, tn, gm, band, col0, ahead_of(g))
     if (g.a_kc && !g.b_kc) CHIMERA_GEMM_LAUNCH(true, false);
     else if (g.a_kc && g.b_kc) CHIMERA_GEMM_LAUNCH(true, true);
     else CHIMERA_GEMM_LAUNCH(false, false);
@@ -1720,7 +1741,8 @@ int launch_group_mixed(int count, const GemmArgs* g, float* const* bsum, int ove
             MixedEntry& e = grp.e[i];
             if (grp.first[i] < p.first) continue;
             const int bm = e.form == TILE_128x256 || e.form == TILE_128 ? 128 : 256, bn = e.form == TILE_256x128 || e.form == TILE_128 ? 128 : 256;
-            e.group_m = raster_group(e.tiles_m, e.tiles_n, std::min((p.tiles + XCDS - 1) / XCDS, PER_XCD), bm, bn);
+            e.band = raster_band(e.tiles_m, e.tiles_n, NUM_CUS, (size_t)e.n * grp.k * sizeof(bf16_t));
+            e.group_m = raster_group(e.tiles_m, e.band ? e.band : e.tiles_n, std::min((p.tiles + XCDS - 1) / XCDS, PER_XCD), bm, bn);
         }
     };
     // rows [0, whole_m) of columns [0, whole_n) on 256x256 tiles, up to `rows` and `cols` cut smaller, then the remainders

@@ -274,11 +274,15 @@ bool wgrad_group_ok(const chimera_stage* st, const GemmArgs (&g)[4]) {
     return st->kernels == 0 && (st->dtype == CHIMERA_BF16 ? gemm_mfma_group_supports(4, g) : gemm_f32_group_supports(4, g));
 }
 // Where a pass moves more bytes than the memory-side cache holds, the gradients pass it by: they would push out what the next products
-// read, and their own next use finds them in HBM either way.  Kept -> passing by: six blocks of 1600 at 632 tokens, forward and backward,
-// 1653 -> 1606 us (the group alone, k = 640, 95.3 -> 90.7), gpt2-1p3b-n32 94.9 -> 94.4 ms, bert48 20.04 -> 19.88; but a block of 1024 at 512
-// tokens whose gradients the cache holds 28.9 -> 38.2 us.
+// read, and their own next use finds them in HBM either way.  Kept -> passing by: gpt2-1p3b-n32 94.9 -> 94.4 ms, bert48 20.04 -> 19.88; but a block
+// of 1024 at 512 tokens whose gradients the cache holds 28.9 -> 38.2 us.  Gradients that are overwritten only fill the cache, which can
+// take some 100 MB of them and write them back later.  Six blocks, forward and backward, 448 and 632 tokens: of 1152 1009 -> 1028 and 1205 -> 1221 us,
+// of 1200 (69 MB) 1335 -> 1373 and 1469 -> 1505, of 1360 (89 MB) 1484 -> 1492 and 1646 -> 1660, of 1600 (123 MB) 1505 -> 1477 and 1729 -> 1681.  With another
+// stage beside there is more to push out: bert48, whose first gradients are a quarter of all, 19.97 -> 19.83 ms.
+constexpr size_t CACHED_GRADIENTS = (size_t)100 << 20;
 int wgrad_group(chimera_stage* st, GemmArgs (&g)[4], float* const (&db)[4], int overwrite, hipStream_t stream) {
-    for (GemmArgs& a : g) a.c_once = pass_leaves_cache(st);
+    const bool once = pass_leaves_cache(st) && (!overwrite || st->beside || st->layer_params * sizeof(float) > CACHED_GRADIENTS);
+    for (GemmArgs& a : g) a.c_once = once;
     double flop = 0;
     for (int i = 0; i < 4; ++i) flop += 2.0 * g[i].m * g[i].n * g[i].k;
     ProfScope prof(PC_GEMM_WGRAD, flop, stream);
