@@ -237,7 +237,7 @@ def main():
         achieved = wg["work"] / (wg["ms"] * 1e-3) / 1e12 if wg["ms"] else 0.0
         out["roofline"] = {
             "kernel": ("%s (the four weight gradients of a block, dW += X^T dY in fp32, and their bias gradients, per block "
-                       "and micro-batch; the figures are those of the first instantiation named)"
+                       "and micro-batch)"
                        % b.lib().chimera_op_gemm_group_last_kernel().decode()
                        if dtype == b.BF16 else "gemm_ref_kernel (weight-gradient GEMMs)"),
             "bound": "mfma", "achieved": achieved, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",

@@ -277,7 +277,8 @@ bool wgrad_group_ok(const chimera_stage* st, const GemmArgs (&g)[4]) {
 // read, and their own next use finds them in HBM either way.  Kept -> passing by: gpt2-1p3b-n32 94.9 -> 94.4 ms, bert48 20.04 -> 19.88; but a block
 // of 1024 at 512 tokens whose gradients the cache holds 28.9 -> 38.2 us.  Gradients that are overwritten only fill the cache, which can
 // take some 100 MB of them and write them back later.  Six blocks, forward and backward, 448 and 632 tokens: of 1152 1009 -> 1028 and 1205 -> 1221 us,
-// of 1200 (69 MB) 1335 -> 1373 and 1469 -> 1505, of 1360 (89 MB) 1484 -> 1492 and 1646 -> 1660, of 1600 (123 MB) 1505 -> 1477 and 1729 -> 1681.  With another
+// of 1200 (69 MB) 1335 -> 1373 and 1469 -> 1505, of 1360 (89 MB) 1484 -> 1492 and 1646 -> 1660, of 1536 (113 MB) 1431 -> 1444 and 1591 -> 1598, of 1600 (123 MB) 1504 -> 1465 and
+// 1714 -> 1672, of 1920 1857 -> 1791 and 2283 -> 2274, of 2048 2088 -> 2138 and 2509 -> 2473, of 2304 2367 -> 2316 and 2843 -> 2780.  With another
 // stage beside there is more to push out: bert48, whose first gradients are a quarter of all, 19.97 -> 19.83 ms.
 constexpr size_t CACHED_GRADIENTS = (size_t)100 << 20;
 int wgrad_group(chimera_stage* st, GemmArgs (&g)[4], float* const (&db)[4], int overwrite, hipStream_t stream) {
