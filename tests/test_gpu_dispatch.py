@@ -752,3 +752,28 @@ def test_float_split_ranges(n, layout):
 # a block whose grouped float weight gradients and bias gradients take 128x128 tiles, tokens with a remainder
 def test_float_stage_on_wide_tiles():
     _stage(b.F32, 768, 12, 203, 1)
+
+
+# operands with NaN between their rows (64x64 and 128x128 tiles), and with rows too far apart for the tiles' offsets (32x32 tiles)
+@pytest.mark.parametrize("m,n,k,gap", [(1032, 584, 72, 8), (2600, 2600, 200, 24), (1032, 584, 8, 1 << 22)])
+@pytest.mark.parametrize("layout", ["fwd", "dgrad", "wgrad"])
+def test_float_split_strides(m, n, k, gap, layout):
+    import torch
+    print("float split strides", m, n, k, gap, layout, flush=True)
+    a_kc, b_kc = {"fwd": (1, 0), "dgrad": (1, 1), "wgrad": (0, 0)}[layout]
+    gen = torch.Generator(device="cuda").manual_seed(m)
+    A, B = torch.randn((m, k), generator=gen, device="cuda"), torch.randn((k, n), generator=gen, device="cuda")
+
+    def spread(X, wide):
+        rows, cols = X.shape
+        Y = torch.full((rows, cols + (gap if wide else 8)), float("nan"), device="cuda")
+        Y[:, :cols] = X
+        return Y
+
+    few = gap > 1 << 20                                           # only eight rows of an operand may lie that far apart
+    da, db = spread(A if a_kc else A.T, not few or not a_kc), spread(B.T if b_kc else B, not few or not b_kc)
+    c = torch.zeros((m, n), device="cuda")
+    b.chimera_op_gemm(da, db, c, m, n, k, a_kc, b_kc, b.EPI_NONE if a_kc else b.EPI_ACCUM_F32, lda=da.shape[1], ldb=db.shape[1])
+    want, size = A.double() @ B.double(), A.double().abs() @ B.double().abs()
+    # as above; the float instructions round once for every second product
+    assert bool(((c.double() - want).abs() <= size * (12 + (k / 2 if few else k / 16)) * 2.0 ** -24).all())
