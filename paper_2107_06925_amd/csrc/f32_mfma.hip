@@ -132,11 +132,12 @@ __device__ __forceinline__ void mask_slice(f32x4 (&v)[4], int k0, int K, int g) 
 }
 
 // ------------------------------------------------------------------ tile forms
-// On the bf16 matrix instructions.  A float is the sum of three bf16 numbers: its upper 16 bits, the rest to nearest, and what that leaves
-// (8 + 8 + 8 bits), so a product of two floats is nine products of their parts.  The three smallest are left out: below 2^-22 of it,
-// 2^-25 as a rule, a rounding's size.  A bf16 instruction rounds once for 16 products where the float one rounds for every second:
-// against float64, relative 2-norm, k = 64, 256, 1024, 4096: 1.06e-7 -> 5.3e-8, 2.06e-7 -> 7.4e-8, 4.06e-7 -> 1.32e-7, 8.10e-7 -> 2.73e-7 (128x128 tiles, whose
-// sums are not halved: 9.2e-8, 1.86e-7, 3.95e-7).  The sums of the large parts' products and of the others are kept apart until the end.
+// On the bf16 matrix instructions.  A float is the sum of three bf16 numbers: itself to nearest, the rest to nearest, and what that leaves
+// (8 + 8 + 8 bits), so a product of two floats is nine products of their parts.  The three smallest are left out: at most 2^-24 of it, one
+// rounding (a first part cut off instead leaves up to 2^-22, all of one sign for some operands).  A bf16 instruction rounds once for 16 products where the float one rounds for every second:
+// against float64, relative 2-norm of random operands, k = 64, 256, 1024, 4096: 1.06e-7 -> 4.8e-8, 2.06e-7 -> 7.1e-8, 4.06e-7 -> 1.30e-7, 8.10e-7 -> 2.74e-7
+// (128x128 tiles, whose sums are not halved, from 256 on: 8.9e-8, 1.86e-7, 3.96e-7); all elements 1.0077362: 5.7e-9 at every k, 2.3e-7 with a first part
+// cut off.  The sums of the large parts' products and of the others are kept apart until the end.
 //
 // What bounds it: with two wavefronts on a SIMD matrix and vector instructions overlap by a third at best (8 of the former alone 140 ns, 64 of the
 // latter 148, both 202), and a 64x64 step of 32 k is 12 and 100 of them; LDS is busy 44 % of the time, without conflicts.  Against tiles of
@@ -184,11 +185,11 @@ template <int PART> __device__ __forceinline__ void split_store(const float (&v)
     unsigned w[3][4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const unsigned x = __float_as_uint(v[2 * j]), y = __float_as_uint(v[2 * j + 1]);
-        const float rx = v[2 * j] - __uint_as_float(x & 0xffff0000u), ry = v[2 * j + 1] - __uint_as_float(y & 0xffff0000u);
+        const unsigned top = __builtin_bit_cast(unsigned, bf16x2{(bf16_t)v[2 * j], (bf16_t)v[2 * j + 1]});
+        const float rx = v[2 * j] - __uint_as_float(top << 16), ry = v[2 * j + 1] - __uint_as_float(top & 0xffff0000u);
         const unsigned mid = __builtin_bit_cast(unsigned, bf16x2{(bf16_t)rx, (bf16_t)ry});
         const float lx = rx - __uint_as_float(mid << 16), ly = ry - __uint_as_float(mid & 0xffff0000u);
-        w[0][j] = __builtin_amdgcn_perm(y, x, 0x07060302u);      // upper halves
+        w[0][j] = top;
         w[1][j] = mid;
         w[2][j] = __builtin_amdgcn_perm(__float_as_uint(ly), __float_as_uint(lx), 0x07060302u);       // no more than eight bits are left
     }

@@ -721,6 +721,24 @@ def test_float_split_products(m, n, k):
     assert bool(((c.double() - 0.5 - z[:m]).abs() <= tol[:m]).all())
 
 
+# what the products leave out does not add up: operands whose parts beyond the first all have one sign and nearly their largest size, sums of
+# the first parts that take no rounding; 64x64 and 128x128 tiles
+@pytest.mark.parametrize("m,n,k", [(1024, 1024, 8), (1024, 1024, 64), (1032, 1032, 256), (2600, 2600, 256)])
+@pytest.mark.parametrize("layout", ["fwd", "dgrad", "wgrad"])
+def test_float_split_of_one_sign(m, n, k, layout):
+    import torch
+    print("float split one sign", m, n, k, layout, flush=True)
+    a_kc, b_kc = {"fwd": (1, 0), "dgrad": (1, 1), "wgrad": (0, 0)}[layout]
+    for value in (1.0077362, 1.0038910):                         # 1 + 2^-7 or 1 + 2^-8, and most of a bit of the first part less or more
+        A, B = (torch.full((m, k) if a_kc else (k, m), value, device="cuda"), torch.full((n, k) if b_kc else (k, n), -value, device="cuda"))
+        c = torch.zeros((m, n), device="cuda")
+        b.chimera_op_gemm(A, B, c, m, n, k, a_kc, b_kc, b.EPI_NONE if a_kc else b.EPI_ACCUM_F32)
+        want = -k * float(A[0, 0]) ** 2
+        # left out: two products of a second part (2^-8 of the value) and a third (2^-17), 2^-24; then the sum of large and small products and that of two halves
+        # of k, a rounding each, and the small products' own (at most 80, of 2^-8 of the sum)
+        assert float((c.double() / want - 1).abs().max()) <= (1 + 2 + 80 * 2.0 ** -8) * 2.0 ** -24
+
+
 # what a split has to keep: every bit of a float (times one, in all ranges of exponents), infinities, NaN, sums near the largest float; 64x64 and 128x128 tiles
 @pytest.mark.parametrize("n", [1024, 2048])
 @pytest.mark.parametrize("layout", ["fwd", "dgrad", "wgrad"])
