@@ -179,8 +179,8 @@ template <bool KC, int BK> struct SplitChunk {
 };
 constexpr int MAX_LD = 1 << 22;                                // 128 rows, or 32 k, of them stay below 2^31 bytes
 
-// Writes a chunk's parts, part p at `at` + p * PART; the upper parts' bits join `bits`.
-template <int PART> __device__ __forceinline__ void split_store(const float (&v)[8], bf16_t* at, unsigned& bits) {
+// Writes a chunk's parts, part p at `at` + p * PART.  `rest` takes in the third parts, whose lower halves are not stored: see loses.
+template <int PART> __device__ __forceinline__ void split_store(const float (&v)[8], bf16_t* at, unsigned& rest) {
     typedef bf16_t bf16x2 __attribute__((ext_vector_type(2)));
     unsigned w[3][4];
 #pragma unroll
@@ -188,17 +188,18 @@ template <int PART> __device__ __forceinline__ void split_store(const float (&v)
         const unsigned top = __builtin_bit_cast(unsigned, bf16x2{(bf16_t)v[2 * j], (bf16_t)v[2 * j + 1]});
         const float rx = v[2 * j] - __uint_as_float(top << 16), ry = v[2 * j + 1] - __uint_as_float(top & 0xffff0000u);
         const unsigned mid = __builtin_bit_cast(unsigned, bf16x2{(bf16_t)rx, (bf16_t)ry});
-        const float lx = rx - __uint_as_float(mid << 16), ly = ry - __uint_as_float(mid & 0xffff0000u);
+        const unsigned lx = __float_as_uint(rx - __uint_as_float(mid << 16)), ly = __float_as_uint(ry - __uint_as_float(mid & 0xffff0000u));
         w[0][j] = top;
         w[1][j] = mid;
-        w[2][j] = __builtin_amdgcn_perm(__float_as_uint(ly), __float_as_uint(lx), 0x07060302u);       // no more than eight bits are left
+        w[2][j] = __builtin_amdgcn_perm(ly, lx, 0x07060302u);
+        rest |= lx | ly;
     }
-    bits |= (w[0][0] | w[0][1]) | (w[0][2] | w[0][3]);
 #pragma unroll
     for (int p = 0; p < 3; ++p) *reinterpret_cast<uint4*>(at + p * PART) = make_uint4(w[p][0], w[p][1], w[p][2], w[p][3]);
 }
-// Numbers below 2^-95 only (all exponents' upper bits are zero), and not just zeros: the instructions have no bits left for their smallest parts
-__device__ __forceinline__ bool all_tiny(unsigned bits) { const unsigned b = (bits | bits >> 16) & 0x7fff; return b && b < 32u << 7; }
+// A third part has no more than eight bits, which bf16 holds, unless some lie below its smallest step, 2^-133: parts of a float from 2^-110 on are exact
+// (the matrix instructions keep subnormal operands and sums), and one smaller number that is not is seen here, whatever lies beside it.
+__device__ __forceinline__ bool loses(unsigned rest) { return rest & 0xffff; }
 
 // 8 wavefronts: two share a 32x32 block, each with half of every k step; four stage A's rows, four B's.
 template <bool A_KC, bool B_KC, int EPI>
@@ -221,7 +222,7 @@ __global__ __launch_bounds__(8 * WAVE, 4) void gemm_f32_tile_kernel(F32Launch L)
     constexpr int D = A_KC ? 2 : 4;                              // steps that loads run ahead
     const int KT = (K + BK - 1) / BK;
     float cs = 0.f;
-    unsigned bits = 0;
+    unsigned rest = 0;
     f32x16 acc, low;                                             // the large parts' products, and the others
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = low[r] = 0.f;
@@ -254,7 +255,7 @@ __global__ __launch_bounds__(8 * WAVE, 4) void gemm_f32_tile_kernel(F32Launch L)
 #pragma unroll
                 for (int j = 0; j < 8; ++j) v[u][j] = kt * BK + oct * 8 + j < K ? v[u][j] : 0.f;
             if (SUMS) cs += ((v[u][0] + v[u][1]) + (v[u][2] + v[u][3])) + ((v[u][4] + v[u][5]) + (v[u][6] + v[u][7]));
-            split_store<PART>(v[u], put + (u & 1) * STEP, bits);
+            split_store<PART>(v[u], put + (u & 1) * STEP, rest);
         };
         auto multiply = [&](int buf) {
             bf16x8 fa[3], fb[3];
@@ -322,8 +323,8 @@ __global__ __launch_bounds__(8 * WAVE, 4) void gemm_f32_tile_kernel(F32Launch L)
             out[r] = wk ? sum + acc[R + r] : acc[r] + sum;
         }
     };
-    // Parts of an infinity give NaN.  Tiles with such sums, or with tiny numbers, are formed again on the float instructions.
-    bool again = all_tiny(bits);
+    // Parts of an infinity give NaN.  Tiles with such sums, or whose parts lost bits, are formed again on the float instructions.
+    bool again = loses(rest);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         acc[r] += low[r];
@@ -380,7 +381,7 @@ __global__ __launch_bounds__(4 * WAVE, 2) void gemm_f32_wide_kernel(F32Launch L)
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, g = lane >> 5, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm0 = (wave >> 1) * 64, wn0 = (wave & 1) * (BN / 2);
     const int KT = (K + BK - 1) / BK;
-    unsigned bits_a = 0, bits_b = 0;
+    unsigned rest = 0;
     float cs = 0.f;
     f32x16 acc[TM][TN], low[TM][TN];
 #pragma unroll
@@ -409,8 +410,8 @@ __global__ __launch_bounds__(4 * WAVE, 2) void gemm_f32_wide_kernel(F32Launch L)
                 if (A_KC && kt * BK + oct_of(true) * 8 + j >= K) va[u][j] = 0.f;
                 if (B_KC && kt * BK + oct_of(true) * 8 + j >= K) vb[u][j] = 0.f;
             }
-        split_store<PART_A>(va[u], put_a + (u & 1) * STEP, bits_a);
-        split_store<PART_B>(vb[u], put_b + (u & 1) * STEP, bits_b);
+        split_store<PART_A>(va[u], put_a + (u & 1) * STEP, rest);
+        split_store<PART_B>(vb[u], put_b + (u & 1) * STEP, rest);
         const float* v = vb[u];
         if (GROUPED) cs += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
     };
@@ -464,7 +465,7 @@ __global__ __launch_bounds__(4 * WAVE, 2) void gemm_f32_wide_kernel(F32Launch L)
         if (kt + u + 1 < KT) stash((u + 1) % D, kt + u + 1, std::true_type{});
         __syncthreads();
     }
-    bool again = all_tiny(bits_a) || all_tiny(bits_b);           // as in gemm_f32_tile_kernel
+    bool again = loses(rest);                                    // as in gemm_f32_tile_kernel
 #pragma unroll
     for (int a = 0; a < TM; ++a)
 #pragma unroll

@@ -767,6 +767,28 @@ def test_float_split_ranges(n, layout):
     assert float((got[rest].double() - want[rest]).abs().max()) <= n * 2.0 ** -24 * float(want[rest].abs().max())
 
 
+# numbers too small for three parts beside ordinary ones: each is seen, whatever a thread or a row has besides; 64x64 and 128x128 tiles
+@pytest.mark.parametrize("n", [1024, 2048])
+@pytest.mark.parametrize("layout", ["fwd", "dgrad", "wgrad"])
+@pytest.mark.parametrize("small", ["a", "b"])
+def test_float_split_of_mixed_magnitudes(n, layout, small):
+    import torch
+    print("float split mixed magnitudes", n, layout, small, flush=True)
+    a_kc, b_kc = {"fwd": (1, 0), "dgrad": (1, 1), "wgrad": (0, 0)}[layout]
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    X, Y = torch.randn((n, n), generator=gen, device="cuda"), torch.randn((n, n), generator=gen, device="cuda")
+    for least, ones, left in ((-118, slice(0, None, 4), n - n // 4), (-125, slice(0, n - 1), 1)):         # ones in every chunk of k; in all places but one
+        A, B = X * 2.0 ** least, Y * 2.0 ** 100
+        A[:, ones], B[ones] = 1.0, 0.0
+        if small == "b":
+            A, B = B.T.contiguous(), A.T.contiguous()
+        c = torch.zeros((n, n), device="cuda")
+        b.chimera_op_gemm(A if a_kc else A.T.contiguous(), B.T.contiguous() if b_kc else B, c, n, n, n, a_kc, b_kc, b.EPI_NONE if a_kc else b.EPI_ACCUM_F32)
+        want, size = A.double() @ B.double(), A.double().abs() @ B.double().abs()
+        # the float instructions, which take every number here with all its bits, round once for every second product that is not zero; few sums at the end
+        assert bool(((c.double() - want).abs() <= size * (left / 2 + 3) * 2.0 ** -24).all())
+
+
 # a block whose grouped float weight gradients and bias gradients take 128x128 tiles, tokens with a remainder
 def test_float_stage_on_wide_tiles():
     _stage(b.F32, 768, 12, 203, 1)
