@@ -141,9 +141,9 @@ __device__ __forceinline__ void mask_slice(f32x4 (&v)[4], int k0, int K, int g) 
 //
 // What bounds it: with two wavefronts on a SIMD matrix and vector instructions overlap by a third at best (8 of the former alone 140 ns, 64 of the
 // latter 148, both 202), and a 64x64 step of 32 k is 12 and 100 of them; LDS is busy 44 % of the time, without conflicts.  Against tiles of
-// v_mfma_f32_32x32x2_f32, which were bound by that instruction: 1024 x 1024 x 1024 A B 27.0 -> 21.3 us, A B^T 25.7 -> 20.5, A^T B 29.0 -> 21.5;
-// 1024 x 3072 x 1024 64.7 -> 50.6; 704 x 2816 x 704 33.2 -> 24.4; 1000 x 1000 x 104 6.5 -> 6.0; two steps of k are slower, 1024 x 1024 x 64
-// 4.84 -> 5.07.  Splitting in registers, a wavefront per k slice of a whole tile, was slower (2048^3 118 -> 161 us: no registers are left to load ahead).
+// v_mfma_f32_32x32x2_f32, which were bound by that instruction: 1024 x 1024 x 1024 A B 24.1 -> 20.0 us, A B^T 23.3 -> 18.5, A^T B 26.9 -> 19.1;
+// 1024 x 3072 x 1024 62.0 -> 47.4; 704 x 2816 x 704 30.9 -> 22.7; two steps of k, 1024 x 1024 x 64, 5.17 either way.
+// Splitting in registers, a wavefront per k slice of a whole tile, was slower (2048^3 118 -> 161 us: no registers are left to load ahead).
 struct SplitBuf { bf16_t part[2][3][64][32]; };                // operand, part, row, k: one step
 // 16-byte chunk c (8 k values) of row r sits at c ^ bits of r: 16 rows of one chunk, as many of four rows, all fall on different banks
 __device__ __forceinline__ int split_chunk(int row, int c) { return c ^ ((row >> 2) & 3); }
@@ -201,6 +201,19 @@ template <int PART> __device__ __forceinline__ void split_store(const float (&v)
 // (the matrix instructions keep subnormal operands and sums), and one smaller number that is not is seen here, whatever lies beside it.
 __device__ __forceinline__ bool loses(unsigned rest) { return rest & 0xffff; }
 
+// Asks the scheduler for one order of a step's instructions: the LDS reads, FIRST matrix instructions, then one of them behind every VALUS vector
+// instructions of the split.  Its own order has most matrix instructions first and the split behind them.  1024 x 1024 x 1024 A B 21.5 -> 20.1 us, A B^T
+// 19.6 -> 18.3; 2048^3 103 -> 95, A B^T 105 -> 92, A^T B 112 -> 102.  (64x64 tiles of A^T B are faster in its own order: 19.5 against 19.9 to 21.0.)
+template <int READS, int FIRST, int REST, int VALUS> __device__ __forceinline__ void interleave() {
+    __builtin_amdgcn_sched_group_barrier(0x100, READS, 0);
+    __builtin_amdgcn_sched_group_barrier(0x008, FIRST, 0);
+#pragma unroll
+    for (int i = 0; i < REST; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x002, VALUS, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    }
+}
+
 // 8 wavefronts: two share a 32x32 block, each with half of every k step; four stage A's rows, four B's.
 template <bool A_KC, bool B_KC, int EPI>
 __global__ __launch_bounds__(8 * WAVE, 4) void gemm_f32_tile_kernel(F32Launch L) {
@@ -219,7 +232,7 @@ __global__ __launch_bounds__(8 * WAVE, 4) void gemm_f32_tile_kernel(F32Launch L)
     constexpr bool GROUPED = EPI == EPI_ACCUM_F32 && !A_KC && !B_KC;        // only those have column sums
     const bool col_sums = GROUPED && p.bsum && tile_m == 0;
     constexpr int STEP = sizeof(SplitBuf) / sizeof(bf16_t), PART = 64 * BK;
-    constexpr int D = A_KC ? 2 : 4;                              // steps that loads run ahead
+    constexpr int D = 2;                                         // steps that loads run ahead (four, A^T B: 19.5 -> 20.4 us)
     const int KT = (K + BK - 1) / BK;
     float cs = 0.f;
     unsigned rest = 0;
@@ -285,6 +298,8 @@ __global__ __launch_bounds__(8 * WAVE, 4) void gemm_f32_tile_kernel(F32Launch L)
                 multiply(u & 1);
                 stash((u + 1) % D, kt + u + 1, std::false_type{});
                 chunk.load(v[(u + 1) % D]);
+                if constexpr (A_KC && B_KC) interleave<6, 1, 5, 8>();
+                else if constexpr (A_KC && !KC) interleave<6, 2, 4, 13>();
                 __syncthreads();
             }
         ask();
@@ -366,8 +381,8 @@ __global__ __launch_bounds__(8 * WAVE, 4) void gemm_f32_tile_kernel(F32Launch L)
 }
 
 // Larger outputs: 128x128, 4 wavefronts of 64x64, two workgroups on a CU, each thread stages a chunk of either operand: half of the vector work and
-// of the LDS reads per matrix instruction.  Float instructions -> 64x64 -> this, A B: 2048^3 156 -> 121 -> 104 us, 2048 x 16384 x 512 319 -> 246 -> 193,
-// 4096 x 4096 x 1024 - -> 226 -> 178.  Loads four steps ahead need more registers than there are (2048^3 131).
+// of the LDS reads per matrix instruction.  Float instructions -> 64x64 -> this, A B: 2048^3 155 -> 121 -> 98 us, 2048 x 16384 x 512 319 -> 246 -> 193 (before
+// interleave), 4096 x 4096 x 1024 - -> 226 -> 178 (before it).  Loads four steps ahead need more registers than there are (2048^3 131).
 template <bool A_KC, bool B_KC, int EPI>
 __global__ __launch_bounds__(4 * WAVE, 2) void gemm_f32_wide_kernel(F32Launch L) {
     constexpr int BM = 128, BN = 128, BK = 16, NT = 4 * WAVE, TM = 2, TN = 2, CPR = BK / 8;
@@ -456,6 +471,8 @@ __global__ __launch_bounds__(4 * WAVE, 2) void gemm_f32_wide_kernel(F32Launch L)
             multiply(u & 1);
             stash((u + 1) % D, kt + u + 1, std::false_type{});
             fetch((u + 1) % D);
+            if constexpr (A_KC && B_KC) interleave<12, 1, 23, 5>();
+            else interleave<12, 4, 20, 6>();
             __syncthreads();
         }
 #pragma unroll
