@@ -411,6 +411,27 @@ def test_bf16_products_of_several_rounds(m, n, k, layout):
     assert float((dc.cpu().double() - want).abs().max()) <= tol * float(want.abs().max())
 
 
+# launches of several rounds whose B exceeds half of the memory-side cache (128 MB): tile columns in bands, several groups of tile rows in each.  9x66 tiles of
+# 256x256 in bands of 28, 28 and 10 (as a weight gradient 8x64 of them in bands of 32, and halves); 6x86, the last column on smaller
+# tiles and the others in bands of 42, 42 and 1; 22x26 tiles of 128x128, two per CU, in bands of 23 and 3
+@pytest.mark.parametrize("m,n,k", [(2056, 16648, 4040), (1512, 21960, 3064), (2816, 3328, 20168)])
+@pytest.mark.parametrize("layout", ["fwd", "dgrad", "wgrad"])
+def test_bf16_products_in_bands_of_columns(m, n, k, layout):
+    import torch
+    print("bf16 bands", m, n, k, layout, flush=True)
+    assert n * k * 2 > 128 << 20
+    a_kc, b_kc = {"fwd": (1, 0), "dgrad": (1, 1), "wgrad": (0, 0)}[layout]
+    gen = torch.Generator(device="cuda").manual_seed(m)
+    A, B = (torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16) for shape in ((m, k), (k, n)))
+    want = A.double() @ B.double()
+    da, db = A if a_kc else A.T.contiguous(), B.T.contiguous() if b_kc else B
+    dc = torch.full((m, n), 0.0 if layout == "wgrad" else float("nan"), dtype=torch.float32 if layout == "wgrad" else torch.bfloat16, device="cuda")
+    b.chimera_op_gemm(da, db, dc, m, n, k, a_kc, b_kc, b.EPI_ACCUM_F32 if layout == "wgrad" else b.EPI_NONE)
+    # float sums of k exact products of the order of sqrt(k), a rounding for 16 or 32 of them; and one rounding to bf16
+    tol = 2.0 ** -24 * k / 16 * 8 + (0 if layout == "wgrad" else 2.0 ** -8)
+    assert float((dc.double() - want).abs().max()) <= tol * float(want.abs().max())
+
+
 # grouped weight gradients with column sums on 256x256 tiles and on both forms of 128x128 tiles
 @pytest.mark.parametrize("k", [64, 128, 192, 320, 576])
 @pytest.mark.parametrize("shapes", [[(1032, 1544), (2056, 1032), (1032, 2312), (1032, 1288)], [(1032, 1544), (1032, 520)],
