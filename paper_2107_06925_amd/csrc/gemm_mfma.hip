@@ -1695,24 +1695,37 @@ int launch_group_mixed(int count, const GemmArgs* g, float* const* bsum, int ove
     const bool quarters = 4 * over <= NUM_CUS;
     const long left = full % NUM_CUS;                        // of the whole tiles alone
     const bool fill = smaller && !quarters && full > NUM_CUS && half + 2 * left <= NUM_CUS;
-    long todo = fill ? left : over <= full && (quarters || (over > half && 2 * over <= NUM_CUS)) ? over : 0;
+    const long todo = fill ? left : over <= full && (quarters || (over > half && 2 * over <= NUM_CUS)) ? over : 0;
     const long most = quarters ? NUM_CUS / 4 : (NUM_CUS - (fill ? half : 0)) / 2;
-    while (todo > 0) {                                           // whole bands of rows or columns, as many tiles as come nearest
-        int best = -1;
-        bool by_rows = true;
-        long got = 0, bands = 0;
-        auto offer = [&](int i, bool rows, long left_over, long per) {
-            if (left_over <= 0 || per <= 0) return;
-            const long n = std::min(left_over, (todo + per - 1) / per), t = n * per;
-            if (t <= most && (best < 0 || std::labs(t - todo) < std::labs(got - todo))) { best = i; by_rows = rows; got = t; bands = n; }
-        };
-        for (int i = 0; i < count; ++i) {
-            offer(i, true, fm[i] - cut_m[i], fn[i] - cut_n[i]);
-            offer(i, false, fn[i] - cut_n[i], fm[i] - cut_m[i]);
-        }
-        if (best < 0) break;
-        (by_rows ? cut_m : cut_n)[best] += (int)bands;
-        todo -= got;
+    // Whole bands of rows or columns of one product, or bands of two kinds where that does not do, that come to `todo` tiles or the fewest more, and
+    // to a round of the smaller tiles at most; less than `todo` would leave the last round as it is.  With one kind only, which may find nothing, ->
+    // so: a block of 2696 at 2048 tokens (117 tiles) 435 -> 420 us, 1496 x 13464 x 2048 (62: a row of 53, two columns of 5) 111 -> 91; but with two kinds wherever
+    // they come nearer a block of 1152 (19 tiles in place of 20) 78 -> 88.
+    auto tiles_of = [&](int i, bool rows) { return (long)(rows ? fn[i] - cut_n[i] : fm[i] - cut_m[i]); };
+    auto bands_of = [&](int i, bool rows) { return (long)(rows ? fm[i] - cut_m[i] : fn[i] - cut_n[i]); };
+    auto take = [&](int i, bool rows, long bands) { (rows ? cut_m : cut_n)[i] += (int)bands; };
+    struct Bands { int i; bool rows; long count; } first{}, last{}, none{};
+    long best = most + 1;
+    auto finish = [&](const Bands& before, long got) {
+        for (int i = 0; i < count; ++i)
+            for (bool rows : {true, false}) {
+                const long per = tiles_of(i, rows), bands = per > 0 ? (todo - got + per - 1) / per : 0;
+                if (bands > 0 && bands <= bands_of(i, rows) && got + bands * per < best) { best = got + bands * per; first = before; last = {i, rows, bands}; }
+            }
+    };
+    if (todo > 0) {
+        finish(none, 0);
+        if (best > most)
+            for (int i = 0; i < count; ++i)
+                for (bool rows : {true, false}) {
+                    const long per = tiles_of(i, rows), bands = per > 0 ? std::min(todo / per, bands_of(i, rows)) : 0;
+                    if (bands <= 0) continue;
+                    take(i, rows, bands);
+                    finish({i, rows, bands}, bands * per);
+                    take(i, rows, -bands);
+                }
+        take(first.i, first.rows, first.count);
+        take(last.i, last.rows, last.count);
     }
     MixedGroup grp{};
     grp.k = g[0].k; grp.flags = (overwrite ? ACCUM_OVERWRITE : 0) | (g[0].c_once ? ACCUM_ONCE : 0);

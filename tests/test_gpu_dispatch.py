@@ -452,11 +452,11 @@ def test_bf16_groups(k, shapes):
 
 
 # groups on tiles of several sizes: remainders of 64 and 8 rows and columns on half tiles, what a full round leaves over on quarters
-# (44 and 20 tiles; bands of rows, and of columns where a row is wider than that) or halves (128), a product that is one half tile high; accumulating (column sums too) and overwriting
+# (44 and 20 tiles; bands of rows, and of columns where a row is wider than that; 62 tiles: a row of 53 and two columns of 5) or halves (128), a product that is one half tile high; accumulating (column sums too) and overwriting
 @pytest.mark.parametrize("k", [64, 192, 320])
 @pytest.mark.parametrize("shapes", [[(5120, 1280), (1280, 5120), (1280, 1280), (1280, 3840)], [(6400, 1600), (1600, 6400), (1600, 1600), (1600, 4800)],
                                     [(5376, 1344), (1344, 5376), (1344, 1344), (1344, 4032)], [(4104, 4104), (72, 2056), (2056, 72)],
-                                    [(1032, 17416)], [(17416, 1032)]])
+                                    [(1032, 17416)], [(17416, 1032)], [(1496, 13464)]])
 def test_bf16_groups_of_mixed_tiles(k, shapes):
     import torch
     print("bf16 mixed group", k, shapes, flush=True)
