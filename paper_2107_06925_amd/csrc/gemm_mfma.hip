@@ -585,7 +585,8 @@ __device__ __forceinline__ void gemm_async_tile(
     constexpr int KSUB = BK / 16 / WGK;                                   // 16-wide k slices per wavefront and step
     static_assert(KSUB >= 1 && KSUB * WGK * 16 == BK, "k split must divide the step");
     constexpr int WM = BM / WGM, WN = BN / WGN;
-    constexpr int TM = WM / 32, TN = WN / 32;
+    constexpr int TM = WM / 32;                                           // a wavefront's 32x32 blocks, below one another
+    static_assert(WN == 32, "rows of 32 columns");
     constexpr int CA = BM * (BK / 8) / NT, CB = BN * (BK / 8) / NT;      // 16-byte pieces per thread and stage
     constexpr int STAGE = (BM + BN) * BK;                                 // elements
     __shared__ __attribute__((aligned(16))) bf16_t lds[NS * STAGE];
@@ -646,7 +647,6 @@ __device__ __forceinline__ void gemm_async_tile(
     // The wavefronts of a block of the tile hold partial sums of it, one per k slice; in the end each finishes its share of the rows, a lane
     // 8 columns of rows row0, row0 + 16, ...
     constexpr int SHARE = WM / WGK, PIECES = (SHARE + 15) / 16;
-    static_assert(TN == 1, "rows of 32 columns");
     const int row0 = wk * SHARE + lane / 4, gcol = j0 + wn0 + lane % 4 * 8;
     // With two workgroups on a CU each hides the other's last trip, and these requests hold back the first operands.  Without them A^T B 1472 x 1280 x 512
     // 7.56 -> 7.24 us, groups of 12 x 384^2 x 1024 10.36 -> 9.97, A B^T with the GeLU derivative 1088 x 1088 x 192 5.54 -> 5.39; but A B x 64 4.2 -> 4.4.
@@ -655,26 +655,22 @@ __device__ __forceinline__ void gemm_async_tile(
     auto ask = [&] { pre.request(i0 + wm0 + row0, gcol, m, n, bias, R, C, ONLY_EPI >= 0 ? ONLY_EPI : epi, epi_flag, res_types); };
     if (EPI_AHEAD) ask();
 
-    f32x16 acc[TM][TN];
+    f32x16 acc[TM][1];
 #pragma unroll
     for (int a = 0; a < TM; ++a)
 #pragma unroll
-        for (int b = 0; b < TN; ++b)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
+        for (int r = 0; r < 16; ++r) acc[a][0][r] = 0.f;
 
     // Optional by-product: bsum[j] += sum over the contraction index of B(k, j), i.e. an extra
     // all-ones row of A.  The wavefronts at the top edge of the first tile row compute it
-    // with one more MFMA per 32 columns (every row of that accumulator is the column sum).
+    // with one more MFMA per step (every row of that accumulator is the column sum).
     const bool col_sums = bsum != nullptr && tile_m == 0 && wm0 == 0;
-    f32x16 cs[TN];
+    f32x16 cs;
     bf16x8 ones;
 #pragma unroll
     for (int q = 0; q < 8; ++q) ones[q] = (bf16_t)1.0f;
 #pragma unroll
-    for (int b = 0; b < TN; ++b)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) cs[b][r] = 0.f;
+    for (int r = 0; r < 16; ++r) cs[r] = 0.f;
 
     const int KT = k / BK;
     auto compute = [&](int stage) {
@@ -683,20 +679,14 @@ __device__ __forceinline__ void gemm_async_tile(
 #pragma unroll
         for (int ks = 0; ks < KSUB; ++ks) {
             const int kk = wk * KSUB + ks;
-            bf16x8 af[TM], bfr[TN];
+            bf16x8 af[TM];
 #pragma unroll
             for (int a = 0; a < TM; ++a) af[a] = read_frag<BM, A_KC>(As, wm0 + a * 32, kk, lane);
+            const bf16x8 bfr = read_frag<BN, B_KC>(Bs, wn0, kk, lane);
 #pragma unroll
-            for (int b = 0; b < TN; ++b) bfr[b] = read_frag<BN, B_KC>(Bs, wn0 + b * 32, kk, lane);
-#pragma unroll
-            for (int a = 0; a < TM; ++a)
-#pragma unroll
-                for (int b = 0; b < TN; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[b], af[a], acc[a][b], 0, 0, 0);
+            for (int a = 0; a < TM; ++a) acc[a][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr, af[a], acc[a][0], 0, 0, 0);
             if constexpr (ONLY_EPI == EPI_ACCUM_F32)
-                if (col_sums)
-#pragma unroll
-                    for (int b = 0; b < TN; ++b) cs[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, bfr[b], cs[b], 0, 0, 0);
+                if (col_sums) cs = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, bfr, cs, 0, 0, 0);
         }
     };
     if (k % BK) {
@@ -726,7 +716,7 @@ __device__ __forceinline__ void gemm_async_tile(
     // ring, leave the order to the compiler: with it fixed there too, and every instruction behind a condition, k = 192 to 768 takes 3 to 5 %
     // longer (A B^T 1280 x 768 x 320 4.68 -> 4.50 us, A B 1088 x 1088 x 512 6.32 -> 6.05).
     auto iteration = [&] {
-        bf16x8 af[SPS][KSUB][TM], bfr[SPS][KSUB][TN];
+        bf16x8 af[SPS][KSUB][TM], bfr[SPS][KSUB];
         int st = cur;
 #pragma unroll
         for (int u = 0; u < SPS; ++u) {
@@ -736,18 +726,17 @@ __device__ __forceinline__ void gemm_async_tile(
             for (int ks = 0; ks < KSUB; ++ks) {
 #pragma unroll
                 for (int a = 0; a < TM; ++a) af[u][ks][a] = read_frag<BM, A_KC>(As, wm0 + a * 32, wk * KSUB + ks, lane);
-#pragma unroll
-                for (int b = 0; b < TN; ++b) bfr[u][ks][b] = read_frag<BN, B_KC>(As + BM * BK, wn0 + b * 32, wk * KSUB + ks, lane);
+                bfr[u][ks] = read_frag<BN, B_KC>(As + BM * BK, wn0, wk * KSUB + ks, lane);
             }
         }
         cur = st;
         __builtin_amdgcn_sched_barrier(0);
-        constexpr int REQ = SPS * (CA + CB), MM = SPS * KSUB * TM * TN, PER = (REQ + MM - 1) / MM;
+        constexpr int REQ = SPS * (CA + CB), MM = SPS * KSUB * TM, PER = (REQ + MM - 1) / MM;
         static_for<MM>([&](auto i_c) {
-            constexpr int i = decltype(i_c)::value, u = i / (KSUB * TM * TN), ks = i / (TM * TN) % KSUB, a = i / TN % TM, b = i % TN;
-            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[u][ks][b], af[u][ks][a], acc[a][b], 0, 0, 0);
+            constexpr int i = decltype(i_c)::value, u = i / (KSUB * TM), ks = i / TM % KSUB, a = i % TM;
+            acc[a][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[u][ks], af[u][ks][a], acc[a][0], 0, 0, 0);
             if constexpr (ONLY_EPI == EPI_ACCUM_F32 && a == 0)
-                if (col_sums) cs[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, bfr[u][ks][b], cs[b], 0, 0, 0);
+                if (col_sums) cs = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, bfr[u][ks], cs, 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
             static_for<PER>([&](auto j_c) {
                 constexpr int r = i * PER + decltype(j_c)::value, it = r % (CA + CB);
@@ -793,11 +782,11 @@ __device__ __forceinline__ void gemm_async_tile(
     float* xcs = slabs + NT / 64 * TM * BAND + wn0 + lane;
     static_for<TM>([&](auto a_c) { Acc32<TM, 1>{acc}.template put<decltype(a_c)::value>(slabs + (wave * TM + decltype(a_c)::value) * BAND, lane); });
     if constexpr (ONLY_EPI == EPI_ACCUM_F32)               // row 0 of a column-sum accumulator: register 0 of lanes 0..31
-        if (col_sums && lane < 32) xcs[wk * BN] = cs[0][0];
+        if (col_sums && lane < 32) xcs[wk * BN] = cs[0];
     __syncthreads();
     if constexpr (ONLY_EPI == EPI_ACCUM_F32)
         if (col_sums && wk == 0 && lane < 32) {
-            float v = cs[0][0];
+            float v = cs[0];
 #pragma unroll
             for (int w = 1; w < WGK; ++w) v += xcs[w * BN];
             const int col = j0 + wn0 + lane;
@@ -1773,7 +1762,6 @@ int launch_group_mixed(int count, const GemmArgs* g, float* const* bsum, int ove
         put(i, quarters ? TILE_128 : TILE_256x128, 0, rows(i), whole_n(i), cols(i) - whole_n(i));
     }
     close(2);
-    note_group_kernel("gemm_bf16_mixed_group_kernel");
     hipLaunchKernelGGL(gemm_bf16_mixed_group_kernel, dim3(local * XCDS), dim3(512), 0, stream, grp);
     CHIMERA_LAUNCH_CHECK("bf16 gemm group");
     return CHIMERA_OK;
@@ -1981,7 +1969,10 @@ int gemm_mfma_bf16_group(int count, const GemmArgs* g, float* const* bsum, int o
     }
     const int forced = forced_tile().bm;
     const int tile = forced == 256 || forced == 128 ? forced : t256 >= 160 ? 256 : small_tiles(t64) ? 64 : 128;
-    if (tile == 256) return launch_group_mixed(count, g, bsum, overwrite, forced == 0, (hipStream_t)stream);
+    if (tile == 256) {
+        note_group_kernel("gemm_bf16_mixed_group_kernel");
+        return launch_group_mixed(count, g, bsum, overwrite, forced == 0, (hipStream_t)stream);
+    }
     return launch_group_tiled(count, g, bsum, overwrite, tile, (hipStream_t)stream);
 }
 

@@ -476,6 +476,22 @@ def test_bf16_groups_of_mixed_tiles(k, shapes):
             assert float((bs.cpu().double() / passes - wb).abs().max()) <= tol * float(wb.abs().max())
 
 
+# a single weight gradient, on the same kernel as large groups, is none: the name for reports stays the last group's
+def test_last_group_kernel_is_of_a_group():
+    import torch
+    print("last group kernel", flush=True)
+    name = lambda: b.lib().chimera_op_gemm_group_last_kernel().decode()
+    X, c = torch.zeros((64, 4096), dtype=torch.bfloat16, device="cuda"), torch.zeros((4096, 4096), device="cuda")
+    b.chimera_op_gemm_group_accumulate([(X[:, :128], X[:, :256], c.view(-1)[:128 * 256].view(128, 256))], 64)
+    small = name()
+    assert "mixed" not in small and small
+    b.chimera_op_gemm(X, X, c, 4096, 4096, 64, 0, 0, b.EPI_ACCUM_F32)
+    assert name() == small
+    b.chimera_op_gemm_group_accumulate([(X, X, c)], 64)
+    assert name() == "gemm_bf16_mixed_group_kernel"
+    torch.cuda.synchronize()
+
+
 # token counts that are no multiple of the contraction steps, and gradients that start from anything
 @pytest.mark.parametrize("dtype,hidden,heads,seq,microbatch", [(b.F32, 64, 2, 75, 1), (b.F32, 136, 2, 37, 3), (b.F32, 256, 4, 130, 2),
                                                                  (b.BF16, 128, 2, 75, 1), (b.BF16, 136, 1, 37, 3), (b.BF16, 560, 7, 99, 1),
