@@ -247,7 +247,7 @@ def main():
             "flop_per_launch": wg["work"] / max(wg["launches"], 1),
             "note": "from one more iteration in which the two stages take turns; kernel_classes, all_stage_gemms and stage_times too",
         }
-        gemm_classes = ("gemm_fwd", "gemm_dgrad", "gemm_wgrad", "gemm_wgrad_tail")
+        gemm_classes = ("gemm_fwd", "gemm_dgrad", "gemm_wgrad")
         gemm_ms = sum(prof[k]["ms"] for k in gemm_classes)
         gemm_flop = sum(prof[k]["work"] for k in gemm_classes)
         all_tf = gemm_flop / (gemm_ms * 1e-3) / 1e12 if gemm_ms else 0.0

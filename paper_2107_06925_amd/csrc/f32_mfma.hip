@@ -312,6 +312,7 @@ __global__ __launch_bounds__(8 * WAVE, 4) void gemm_f32_tile_kernel(F32Launch L)
         }
         if (SUMS && !stages_a) reinterpret_cast<float*>(lds)[8 * 8 * WAVE + oct * BN + srow] = cs;      // behind the exchange of sums
     };
+    // Wavefronts of A and of B may take different arms, each with its own barriers: one before the loop and one behind each of the KT steps in both.
     auto roles = [&](auto sums_c) {
         if constexpr (A_KC == B_KC) steps(std::bool_constant<A_KC>{}, sums_c, stages_a ? A : B, stages_a ? lda : ldb, stages_a ? i0 : j0, stages_a ? m : n);
         else if (stages_a) steps(std::bool_constant<A_KC>{}, std::false_type{}, A, lda, i0, m);

@@ -33,7 +33,7 @@ static inline size_t align_up(size_t v, size_t a = 256) { return (v + a - 1) / a
 
 // Optional per-kernel-class timing: a HIP event pair around every launch of a
 // class on the stage's stream, summed after the stream has been waited for.
-enum ProfClass { PC_GEMM_FWD, PC_GEMM_DGRAD, PC_GEMM_WGRAD, PC_ATTN_FWD, PC_ATTN_BWD, PC_LN_FWD, PC_LN_BWD, PC_COLSUM, PC_GEMM_WGRAD_TAIL, PC_COUNT };
+enum ProfClass { PC_GEMM_FWD, PC_GEMM_DGRAD, PC_GEMM_WGRAD, PC_ATTN_FWD, PC_ATTN_BWD, PC_LN_FWD, PC_LN_BWD, PC_COLSUM, PC_RESERVED, PC_COUNT };      // PC_RESERVED: nothing fills it; callers read it as zero
 struct ProfRec { hipEvent_t a, b; int cls; double work; };
 struct Profiler {
     bool on = false;
