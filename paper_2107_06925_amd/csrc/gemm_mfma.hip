@@ -193,7 +193,6 @@ template <typename T> struct Raw8;
 template <> struct Raw8<bf16_t> {
     uint4 q;
     __device__ __forceinline__ void load(const bf16_t* p) { q = *reinterpret_cast<const uint4*>(p); }
-    __device__ __forceinline__ void load_once(const bf16_t* p) { load(p); }
     __device__ __forceinline__ void unpack(float* o) const {
         const unsigned w[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
@@ -204,10 +203,6 @@ template <> struct Raw8<float> {
     float4 lo, hi;
     __device__ __forceinline__ void load(const float* p) {
         lo = *reinterpret_cast<const float4*>(p); hi = *reinterpret_cast<const float4*>(p + 4);
-    }
-    __device__ __forceinline__ void load_once(const float* p) {
-        lo = __builtin_bit_cast(float4, __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p)));
-        hi = __builtin_bit_cast(float4, __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p + 4)));
     }
     __device__ __forceinline__ void unpack(float* o) const {
         o[0] = lo.x; o[1] = lo.y; o[2] = lo.z; o[3] = lo.w; o[4] = hi.x; o[5] = hi.y; o[6] = hi.z; o[7] = hi.w;
@@ -283,12 +278,7 @@ __device__ __forceinline__ void finish8(float* v, const float* bv, const float* 
     } else {
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] += rv[e];    // rv = 0 when the result replaces C
-        if (epi_flag & ACCUM_ONCE) {
-            __builtin_nontemporal_store(f32x4{v[0], v[1], v[2], v[3]}, reinterpret_cast<f32x4*>(Cf + idx));
-            __builtin_nontemporal_store(f32x4{v[4], v[5], v[6], v[7]}, reinterpret_cast<f32x4*>(Cf + idx + 4));
-        } else {
-            store8(Cf + idx, v);
-        }
+        store8(Cf + idx, v);
     }
 }
 // What a launch's epilogue is, as template arguments of `f`: f.operator()<EPI, R is float, C is float>()
@@ -307,22 +297,74 @@ template <typename F> __device__ __forceinline__ void with_epilogue(int epi, int
         default: f.template operator()<EPI_ACCUM_F32, false, false>(); break;
     }
 }
+// The float accumulate of one wavefront.  A lane takes 4 columns, so that an instruction's pieces are whole rows of the wavefront's tile: with 8, in two
+// instructions, each had every other 16 bytes of the lines, and C, where it passes the caches by, was written in parts of lines.  8 columns -> 4: blocks
+// of 1344, 1792 and 2560 at 2048 tokens 95.6 -> 94.5, 172.6 -> 163.2 and 363 -> 355 us; six blocks of 1600 and 2048, forward and backward, at 448 tokens
+// 1501 -> 1466 and 2099 -> 1879, at 632 1689 -> 1667 and 2457 -> 2357.
+template <bool ONCE, int TM, int TN, typename Acc>
+__device__ __forceinline__ void accumulate(const Acc& acc, float* slab, int row_base, int col_base, int m, int n, float* __restrict__ C, int epi_flag, int lane) {
+    constexpr int CPR = EpiSlab<TN>::WN / 4, RPP = 64 / CPR, NP = 32 / RPP;       // lanes per row, rows at once, passes per band of 32 rows
+    constexpr int DEPTH = TM < 2 ? TM : 2;                                         // bands whose old values are asked for ahead
+    const int pr = lane / CPR, piece = lane % CPR, gcol = col_base + piece * 4, lcol = min(gcol, n - 4);
+    const bool reads = !(epi_flag & ACCUM_OVERWRITE);
+    f32x4 old[DEPTH][NP];
+    auto request = [&](int a, auto slot_c) {
+        constexpr int SLOT = decltype(slot_c)::value;
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            // pieces outside the matrix are requested from its last row / last piece (never used)
+            const f32x4* from = reinterpret_cast<const f32x4*>(C + (size_t)min(row_base + a * 32 + j * RPP + pr, m - 1) * n + lcol);
+            if constexpr (ONCE) old[SLOT][j] = __builtin_nontemporal_load(from);
+            else old[SLOT][j] = *from;
+        }
+    };
+    if (reads) {
+        request(0, std::integral_constant<int, 0>{});
+        if constexpr (TM > 1) request(1, std::integral_constant<int, 1>{});
+    }
+    auto band = [&](auto a_c) {
+        constexpr int a = decltype(a_c)::value, SLOT = a % DEPTH;
+        acc.template put<a>(slab, lane);
+        __builtin_amdgcn_s_waitcnt(0xc07f);                   // lgkmcnt(0): the slab is written (wavefront-private)
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            const int lr = j * RPP + pr, grow = row_base + a * 32 + lr;
+            f32x4 v = *reinterpret_cast<const f32x4*>(EpiSlab<TN>::at(slab, lr, piece));
+            if (reads) v += old[SLOT][j];
+            if (grow >= m || gcol >= n) continue;
+            f32x4* to = reinterpret_cast<f32x4*>(C + (size_t)grow * n + gcol);
+            if constexpr (ONCE) __builtin_nontemporal_store(v, to);
+            else *to = v;
+        }
+        __builtin_amdgcn_wave_barrier();                      // all lanes have read the slab before it is rewritten
+        if constexpr (a + DEPTH < TM)
+            if (reads) request(a + DEPTH, std::integral_constant<int, SLOT>{});
+    };
+    band(std::integral_constant<int, 0>{});
+    if constexpr (TM > 1) band(std::integral_constant<int, 1>{});
+    if constexpr (TM > 2) band(std::integral_constant<int, 2>{});
+    if constexpr (TM > 3) band(std::integral_constant<int, 3>{});
+}
 template <int EPI, bool RF32, bool CF32, int TM, int TN, typename Acc>
 __device__ __forceinline__ void epilogue(const Acc& acc, float* slab, int row_base, int col_base, int m,
                                          int n, const bf16_t* __restrict__ bias, const bf16_t* __restrict__ R,
                                          void* __restrict__ c, bf16_t* __restrict__ C2, int epi_flag, int lane) {
+    if constexpr (EPI == EPI_ACCUM_F32) {
+        if (epi_flag & ACCUM_ONCE) accumulate<true, TM, TN>(acc, slab, row_base, col_base, m, n, (float*)c, epi_flag, lane);
+        else accumulate<false, TM, TN>(acc, slab, row_base, col_base, m, n, (float*)c, epi_flag, lane);
+        return;
+    }
     constexpr int WN = EpiSlab<TN>::WN;
     constexpr int CPR = WN / 8;                // 8-column pieces per row
     constexpr int RPP = 64 / CPR;              // rows covered by the 64 lanes at once
     constexpr int NP = 32 / RPP;               // passes per band of 32 rows
-    constexpr bool READS_F32 = EPI == EPI_ACCUM_F32 || (EPI == EPI_BIAS_RESIDUAL && RF32);
-    constexpr bool READS = EPI == EPI_BIAS_RESIDUAL || EPI == EPI_DGELU || EPI == EPI_ACCUM_F32;
-    using RT = std::conditional_t<READS_F32, float, bf16_t>;
-    constexpr int DEPTH = !READS ? 1 : (READS_F32 ? (TM < 2 ? TM : 2) : TM);
+    constexpr bool READS = EPI == EPI_BIAS_RESIDUAL || EPI == EPI_DGELU;
+    using RT = std::conditional_t<EPI == EPI_BIAS_RESIDUAL && RF32, float, bf16_t>;
+    constexpr int DEPTH = !READS ? 1 : (sizeof(RT) == 4 ? (TM < 2 ? TM : 2) : TM);
     const int pr = lane / CPR, pc = (lane % CPR) * 8;
     const int gcol = col_base + pc;
-    const bool reads = READS && !(EPI == EPI_ACCUM_F32 && (epi_flag & ACCUM_OVERWRITE));      // an overwriting accumulate reads nothing
-    const RT* Rsrc = EPI == EPI_ACCUM_F32 ? reinterpret_cast<const RT*>(c) : reinterpret_cast<const RT*>(R);
+    const RT* Rsrc = reinterpret_cast<const RT*>(R);
     // pieces outside the matrix are requested from its last row / last piece (never used)
     const int lcol = min(gcol, n - 8);
     Raw8<RT> ahead[DEPTH][NP];
@@ -331,9 +373,7 @@ __device__ __forceinline__ void epilogue(const Acc& acc, float* slab, int row_ba
 #pragma unroll
         for (int j = 0; j < NP; ++j) {
             const int grow = min(row_base + a * 32 + j * RPP + pr, m - 1);
-            const RT* from = Rsrc + (size_t)grow * n + lcol;
-            if (EPI == EPI_ACCUM_F32 && (epi_flag & ACCUM_ONCE)) ahead[SLOT][j].load_once(from);
-            else ahead[SLOT][j].load(from);
+            ahead[SLOT][j].load(Rsrc + (size_t)grow * n + lcol);
         }
     };
     float bv[8];
@@ -343,12 +383,10 @@ __device__ __forceinline__ void epilogue(const Acc& acc, float* slab, int row_ba
         if (gcol < n) load8(bias + gcol, bv);
     }
     if constexpr (READS) {
-        if (reads) {
-            request(0, std::integral_constant<int, 0>{});
-            if constexpr (DEPTH > 1 && TM > 1) request(1, std::integral_constant<int, 1 % DEPTH>{});
-            if constexpr (DEPTH > 2 && TM > 2) request(2, std::integral_constant<int, 2 % DEPTH>{});
-            if constexpr (DEPTH > 3 && TM > 3) request(3, std::integral_constant<int, 3 % DEPTH>{});
-        }
+        request(0, std::integral_constant<int, 0>{});
+        if constexpr (DEPTH > 1 && TM > 1) request(1, std::integral_constant<int, 1 % DEPTH>{});
+        if constexpr (DEPTH > 2 && TM > 2) request(2, std::integral_constant<int, 2 % DEPTH>{});
+        if constexpr (DEPTH > 3 && TM > 3) request(3, std::integral_constant<int, 3 % DEPTH>{});
     }
     static_assert(TM <= 4, "at most four bands per wavefront");
     auto band = [&](auto a_c) {
@@ -365,18 +403,12 @@ __device__ __forceinline__ void epilogue(const Acc& acc, float* slab, int row_ba
             load_vec<float>(EpiSlab<TN>::at(slab, lr, pc / 4), v);
             load_vec<float>(EpiSlab<TN>::at(slab, lr, pc / 4 + 1), v + 4);
             float rv[8];
-            if constexpr (READS) {
-                if (reads) ahead[SLOT][j].unpack(rv);
-                else
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) rv[e] = 0.f;
-            }
+            if constexpr (READS) ahead[SLOT][j].unpack(rv);
             if (grow >= m || gcol >= n) continue;
             finish8<EPI, CF32>(v, bv, rv, (size_t)grow * n + gcol, c, C2, epi_flag);
         }
         __builtin_amdgcn_wave_barrier();                      // all lanes have read the slab before it is rewritten
-        if constexpr (READS && a + DEPTH < TM)
-            if (reads) request(a + DEPTH, std::integral_constant<int, SLOT>{});
+        if constexpr (READS && a + DEPTH < TM) request(a + DEPTH, std::integral_constant<int, SLOT>{});
     };
     band(std::integral_constant<int, 0>{});
     if constexpr (TM > 1) band(std::integral_constant<int, 1>{});

@@ -274,16 +274,12 @@ bool wgrad_group_ok(const chimera_stage* st, const GemmArgs (&g)[4]) {
     return st->kernels == 0 && (st->dtype == CHIMERA_BF16 ? gemm_mfma_group_supports(4, g) : gemm_f32_group_supports(4, g));
 }
 // Where a pass moves more bytes than the memory-side cache holds, the gradients pass it by: they would push out what the next products
-// read, and their own next use finds them in HBM either way.  Kept -> passing by: gpt2-1p3b-n32 94.9 -> 94.4 ms, bert48 20.04 -> 19.88; but a block
-// of 1024 at 512 tokens whose gradients the cache holds 28.9 -> 38.2 us.  Gradients that are overwritten only fill the cache, which can
-// take some 100 MB of them and write them back later.  Six blocks, forward and backward, 448 and 632 tokens: of 1152 1009 -> 1028 and 1205 -> 1221 us,
-// of 1200 (69 MB) 1335 -> 1373 and 1469 -> 1505, of 1360 (89 MB) 1484 -> 1492 and 1646 -> 1660, of 1536 (113 MB) 1431 -> 1444 and 1591 -> 1598, of 1600 (123 MB) 1504 -> 1465 and
-// 1714 -> 1672, of 1920 1857 -> 1791 and 2283 -> 2274, of 2048 2088 -> 2138 and 2509 -> 2473, of 2304 2367 -> 2316 and 2843 -> 2780.  With another
-// stage beside there is more to push out: bert48, whose first gradients are a quarter of all, 19.97 -> 19.83 ms.
-constexpr size_t CACHED_GRADIENTS = (size_t)100 << 20;
+// read, and their own next use finds them in HBM either way.  A block of 1024 at 512 tokens whose gradients the cache holds 28.9 -> 38.2 us.  Kept -> passing by, six
+// blocks, forward and backward with gradients overwritten, 448, 632 and 1264 tokens: of 1200 1342 -> 1310, 1474 -> 1438 and 2189 -> 2161 us, of 1408 1305 -> 1249, 1446
+// -> 1397 and 2198 -> 2172, of 1536 1443 -> 1385, 1623 -> 1564 and 2417 -> 2352, of 1600 1527 -> 1466, 1727 -> 1667 and 2595 -> 2552, of 2048 2011 -> 1879, 2466 -> 2357
+// and 3445 -> 3348.
 int wgrad_group(chimera_stage* st, GemmArgs (&g)[4], float* const (&db)[4], int overwrite, hipStream_t stream) {
-    const bool once = pass_leaves_cache(st) && (!overwrite || st->beside || st->layer_params * sizeof(float) > CACHED_GRADIENTS);
-    for (GemmArgs& a : g) a.c_once = once;
+    for (GemmArgs& a : g) a.c_once = pass_leaves_cache(st);
     double flop = 0;
     for (int i = 0; i < 4; ++i) flop += 2.0 * g[i].m * g[i].n * g[i].k;
     ProfScope prof(PC_GEMM_WGRAD, flop, stream);
