@@ -350,7 +350,7 @@ int chimera_worker_last_replay(int* h_how);
  * 6 LayerNorm backward, 7 column sums, 8 none any more (a block's weight gradients are one launch, class 2; it
  * reads as zero).  chimera_profile_read must be called
  * with the stream idle; it returns the summed milliseconds, the number of
- * launches and the summed algorithmic work (flop for classes 0-4 and 8, bytes for
+ * launches and the summed algorithmic work (flop for classes 0-4, bytes for
  * 5-7) since the last chimera_profile_reset. */
 int chimera_profile_enable(int on);
 int chimera_profile_reset(void);
@@ -369,6 +369,10 @@ int chimera_profile_read(int cls, double* h_ms, long long* h_launches, double* h
  * C2 = GeLU(C); 3 C = acc + bias[n] + R[m,n]; 4 C = acc * GeLU'(R[m,n]);
  * 5 C (float, always) += acc.  C, C2, R have leading dimension n.
  * EINVAL if k, n or a leading dimension is not a multiple of 8.
+ * CHIMERA_F32, impl 0: larger products run on the bf16 matrix instructions, each operand as
+ * the sum of three bf16 numbers; of a product of two elements at most 2^-24 of it is left
+ * out.  Operands that three do not hold (numbers below 2^-110 with bits below 2^-133), and
+ * sums that are not finite, are seen, and their tile is formed again on the float instructions.
  * d_workspace (may be NULL): chimera_op_gemm_workspace_bytes(m, n, k) bytes, 256-byte
  * aligned, whose first 4096 bytes are zero before the first call; with it, and with a
  * forced tile of 256x256 and splits > 1 (chimera_op_gemm_tuning), the bf16

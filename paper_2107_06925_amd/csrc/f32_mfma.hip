@@ -134,15 +134,16 @@ __device__ __forceinline__ void mask_slice(f32x4 (&v)[4], int k0, int K, int g) 
 // ------------------------------------------------------------------ tile forms
 // On the bf16 matrix instructions.  A float is the sum of three bf16 numbers: itself to nearest, the rest to nearest, and what that leaves
 // (8 + 8 + 8 bits), so a product of two floats is nine products of their parts.  The three smallest are left out: at most 2^-24 of it, one
-// rounding (a first part cut off instead leaves up to 2^-22, all of one sign for some operands).  A bf16 instruction rounds once for 16 products where the float one rounds for every second:
-// against float64, relative 2-norm of random operands, k = 64, 256, 1024, 4096: 1.06e-7 -> 4.8e-8, 2.06e-7 -> 7.1e-8, 4.06e-7 -> 1.30e-7, 8.10e-7 -> 2.74e-7
-// (128x128 tiles, whose sums are not halved, from 256 on: 8.9e-8, 1.86e-7, 3.96e-7); all elements 1.0077362: 5.7e-9 at every k, 2.3e-7 with a first part
-// cut off.  The sums of the large parts' products and of the others are kept apart until the end.
+// rounding (a first part cut off instead leaves up to 2^-22, all of one sign for some operands).  A bf16 instruction rounds once for 16
+// products where the float one rounds for every second: against float64, relative 2-norm of random operands, k = 64, 256, 1024, 4096:
+// 1.06e-7 -> 4.8e-8, 2.06e-7 -> 7.1e-8, 4.06e-7 -> 1.30e-7, 8.10e-7 -> 2.74e-7 (128x128 tiles, whose sums are not halved, from 256 on:
+// 8.9e-8, 1.86e-7, 3.96e-7); all elements 1.0077362: 5.7e-9 at every k, 2.3e-7 with a first part cut off.  The sums of the large parts'
+// products and of the others are kept apart until the end.
 //
-// What bounds it: with two wavefronts on a SIMD matrix and vector instructions overlap by a third at best (8 of the former alone 140 ns, 64 of the
-// latter 148, both 202), and a 64x64 step of 32 k is 12 and 100 of them; LDS is busy 44 % of the time, without conflicts.  Against tiles of
-// v_mfma_f32_32x32x2_f32, which were bound by that instruction: 1024 x 1024 x 1024 A B 24.1 -> 20.0 us, A B^T 23.3 -> 18.5, A^T B 26.9 -> 19.1;
-// 1024 x 3072 x 1024 62.0 -> 47.4; 704 x 2816 x 704 30.9 -> 22.7; two steps of k, 1024 x 1024 x 64, 5.17 either way.
+// What bounds it: with two wavefronts on a SIMD matrix and vector instructions overlap by a third at best (8 of the former alone 140 ns, 64
+// of the latter 148, both 202), and a 64x64 step of 32 k is 12 and 100 of them; LDS is busy 44 % of the time, without conflicts.  Against
+// tiles of v_mfma_f32_32x32x2_f32, which were bound by that instruction: 1024 x 1024 x 1024 A B 24.1 -> 20.0 us, A B^T 23.3 -> 18.5, A^T B
+// 26.9 -> 19.1; 1024 x 3072 x 1024 62.0 -> 47.4; 704 x 2816 x 704 30.9 -> 22.7; two steps of k, 1024 x 1024 x 64, 5.17 either way.
 // Splitting in registers, a wavefront per k slice of a whole tile, was slower (2048^3 118 -> 161 us: no registers are left to load ahead).
 struct SplitBuf { bf16_t part[2][3][64][32]; };                // operand, part, row, k: one step
 // 16-byte chunk c (8 k values) of row r sits at c ^ bits of r: 16 rows of one chunk, as many of four rows, all fall on different banks
@@ -197,13 +198,15 @@ template <int PART> __device__ __forceinline__ void split_store(const float (&v)
 #pragma unroll
     for (int p = 0; p < 3; ++p) *reinterpret_cast<uint4*>(at + p * PART) = make_uint4(w[p][0], w[p][1], w[p][2], w[p][3]);
 }
-// A third part has no more than eight bits, which bf16 holds, unless some lie below its smallest step, 2^-133: parts of a float from 2^-110 on are exact
-// (the matrix instructions keep subnormal operands and sums), and one smaller number that is not is seen here, whatever lies beside it.
+// A third part has no more than eight bits, which bf16 holds, unless some lie below its smallest step, 2^-133: parts of a float from 2^-110
+// on are exact (the matrix instructions keep subnormal operands and sums), and one smaller number that is not is seen here, whatever lies
+// beside it.
 __device__ __forceinline__ bool loses(unsigned rest) { return rest & 0xffff; }
 
-// Asks the scheduler for one order of a step's instructions: the LDS reads, FIRST matrix instructions, then one of them behind every VALUS vector
-// instructions of the split.  Its own order has most matrix instructions first and the split behind them.  1024 x 1024 x 1024 A B 21.5 -> 20.1 us, A B^T
-// 19.6 -> 18.3; 2048^3 103 -> 95, A B^T 105 -> 92, A^T B 112 -> 102.  (64x64 tiles of A^T B are faster in its own order: 19.5 against 19.9 to 21.0.)
+// Asks the scheduler for one order of a step's instructions: the LDS reads, FIRST matrix instructions, then one of them behind every VALUS
+// vector instructions of the split.  Its own order has most matrix instructions first and the split behind them.  1024 x 1024 x 1024 A B
+// 21.5 -> 20.1 us, A B^T 19.6 -> 18.3; 2048^3 103 -> 95, A B^T 105 -> 92, A^T B 112 -> 102.  (64x64 tiles of A^T B are faster in its own
+// order: 19.5 against 19.9 to 21.0.)
 template <int READS, int FIRST, int REST, int VALUS> __device__ __forceinline__ void interleave() {
     __builtin_amdgcn_sched_group_barrier(0x100, READS, 0);
     __builtin_amdgcn_sched_group_barrier(0x008, FIRST, 0);
@@ -381,9 +384,10 @@ __global__ __launch_bounds__(8 * WAVE, 4) void gemm_f32_tile_kernel(F32Launch L)
         if (row_of(r) < m) finish_one<EPI>(p, L.flag, (size_t)row_of(r) * n + col, out[r], bias, other[r]);
 }
 
-// Larger outputs: 128x128, 4 wavefronts of 64x64, two workgroups on a CU, each thread stages a chunk of either operand: half of the vector work and
-// of the LDS reads per matrix instruction.  Float instructions -> 64x64 -> this, A B: 2048^3 155 -> 121 -> 98 us, 2048 x 16384 x 512 319 -> 246 -> 193 (before
-// interleave), 4096 x 4096 x 1024 - -> 226 -> 178 (before it).  Loads four steps ahead need more registers than there are (2048^3 131).
+// Larger outputs: 128x128, 4 wavefronts of 64x64, two workgroups on a CU, each thread stages a chunk of either operand: half of the vector
+// work and of the LDS reads per matrix instruction.  Float instructions -> 64x64 -> this, A B: 2048^3 155 -> 121 -> 98 us, 2048 x 16384 x
+// 512 319 -> 246 -> 193 (before interleave), 4096 x 4096 x 1024 - -> 226 -> 178 (before it).  Loads four steps ahead need more registers
+// than there are (2048^3 131).
 template <bool A_KC, bool B_KC, int EPI>
 __global__ __launch_bounds__(4 * WAVE, 2) void gemm_f32_wide_kernel(F32Launch L) {
     constexpr int BM = 128, BN = 128, BK = 16, NT = 4 * WAVE, TM = 2, TN = 2, CPR = BK / 8;
@@ -493,7 +497,8 @@ __global__ __launch_bounds__(4 * WAVE, 2) void gemm_f32_wide_kernel(F32Launch L)
                 acc[a][b][r] += low[a][b][r];
                 again |= !(fabsf(acc[a][b][r]) < INFINITY);
             }
-    // Both of a wavefront's rows against both of its columns: 2048^3 in tiles that are all formed again 386 -> 277 us (one 32x32 block after the other).
+    // Both of a wavefront's rows against both of its columns: 2048^3 in tiles that are all formed again 386 -> 277 us (one 32x32 block
+    // after the other).
     if (__syncthreads_or(again)) {
         int rows[TM], cols[TN];
 #pragma unroll
@@ -699,12 +704,13 @@ enum Form { WIDE128, TILE64, SMALL, TINY };
 // x 1024 10.6 -> 9.2.
 constexpr long TINY_TILES = 2 * NUM_CUS;
 
-// Form of a launch.  Up to half a 64x64 tile per CU the small form's 32x32 tiles spread the work further (512 x 1024 x 1024, 128 tiles: 19 to 21 us;
-// 512 x 512 x 2048, 64 tiles: 19 against 30 to 47); beyond that the larger tiles' shared operands win (512 x 1536 x 512, 192 tiles: 10.7 to
-// 15.3 against 15.0 to 17.4; 1024 x 1024 x 4096, 256 tiles: 62 to 88 against 129 to 149).  A round of 128x128 tiles (one per CU) takes as long
-// as 3.5 of 64x64, each of several 3.25, and begins and ends more slowly: 64x64 -> 128x128, A B and A^T B, 1024 x 4096 x 512 36.5 -> 33.6 and 38.0 -> 38.3 us,
-// x 1024 65.0 -> 55.0 and 65.7 -> 61.3, x 256 21.6 -> 21.4 and 24.2 -> 27.1; 1280 x 3840 x 512 (300 tiles) 43.1 -> 43.9 and 45.2 -> 53.5;
-// 1280 x 5120 x 640 (400) 68.9 -> 56.9 and 70.9 -> 66.3; 4096 x 4096 x 256 76 -> 57 and 82 -> 77; A^T B 1024 x 4096 x 128 16.6 -> 20.7.
+// Form of a launch.  Up to half a 64x64 tile per CU the small form's 32x32 tiles spread the work further (512 x 1024 x 1024, 128 tiles: 19
+// to 21 us; 512 x 512 x 2048, 64 tiles: 19 against 30 to 47); beyond that the larger tiles' shared operands win (512 x 1536 x 512, 192
+// tiles: 10.7 to 15.3 against 15.0 to 17.4; 1024 x 1024 x 4096, 256 tiles: 62 to 88 against 129 to 149).  A round of 128x128 tiles (one per
+// CU) takes as long as 3.5 of 64x64, each of several 3.25, and begins and ends more slowly: 64x64 -> 128x128, A B and A^T B, 1024 x 4096 x
+// 512 36.5 -> 33.6 and 38.0 -> 38.3 us, x 1024 65.0 -> 55.0 and 65.7 -> 61.3, x 256 21.6 -> 21.4 and 24.2 -> 27.1; 1280 x 3840 x 512 (300
+// tiles) 43.1 -> 43.9 and 45.2 -> 53.5; 1280 x 5120 x 640 (400) 68.9 -> 56.9 and 70.9 -> 66.3; 4096 x 4096 x 256 76 -> 57 and 82 -> 77; A^T
+// B 1024 x 4096 x 128 16.6 -> 20.7.
 Form choose_form(int count, const GemmArgs* g) {
     long t64 = 0, t128 = 0;
     for (int i = 0; i < count; ++i) {

@@ -297,10 +297,10 @@ template <typename F> __device__ __forceinline__ void with_epilogue(int epi, int
         default: f.template operator()<EPI_ACCUM_F32, false, false>(); break;
     }
 }
-// The float accumulate of one wavefront.  A lane takes 4 columns, so that an instruction's pieces are whole rows of the wavefront's tile: with 8, in two
-// instructions, each had every other 16 bytes of the lines, and C, where it passes the caches by, was written in parts of lines.  8 columns -> 4: blocks
-// of 1344, 1792 and 2560 at 2048 tokens 95.6 -> 94.5, 172.6 -> 163.2 and 363 -> 355 us; six blocks of 1600 and 2048, forward and backward, at 448 tokens
-// 1501 -> 1466 and 2099 -> 1879, at 632 1689 -> 1667 and 2457 -> 2357.
+// The float accumulate of one wavefront.  A lane takes 4 columns, so that an instruction's pieces are whole rows of the wavefront's tile:
+// with 8, in two instructions, each had every other 16 bytes of the lines, and C, where it passes the caches by, was written in parts of
+// lines.  8 columns -> 4: blocks of 1344, 1792 and 2560 at 2048 tokens 95.6 -> 94.5, 172.6 -> 163.2 and 363 -> 355 us; six blocks of 1600
+// and 2048, forward and backward, at 448 tokens 1501 -> 1466 and 2099 -> 1879, at 632 1689 -> 1667 and 2457 -> 2357.
 template <bool ONCE, int TM, int TN, typename Acc>
 __device__ __forceinline__ void accumulate(const Acc& acc, float* slab, int row_base, int col_base, int m, int n, float* __restrict__ C, int epi_flag, int lane) {
     constexpr int CPR = EpiSlab<TN>::WN / 4, RPP = 64 / CPR, NP = 32 / RPP;       // lanes per row, rows at once, passes per band of 32 rows
@@ -680,8 +680,9 @@ __device__ __forceinline__ void gemm_async_tile(
     // 8 columns of rows row0, row0 + 16, ...
     constexpr int SHARE = WM / WGK, PIECES = (SHARE + 15) / 16;
     const int row0 = wk * SHARE + lane / 4, gcol = j0 + wn0 + lane % 4 * 8;
-    // With two workgroups on a CU each hides the other's last trip, and these requests hold back the first operands.  Without them A^T B 1472 x 1280 x 512
-    // 7.56 -> 7.24 us, groups of 12 x 384^2 x 1024 10.36 -> 9.97, A B^T with the GeLU derivative 1088 x 1088 x 192 5.54 -> 5.39; but A B x 64 4.2 -> 4.4.
+    // With two workgroups on a CU each hides the other's last trip, and these requests hold back the first operands.  Without them A^T B
+    // 1472 x 1280 x 512 7.56 -> 7.24 us, groups of 12 x 384^2 x 1024 10.36 -> 9.97, A B^T with the GeLU derivative 1088 x 1088 x 192 5.54
+    // -> 5.39; but A B x 64 4.2 -> 4.4.
     constexpr bool EPI_AHEAD = SPS > 1 || (A_KC && !B_KC);
     EpiAhead<PIECES> pre;
     auto ask = [&] { pre.request(i0 + wm0 + row0, gcol, m, n, bias, R, C, ONLY_EPI >= 0 ? ONLY_EPI : epi, epi_flag, res_types); };
@@ -1692,7 +1693,7 @@ int launch_group(const GemmGroup& grp, hipStream_t s) {
 
 // A group on tiles of 256x256, its remainders of up to 128 rows or columns on halves of them, begun first, and what full rounds leave
 // over on quarters or halves, begun last.  Against 256x256 tiles throughout, with the last row bands of one product in a launch of
-// 128x128 tiles of its own: blocks of 1280, 1344, 1408, 1600 and 1792 at 2048 tokens 106 -> 101, 132 -> 114, 137 -> 123, 169 -> 157 and 207 -> 191 us;
+// 128x128 tiles of its own: blocks of 1280, 1344, 1408, 1600 and 1792 at 2048 tokens 106 -> 103, 132 -> 109, 137 -> 116, 169 -> 152 and 207 -> 188 us;
 // of 1024, 1536 and 2048, which have neither remainders nor a rest, within 1 %.  gpt2-1p3b-n32 96.0 -> 93.6 ms.
 // (1) A remainder costs a half tile, not a whole one: a block of 1600 needs 450 + 82 halves instead of 532.
 // (2) All workgroups of a launch that starts with one size reach their epilogues together, and the chip then waits for HBM: 256 tiles of += x 64
@@ -1718,10 +1719,10 @@ int launch_group_mixed(int count, const GemmArgs* g, float* const* bsum, int ove
     const bool fill = smaller && !quarters && full > NUM_CUS && half + 2 * left <= NUM_CUS;
     const long todo = fill ? left : over <= full && (quarters || (over > half && 2 * over <= NUM_CUS)) ? over : 0;
     const long most = quarters ? NUM_CUS / 4 : (NUM_CUS - (fill ? half : 0)) / 2;
-    // Whole bands of rows or columns of one product, or bands of two kinds where that does not do, that come to `todo` tiles or the fewest more, and
-    // to a round of the smaller tiles at most; less than `todo` would leave the last round as it is.  With one kind only, which may find nothing, ->
-    // so: a block of 2696 at 2048 tokens (117 tiles) 435 -> 420 us, 1496 x 13464 x 2048 (62: a row of 53, two columns of 5) 111 -> 91; but with two kinds wherever
-    // they come nearer a block of 1152 (19 tiles in place of 20) 78 -> 88.
+    // Whole bands of rows or columns of one product, or bands of two kinds where that does not do, that come to `todo` tiles or the fewest
+    // more, and to a round of the smaller tiles at most; less than `todo` would leave the last round as it is.  With one kind only, which
+    // may find nothing, -> so: a block of 2696 at 2048 tokens (117 tiles) 435 -> 420 us, 1496 x 13464 x 2048 (62: a row of 53, two columns
+    // of 5) 111 -> 91; but with two kinds wherever they come nearer a block of 1152 (19 tiles in place of 20) 78 -> 88.
     auto tiles_of = [&](int i, bool rows) { return (long)(rows ? fn[i] - cut_n[i] : fm[i] - cut_m[i]); };
     auto bands_of = [&](int i, bool rows) { return (long)(rows ? fm[i] - cut_m[i] : fn[i] - cut_n[i]); };
     auto take = [&](int i, bool rows, long bands) { (rows ? cut_m : cut_n)[i] += (int)bands; };

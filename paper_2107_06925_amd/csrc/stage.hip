@@ -32,8 +32,9 @@ int fail(int code, const char* fmt, ...) {
 static inline size_t align_up(size_t v, size_t a = 256) { return (v + a - 1) / a * a; }
 
 // Optional per-kernel-class timing: a HIP event pair around every launch of a
-// class on the stage's stream, summed after the stream has been waited for.
-enum ProfClass { PC_GEMM_FWD, PC_GEMM_DGRAD, PC_GEMM_WGRAD, PC_ATTN_FWD, PC_ATTN_BWD, PC_LN_FWD, PC_LN_BWD, PC_COLSUM, PC_RESERVED, PC_COUNT };      // PC_RESERVED: nothing fills it; callers read it as zero
+// class on the stage's stream, summed after the stream has been waited for.  Nothing fills
+// PC_RESERVED; callers read it as zero.
+enum ProfClass { PC_GEMM_FWD, PC_GEMM_DGRAD, PC_GEMM_WGRAD, PC_ATTN_FWD, PC_ATTN_BWD, PC_LN_FWD, PC_LN_BWD, PC_COLSUM, PC_RESERVED, PC_COUNT };
 struct ProfRec { hipEvent_t a, b; int cls; double work; };
 struct Profiler {
     bool on = false;
@@ -274,10 +275,10 @@ bool wgrad_group_ok(const chimera_stage* st, const GemmArgs (&g)[4]) {
     return st->kernels == 0 && (st->dtype == CHIMERA_BF16 ? gemm_mfma_group_supports(4, g) : gemm_f32_group_supports(4, g));
 }
 // Where a pass moves more bytes than the memory-side cache holds, the gradients pass it by: they would push out what the next products
-// read, and their own next use finds them in HBM either way.  A block of 1024 at 512 tokens whose gradients the cache holds 28.9 -> 38.2 us.  Kept -> passing by, six
-// blocks, forward and backward with gradients overwritten, 448, 632 and 1264 tokens: of 1200 1342 -> 1310, 1474 -> 1438 and 2189 -> 2161 us, of 1408 1305 -> 1249, 1446
-// -> 1397 and 2198 -> 2172, of 1536 1443 -> 1385, 1623 -> 1564 and 2417 -> 2352, of 1600 1527 -> 1466, 1727 -> 1667 and 2595 -> 2552, of 2048 2011 -> 1879, 2466 -> 2357
-// and 3445 -> 3348.
+// read, and their own next use finds them in HBM either way.  A block of 1024 at 512 tokens whose gradients the cache holds 28.9 -> 38.2
+// us.  Kept -> passing by, six blocks, forward and backward with gradients overwritten, 448, 632 and 1264 tokens: of 1200 1342 -> 1310,
+// 1474 -> 1438 and 2189 -> 2161 us, of 1408 1305 -> 1249, 1446 -> 1397 and 2198 -> 2172, of 1536 1443 -> 1385, 1623 -> 1564 and 2417 ->
+// 2352, of 1600 1527 -> 1466, 1727 -> 1667 and 2595 -> 2552, of 2048 2011 -> 1879, 2466 -> 2357 and 3445 -> 3348.
 int wgrad_group(chimera_stage* st, GemmArgs (&g)[4], float* const (&db)[4], int overwrite, hipStream_t stream) {
     for (GemmArgs& a : g) a.c_once = pass_leaves_cache(st);
     double flop = 0;
