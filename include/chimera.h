@@ -371,8 +371,9 @@ int chimera_profile_read(int cls, double* h_ms, long long* h_launches, double* h
  * EINVAL if k, n or a leading dimension is not a multiple of 8.
  * CHIMERA_F32, impl 0: larger products run on the bf16 matrix instructions, each operand as
  * the sum of three bf16 numbers; of a product of two elements at most 2^-24 of it is left
- * out.  Operands that three do not hold (numbers below 2^-110 with bits below 2^-133), and
- * sums that are not finite, are seen, and their tile is formed again on the float instructions.
+ * out.  A tile is formed again on the float instructions where sums are not finite, and where
+ * operands that three do not hold (numbers below 2^-110 with bits below 2^-133) would change a
+ * result by a quarter of a rounding or more.
  * d_workspace (may be NULL): chimera_op_gemm_workspace_bytes(m, n, k) bytes, 256-byte
  * aligned, whose first 4096 bytes are zero before the first call; with it, and with a
  * forced tile of 256x256 and splits > 1 (chimera_op_gemm_tuning), the bf16

@@ -200,8 +200,29 @@ template <int PART> __device__ __forceinline__ void split_store(const float (&v)
 }
 // A third part has no more than eight bits, which bf16 holds, unless some lie below its smallest step, 2^-133: parts of a float from 2^-110
 // on are exact (the matrix instructions keep subnormal operands and sums), and one smaller number that is not is seen here, whatever lies
-// beside it.
+// beside it.  (Operands split as 2^16 times what they are would all be exact, but take a multiplication each: 2 to 10 % of every product.)
 __device__ __forceinline__ bool loses(unsigned rest) { return rest & 0xffff; }
+// Whether that can matter to a result: each of a product's k terms lost less than 2^-133 times its other factor, of which `a` and `b` are the
+// largest of the result's row and column.  What is below a quarter of a rounding of the result is let pass: one GeLU of -10 among
+// ordinary numbers would otherwise have its tiles formed again.  Such numbers in every tile, formed again -> looked at like this, 2048^3
+// A B 283 -> 166 us, A B^T 246 -> 153, A^T B 257 -> 186 (none: 98, 97, 108); 1024^3 52 -> 25, 47 -> 24, 56 -> 25 (18.3, 17.9, 18.9).  A sum
+// that comes to zero by chance has its tile formed again.
+__device__ __forceinline__ bool matters(float result, float a, float b, int k) {
+    return a > 0.f && b > 0.f && !(fabsf(result) >= fmaxf(a, b) * ((float)k * 0x1p-106f));
+}
+// The largest value of the chunks that a thread stages, into `to`, of the chunks' row.  Not unrolled: by four, 2048^3 with small numbers
+// 166 -> 124 us, but the kernels' code is longer, and a worker of 192-wide float blocks, none of whose numbers are small, 14.2 -> 14.5 ms.
+template <bool KC, int BK> __device__ __forceinline__ void largest(SplitChunk<KC, BK> chunk, int steps, unsigned* to) {
+    float most = 0.f;
+#pragma unroll 1
+    for (int kt = 0; kt < steps; ++kt) {
+        float v[8];
+        chunk.load(v);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) most = fmaxf(most, fabsf(v[j]));
+    }
+    atomicMax(to, __float_as_uint(most));                        // (not negative: ordered as integers too)
+}
 
 // Asks the scheduler for one order of a step's instructions: the LDS reads, FIRST matrix instructions, then one of them behind every VALUS
 // vector instructions of the split.  Its own order has most matrix instructions first and the split behind them.  1024 x 1024 x 1024 A B
@@ -315,6 +336,11 @@ __global__ __launch_bounds__(8 * WAVE, 4) void gemm_f32_tile_kernel(F32Launch L)
         }
         if (SUMS && !stages_a) reinterpret_cast<float*>(lds)[8 * 8 * WAVE + oct * BN + srow] = cs;      // behind the exchange of sums
     };
+    auto chunks_largest = [&](auto kc_c, const float* __restrict__ from, int ld, int row0, int rows, unsigned* to) {
+        constexpr bool KC = decltype(kc_c)::value;
+        const int srow = KC ? (tid & 255) >> 2 : lane, oct = KC ? tid & 3 : wave & 3;
+        largest(SplitChunk<KC, BK>(from, ld, row0, rows, BM, K, srow, oct), KT, to + srow);
+    };
     // Wavefronts of A and of B may take different arms, each with its own barriers: one before the loop and one behind each of the KT steps in both.
     auto roles = [&](auto sums_c) {
         if constexpr (A_KC == B_KC) steps(std::bool_constant<A_KC>{}, sums_c, stages_a ? A : B, stages_a ? lda : ldb, stages_a ? i0 : j0, stages_a ? m : n);
@@ -327,10 +353,11 @@ __global__ __launch_bounds__(8 * WAVE, 4) void gemm_f32_tile_kernel(F32Launch L)
     } else roles(std::false_type{});
     // Two wavefronts with partial sums of one block: each hands over one half of its registers and
     // finishes the other (registers 0..7 or 8..15, i.e. 16 of its rows).
-    static_assert(sizeof(lds) >= (8 * R * WAVE + 4 * BN + 8) * sizeof(float), "LDS too small for the exchange");
+    static_assert(sizeof(lds) >= (8 * R * WAVE + 4 * BN + 8 + BM + BN) * sizeof(float), "LDS too small for the exchange");
     float* xch = reinterpret_cast<float*>(lds);
     float* xcs = xch + 8 * R * WAVE;
     int* redo = reinterpret_cast<int*>(xcs + 4 * BN);
+    unsigned* most = reinterpret_cast<unsigned*>(redo + 8);      // of A's rows, then of B's
     float out[R];
     auto meet = [&] {
 #pragma unroll
@@ -342,20 +369,42 @@ __global__ __launch_bounds__(8 * WAVE, 4) void gemm_f32_tile_kernel(F32Launch L)
             out[r] = wk ? sum + acc[R + r] : acc[r] + sum;
         }
     };
-    // Parts of an infinity give NaN.  Tiles with such sums, or whose parts lost bits, are formed again on the float instructions.
-    bool again = loses(rest);
+    // Parts of an infinity give NaN.  Tiles with such sums, or whose parts lost bits that matter, are formed again on the float instructions.
+    bool again = false;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         acc[r] += low[r];
         again |= !(fabsf(acc[r]) < INFINITY);
     }
-    again = __any(again);
-    if (lane == 0) redo[wave] = again;
+    const bool odd = __any(again || loses(rest));
+    if (lane == 0) redo[wave] = odd;
     meet();
     int any = 0;
 #pragma unroll
     for (int w = 0; w < 8; ++w) any |= redo[w];
-    if (any) {
+    auto either = [&](bool mine) {                               // of the workgroup's threads (__syncthreads_or has LDS of its own)
+        __syncthreads();                       // everyone has read the last answer
+        mine = __any(mine);
+        if (lane == 0) redo[wave] = mine;
+        __syncthreads();
+        int all = 0;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) all |= redo[w];
+        return all;
+    };
+    if (any && !either(again)) [[unlikely]] {                    // lost bits only
+        if (tid < BM + BN) most[tid] = 0;
+        __syncthreads();
+        if (stages_a) chunks_largest(std::bool_constant<A_KC>{}, A, lda, i0, m, most);
+        else chunks_largest(std::bool_constant<B_KC>{}, B, ldb, j0, n, most + BM);
+        __syncthreads();
+        bool matter = false;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            matter |= matters(out[r], __uint_as_float(most[row_of(r) - i0]), __uint_as_float(most[BM + wn0 + l32]), K);
+        any = either(matter);
+    }
+    if (any) [[unlikely]] {
         const int row = min(i0 + wm0 + l32, m - 1), col = min(j0 + wn0 + l32, n - 1);
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[r] = 0.f;
@@ -487,7 +536,7 @@ __global__ __launch_bounds__(4 * WAVE, 2) void gemm_f32_wide_kernel(F32Launch L)
         if (kt + u + 1 < KT) stash((u + 1) % D, kt + u + 1, std::true_type{});
         __syncthreads();
     }
-    bool again = loses(rest);                                    // as in gemm_f32_tile_kernel
+    bool again = false;                                          // as in gemm_f32_tile_kernel
 #pragma unroll
     for (int a = 0; a < TM; ++a)
 #pragma unroll
@@ -497,9 +546,27 @@ __global__ __launch_bounds__(4 * WAVE, 2) void gemm_f32_wide_kernel(F32Launch L)
                 acc[a][b][r] += low[a][b][r];
                 again |= !(fabsf(acc[a][b][r]) < INFINITY);
             }
+    bool redo = __syncthreads_or(again || loses(rest));
+    if (redo && !__syncthreads_or(again)) [[unlikely]] {         // lost bits only
+        unsigned* most = reinterpret_cast<unsigned*>(lds);       // of A's rows, then of B's
+        most[tid] = 0;
+        __syncthreads();
+        largest(SplitChunk<A_KC, BK>(p.a, p.lda, i0, m, BM, K, row_of(A_KC), oct_of(A_KC)), KT, most + row_of(A_KC));
+        largest(SplitChunk<B_KC, BK>(p.b, p.ldb, j0, n, BN, K, row_of(B_KC), oct_of(B_KC)), KT, most + BM + row_of(B_KC));
+        __syncthreads();
+#pragma unroll
+        for (int a = 0; a < TM; ++a)
+#pragma unroll
+            for (int b = 0; b < TN; ++b)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    again |= matters(acc[a][b][r], __uint_as_float(most[wm0 + a * 32 + l32]),
+                                     __uint_as_float(most[BM + wn0 + b * 32 + 8 * (r >> 2) + 4 * g + (r & 3)]), K);
+        redo = __syncthreads_or(again);
+    }
     // Both of a wavefront's rows against both of its columns: 2048^3 in tiles that are all formed again 386 -> 277 us (one 32x32 block
     // after the other).
-    if (__syncthreads_or(again)) {
+    if (redo) [[unlikely]] {
         int rows[TM], cols[TN];
 #pragma unroll
         for (int a = 0; a < TM; ++a) rows[a] = min(i0 + wm0 + a * 32 + l32, m - 1);

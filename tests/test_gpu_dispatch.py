@@ -826,6 +826,28 @@ def test_float_split_of_mixed_magnitudes(n, layout, small):
         assert bool(((c.double() - want).abs() <= size * (left / 2 + 3) * 2.0 ** -24).all())
 
 
+# single numbers too small for three parts in every tile of ordinary ones, which loses nothing that a result holds; beside them rows of zeros, and a row
+# and a column of such numbers only, whose results would lose half of their bits; 64x64 and 128x128 tiles, ragged
+@pytest.mark.parametrize("m,n,k", [(1032, 1016, 392), (2120, 2056, 200)])
+@pytest.mark.parametrize("layout", ["fwd", "dgrad", "wgrad"])
+def test_float_split_of_few_small_numbers(m, n, k, layout):
+    import torch
+    print("float split few small", m, n, k, layout, flush=True)
+    a_kc, b_kc = {"fwd": (1, 0), "dgrad": (1, 1), "wgrad": (0, 0)}[layout]
+    gen = torch.Generator(device="cuda").manual_seed(m)
+    A, B = torch.randn((m, k), generator=gen, device="cuda"), torch.randn((k, n), generator=gen, device="cuda")
+    A[::7, ::11] *= 2.0 ** -121
+    A[5::64], B[:, 9::64], B[3] = 0.0, 0.0, 0.0
+    A[m - 1] *= 2.0 ** -125
+    B[:, 200] *= 2.0 ** -125
+    c = torch.zeros((m, n), device="cuda")
+    b.chimera_op_gemm(A if a_kc else A.T.contiguous(), B.T.contiguous() if b_kc else B, c, m, n, k, a_kc, b_kc, b.EPI_NONE if a_kc else b.EPI_ACCUM_F32)
+    want, size = A.double() @ B.double(), A.double().abs() @ B.double().abs()
+    # a rounding for every second product on the float instructions, fewer on the others, and few sums at the end; what two such numbers make is below the
+    # smallest float, a product of one and an ordinary one may end in subnormal sums
+    assert bool(((c.double() - want).abs() <= size * (k / 2 + 9) * 2.0 ** -24 + k * 2.0 ** -149).all())
+
+
 # a block whose grouped float weight gradients and bias gradients take 128x128 tiles, tokens with a remainder
 def test_float_stage_on_wide_tiles():
     _stage(b.F32, 768, 12, 203, 1)
